@@ -239,3 +239,56 @@ def tolerance(case):
     # similarities: fp32 sums of C terms, or fp32 values in 24-bit pieces.  Of the whole numbers only
     # the best cell of a replaced token, whose candidates can tie within rounding, may differ.
     return {"rel": 2e-6, "max": 1e-5, "differ": 1e-3}
+
+
+def _window_exact(x, anchor, r):
+    """Cosines of the frame x with every in-grid cell of its window of the anchor frame, [B,K,H,W] in fp64."""
+    B, H, W, C = x.shape
+    xd, ad = x.double(), anchor.double()
+    xn, an = xd.norm(dim=-1), ad.norm(dim=-1)
+    win = torch.full((B, (2 * r + 1) ** 2, H, W), -math.inf, dtype=torch.float64, device=x.device)
+    for slot in range(win.shape[1]):
+        dy, dx = slot // (2 * r + 1) - r, slot % (2 * r + 1) - r
+        ys, xs = slice(max(0, -dy), min(H, H - dy)), slice(max(0, -dx), min(W, W - dx))
+        ya, xa = slice(max(0, dy), min(H, H + dy)), slice(max(0, dx), min(W, W + dx))
+        dot = torch.zeros_like(xn[:, ys, xs])
+        for c in range(0, C, 512):
+            dot += (xd[:, ys, xs, c:c + 512] * ad[:, ya, xa, c:c + 512]).sum(-1)
+        win[:, slot, ys, xs] = dot / (xn[:, ys, xs] * an[:, ya, xa])
+    return win
+
+
+def exact(case, seed):
+    """The similarities in 64 bits; everything else of the outputs is copies and whole numbers."""
+    path, r = case["path"], case["r"]
+    if path in ("restore", "adaptive"):
+        return None
+    x, clean = _frames(case, seed, shared_motion=path == "tied")
+    B, F = x.shape[:2]
+    clip = torch.arange(B, device="cuda")
+    if path == "segment":
+        a, frame = None, clean
+    else:
+        sums = torch.stack([x[:, k].double().sum((1, 2)) for k in range(F)], 1)
+        score = torch.nn.functional.cosine_similarity(sums, sums.sum(1, keepdim=True), dim=-1)
+        a = score.mean(0).argmax().expand(B) if path == "tied" else score.argmax(1)
+        frame = x[clip, a]
+    best, mean = [], []
+    for k in range(F):
+        win = _window_exact(x[:, k], frame, r)
+        if path == "tied":                                 # one cell for all views: the best in the mean
+            m, slot = win.mean(0, keepdim=True).max(1)
+            mean.append(m[0])
+            best.append(win.gather(1, slot[:, None].expand(B, 1, *slot.shape[1:]))[:, 0])
+        else:
+            best.append(win.amax(1))
+        if a is not None:
+            best[-1] = torch.where((a == k)[:, None, None], 1.0, best[-1])
+            if path == "tied":
+                mean[-1] = torch.where(a[0] == k, 1.0, mean[-1])
+    want = dict.fromkeys(_PASS if path != "tied" else ("tokens_out", "pos_ids", "src_index", "kept_count", "anchor_index",
+                                                       "fuse_map", "best_sim", "best_idx", "mean_sim"))
+    want["best_sim"] = torch.stack(best, 1).flatten(2)
+    if path == "tied":
+        want["mean_sim"] = torch.stack(mean, 0).flatten(1)
+    return want
