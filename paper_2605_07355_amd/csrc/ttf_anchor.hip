@@ -607,7 +607,7 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
         if (best_idx) best_idx[o] = first + (int)threadIdx.x;
         if (!PAD && threadIdx.x == 0) keep16[o / 16] = 0xffffu;
     }
-    const int KS = C / 32;
+    const int KS = (C + 31) / 32;
     const uint16_t* frame = ext_anchor ? ext_anchor + (size_t)b * N * C : x + ((size_t)b * F + a) * N * C;
     const bool real = (lane >> 2) < ncol;                    // this lane's token exists (padding reads the tile's first)
     const uint16_t* src = frame + (size_t)(first + (real ? lane >> 2 : 0)) * C + (lane & 3) * 8;
@@ -621,7 +621,9 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
         for (int u = 0; u < UN; ++u) {
             const int ks = k0 + 8 * u;
             if (ks < KS) {
-                v[u] = *reinterpret_cast<const uint4*>(src + (size_t)ks * 32);
+                // (the last K-step of tail_channels() rows ends on pieces past the row: zeros)
+                v[u] = uint4{0u, 0u, 0u, 0u};
+                if (ks * 32 + (lane & 3) * 8 < C) v[u] = *reinterpret_cast<const uint4*>(src + (size_t)ks * 32);
                 if (PAD && !real) v[u] = uint4{0u, 0u, 0u, 0u};
             }
         }

@@ -26,16 +26,17 @@ hipError_t launch_window_search_mfma_f32(const ttf_params& p, const void* x, boo
                                          int32_t* best_idx, float* win_sim, hipStream_t s);
 
 // bf16 and fp32 tokens with r <= 2 and C % 32 == 0 take the matrix-core kernels (grids exactly 16 or 32
-// wide with whole keep words the aligned ones, every other grid the padded-tile ones); larger radii and
+// wide with whole keep words the aligned ones, every other grid the padded-tile ones), bf16 tokens also with
+// the channel counts of tail_channels() (`tail`: the workspace has room for them); larger radii and
 // other channel counts take the general wave-per-token kernel.  The environment variable TTF_SEARCH=general, read once per process, forces
 // the general kernels (for comparisons).
-bool use_mfma_path(const ttf_params& p)
+bool use_mfma_path(const ttf_params& p, bool tail = true)
 {
     static const bool general = [] {
         const char* force = std::getenv("TTF_SEARCH");
         return force && std::strcmp(force, "general") == 0;
     }();
-    return !general && (mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p));
+    return !general && (tail || !tail_channels(p)) && (mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p));
 }
 
 // Anchor preparation of the matrix-core path for the element type at hand (fp32: three bf16 planes).
@@ -54,7 +55,7 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
                                 const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
                                 int32_t* best_idx, float* win_sim, hipStream_t s)
 {
-    if (use_mfma_path(p)) {
+    if (use_mfma_path(p, w.tail)) {
         if (p.dtype == TTF_F32)
             return launch_window_search_mfma_f32(p, x, ext_anchor != nullptr, w, anchor_index, fuse_map, best_sim,
                                                  best_idx, win_sim, s);
@@ -155,8 +156,10 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
 
     ttf_params p = *params;
     p.r = p.r > (p.H > p.W ? p.H : p.W) ? (p.H > p.W ? p.H : p.W) : p.r;   // beyond the grid = whole grid
-    const Workspace w = carve(p, workspace);
+    Workspace w = carve(p, workspace);
+    if (workspace_bytes < w.bytes) w = carve(p, workspace, false);
     if (workspace_bytes < w.bytes) return TTF_ERR_WORKSPACE_TOO_SMALL;
+    const bool mfma = use_mfma_path(p, w.tail);
     const bool pick = !ext_anchor && p.anchor_mode == TTF_ANCHOR_AUTO;       // the automatic anchor rule runs
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -185,7 +188,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     // every output is what the exact rule gives.
     const int spec_pref = g_speculation.load(std::memory_order_relaxed);
     const unsigned long long in_bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * 2ull;
-    const bool spec = pick && use_mfma_path(p) && mfma_search_speculative(p) &&
+    const bool spec = pick && mfma && mfma_search_speculative(p) &&
                       (spec_pref > 0 ||
                        (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F <= kSpeculationMaxFrames));
 
@@ -195,7 +198,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     mark();
     if (pick && !spec) TTF_STEP(launch_anchor_scores(p, w, false, s));
     mark();
-    if (use_mfma_path(p))
+    if (mfma)
         TTF_STEP(launch_anchor_prepare_any(p, features, ext_anchor, w, out->anchor_index, out->fuse_map,
                                            out->best_sim, out->best_idx, false, spec ? 1 : 0, s));
     else TTF_STEP(launch_anchor_norms(p, features, ext_anchor, w, out->anchor_index, false, s));
@@ -259,7 +262,7 @@ ttf_status ttf_compress_static(const ttf_params* params, const void* features, c
     const ttf_status st = check_params(params);
     if (st != TTF_OK) return st;
     if (!features || !out) return TTF_ERR_INVALID_ARG;
-    if (carve(*params, nullptr).bytes > (size_t)TTF_STATIC_WORKSPACE_BYTES) return TTF_ERR_WORKSPACE_TOO_SMALL;
+    if (carve(*params, nullptr, false).bytes > (size_t)TTF_STATIC_WORKSPACE_BYTES) return TTF_ERR_WORKSPACE_TOO_SMALL;
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess && (dev < 0 || dev >= kMaxDevices)) e = hipErrorInvalidDevice;
@@ -316,7 +319,8 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
     if (!aligned(features, 16) || !aligned(out->tokens_out, 16) || !aligned(workspace, 256))
         return TTF_ERR_UNSUPPORTED;
     const ttf_params& p = *params;
-    const TiedWorkspace tw = carve_tied(p, workspace);
+    TiedWorkspace tw = carve_tied(p, workspace);
+    if (workspace_bytes < tw.bytes) tw = carve_tied(p, workspace, false);
     if (workspace_bytes < tw.bytes) return TTF_ERR_WORKSPACE_TOO_SMALL;
     const Workspace& w = tw.base;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -330,7 +334,7 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
         TTF_STEP(launch_anchor_scores(p, w, false, s));
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));
-    if (use_mfma_path(p))
+    if (use_mfma_path(p, w.tail))
         TTF_STEP(launch_anchor_prepare_any(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
                                            true, 0, s));
     else TTF_STEP(launch_anchor_norms(p, features, nullptr, w, out->anchor_index, true, s));
@@ -423,7 +427,7 @@ ttf_status ttf_regate(const ttf_params* params, const void* features, const floa
     if (!aligned(features, 16) || !aligned(out->tokens_out, 16) || !aligned(workspace, 256))
         return TTF_ERR_UNSUPPORTED;
     const ttf_params& p = *params;
-    const Workspace w = carve(p, workspace);
+    const Workspace w = carve(p, workspace, false);
     if (workspace_bytes < w.bytes) return TTF_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = launch_regate(p, w, out->best_sim, out->best_idx, out->anchor_index, thresholds,

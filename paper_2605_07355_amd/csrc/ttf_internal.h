@@ -33,7 +33,7 @@ struct Workspace {
     double*   clip_part;     // [B,S]    per slice: |clip sum|^2          (S = ceil(C/256))
     float*    anchor_inv;    // [B,NP]   1/||x_{a,j}|| of every anchor token (0 for a zero token); NP = token count
                              //          of the grid with rows padded to whole 16-column tiles (N when W % 16 == 0)
-    uint16_t* anchor_frag;   // [B,NP/16,C/32,64,8] bf16 anchor frame in MFMA fragment order (matrix-core path)
+    uint16_t* anchor_frag;   // [B,NP/16,ceil(C/32),64,8] bf16 anchor frame in MFMA fragment order (matrix-core path)
     uint64_t* keep_bits;     // [B,F,NW] bit i%64 of word i/64 set iff token i is kept (NW=ceil(N/64))
     int32_t*  frame_base;    // [B,F]    output row of the first kept token of every frame
     int32_t*  src_row;       // [B*F*N]  input token (flat over clips and frames) that output row r copies
@@ -42,6 +42,7 @@ struct Workspace {
                              // shares (one per run of tokens)
     int32_t*  spec;          // [B,4]    guessed anchor, guess trusted (1/0), second search needed (1/0), unused
     float*    strip_sum;     // [B,F,spec_strips(),C] sum of every 32-cell strip of every frame, written by the search
+    bool      tail;          // anchor_frag holds the whole last K-step of tail_channels() rows
     size_t    bytes;
 };
 
@@ -80,7 +81,20 @@ inline bool speculation_shape(const ttf_params& p)
     return 10ll * p.H * p.W >= 7ll * 32 * spec_strips(p);
 }
 
-inline Workspace carve(const ttf_params& p, void* base)
+// bf16 rows that are whole 16-byte pieces but not whole 32-channel K-steps: the matrix-core kernels end
+// on a K-step whose missing channels count as zero.  From 768 channels on: shorter rows keep the
+// wave-per-token kernels, whose sums are then the more exact ones (relative error of the similarities
+// against 64 bits, wave-per-token / matrix cores: C 264 7.9e-8 / 8.8e-8, 520 7.7e-8 / 7.9e-8, 1000
+// 7.8e-8 / 7.5e-8, 4072 9.1e-8 / 8.2e-8).
+inline bool tail_channels(const ttf_params& p)
+{
+    return p.dtype == TTF_BF16 && p.C % 32 != 0 && p.C % 8 == 0 && p.C >= 768;
+}
+
+// tail: with room for the whole last K-step of tail_channels() rows in the anchor's fragment copy.
+// Without it the workspace is a little smaller and such rows take the general kernels (callers whose
+// workspace is that small: the fixed one, or one sized for the rows as they are).
+inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
 {
     const size_t B = p.B, F = p.F, N = (size_t)p.H * p.W, C = p.C, NW = (N + 63) / 64;
     const size_t NP = (size_t)p.H * ((p.W + 15) / 16) * 16;   // grid rows padded to whole 16-column tiles
@@ -92,7 +106,8 @@ inline Workspace carve(const ttf_params& p, void* base)
     const size_t o_cp = take(B * S * sizeof(double));
     const size_t o_ai = take(B * NP * sizeof(float));
     // anchor frame in fragment order: bf16 as is, fp32 as three bf16 planes (where the matrix-core path can run)
-    const size_t o_af = take(p.dtype == TTF_BF16 ? B * NP * C * sizeof(uint16_t)
+    const bool whole = tail && tail_channels(p);
+    const size_t o_af = take(p.dtype == TTF_BF16 ? B * NP * (whole ? align_up(C, 32) : C) * sizeof(uint16_t)
                                                  : (C % 32 == 0 ? 3 * B * NP * C * sizeof(uint16_t) : 0));
     const size_t o_kb = take(B * F * NW * sizeof(uint64_t));
     const size_t o_fb = take(B * F * sizeof(int32_t));
@@ -114,6 +129,7 @@ inline Workspace carve(const ttf_params& p, void* base)
     w.guess_sum   = reinterpret_cast<float*>(c + o_gs);
     w.spec        = reinterpret_cast<int32_t*>(c + o_sp2);
     w.strip_sum   = reinterpret_cast<float*>(c + o_ss);
+    w.tail = whole;
     w.bytes = off;
     return w;
 }
@@ -171,10 +187,10 @@ struct TiedWorkspace {
     int32_t*  row_offsets;   // [2]
     size_t    bytes;
 };
-inline TiedWorkspace carve_tied(const ttf_params& p, void* base)
+inline TiedWorkspace carve_tied(const ttf_params& p, void* base, bool tail = true)
 {
     TiedWorkspace t;
-    t.base = carve(p, base);
+    t.base = carve(p, base, tail);
     const size_t K = (size_t)(2 * p.r + 1) * (2 * p.r + 1);
     const size_t o_ws = t.base.bytes;
     const size_t o_ro = align_up(o_ws + (size_t)p.B * p.F * p.H * p.W * K * sizeof(float), 256);

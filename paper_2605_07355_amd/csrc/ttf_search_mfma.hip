@@ -37,6 +37,8 @@
 #include "ttf_internal.h"
 #include "ttf_search_tile.h"
 
+#include <algorithm>
+
 namespace ttf {
 namespace {
 
@@ -350,8 +352,13 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
 // without a trusted guess skipped; 2: second search of the marked clips only).
 // RAG: the K-step count need not be a multiple of KSW; the slots of the last pass beyond it read the
 // last K-step again (valid memory) with the source fragment replaced by zeros.
-template <int CT, int RAD, int KSW, int FW, bool ALL, bool PAD = false, int SPEC = 0, bool RAG = false>
-__global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
+// TAIL (with RAG): the row ends inside the last K-step (tail_channels()); 16-byte pieces past its end are
+// read from the row's last piece and replaced by zeros.  The alternative for such rows is the
+// wave-per-token kernels, whose lanes add few terms in a row; to be no less exact the products of every
+// three passes (the unrolled loop body) are added to a second set of accumulators and what that addition
+// rounds off stays in the first (compensated sum; one wave per SIMD where two sets need its registers).
+template <int CT, int RAD, int KSW, int FW, bool ALL, bool PAD = false, int SPEC = 0, bool RAG = false, bool TAIL = false>
+__global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) void k_search_mfma_shared(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ anchor_frag,
     const int32_t* __restrict__ anchor_index, const float* __restrict__ anchor_inv,
     int32_t* __restrict__ fuse_map, float* __restrict__ best_sim, int32_t* __restrict__ best_idx,
@@ -401,7 +408,9 @@ __global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
     const int c0 = CT == 3 ? 2 * (tp % spr) : 0;
     const int i0 = CT == 3 ? y0 * W : tp * 32;
     const int ylo = y0 - RAD;
-    const int KS = C / 32;
+    static_assert(!TAIL || (RAG && PAD), "rows that end inside a K-step: padded ragged search");
+    const int KS = (C + (TAIL ? 31 : 0)) / 32;
+    const int row_left = C - 8 - (lane & 3) * 8;             // TAIL: offset of the row's last piece from sp
     const int passes = RAG ? (KS + KSW - 1) / KSW : KS / KSW;
 
     const uint16_t* sp[NS];
@@ -440,6 +449,35 @@ __global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
         for (int q = 0; q < NPS; ++q) acc[s][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
+    f32x4 folded[TAIL ? NS : 1][NPS];                        // TAIL: sums of the passes folded so far
+    float nfold[NS];
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            nfold[s] = 0.f;
+#pragma unroll
+            for (int q = 0; q < NPS; ++q) folded[s][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    // (a squared norm that overflows leaves nothing behind, so that it stays infinite; products can only
+    // overflow where a norm does, whose inverse, zero, makes the cosine NaN either way)
+#define TTF_FOLD_ONE(sum_, part_)                                                                             \
+    do {                                                                                                      \
+        const float was_ = (sum_), add_ = (part_);                                                            \
+        (sum_) = was_ + add_;                                                                                 \
+        (part_) = add_ - ((sum_) - was_);                                                                     \
+    } while (0)
+#define TTF_FOLD()                                                                                            \
+    do {                                                                                                      \
+        _Pragma("unroll") for (int s = 0; s < NS; ++s) {                                                      \
+            TTF_FOLD_ONE(nfold[s], nv[s]);                                                                    \
+            nv[s] = nfold[s] < __builtin_inff() ? nv[s] : 0.f;                                                \
+            _Pragma("unroll") for (int q = 0; q < NPS; ++q) {                                                 \
+                _Pragma("unroll") for (int e = 0; e < 4; ++e) TTF_FOLD_ONE(folded[s][q][e], acc[s][q][e]);    \
+            }                                                                                                 \
+        }                                                                                                     \
+    } while (0)
+
     u32x4 A[3][NS][KSW];                                     // native vectors: plain SSA values, never memory
     u32x4 G[GL];
     // (macros, not lambdas: captured by a lambda the staged fragments were kept in scratch memory)
@@ -457,7 +495,8 @@ __global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
         _Pragma("unroll") for (int ks = 0; ks < KSW; ++ks) {                                                  \
             _Pragma("unroll") for (int s = 0; s < NS; ++s)                                                    \
                 Abuf[s][ks] = *reinterpret_cast<const u32x4*>(                                                \
-                    sp[s] + (RAG ? min(pq * KSW + ks, KS - 1) : pq * KSW + ks) * 32);                         \
+                    sp[s] + (TAIL ? min((pq * KSW + ks) * 32, row_left)                                       \
+                                  : (RAG ? min(pq * KSW + ks, KS - 1) : pq * KSW + ks) * 32));                \
         }                                                                                                     \
     } while (0)
 #define TTF_STAGE(buf_)                                                                                       \
@@ -495,7 +534,7 @@ __global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
             for (int s = 0; s < NS; ++s) {
                 uint32_t r[4] = {Abuf[s][ks][0], Abuf[s][ks][1], Abuf[s][ks][2], Abuf[s][ks][3]};
                 if constexpr (RAG) {                             // a slot past the last K-step adds nothing
-                    const bool real = ks0 + ks < KS;             // wave-uniform
+                    const bool real = TAIL ? (ks0 + ks) * 32 <= row_left : ks0 + ks < KS;   // (wave-uniform without TAIL)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) r[e] = real ? r[e] : 0u;
                 }
@@ -582,11 +621,25 @@ __global__ __launch_bounds__(256, 2) void k_search_mfma_shared(
         TTF_PASS(0);
         if (pass + 1 < passes) TTF_PASS(1);                  // wave-uniform
         if (pass + 2 < passes) TTF_PASS(2);
+        if constexpr (TAIL) TTF_FOLD();
     }
 #undef TTF_PASS
 #undef TTF_REQUEST_ANCHOR
 #undef TTF_REQUEST_SOURCE
 #undef TTF_STAGE
+    if constexpr (TAIL) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            nv[s] += nfold[s];
+#pragma unroll
+            for (int q = 0; q < NPS; ++q) {
+                acc[s][q][0] += folded[s][q][0]; acc[s][q][1] += folded[s][q][1];
+                acc[s][q][2] += folded[s][q][2]; acc[s][q][3] += folded[s][q][3];
+            }
+        }
+    }
+#undef TTF_FOLD
+#undef TTF_FOLD_ONE
 
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -776,7 +829,9 @@ hipError_t launch_padded(const ttf_params& p, const void* x, bool external_ancho
     const size_t words = (size_t)p.B * p.F * NW;
     if (nsrc >= 1) {
         constexpr int FWS = S::NPS <= 3 ? 2 : 1, KSWS = 2;
-        const int groups = (nsrc + 4 * FWS - 1) / (4 * FWS);
+        const bool tail = p.C % 32 != 0;                     // the row ends inside a K-step: one frame per wave
+        const int fpw = tail ? 1 : FWS;
+        const int groups = (nsrc + 4 * fpw - 1) / (4 * fpw);
         const int strips = CT == 1 ? (p.H + 1) / 2 : (CT == 2 ? p.H : p.H * (((p.W + 15) / 16 + 1) / 2));
         const size_t wgs = (size_t)p.B * groups * strips;
         const size_t lds = 2 * KSWS * (size_t)S::NA * 1024;
@@ -788,7 +843,7 @@ hipError_t launch_padded(const ttf_params& p, const void* x, bool external_ancho
                                                    p.H, p.C, p.t, groups, p.W, w.spec, w.strip_sum);
             return hipGetLastError();
         };
-        const bool ragged = (p.C / 32) % KSWS != 0;          // odd K-step count: the variant with a guarded last pass
+        const bool ragged = p.C % (32 * KSWS) != 0;          // odd K-step count: the variant with a guarded last pass
         {
             // speculative pass (every frame walked, strip sums written; the keep words are packed after the
             // last search of the call), and the second search of the clips it leaves
@@ -804,8 +859,15 @@ hipError_t launch_padded(const ttf_params& p, const void* x, bool external_ancho
             }
         }
         if (spec_mode != 0) return hipErrorInvalidValue;
+        auto go_tail = [&]() {
+            if constexpr (CT == 3 && RAD == 2) return hipErrorInvalidValue;   // (mfma_search_padded() sends none here)
+            else
+                return win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, 1, true, true, 0, true, true>)
+                               : go(k_search_mfma_shared<CT, RAD, KSWS, 1, false, true, 0, true, true>);
+        };
         const hipError_t e =
-            ragged ? (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true, 0, true>)
+            tail     ? go_tail()
+            : ragged ? (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true, 0, true>)
                               : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true, 0, true>))
                    : (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true>)
                               : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true>));
@@ -827,7 +889,7 @@ hipError_t launch_pack_keep(const ttf_params& p, const int32_t* fuse_map, const 
     return hipGetLastError();
 }
 
-// True when the matrix-core kernels cover this problem: bf16, grid width 16 or 32, radius <= 2,
+// True when the aligned matrix-core kernels cover this problem: bf16, grid width 16 or 32, radius <= 2,
 // channel count a multiple of 32 (whole K-steps; where they do not divide over waves and passes the
 // ragged variants run), and a token count per frame that is a multiple of 64 so that 64-bit keep
 // words are whole.
@@ -839,14 +901,30 @@ bool mfma_search_supported(const ttf_params& p)
     return false;
 }
 
-// Same element type, radius and channel conditions, but any grid: served by the padded-tile
-// kernels.
+// Same element type and radius, but any grid, and rows that end inside a K-step (tail_channels()) too:
+// served by the padded-tile kernels.
+//
+// Rows that end inside a K-step need enough workgroups: one walks the whole channel axis, so a handful
+// takes longer than the wave-per-token kernels, which spread the tokens over hundreds of waves.  Whole
+// calls, wave-per-token -> matrix cores, us: 32 workgroups (B1 F16 16x16 C1000) 46 -> 54; 64 (B1 F17 16x32
+// C4072) 124 -> 130, (B2 F16 16x16 C2008) 79 -> 76; 96 (B1 F16 24x24 C1000 r0) 77 -> 68; 128 (B2 F32 16x16
+// C1000) 88 -> 64; 432 (B3 F23 24x18 C1000) 145 -> 86; 1320 (B12 F45 10x32 C1552) 831 -> 338.  Wider than
+// 32, where a strip fetches twice the anchor tiles: 72 (B1 F17 9x40 C1000) 60 -> 75; 160 (20x40) 106 -> 96.
+// On grids wider than 32 the 5x5 window keeps the wave-per-token kernels: two sets of its accumulators
+// do not fit the registers (419 spilled, B1 F16 20x40 C1000 0.143 against 0.189 ms).
 bool mfma_search_padded(const ttf_params& p)
 {
-    if (p.dtype != TTF_BF16 || p.r > 2 || p.C % 32 != 0) return false;
+    if (p.dtype != TTF_BF16 || p.r > 2 || !(p.C % 32 == 0 || tail_channels(p))) return false;
+    if (tail_channels(p)) {
+        const int ct = p.W <= 16 ? 1 : (p.W <= 32 ? 2 : 3);
+        if (ct == 3 && p.r == 2) return false;
+        const long long groups = (std::max(p.F - 1, 1) + 3) / 4;
+        const long long strips = ct == 1 ? (p.H + 1) / 2 : (ct == 2 ? p.H : (long long)p.H * (((p.W + 15) / 16 + 1) / 2));
+        if (p.B * groups * strips < (ct == 3 ? 144 : 96)) return false;
+    }
     // the padded kernels index a clip's anchor fragments with 32-bit offsets
     const long long padded_tokens = (long long)p.H * ((p.W + 15) / 16) * 16;
-    if (padded_tokens * p.C >= (1ll << 31)) return false;
+    if (padded_tokens * (long long)align_up(p.C, 32) >= (1ll << 31)) return false;
     return !mfma_search_supported(p);
 }
 
