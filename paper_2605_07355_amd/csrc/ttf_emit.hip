@@ -1,15 +1,20 @@
 // Sequence compaction and positional alignment (Section 3: stacked X' = [anchor rows ; kept
 // source rows], retention mask m_{k,i}, gather of X and P by I_keep, L' = N + P).
 //
-// The search leaves one keep bit per token.  A single small block turns per-frame popcounts
-// into output row offsets (anchor frame first inside each clip, clips packed one after the
-// other); the emit kernel then copies every kept row bit-exactly and writes its original
-// (k, y, x) triple and flat index.
+// The search leaves one keep bit per token.  Small and ordinary calls count the rows ahead of a run of
+// keep words where they are needed (anchor frame first inside each clip, clips packed one after the
+// other); on large ones, and for short rows, a single small block turns per-frame popcounts into output
+// row offsets first.  Every kept row is copied bit-exactly, with its original (k, y, x) triple and flat index.
 #include "ttf_device.h"
 #include "ttf_internal.h"
 
 namespace ttf {
 namespace {
+
+constexpr int kPlaceWords = 16;                // keep words per block of k_place_ids
+constexpr size_t kPlaceAllWords = 256;         // at most this many keep words: offsets, ids and rows in one launch
+constexpr size_t kPlaceAllBytes = 64ull << 20; // ... and this much input
+constexpr size_t kPlaceIdsWords = 4096;        // at most this many: offsets and ids in one launch
 
 // Exclusive scan over the sequence  [N, c(b,0), ..., c(b,F-1)]  for b = 0..B-1, where c(b,k) is
 // the number of kept tokens of source frame k and 0 for the anchor frame.  The entry in front
@@ -116,15 +121,152 @@ __global__ __launch_bounds__(256) void k_emit_rows(const char* __restrict__ x,
     }
 }
 
+// Rows placed ahead of a run of keep words, counted by the block itself from the keep words (no scan in
+// front): the anchor frame's keep bits are all set, so the rows of every clip before b and of the words of
+// clip b before `word` are their popcounts.  All 256 threads call it; every thread gets both counts.
+__device__ __forceinline__ void count_rows_before(const uint64_t* __restrict__ keep_bits, size_t clip_word,
+                                                  size_t word, int& clips, int& words)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ int part[2][4];
+    int c = 0, m = 0;
+    const size_t end = clip_word + word;
+#pragma unroll 8
+    for (size_t i = threadIdx.x; i < end; i += 256) {
+        const int n = __popcll(keep_bits[i]);
+        c += i < clip_word ? n : 0;
+        m += i < clip_word ? 0 : n;
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        c += __shfl_xor(c, d, 64);
+        m += __shfl_xor(m, d, 64);
+    }
+    if (lane == 0) { part[0][wave] = c; part[1][wave] = m; }
+    __syncthreads();
+    clips = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]);
+    words = (part[1][0] + part[1][1]) + (part[1][2] + part[1][3]);
+}
+
+// Output row of the first kept token of a keep word of frame k: `clips` rows of the clips before, `words`
+// kept tokens of the clip's words before it (in flat order).  The anchor frame a comes first: its rows
+// stand ahead of every frame before it, and its own words are full.
+__device__ __forceinline__ int first_row(int clips, int words, int k, int a, int word_in_frame, int N)
+{
+    return clips + (k == a ? 64 * word_in_frame : (k < a ? words + N : words));
+}
+
+// Offsets, ids and rows in one launch, for calls of at most kPlaceAllWords keep words: there the copy is
+// short and the two launches ahead of it (offsets, ids) take longer than their work.  Block = 16 tokens
+// (a quarter of a keep word) of one frame, its kept tokens dealt to the four waves by rank; it counts the rows
+// ahead of it itself (whole calls: B1 F4 8x8 C256 fp32 28.9 -> 23.8 us, segment
+// of B1 F8 16x16 C4096 29.1 -> 24.4, B1 F32 16x16 C2048 50.5 -> 47.4).  Larger calls keep the faster copy of
+// k_copy_rows.  tied_rows as for
+// k_emit_rows: blockIdx.y = clip, the mask is the shared one ([F,NW]).
+template <int U>
+__global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, const uint64_t* __restrict__ keep_bits,
+                                                    const int32_t* __restrict__ anchor_index,
+                                                    int32_t* __restrict__ kept_count, int32_t* __restrict__ row_offsets,
+                                                    char* __restrict__ tokens_out, int32_t* __restrict__ pos_ids,
+                                                    int32_t* __restrict__ src_index, int F, int N, int W, int NW,
+                                                    size_t row_bytes, size_t cap, int frame_offset, size_t tied_rows)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int quarter = blockIdx.x & 3;
+    const size_t wd = blockIdx.x >> 2;                       // keep word over all clips
+    const int per_clip = F * NW;
+    const int b = (int)(wd / per_clip), word = (int)(wd % per_clip);
+    const int k = word / NW, q = word % NW;
+    const bool ids = blockIdx.y == 0;
+    const uint64_t wbits = keep_bits[wd];
+    const bool last = word == per_clip - 1 && quarter == 3 && ids;   // this block closes the clip's counts
+    uint64_t rem = wbits & (0xffffull << (16 * quarter));
+    if (rem == 0 && !last) return;
+    int clips, words;
+    count_rows_before(keep_bits, (size_t)b * per_clip, word, clips, words);
+    if (last && threadIdx.x == 0) {
+        const int kept = words + __popcll(wbits);
+        if (b == 0) row_offsets[0] = 0;
+        row_offsets[b + 1] = clips + kept;
+        kept_count[b] = kept;
+    }
+    const size_t frame = (tied_rows ? (size_t)blockIdx.y * F : (size_t)b * F) + k;
+    const size_t row0 = blockIdx.y * tied_rows;
+    const size_t first = (size_t)first_row(clips, words, k, anchor_index[b], q, N) +
+                         __popcll(wbits & ((1ull << (16 * quarter)) - 1ull));
+    for (int rank = 0; rem != 0; ++rank) {
+        const int bit = __ffsll((unsigned long long)rem) - 1;
+        rem &= rem - 1;
+        if ((rank & 3) != wave) continue;
+        const int i = q * 64 + bit;
+        const size_t row = first + rank;
+        copy_row<U>(x + (frame * (size_t)N + i) * row_bytes, tokens_out + (row0 + row) * row_bytes, row_bytes, lane);
+        if (ids && lane == 0) {
+            pos_ids[row] = k + frame_offset;
+            pos_ids[cap + row] = i / W;
+            pos_ids[2 * cap + row] = i % W;
+            src_index[row] = k * N + i;
+        }
+    }
+}
+
 // Rows of 1 KiB and more are emitted in two steps, so that the copy runs in the shape a plain device
 // copy is fastest in on this chip -- many small blocks, a whole block on one row, one or two 16-byte
 // pieces per thread (measured on 1 GiB: 6.4-6.5 TB/s against 5.8 for eight pieces per lane in a
 // loop) -- without launching blocks for fused tokens (a block per input token costs 0.17 ms of
 // launches alone on 262 144 tokens of which 17 % are kept).
 //
-// Step 1, one wave per keep word: the ids of every kept token and, in src_row[r], the input token
-// that output row r copies.  tied_rows > 0: the mask is the shared one ([F,NW]); ids and src_row
-// are those of one clip.
+// Step 1: the offsets (row_offsets, kept_count), the ids of every kept token and, in src_row[r], the input
+// token that output row r copies.  Block = kPlaceWords consecutive keep words of one clip, which counts the
+// rows ahead of it itself from L2 instead of waiting for a scan kernel (whole calls: 512 words 164.0 -> 161.8
+// us, 1024 words 84.7 -> 83.3, 4096 words 919 -> 917).  Tied-batch mode: the mask is the shared one, one clip.
+__global__ __launch_bounds__(256) void k_place_ids(const uint64_t* __restrict__ keep_bits,
+                                                   const int32_t* __restrict__ anchor_index,
+                                                   int32_t* __restrict__ kept_count, int32_t* __restrict__ row_offsets,
+                                                   int32_t* __restrict__ pos_ids, int32_t* __restrict__ src_index,
+                                                   int32_t* __restrict__ src_row, int F, int N, int W, int NW,
+                                                   int runs, size_t cap, int frame_offset)
+{
+    static_assert(kPlaceWords % 4 == 0 && kPlaceWords <= 64, "whole words per wave, one lane per word");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int per_clip = F * NW;
+    const int b = blockIdx.x / runs, run = blockIdx.x % runs;
+    const int w0 = run * kPlaceWords;
+    const uint64_t* kb = keep_bits + (size_t)b * per_clip;
+    int clips, words;
+    count_rows_before(keep_bits, (size_t)b * per_clip, w0, clips, words);
+    // kept tokens of the run's words: lane l holds word w0 + l, inclusive sums over the lanes
+    const int n = (lane < kPlaceWords && w0 + lane < per_clip) ? __popcll(kb[w0 + lane]) : 0;
+    int inc = n;
+#pragma unroll
+    for (int d = 1; d < kPlaceWords; d <<= 1) {
+        const int o = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += o;
+    }
+    if (run == runs - 1 && threadIdx.x == kPlaceWords - 1) {
+        if (b == 0) row_offsets[0] = 0;
+        row_offsets[b + 1] = clips + words + inc;
+        kept_count[b] = words + inc;
+    }
+    const int a = anchor_index[b];
+    for (int u = wave; u < kPlaceWords && w0 + u < per_clip; u += 4) {   // wave-uniform
+        const int ahead = words + __shfl(inc - n, u, 64);
+        const int word = w0 + u, k = word / NW, q = word % NW;
+        const uint64_t wbits = kb[word];
+        if (((wbits >> lane) & 1ull) == 0) continue;
+        const size_t row = (size_t)first_row(clips, ahead, k, a, q, N) + __popcll(wbits & ((1ull << lane) - 1ull));
+        const int i = q * 64 + lane;
+        pos_ids[row] = k + frame_offset;
+        pos_ids[cap + row] = i / W;
+        pos_ids[2 * cap + row] = i % W;
+        src_index[row] = k * N + i;
+        src_row[row] = (int32_t)(((size_t)b * F + k) * (size_t)N + i);
+    }
+}
+
+// The same ids behind k_offsets_scan, one wave per keep word: calls of more than kPlaceIdsWords keep words,
+// where every block counting from the start would read more than the scan costs.  tied_rows > 0: the mask is the
+// shared one ([F,NW]); ids and src_row are those of one clip.
 __global__ __launch_bounds__(256) void k_emit_ids(const uint64_t* __restrict__ keep_bits,
                                                   const int32_t* __restrict__ frame_base,
                                                   int32_t* __restrict__ pos_ids, int32_t* __restrict__ src_index,
@@ -176,12 +318,27 @@ __global__ __launch_bounds__(256) void k_copy_rows(const char* __restrict__ x, c
     }
 }
 
+// How the rows of a call are placed.
+enum class Placement { all, ids, scan };
+constexpr size_t kRowBlockMin = 1024;          // shortest rows that k_copy_rows takes
+inline Placement placement(const ttf_params& p, bool tied)
+{
+    const size_t words = (size_t)(tied ? 1 : p.B) * p.F * (((size_t)p.H * p.W + 63) / 64);
+    const size_t row_bytes = (size_t)p.C * (p.dtype == TTF_BF16 ? 2 : 4);
+    const size_t tokens_bytes = (size_t)p.B * p.F * p.H * p.W * row_bytes;
+    if (tied && p.B > 65535) return Placement::scan;         // (clips ride on gridDim.y)
+    if (words <= kPlaceAllWords && tokens_bytes <= kPlaceAllBytes) return Placement::all;
+    if (row_bytes % 16 == 0 && row_bytes >= kRowBlockMin && words <= kPlaceIdsWords) return Placement::ids;
+    return Placement::scan;
+}
+
 }  // namespace
 
 hipError_t launch_offsets_scan(const ttf_params& p, const Workspace& w, const int32_t* anchor_index,
                                int32_t* kept_count, int32_t* row_offsets, bool tied, hipStream_t s)
 {
     const int N = p.H * p.W, NW = (N + 63) / 64;
+    if (placement(p, tied) != Placement::scan) return hipSuccess;   // the emission counts for itself
     // tied-batch mode: one shared mask, i.e. the scan of a single clip
     k_offsets_scan<<<1, 1024, 0, s>>>(w.keep_bits, anchor_index, w.frame_base, kept_count, row_offsets,
                                       tied ? 1 : p.B, p.F, N, NW);
@@ -189,8 +346,9 @@ hipError_t launch_offsets_scan(const ttf_params& p, const Workspace& w, const in
 }
 
 hipError_t launch_emit_rows(const ttf_params& p, const void* x, const Workspace& w,
-                            const int32_t* total_rows, void* tokens_out, int32_t* pos_ids,
-                            int32_t* src_index, int frame_offset, bool tied, hipStream_t s)
+                            const int32_t* anchor_index, int32_t* kept_count, int32_t* row_offsets,
+                            void* tokens_out, int32_t* pos_ids, int32_t* src_index, int frame_offset, bool tied,
+                            hipStream_t s)
 {
     const int N = p.H * p.W, NW = (N + 63) / 64;
     const size_t row_bytes = (size_t)p.C * (p.dtype == TTF_BF16 ? 2 : 4);
@@ -199,11 +357,28 @@ hipError_t launch_emit_rows(const ttf_params& p, const void* x, const Workspace&
     const unsigned grid = (unsigned)((size_t)p.B * p.F * NW * 4);
     const char* xs = static_cast<const char*>(x);
     char* out = static_cast<char*>(tokens_out);
-    constexpr size_t kRowBlockMin = 1024;
+    const Placement place = placement(p, tied);
+    if (place == Placement::all) {
+        const unsigned blocks = (unsigned)((size_t)(tied ? 1 : p.B) * p.F * NW * 4);
+        auto go = [&](auto kernel) {
+            kernel<<<dim3(blocks, tied ? p.B : 1), 256, 0, s>>>(xs, w.keep_bits, anchor_index, kept_count, row_offsets, out,
+                                                                pos_ids, src_index, p.F, N, p.W, NW, row_bytes, cap,
+                                                                frame_offset, tied_rows);
+            return hipGetLastError();
+        };
+        return row_bytes % 16 == 0 ? go(k_place_rows<16>) : (row_bytes % 4 == 0 ? go(k_place_rows<4>) : go(k_place_rows<2>));
+    }
     if (row_bytes % 16 == 0 && row_bytes >= kRowBlockMin && (!tied || p.B <= 65535)) {   // (clips ride on gridDim.y)
         const size_t words = (size_t)(tied ? 1 : p.B) * p.F * NW;
-        k_emit_ids<<<(unsigned)((words + 3) / 4), 256, 0, s>>>(w.keep_bits, w.frame_base, pos_ids, src_index, w.src_row,
-                                                              p.F, N, p.W, NW, words, cap, frame_offset);
+        if (place == Placement::ids) {
+            const int runs = (p.F * NW + kPlaceWords - 1) / kPlaceWords;
+            k_place_ids<<<(unsigned)((tied ? 1 : p.B) * runs), 256, 0, s>>>(w.keep_bits, anchor_index, kept_count, row_offsets,
+                                                                           pos_ids, src_index, w.src_row, p.F, N, p.W, NW,
+                                                                           runs, cap, frame_offset);
+        } else {
+            k_emit_ids<<<(unsigned)((words + 3) / 4), 256, 0, s>>>(w.keep_bits, w.frame_base, pos_ids, src_index, w.src_row,
+                                                                  p.F, N, p.W, NW, words, cap, frame_offset);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         // a quarter as many blocks as there could be rows: at the usual kept fractions every block has
@@ -211,7 +386,7 @@ hipError_t launch_emit_rows(const ttf_params& p, const void* x, const Workspace&
         const unsigned threads = (unsigned)(row_bytes >= 4096 ? 256 : row_bytes / 1024 * 64);
         const size_t want = (cap + 3) / 4;
         const unsigned blocks = (unsigned)(want < kMaxBlocks256 ? want : kMaxBlocks256);
-        k_copy_rows<<<dim3(blocks, tied ? p.B : 1), threads, 0, s>>>(xs, w.src_row, total_rows, out, row_bytes,
+        k_copy_rows<<<dim3(blocks, tied ? p.B : 1), threads, 0, s>>>(xs, w.src_row, row_offsets + (tied ? 1 : p.B), out, row_bytes,
                                                                      tied_rows, tied_rows);
         return hipGetLastError();
     }

@@ -173,10 +173,9 @@ hipError_t launch_pack_keep(const ttf_params& p, const int32_t* fuse_map, const 
                             const Workspace& w, hipStream_t s);
 hipError_t launch_offsets_scan(const ttf_params& p, const Workspace& w, const int32_t* anchor_index,
                                int32_t* kept_count, int32_t* row_offsets, bool tied, hipStream_t s);
-// `total_rows`: device address of the number of output rows (of one clip's share in tied-batch mode),
-// as the offsets scan has left it.
-hipError_t launch_emit_rows(const ttf_params& p, const void* x, const Workspace& w,
-                            const int32_t* total_rows, void* tokens_out, int32_t* pos_ids,
+// Output rows, ids and -- where launch_offsets_scan leaves that to it -- kept_count and row_offsets.
+hipError_t launch_emit_rows(const ttf_params& p, const void* x, const Workspace& w, const int32_t* anchor_index,
+                            int32_t* kept_count, int32_t* row_offsets, void* tokens_out, int32_t* pos_ids,
                             int32_t* src_index, int frame_offset, bool tied, hipStream_t s);
 
 // Tied-batch mode.  Workspace behind the common sections: every window similarity of every
