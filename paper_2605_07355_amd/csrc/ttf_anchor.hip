@@ -5,6 +5,7 @@
 // everything after that in fp64 on [B,F,C] numbers.  The last kernel of the stage picks the arg
 // max (lowest k on ties) and computes 1/||x_{a,j}|| for the anchor tokens, which the window
 // search uses as the anchor half of every cosine denominator.
+#include <algorithm>
 #include <type_traits>
 
 #include "ttf_device.h"
@@ -15,45 +16,42 @@ namespace {
 
 constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every clip is already in anchor_index
 
-// One block = one frame x one slice of 64*V channels.  Wave w adds rows w, w+4, ...; the four
-// partial sums are combined through LDS in wave order, so the result is order-stable.
+// One block = one frame x one slice of 64*V channels x one of `parts` runs of rows.  Wave w adds rows w,
+// w+4, ... of the run; the four partial sums are combined through LDS in wave order, so the result is
+// order-stable, and stored as share `part` of the frame: out[frame][part][C].  Bound by latency where there
+// are few blocks (B1 F32 16x16 C2048: 128 without parts, 2.5 TB/s); eight rows are in flight per wave.  Whole
+// calls without -> with parts: that one 47.4 -> 44.5 us, B3 F23 24x18 C1000 84.8 -> 74.0.
 // `spec` (may be null): per clip {guessed anchor, guess trusted, ...}; clips with a trusted guess get
 // their exact sums from the search and are skipped here.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, float* __restrict__ frame_sum,
-                                                    int N, int C, int F, const int32_t* __restrict__ spec)
+__global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, float* __restrict__ out,
+                                                    int N, int C, int F, int parts, const int32_t* __restrict__ spec)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const size_t frame = blockIdx.x;
+    const size_t frame = blockIdx.x / parts;
+    const int run = blockIdx.x % parts;
     if (spec && spec[4 * (frame / F) + 1]) return;
     const int c0 = (blockIdx.y * 64 + lane) * V;
+    const int per = (N + parts - 1) / parts;
+    const int lo = run * per, hi = min(N, lo + per);
     __shared__ float part[4][64 * V];
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     if (c0 < C) {
         const T* base = x + frame * (size_t)N * C + c0;
-        int i = wave;
-        for (; i + 12 < N; i += 16) {          // four rows in flight per wave
-            RowVec<T, V> r0, r1, r2, r3;
-            r0.template load<true>(base + (size_t)i * C);
-            r1.template load<true>(base + (size_t)(i + 4) * C);
-            r2.template load<true>(base + (size_t)(i + 8) * C);
-            r3.template load<true>(base + (size_t)(i + 12) * C);
+        for (int i0 = lo + wave; i0 < hi; i0 += 32) {
+            RowVec<T, V> r[8];
 #pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r0.v[e];
+            for (int u = 0; u < 8; ++u)
+                if (i0 + 4 * u < hi) r[u].template load<true>(base + (size_t)(i0 + 4 * u) * C);
 #pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r1.v[e];
+            for (int u = 0; u < 8; ++u) {
+                if (i0 + 4 * u < hi) {
 #pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r2.v[e];
-#pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r3.v[e];
-        }
-        for (; i < N; i += 4) {
-            RowVec<T, V> r0;
-            r0.template load<true>(base + (size_t)i * C);
-#pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r0.v[e];
+                    for (int e = 0; e < V; ++e) acc[e] += r[u].v[e];
+                }
+            }
         }
     }
 #pragma unroll
@@ -63,7 +61,7 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             const int q = lane * V + e;
-            frame_sum[frame * (size_t)C + c0 + e] = ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q];
+            out[blockIdx.x * (size_t)C + c0 + e] = ((part[0][q] + part[1][q]) + part[2][q]) + part[3][q];
         }
     }
 }
@@ -132,7 +130,7 @@ __device__ __forceinline__ void anchor_partials_body(const float* __restrict__ f
     // this lane's four channels of one frame sum: one 16-byte load when the row allows it
     const bool vec = (C % 4 == 0) && ok[3];
     auto load4 = [&](const float* row, float* out) {
-        if constexpr (STRIPS) {                        // (C % 128 == 0 on this path: always 16-byte loads)
+        if constexpr (STRIPS) {                        // (C % 4 == 0 on this path: always 16-byte loads)
             if (!ok[3]) return;                        // the last slice may reach beyond C
             for (int s0 = 0; s0 < strips; s0 += 8) {
                 float4 q[8];
@@ -217,7 +215,8 @@ __device__ __forceinline__ void anchor_partials_body(const float* __restrict__ f
 }
 
 // MIXED: clips with a trusted anchor guess (spec[b][1]) have their frame sums as strip sums
-// (strip_sum [B,F,strips,C]), the other clips in frame_sum [B,F,C]; otherwise every clip in frame_sum.
+// (strip_sum [B,F,strips,C]), the other clips in frame_sum [B,F,C]; otherwise every clip in frame_sum, or
+// (spec null, strip_sum given) every clip as the shares that k_frame_sums leaves in strip_sum.
 template <bool MIXED>
 __global__ __launch_bounds__(1024) void k_anchor_partials(const float* __restrict__ frame_sum,
                                                          double* __restrict__ score_part,
@@ -229,7 +228,7 @@ __global__ __launch_bounds__(1024) void k_anchor_partials(const float* __restric
     const int slice = (blockIdx.x / FG) % S;
     const size_t b = blockIdx.x / FG / S;
     __shared__ double gsh[16][256];
-    if (MIXED && spec[4 * b + 1] != 0)                   // block-uniform
+    if (MIXED && (!spec || spec[4 * b + 1] != 0))        // block-uniform
         anchor_partials_body<2, true>(strip_sum + b * (size_t)F * strips * C, score_part, clip_part, b, slice, fg, F,
                                       C, S, FG, strips, gsh);
     else
@@ -772,6 +771,29 @@ hipError_t by_layout(const ttf_params& p, F&& f)
 
 }  // namespace
 
+// Rows whose 16-byte pieces one block of k_frame_sums_slab sums over a whole frame.
+static bool frame_sums_by_slab(const ttf_params& p)
+{
+    const int V = p.dtype == TTF_BF16 ? 8 : 4;
+    return p.C % (256 * V) == 0 && (size_t)p.B * p.F * (p.C / (256 * V)) >= 512;
+}
+
+// Runs of rows a frame is cut into by k_frame_sums: as many as make about 1024 blocks, of at least 32 rows.
+// The shares stand in the anchor's fragment copy, which is written after the anchor has been chosen, so
+// they have to fit there (short clips and long rows may get fewer).  Row lengths of whole 16-byte pieces
+// only: k_anchor_partials adds the shares with 16-byte loads.
+static int frame_sum_parts(const ttf_params& p, const Workspace& w)
+{
+    const int V = p.dtype == TTF_BF16 ? 8 : 4;
+    if (p.C % V != 0 || frame_sums_by_slab(p)) return 1;
+    const size_t blocks = (size_t)p.B * p.F * ((p.C + 64 * V - 1) / (64 * V));
+    const size_t share = (size_t)p.B * p.F * p.C * sizeof(float);
+    size_t parts = std::min<size_t>(8, (1024 + blocks / 2) / blocks);
+    parts = std::min<size_t>(parts, (size_t)p.H * p.W / 32);
+    parts = std::min<size_t>(parts, w.frag_bytes / share);
+    return parts < 2 ? 1 : (int)parts;
+}
+
 hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, hipStream_t s)
 {
     const int N = p.H * p.W;
@@ -779,13 +801,16 @@ hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace
     return by_layout(p, [&](auto tag, auto vtag) {
         using T = decltype(tag);
         constexpr int V = decltype(vtag)::value;
-        if (V > 1 && p.C % (256 * V) == 0 && (size_t)p.B * p.F * (p.C / (256 * V)) >= 512) {
+        if (V > 1 && frame_sums_by_slab(p)) {
             dim3 slabs((unsigned)(p.B * p.F), (unsigned)(p.C / (256 * V)));
             k_frame_sums_slab<T, V><<<slabs, 256, 0, s>>>(static_cast<const T*>(x), w.frame_sum, N, p.C, p.F, spec);
             return hipGetLastError();
         }
-        dim3 grid((unsigned)(p.B * p.F), (unsigned)((p.C + 64 * V - 1) / (64 * V)));
-        k_frame_sums<T, V><<<grid, 256, 0, s>>>(static_cast<const T*>(x), w.frame_sum, N, p.C, p.F, spec);
+        // (beside a speculative search the fragment copy is in use: no parts)
+        const int parts = skip_trusted ? 1 : frame_sum_parts(p, w);
+        float* out = parts > 1 ? reinterpret_cast<float*>(w.anchor_frag) : w.frame_sum;
+        dim3 grid((unsigned)(p.B * p.F * parts), (unsigned)((p.C + 64 * V - 1) / (64 * V)));
+        k_frame_sums<T, V><<<grid, 256, 0, s>>>(static_cast<const T*>(x), out, N, p.C, p.F, parts, spec);
         return hipGetLastError();
     });
 }
@@ -806,7 +831,11 @@ hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, bool mi
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (mixed && strips <= 8)
+    const int parts = mixed ? 1 : frame_sum_parts(p, w);
+    if (parts > 1)
+        k_anchor_partials<true><<<grid, 1024, 0, s>>>(w.frame_sum, w.score_part, w.clip_part, p.F, p.C, S, FG, parts,
+                                                      reinterpret_cast<const float*>(w.anchor_frag), nullptr);
+    else if (mixed && strips <= 8)
         k_anchor_partials<true><<<grid, 1024, 0, s>>>(w.frame_sum, w.score_part, w.clip_part, p.F, p.C, S, FG, strips,
                                                       w.strip_sum, w.spec);
     else

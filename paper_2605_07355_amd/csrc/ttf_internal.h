@@ -42,6 +42,7 @@ struct Workspace {
                              // shares (one per run of tokens)
     int32_t*  spec;          // [B,4]    guessed anchor, guess trusted (1/0), second search needed (1/0), unused
     float*    strip_sum;     // [B,F,spec_strips(),C] sum of every 32-cell strip of every frame, written by the search
+    size_t    frag_bytes;    // size of anchor_frag; until the anchor is chosen it holds the frame-sum shares
     bool      tail;          // anchor_frag holds the whole last K-step of tail_channels() rows
     size_t    bytes;
 };
@@ -129,6 +130,7 @@ inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
     w.guess_sum   = reinterpret_cast<float*>(c + o_gs);
     w.spec        = reinterpret_cast<int32_t*>(c + o_sp2);
     w.strip_sum   = reinterpret_cast<float*>(c + o_ss);
+    w.frag_bytes = o_kb - o_af;
     w.tail = whole;
     w.bytes = off;
     return w;
