@@ -7,7 +7,7 @@
 // M = (F-1) N source tokens, t = the rank-th smallest s^ with rank = clamp(ceil((1-phi) M), 1, M);
 // only tokens strictly above it are fused, so at most floor(phi M) are.  It is found exactly by a
 // most-significant-digit-first radix selection over an order-preserving integer image of the
-// floats: four passes of 256-bin counting, one workgroup per clip, integer LDS counters only
+// floats: four counts over 256 bins, one workgroup per clip, integer LDS counters only
 // (counts do not depend on the order of the additions).
 #include "ttf_device.h"
 #include "ttf_internal.h"
@@ -26,6 +26,14 @@ __device__ __forceinline__ float key_value(uint32_t k)
     const uint32_t u = (k & 0x80000000u) ? (k & 0x7fffffffu) : ~k;
     return __builtin_bit_cast(float, u);
 }
+
+// What bounds it: one workgroup per clip counts a few thousand to a few hundred thousand values four times.
+// Clips of at most 8 values per thread are read once and stay in registers (B8, 8192 values: whole
+// select + re-gate call 83.3 -> 82.9 us; 16 values per thread, twice the unrolled code: 87.6); for longer ones
+// the third pass reads the values a last time and, once the digits so far have thinned them out, leaves
+// the keys that still match in LDS for the last two counts (B1 F236 32x17: 234 -> 207 us).
+constexpr int kSelectUnroll = 8;                    // values in flight per thread
+constexpr int kSelectList = 8192;                    // keys kept in LDS (32 KiB)
 
 __global__ __launch_bounds__(1024) void k_select_threshold(const float* __restrict__ best_sim,
                                                            const int32_t* __restrict__ anchor_index,
@@ -50,42 +58,60 @@ __global__ __launch_bounds__(1024) void k_select_threshold(const float* __restri
     __shared__ unsigned total[256];
     __shared__ uint32_t s_prefix;
     __shared__ long long s_k;
-    if (threadIdx.x == 0) { s_prefix = 0u; s_k = rank - 1; }
+    __shared__ unsigned s_match;                     // keys that match the digits chosen so far
+    __shared__ unsigned s_listed;
+    __shared__ uint32_t list[kSelectList];
+    if (threadIdx.x == 0) { s_prefix = 0u; s_k = rank - 1; s_match = 0xffffffffu; s_listed = 0u; }
     uint32_t mask = 0u;
+    const bool resident = FN <= kSelectUnroll * 1024;
+    bool listed = false;                             // uniform over the block
+    float v[kSelectUnroll];
     for (int shift = 24; shift >= 0; shift -= 8) {
         for (int q = lane; q < 256; q += 64) hist[wave][q] = 0u;
         __syncthreads();
         const uint32_t prefix = s_prefix;
-        // eight independent loads in flight per thread before their counts are added
-        for (long long j0 = threadIdx.x; j0 < FN; j0 += 8 * 1024) {
-            float v[8];
+        const bool collect = !resident && !listed && s_match <= (unsigned)kSelectList;
+        if (!listed) {
+            // all loads of a round in flight before their counts are added
+            for (long long j0 = threadIdx.x; j0 < FN; j0 += kSelectUnroll * 1024) {
+                if (!resident || shift == 24) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const long long j = j0 + 1024 * u;
-                v[u] = j < FN ? sim[j] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const long long j = j0 + 1024 * u;
-                const uint32_t key = order_key(v[u]);
-                const bool act = j < FN && (j < skip_lo || j >= skip_hi) && (key & mask) == prefix;
-                const uint32_t bin = (key >> shift) & 255u;
-                if (shift == 24) {
-                    // leading digit (sign and high exponent bits): similarities crowd into a few bins,
-                    // so lanes with equal bins are counted together and one lane adds the count
-                    uint64_t todo = __ballot(act);
-                    while (todo) {
-                        const int leader = __ffsll((unsigned long long)todo) - 1;
-                        const uint32_t lb = (uint32_t)__shfl((int)bin, leader, 64);
-                        const uint64_t same = __ballot(act && bin == lb);
-                        if (lane == leader) hist[wave][lb] += (unsigned)__popcll(same);
-                        todo &= ~same;
+                    for (int u = 0; u < kSelectUnroll; ++u) {
+                        const long long j = j0 + 1024 * u;
+                        v[u] = j < FN ? sim[j] : 0.f;
                     }
-                } else if (act) {
-                    atomicAdd(&hist[wave][bin], 1u);
+                }
+#pragma unroll
+                for (int u = 0; u < kSelectUnroll; ++u) {
+                    const long long j = j0 + 1024 * u;
+                    const uint32_t key = order_key(v[u]);
+                    const bool act = j < FN && (j < skip_lo || j >= skip_hi) && (key & mask) == prefix;
+                    const uint32_t bin = (key >> shift) & 255u;
+                    if (shift == 24) {
+                        // leading digit (sign and high exponent bits): similarities crowd into a few bins,
+                        // so lanes with equal bins are counted together and one lane adds the count
+                        uint64_t todo = __ballot(act);
+                        while (todo) {
+                            const int leader = __ffsll((unsigned long long)todo) - 1;
+                            const uint32_t lb = (uint32_t)__builtin_amdgcn_readlane((int)bin, leader);
+                            const uint64_t same = __ballot(act && bin == lb);
+                            if (lane == leader) atomicAdd(&hist[wave][lb], (unsigned)__popcll(same));
+                            todo &= ~same;
+                        }
+                    } else if (act) {
+                        atomicAdd(&hist[wave][bin], 1u);
+                        if (collect) list[atomicAdd(&s_listed, 1u)] = key;   // (at most s_match of them)
+                    }
                 }
             }
+        } else {
+            const unsigned n = s_listed;
+            for (unsigned i = threadIdx.x; i < n; i += 1024) {
+                const uint32_t key = list[i];
+                if ((key & mask) == prefix) atomicAdd(&hist[wave][(key >> shift) & 255u], 1u);
+            }
         }
+        listed = listed || collect;
         __syncthreads();
         if (threadIdx.x < 256) {
             unsigned c = 0;
@@ -115,6 +141,7 @@ __global__ __launch_bounds__(1024) void k_select_threshold(const float* __restri
                 int e = 0;
                 while (e < 3 && rest >= (long long)c[e]) { rest -= c[e]; ++e; }
                 s_k = rest;
+                s_match = c[e];
                 s_prefix = prefix | ((uint32_t)(4 * lane + e) << shift);
             }
         }
