@@ -115,7 +115,7 @@ ttf_status ttf_workspace_size(const ttf_params* params, size_t* bytes);
  * more than 2^25 tokens (frames rounded up to 64), r < 0, t not finite, anchor_index outside [-F,F) in FIXED mode, unknown
  * anchor_mode), UNSUPPORTED (unknown dtype; features, tokens_out or workspace misaligned),
  * WORKSPACE_TOO_SMALL, HIP.  Any C, grid and radius work.  Fast paths: bf16 and fp32 input with
- * C % 32 == 0 and r <= 2 runs the window search on the matrix cores (fp32 as three bf16 pieces
+ * C % 32 == 0 (large bf16 problems of at least 768 channels: C % 8 == 0) and r <= 2 runs the window search on the matrix cores (fp32 as three bf16 pieces
  * per value, 24 significant bits) (any grid; grids exactly 16
  * or 32 tokens wide with H*W % 64 == 0 are the best case); rows whose byte length is a multiple
  * of 16 are read and copied with 16-byte accesses.
@@ -132,7 +132,8 @@ ttf_status ttf_compress(const ttf_params* params, const void* features,
  * used on holds its own copy from the first use until the process ends).  The call allocates and
  * frees nothing.
  *   - Problems whose ttf_workspace_size() exceeds TTF_STATIC_WORKSPACE_BYTES are refused with
- *     TTF_ERR_WORKSPACE_TOO_SMALL before anything is launched.
+ *     TTF_ERR_WORKSPACE_TOO_SMALL before anything is launched.  (bf16 rows with C % 32 != 0 count as they
+ *     are, without the room that lets large problems of such rows take the matrix-core search.)
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  *     streams, two threads) race and give undefined outputs; order them on one stream or with events.
  *     The array keeps the previous call's contents; nothing in it needs to start at zero.
