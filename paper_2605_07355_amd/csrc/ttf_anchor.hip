@@ -16,11 +16,14 @@ namespace {
 
 constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every clip is already in anchor_index
 
-// One block = one frame x one slice of 64*V channels x one of `parts` runs of rows.  Wave w adds rows w,
-// w+4, ... of the run; the four partial sums are combined through LDS in wave order, so the result is
-// order-stable, and stored as share `part` of the frame: out[frame][part][C].  Bound by latency where there
-// are few blocks (B1 F32 16x16 C2048: 128 without parts, 2.5 TB/s); eight rows are in flight per wave.  Whole
-// calls without -> with parts: that one 47.4 -> 44.5 us, B3 F23 24x18 C1000 84.8 -> 74.0.
+// One block = one frame x one slice of 64*V channels x one of `parts` runs of rows (whole rounds of 16 rows
+// but for the last run).  Wave w adds rows w, w+4, ... of the run; the four partial sums are combined through
+// LDS in wave order, so the result is order-stable, and stored as share `part` of the frame:
+// out[frame][part][C].  Bound by HBM on large inputs and by latency where there are few blocks.  Four rows are
+// in flight per wave, and none behind a guard of its own: a load under a guard is waited for before the next
+// one is issued.  Kernel alone, eight guarded rows -> four plain ones: B64 F32 16x16 C256 76 -> 45 us (6.0
+// TB/s), B16 F32 16x16 C4000 196 -> 178, B1 F64 14x14 C2048 26 -> 12.  One block per frame and slice -> parts:
+// B1 F32 16x16 C2048 13.5 -> 7.8, B3 F23 24x18 C1000 22 -> 13, B1 F32 64x64 C256 151 -> 22.
 // `spec` (may be null): per clip {guessed anchor, guess trusted, ...}; clips with a trusted guess get
 // their exact sums from the search and are skipped here.
 template <typename T, int V>
@@ -32,7 +35,7 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
     const int run = blockIdx.x % parts;
     if (spec && spec[4 * (frame / F) + 1]) return;
     const int c0 = (blockIdx.y * 64 + lane) * V;
-    const int per = (N + parts - 1) / parts;
+    const int per = ((N + parts - 1) / parts + 15) / 16 * 16;
     const int lo = run * per, hi = min(N, lo + per);
     __shared__ float part[4][64 * V];
     float acc[V];
@@ -40,18 +43,22 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     if (c0 < C) {
         const T* base = x + frame * (size_t)N * C + c0;
-        for (int i0 = lo + wave; i0 < hi; i0 += 32) {
-            RowVec<T, V> r[8];
+        int i = lo + wave;
+        for (; i + 12 < hi; i += 16) {         // four rows in flight per wave
+            RowVec<T, V> r[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (i0 + 4 * u < hi) r[u].template load<true>(base + (size_t)(i0 + 4 * u) * C);
+            for (int u = 0; u < 4; ++u) r[u].template load<true>(base + (size_t)(i + 4 * u) * C);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + 4 * u < hi) {
+            for (int u = 0; u < 4; ++u) {
 #pragma unroll
-                    for (int e = 0; e < V; ++e) acc[e] += r[u].v[e];
-                }
+                for (int e = 0; e < V; ++e) acc[e] += r[u].v[e];
             }
+        }
+        for (; i < hi; i += 4) {
+            RowVec<T, V> r0;
+            r0.template load<true>(base + (size_t)i * C);
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[e] += r0.v[e];
         }
     }
 #pragma unroll
@@ -791,7 +798,9 @@ static int frame_sum_parts(const ttf_params& p, const Workspace& w)
     size_t parts = std::min<size_t>(8, (1024 + blocks / 2) / blocks);
     parts = std::min<size_t>(parts, (size_t)p.H * p.W / 32);
     parts = std::min<size_t>(parts, w.frag_bytes / share);
-    return parts < 2 ? 1 : (int)parts;
+    if (parts < 2) return 1;
+    const size_t N = (size_t)p.H * p.W, per = align_up((N + parts - 1) / parts, 16);
+    return (int)((N + per - 1) / per);                       // (no run is empty)
 }
 
 hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, hipStream_t s)
