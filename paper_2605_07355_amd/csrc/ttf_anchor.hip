@@ -785,7 +785,11 @@ static bool frame_sums_by_slab(const ttf_params& p)
     return p.C % (256 * V) == 0 && (size_t)p.B * p.F * (p.C / (256 * V)) >= 512;
 }
 
-// Runs of rows a frame is cut into by k_frame_sums: as many as make about 1024 blocks, of at least 32 rows.
+// Runs of rows a frame is cut into by k_frame_sums: as many as make no more than 512 blocks, two for every CU,
+// of at least 32 rows.  Beyond that a share more costs more than it hides (sums and their addition together,
+// us, by blocks without parts): 128 blocks (B4 F16 16x16 C1024) 22 / two 16 / four 14 / eight 14.6; 240 (B1 F40
+// 32x32 C3000) 58.5 / two 46 / four 51; 350 (B1 F50 32x16 C3328) 37.4 / two 37.5 / three 41; 512 (B4 F64 16x16
+// C1024) 29.6 / two 31.2; 612 (B9 F34 32x32 C320 fp32) 72 / two 82.
 // The shares stand in the anchor's fragment copy, which is written after the anchor has been chosen, so
 // they have to fit there (short clips and long rows may get fewer).  Row lengths of whole 16-byte pieces
 // only: k_anchor_partials adds the shares with 16-byte loads.
@@ -795,7 +799,7 @@ static int frame_sum_parts(const ttf_params& p, const Workspace& w)
     if (p.C % V != 0 || frame_sums_by_slab(p)) return 1;
     const size_t blocks = (size_t)p.B * p.F * ((p.C + 64 * V - 1) / (64 * V));
     const size_t share = (size_t)p.B * p.F * p.C * sizeof(float);
-    size_t parts = std::min<size_t>(8, (1024 + blocks / 2) / blocks);
+    size_t parts = std::min<size_t>(8, 512 / blocks);
     parts = std::min<size_t>(parts, (size_t)p.H * p.W / 32);
     parts = std::min<size_t>(parts, w.frag_bytes / share);
     if (parts < 2) return 1;
