@@ -12,8 +12,19 @@ namespace ttf {
 namespace {
 
 constexpr int kPlaceWords = 16;                // keep words per block of k_place_ids
+// The forms of the row placement, us of a re-gating call with a third of the tokens kept (graph replays):
+// k_place_rows / k_place_ids + k_copy_rows / scan + k_emit_ids + k_copy_rows.
+//   256 words: 1 KiB rows 8.8 / 10.2 / 11.6, 4 KiB rows (64 MiB) 15.1 / 16.1 / 17.7, 8 KiB (128 MiB) 23.6 / 23.1 / 24.4;
+//   384 words, 2 KiB rows (48 MiB): 14.7 / 14.5 / 16.0;  512 words, 2 KiB rows (64 MiB): 16.9 / 16.3 / 17.5;
+//   1024 words, 1 KiB rows: 20.9 / 16.8 / 17.7.
+// A wave of k_place_rows copies up to four rows one after the other, so rows have a limit too: 64 words of 8 KiB
+// rows 11.0 / 12.1 / 13.1, of 16 KiB rows 18.1 / 15.8 / 17.0, 4 words of 128 KiB rows 52 / 24 / 26.  (Rows that
+// are not whole 16-byte pieces are copied by a wave each in every form.)
+// Counting in every block of k_place_ids against the scan: 4096 words 39.4 / 41.7, 8192 69.3 / 73.0, 16384 131.6 /
+// 137.0 (1 KiB rows); the line stands below the crossing, which was not met.
 constexpr size_t kPlaceAllWords = 256;         // at most this many keep words: offsets, ids and rows in one launch
 constexpr size_t kPlaceAllBytes = 64ull << 20; // ... and this much input
+constexpr size_t kPlaceAllRow = 8192;          // ... in rows of whole 16-byte pieces of at most this length
 constexpr size_t kPlaceIdsWords = 4096;        // at most this many: offsets and ids in one launch
 
 // Exclusive scan over the sequence  [N, c(b,0), ..., c(b,F-1)]  for b = 0..B-1, where c(b,k) is
@@ -160,9 +171,13 @@ __device__ __forceinline__ int first_row(int clips, int words, int k, int a, int
 // short and the two launches ahead of it (offsets, ids) take longer than their work.  Block = 16 tokens
 // (a quarter of a keep word) of one frame, its kept tokens dealt to the four waves by rank; it counts the rows
 // ahead of it itself (whole calls: B1 F4 8x8 C256 fp32 28.9 -> 23.8 us, segment
-// of B1 F8 16x16 C4096 29.1 -> 24.4, B1 F32 16x16 C2048 50.5 -> 47.4).  Larger calls keep the faster copy of
-// k_copy_rows.  tied_rows as for
-// k_emit_rows: blockIdx.y = clip, the mask is the shared one ([F,NW]).
+// of B1 F8 16x16 C4096 29.1 -> 24.4, B1 F32 16x16 C2048 50.5 -> 47.4).  Larger calls and longer rows keep the
+// faster copy of k_copy_rows.  tied_rows as for k_emit_rows: blockIdx.y = clip, the mask is the shared one ([F,NW]).
+//
+// Blocks go round robin to the XCDs, and inside an XCD to its CUs.  The quarter a block takes moves on with its
+// word, so that the filled quarters of short frames (N <= 48) meet every XCD; each 256 blocks are turned by
+// five CUs against those before, so that anchor frames a power of two of words apart do not meet on one CU
+// (re-gating, quarters in block order -> so: B64 F4 4x4, 8 KiB rows 26.2 -> 14.1 us, B4 F64 8x8, 4 KiB rows 18.9 -> 15.5).
 template <int U>
 __global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, const uint64_t* __restrict__ keep_bits,
                                                     const int32_t* __restrict__ anchor_index,
@@ -172,10 +187,12 @@ __global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, 
                                                     size_t row_bytes, size_t cap, int frame_offset, size_t tied_rows)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int quarter = blockIdx.x & 3;
-    const size_t wd = blockIdx.x >> 2;                       // keep word over all clips
+    const unsigned turn = (blockIdx.x | 255u) < gridDim.x ? 40u * (blockIdx.x >> 8) : 0u;
+    const unsigned slot = (blockIdx.x & ~255u) | ((blockIdx.x + turn) & 255u);
+    const int wd = (int)(slot >> 2);                         // keep word over all clips
+    const int quarter = (int)((slot + (slot >> 3)) & 3u);
     const int per_clip = F * NW;
-    const int b = (int)(wd / per_clip), word = (int)(wd % per_clip);
+    const int b = wd / per_clip, word = wd % per_clip;
     const int k = word / NW, q = word % NW;
     const bool ids = blockIdx.y == 0;
     const uint64_t wbits = keep_bits[wd];
@@ -327,7 +344,8 @@ inline Placement placement(const ttf_params& p, bool tied)
     const size_t row_bytes = (size_t)p.C * (p.dtype == TTF_BF16 ? 2 : 4);
     const size_t tokens_bytes = (size_t)p.B * p.F * p.H * p.W * row_bytes;
     if (tied && p.B > 65535) return Placement::scan;         // (clips ride on gridDim.y)
-    if (words <= kPlaceAllWords && tokens_bytes <= kPlaceAllBytes) return Placement::all;
+    if (words <= kPlaceAllWords && tokens_bytes <= kPlaceAllBytes && (row_bytes <= kPlaceAllRow || row_bytes % 16 != 0))
+        return Placement::all;
     if (row_bytes % 16 == 0 && row_bytes >= kRowBlockMin && words <= kPlaceIdsWords) return Placement::ids;
     return Placement::scan;
 }

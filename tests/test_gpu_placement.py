@@ -1,6 +1,9 @@
 """GPU parity of the row placement at the limits of its forms: everything in one launch (at most 256 keep
 words), offsets with the ids (at most 4096, rows of 1 KiB and more), and behind a scan (beyond, or short rows)."""
+import statistics
+
 import pytest
+import torch
 
 from workloads import CONFIGS
 
@@ -24,3 +27,41 @@ def test_row_placement(B, F, H, W, C, anchor):
     if anchor == "auto" and F > 300:
         anchor = F // 2                              # (thousands of frames of one scene: no clear winner to demand)
     _parity(cfg, seed=40 + F, anchor=anchor)
+
+
+def _regate_us(B, F, H, W, row_bytes):
+    """Time of a re-gating call with a third of the tokens kept, from replays of a graph of ten."""
+    import paper_2605_07355_amd as ttf
+    C = row_bytes // 2
+    x = torch.randn((B, F, H, W, C), device="cuda", dtype=torch.bfloat16)
+    buf = ttf.TTFBuffers.allocate(B, F, H, W, C, x.dtype, x.device)
+    buf.best_sim.copy_(torch.rand((B, F, H * W), generator=torch.Generator().manual_seed(F)))
+    buf.best_idx.zero_()
+    buf.anchor_index.fill_(F // 2)
+    out = ttf.TTFOutput(buf, B, F, H, W, C)
+    ttf.ttf_regate(x, out, t=0.33)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(10):
+            ttf.ttf_regate(x, out, t=0.33)
+    times = []
+    for _ in range(12):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(3):
+            graph.replay()
+        e1.record()
+        torch.cuda.synchronize()
+        times.append(e0.elapsed_time(e1) / 30 * 1e3)
+    return statistics.median(times[2:])
+
+
+@pytest.mark.parametrize("B,F,H,W,row_bytes,times", [
+    (64, 4, 4, 4, 8192, 1.7),        # one filled quarter a word: 14 us, 26 where they meet on two XCDs
+    (1, 4, 8, 8, 131072, 3.2),       # four words of long rows: 24 us, 52 with a wave per row
+])
+def test_time_of_unusual_row_sets(B, F, H, W, row_bytes, times):
+    """Against 64 whole words of 8 KiB rows, as many bytes (11 us)."""
+    plain = _regate_us(1, 64, 8, 8, 8192)
+    assert _regate_us(B, F, H, W, row_bytes) <= times * plain
