@@ -1,6 +1,7 @@
 // C ABI of the TTF library: argument checks, workspace carving, the launch sequence of
 // Section 3 (anchor selection -> window search + gate -> offsets -> row emission) and the
 // optional per-stage event timing.  Nothing here allocates device memory.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -27,16 +28,17 @@ hipError_t launch_window_search_mfma_f32(const ttf_params& p, const void* x, boo
 
 // bf16 and fp32 tokens with r <= 2 and C % 32 == 0 take the matrix-core kernels (grids exactly 16 or 32
 // wide with whole keep words the aligned ones, every other grid the padded-tile ones), bf16 tokens also with
-// the channel counts of tail_channels() (`tail`: the workspace has room for them); larger radii and
-// other channel counts take the general wave-per-token kernel.  The environment variable TTF_SEARCH=general, read once per process, forces
-// the general kernels (for comparisons).
+// the channel counts of tail_channels() where the workspace has room for them (`tail`) and it pays; larger
+// radii and other channel counts take the general wave-per-token kernel.  The environment variable
+// TTF_SEARCH=general, read once per process, forces the general kernels (for comparisons).
 bool use_mfma_path(const ttf_params& p, bool tail = true)
 {
     static const bool general = [] {
         const char* force = std::getenv("TTF_SEARCH");
         return force && std::strcmp(force, "general") == 0;
     }();
-    return !general && (tail || !tail_channels(p)) && (mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p));
+    if (general || (tail_channels(p) && !(tail && tail_search_pays(p, std::max(p.F - 1, 1))))) return false;
+    return mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p);
 }
 
 // Anchor preparation of the matrix-core path for the element type at hand (fp32: three bf16 planes).

@@ -167,6 +167,7 @@ hipError_t launch_anchor_prepare_mfma_f32(const ttf_params& p, const void* x, co
                                           float* best_sim, int32_t* best_idx, bool anchor_given, hipStream_t s);
 bool mfma_search_supported(const ttf_params& p);   // grids exactly 16 or 32 wide with whole keep words
 bool mfma_search_padded(const ttf_params& p);      // every other grid (tile rows padded to 16 columns)
+bool tail_search_pays(const ttf_params& p, int frames);   // tail_channels() rows: large enough for them
 hipError_t launch_window_search(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                                 const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
                                 int32_t* best_idx, float* win_sim, hipStream_t s);

@@ -904,30 +904,42 @@ bool mfma_search_supported(const ttf_params& p)
 }
 
 // Same element type and radius, but any grid, and rows that end inside a K-step (tail_channels()) too:
-// served by the padded-tile kernels.
-//
-// Rows that end inside a K-step need enough workgroups: one walks the whole channel axis, so a handful
-// takes longer than the wave-per-token kernels, which spread the tokens over hundreds of waves.  Whole
-// calls, wave-per-token -> matrix cores, us: 32 workgroups (B1 F16 16x16 C1000) 46 -> 54; 64 (B1 F17 16x32
-// C4072) 124 -> 130, (B2 F16 16x16 C2008) 79 -> 76; 96 (B1 F16 24x24 C1000 r0) 77 -> 68; 128 (B2 F32 16x16
-// C1000) 88 -> 64; 432 (B3 F23 24x18 C1000) 145 -> 86; 1320 (B12 F45 10x32 C1552) 831 -> 338.  Wider than
-// 32, where a strip fetches twice the anchor tiles: 72 (B1 F17 9x40 C1000) 60 -> 75; 160 (20x40) 106 -> 96.
-// On grids wider than 32 the 5x5 window keeps the wave-per-token kernels: two sets of its accumulators
-// do not fit the registers (419 spilled, B1 F16 20x40 C1000 0.143 against 0.189 ms).
+// served by the padded-tile kernels.  For such rows not the 5x5 window on grids wider than 32, whose two
+// sets of accumulators do not fit the registers (419 spilled, B1 F16 20x40 C1000: wave-per-token 0.143 ms,
+// this 0.189).
 bool mfma_search_padded(const ttf_params& p)
 {
     if (p.dtype != TTF_BF16 || p.r > 2 || !(p.C % 32 == 0 || tail_channels(p))) return false;
-    if (tail_channels(p)) {
-        const int ct = p.W <= 16 ? 1 : (p.W <= 32 ? 2 : 3);
-        if (ct == 3 && p.r == 2) return false;
-        const long long groups = (std::max(p.F - 1, 1) + 3) / 4;
-        const long long strips = ct == 1 ? (p.H + 1) / 2 : (ct == 2 ? p.H : (long long)p.H * (((p.W + 15) / 16 + 1) / 2));
-        if (p.B * groups * strips < (ct == 3 ? 144 : 96)) return false;
-    }
+    if (tail_channels(p) && p.W > 32 && p.r == 2) return false;
     // the padded kernels index a clip's anchor fragments with 32-bit offsets
     const long long padded_tokens = (long long)p.H * ((p.W + 15) / 16) * 16;
     if (padded_tokens * (long long)align_up(p.C, 32) >= (1ll << 31)) return false;
     return !mfma_search_supported(p);
+}
+
+// Whether rows that end inside a K-step, `frames` of them walked per clip, are searched faster on the matrix
+// cores than by the wave-per-token kernels.  The latter run a workgroup of 16 waves per quarter keep word, two
+// at a time on a CU, so their time steps with the keep words and quarters that hold tokens; the former run a
+// workgroup per 32-cell strip of four frames, however many of those cells and frames exist, and each walks the
+// whole channel axis, so a handful takes longer than hundreds of waves.  Hence lines on both counts, in
+// proportion to the rounds that the strips' workgroups make on the chip.  Measured on 1500 random shapes
+// of 96 to 1200 workgroups and C 776 to 4072 (whole calls, matrix cores / wave-per-token):
+//   up to 16 columns, r <= 1: below 80 words or 192 quarters 0.9-2.1 (B8 F9 16x4 C4072 89 / 65 us, B1 F49 16x1
+//     C4072 75 / 48), above 0.2-1.1 (B3 F33 20x4 C1512 49 / 67); r 2: 192 quarters alone;
+//   up to 32, r <= 1: below 384 quarters 0.8-1.5 (B8 F2 14x28 C1512 53 / 40), above 0.2-1.06; r 2: 192;
+//   wider: r 0 256 quarters, r 1 640 (below 1.0-1.7: B6 F2 16x72 C1512 108 / 64, above 0.5-1.04), against rounds
+//     of 192 workgroups, which fetch twice the anchor tiles.
+bool tail_search_pays(const ttf_params& p, int frames)
+{
+    const int ct = p.W <= 16 ? 1 : (p.W <= 32 ? 2 : 3);
+    const long long n = (long long)p.H * p.W, walked = (long long)p.B * frames;
+    const long long strips = ct == 1 ? (p.H + 1) / 2 : (ct == 2 ? p.H : (long long)p.H * (((p.W + 15) / 16 + 1) / 2));
+    const long long wgs = (long long)p.B * ((frames + 3) / 4) * strips;
+    if (wgs < (ct == 3 ? 144 : 96)) return false;
+    const long long resident = ct == 3 ? 192 : 512, rounds = std::max(wgs, resident);   // (in 1/resident of a round)
+    const long long words = ct == 1 && p.r <= 1 ? 80 : 0;
+    const long long quarters = ct == 3 ? (p.r == 0 ? 256 : 640) : (ct == 2 && p.r <= 1 ? 384 : 192);
+    return walked * ((n + 63) / 64) * resident >= words * rounds && walked * ((n + 15) / 16) * resident >= quarters * rounds;
 }
 
 // True when the speculative anchor path can run this problem's search.
