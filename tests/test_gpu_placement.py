@@ -65,3 +65,25 @@ def test_time_of_unusual_row_sets(B, F, H, W, row_bytes, times):
     """Against 64 whole words of 8 KiB rows, as many bytes (11 us)."""
     plain = _regate_us(1, 64, 8, 8, 8192)
     assert _regate_us(B, F, H, W, row_bytes) <= times * plain
+
+
+@pytest.mark.parametrize("B,F,H,W,C,one_launch", [
+    (1, 49, 16, 4, 2504, True),      # 5008-byte rows
+    (1, 49, 16, 4, 3592, False),     # 7184: single pieces at their end (regate of 128 words: 17.7 us, by waves 22.9)
+    (1, 49, 16, 4, 4072, False),
+    (1, 8, 8, 8, 4096, True),        # 8 KiB: one whole round a lane
+    (1, 8, 8, 8, 8192, False),
+    (1, 8, 8, 8, 4097, True),        # no whole 16-byte pieces: a wave a row in every form
+])
+def test_rows_that_are_placed_by_waves(B, F, H, W, C, one_launch):
+    """The list of source rows at the end of the workspace is written by the two-launch form only."""
+    import paper_2605_07355_amd as ttf
+    x = torch.randn((B, F, H, W, C), device="cuda").to(torch.bfloat16)
+    buf = ttf.TTFBuffers.allocate(B, F, H, W, C, x.dtype, x.device)
+    buf.workspace.fill_(0xCD)
+    ttf.ttf_compress(x, buffers=buf)
+    torch.cuda.synchronize()
+    head = -buf.workspace.data_ptr() % 256
+    end = head + ttf.ttf_workspace_size(B, F, H, W, C, x.dtype)
+    size = (B * F * H * W * 4 + 255) // 256 * 256
+    assert (buf.workspace[end - size:end] == 0xCD).all().item() == one_launch
