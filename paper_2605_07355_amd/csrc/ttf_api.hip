@@ -1,7 +1,6 @@
 // C ABI of the TTF library: argument checks, workspace carving, the launch sequence of
 // Section 3 (anchor selection -> window search + gate -> offsets -> row emission) and the
 // optional per-stage event timing.  Nothing here allocates device memory.
-#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -28,16 +27,17 @@ hipError_t launch_window_search_mfma_f32(const ttf_params& p, const void* x, boo
 
 // bf16 and fp32 tokens with r <= 2 and C % 32 == 0 take the matrix-core kernels (grids exactly 16 or 32
 // wide with whole keep words the aligned ones, every other grid the padded-tile ones), bf16 tokens also with
-// the channel counts of tail_channels() where the workspace has room for them (`tail`) and it pays; larger
+// the channel counts of tail_channels() where the workspace has room for them (`tail`) and it pays for the
+// frames that are walked (all of them against an external anchor, all but the anchor otherwise); larger
 // radii and other channel counts take the general wave-per-token kernel.  The environment variable
 // TTF_SEARCH=general, read once per process, forces the general kernels (for comparisons).
-bool use_mfma_path(const ttf_params& p, bool tail = true)
+bool use_mfma_path(const ttf_params& p, bool tail, bool external_anchor)
 {
     static const bool general = [] {
         const char* force = std::getenv("TTF_SEARCH");
         return force && std::strcmp(force, "general") == 0;
     }();
-    if (general || (tail_channels(p) && !(tail && tail_search_pays(p, std::max(p.F - 1, 1))))) return false;
+    if (general || (tail_channels(p) && !(tail && tail_search_pays(p, external_anchor ? p.F : p.F - 1)))) return false;
     return mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p);
 }
 
@@ -57,7 +57,7 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
                                 const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
                                 int32_t* best_idx, float* win_sim, hipStream_t s)
 {
-    if (use_mfma_path(p, w.tail)) {
+    if (use_mfma_path(p, w.tail, ext_anchor != nullptr)) {
         if (p.dtype == TTF_F32)
             return launch_window_search_mfma_f32(p, x, ext_anchor != nullptr, w, anchor_index, fuse_map, best_sim,
                                                  best_idx, win_sim, s);
@@ -161,7 +161,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     Workspace w = carve(p, workspace);
     if (workspace_bytes < w.bytes) w = carve(p, workspace, false);
     if (workspace_bytes < w.bytes) return TTF_ERR_WORKSPACE_TOO_SMALL;
-    const bool mfma = use_mfma_path(p, w.tail);
+    const bool mfma = use_mfma_path(p, w.tail, ext_anchor != nullptr);
     const bool pick = !ext_anchor && p.anchor_mode == TTF_ANCHOR_AUTO;       // the automatic anchor rule runs
 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
@@ -336,7 +336,7 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
         TTF_STEP(launch_anchor_scores(p, w, false, s));
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));
-    if (use_mfma_path(p, w.tail))
+    if (use_mfma_path(p, w.tail, false))
         TTF_STEP(launch_anchor_prepare_any(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
                                            true, 0, s));
     else TTF_STEP(launch_anchor_norms(p, features, nullptr, w, out->anchor_index, true, s));
@@ -458,7 +458,7 @@ ttf_status ttf_search_route(const ttf_params* params, int* route)
     const ttf_status st = check_params(params);
     if (st != TTF_OK) return st;
     const ttf_params& p = *params;
-    *route = !use_mfma_path(p)              ? TTF_ROUTE_GENERAL
+    *route = !use_mfma_path(p, true, false) ? TTF_ROUTE_GENERAL
            : p.dtype == TTF_F32             ? TTF_ROUTE_MFMA_F32
            : mfma_search_supported(p)       ? TTF_ROUTE_MFMA_BF16
                                             : TTF_ROUTE_MFMA_BF16_PADDED;

@@ -114,3 +114,21 @@ def test_non_finite_values_in_the_last_pieces():
     assert torch.equal(a[~fin & ~torch.isnan(b)], b[~fin & ~torch.isnan(b)]) and (~fin).any()
     assert (a[fin] - b[fin]).abs().max().item() <= 2 * SIM_TOL
     assert torch.equal(outs[0].kept_count, outs[1].kept_count)
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r", [
+    (6, 5, 16, 16, 1000, 1),     # five frames are walked, in two groups of four: 96 workgroups
+    (6, 4, 16, 16, 1000, 1),     # four: 48, wave per token
+    (4, 9, 14, 18, 776, 0),
+])
+def test_a_segment_takes_the_search_of_its_clip(B, F, H, W, C, r):
+    """A segment is the clip [anchor ; segment] with its anchor fixed to frame 0: the same kernels, the same bits."""
+    import paper_2605_07355_amd as ttf
+    x = torch.randn((B, F + 1, H, W, C), generator=torch.Generator().manual_seed(C)).to(torch.bfloat16).cuda()
+    x[:, 2:] += x[:, :1]
+    clip = ttf.ttf_compress(x, r=r, t=0.6, anchor=0).buffers
+    seg = ttf.ttf_compress_segment(x[:, 1:].contiguous(), x[:, 0].contiguous(), 0, r=r, t=0.6).buffers
+    torch.cuda.synchronize()
+    assert torch.equal(seg.best_sim, clip.best_sim[:, 1:])
+    assert torch.equal(seg.best_idx, clip.best_idx[:, 1:])
+    assert torch.equal(seg.fuse_map, clip.fuse_map[:, 1:])
