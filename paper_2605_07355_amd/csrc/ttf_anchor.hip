@@ -654,10 +654,23 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
     if ((lane & 3) == 0) part[wave][lane >> 2] = nn;
     __syncthreads();
     if (threadIdx.x < 16) {
-        float ss = part[0][threadIdx.x];
+        float ss = part[0][threadIdx.x], inv;
+        if (PAD && C % 32 != 0) {
+            // rows that end inside a K-step: eight shares and inverse root rounded once each, so that the
+            // similarities are no less exact than the wave-per-token kernels' (relative error against 64 bits at
+            // C 776 and 4072: theirs 7.4e-8 and 9.1e-8; here with fp32 shares and root 7.7e-8 and 8.2e-8, so 7.2e-8
+            // and 7.3e-8)
+            double sum = (double)ss;
 #pragma unroll
-        for (int w = 1; w < 8; ++w) ss += part[w][threadIdx.x];
-        anchor_inv[((size_t)b * tiles + tile) * 16 + threadIdx.x] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+            for (int w = 1; w < 8; ++w) sum += (double)part[w][threadIdx.x];
+            ss = (float)sum;                                 // (overflows as the fp32 sum does)
+            inv = (float)(1.0 / sqrt((double)ss));
+        } else {
+#pragma unroll
+            for (int w = 1; w < 8; ++w) ss += part[w][threadIdx.x];
+            inv = 1.0f / sqrtf(ss);
+        }
+        anchor_inv[((size_t)b * tiles + tile) * 16 + threadIdx.x] = ss > 0.f ? inv : 0.f;
     }
 }
 
