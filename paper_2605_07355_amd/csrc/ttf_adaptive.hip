@@ -27,11 +27,12 @@ __device__ __forceinline__ float key_value(uint32_t k)
     return __builtin_bit_cast(float, u);
 }
 
-// What bounds it: one workgroup per clip counts a few thousand to a few hundred thousand values four times.
-// Clips of at most 8 values per thread are read once and stay in registers (B8, 8192 values: whole
-// select + re-gate call 83.3 -> 82.9 us; 16 values per thread, twice the unrolled code: 87.6); for longer ones
-// the third pass reads the values a last time and, once the digits so far have thinned them out, leaves
-// the keys that still match in LDS for the last two counts (B1 F236 32x17: 234 -> 207 us).
+// What bounds it: one workgroup per clip counts a few hundred to a million values four times.  Once the
+// digits chosen so far leave at most kSelectList keys, the next count also lists them in LDS, and the counts
+// after it read the list: two or three reads of the values, four where more keys than that share two digits
+// (equal values, say).  Kernel alone, four reads -> this: one clip of 256 values 8.2 -> 6.8 us, eight
+// of 8192 14.0 -> 12.3, one of 128 384 132 -> 104, one of 1 048 576 1036 -> 802; equal values the same.  Values
+// kept in registers between the counts (8192 and fewer) made it slower: 8.8 and 13.4 us.
 constexpr int kSelectUnroll = 8;                    // values in flight per thread
 constexpr int kSelectList = 8192;                    // keys kept in LDS (32 KiB)
 
@@ -63,23 +64,20 @@ __global__ __launch_bounds__(1024) void k_select_threshold(const float* __restri
     __shared__ uint32_t list[kSelectList];
     if (threadIdx.x == 0) { s_prefix = 0u; s_k = rank - 1; s_match = 0xffffffffu; s_listed = 0u; }
     uint32_t mask = 0u;
-    const bool resident = FN <= kSelectUnroll * 1024;
     bool listed = false;                             // uniform over the block
-    float v[kSelectUnroll];
     for (int shift = 24; shift >= 0; shift -= 8) {
         for (int q = lane; q < 256; q += 64) hist[wave][q] = 0u;
         __syncthreads();
         const uint32_t prefix = s_prefix;
-        const bool collect = !resident && !listed && s_match <= (unsigned)kSelectList;
+        const bool collect = !listed && s_match <= (unsigned)kSelectList;
         if (!listed) {
             // all loads of a round in flight before their counts are added
             for (long long j0 = threadIdx.x; j0 < FN; j0 += kSelectUnroll * 1024) {
-                if (!resident || shift == 24) {
+                float v[kSelectUnroll];
 #pragma unroll
-                    for (int u = 0; u < kSelectUnroll; ++u) {
-                        const long long j = j0 + 1024 * u;
-                        v[u] = j < FN ? sim[j] : 0.f;
-                    }
+                for (int u = 0; u < kSelectUnroll; ++u) {
+                    const long long j = j0 + 1024 * u;
+                    v[u] = j < FN ? sim[j] : 0.f;
                 }
 #pragma unroll
                 for (int u = 0; u < kSelectUnroll; ++u) {

@@ -1,5 +1,5 @@
-"""GPU parity of the threshold selection around the sizes where its forms change: values kept in registers
-(at most 8192 per clip), keys listed once at most 8192 match, and fields that never thin out (equal values)."""
+"""GPU parity of the threshold selection around the sizes where its forms change: clips of one round of loads
+(8192 values) and more, keys listed once at most 8192 match, and fields that never thin out (equal values)."""
 import numpy as np
 import pytest
 import torch
