@@ -2,11 +2,14 @@
 words), offsets with the ids (at most 4096, rows of 1 KiB and more), and behind a scan (beyond, or short rows)."""
 import statistics
 
+import numpy as np
 import pytest
 import torch
 
-from workloads import CONFIGS
+from workloads import CONFIGS, similarity_field
 
+from helpers import SENTINEL
+from test_gpu_next import _compare_segment, _compare_tied, _run_segment, _run_tied, _segment_case, _tied_case
 from test_gpu_parity import _parity
 
 pytestmark = pytest.mark.gpu
@@ -21,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (5, 33, 9, 9, 512),      # 330 words, clips of 66: four whole runs and one of two words
     (2, 2048, 1, 2, 512),    # 4096 words: the last without a scan
     (1, 4097, 1, 2, 512),    # 4097 words
+    (3, 86, 32, 33, 512),    # 4386 words, 17 a frame, the last one half full: behind the scan, rows of 1 KiB
 ])
 def test_row_placement(B, F, H, W, C, anchor):
     cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, sigma=0.5)
@@ -87,3 +91,82 @@ def test_rows_that_are_placed_by_waves(B, F, H, W, C, one_launch):
     end = head + ttf.ttf_workspace_size(B, F, H, W, C, x.dtype)
     size = (B * F * H * W * 4 + 255) // 256 * 256
     assert (buf.workspace[end - size:end] == 0xCD).all().item() == one_launch
+
+
+def _expected_rows(sim, anchor, t, N):
+    """Flat index (over clips and frames) of every output row, and the rows of every clip, at threshold t."""
+    rows, counts = [], []
+    B, F = sim.shape[:2]
+    for b in range(B):
+        keep = sim[b] <= t
+        first = [] if anchor[b] < 0 else list(anchor[b] * N + np.arange(N))
+        if anchor[b] >= 0:
+            keep[anchor[b]] = False
+        clip = np.concatenate([np.array(first, np.int64), np.flatnonzero(keep.reshape(-1))])
+        rows.append(clip + b * F * N)
+        counts.append(clip.size)
+    return np.concatenate(rows), np.array(counts)
+
+
+@pytest.mark.parametrize("segment", [False, True])
+@pytest.mark.parametrize("B,F,H,W,C", [
+    (3, 86, 32, 33, 512),        # 4386 words behind the scan, 17 a frame
+    (2, 129, 16, 64, 512),       # 4128 words, 16 a frame, all full
+    (64, 65, 3, 5, 520),         # 4160 words of 15 tokens
+    (3, 80, 32, 33, 512),        # 4080 words: ids with the offsets
+    (5, 51, 9, 7, 500),          # 255 words, 1000-byte rows: one launch
+    (16, 5, 13, 15, 1024),       # 320 words, four a frame
+])
+def test_rows_of_stored_similarities(B, F, H, W, C, segment):
+    """Placement alone, behind the re-gating entry point: every output row, id, count and offset, rows past the last
+    untouched.  No decision margins are needed: the similarities are given."""
+    import paper_2605_07355_amd as ttf
+    N, t = H * W, 0.6
+    sim, anchor = similarity_field(B, F, N, seed=B + F)
+    if segment:
+        anchor = np.full(B, -1, np.int32)
+    x = torch.randint(-2 ** 15, 2 ** 15, (B, F, H, W, C), dtype=torch.int16, device="cuda",
+                      generator=torch.Generator(device="cuda").manual_seed(7)).view(torch.bfloat16)
+    buf = ttf.TTFBuffers.allocate(B, F, H, W, C, x.dtype, x.device)
+    buf.tokens_out.view(torch.uint8).fill_(0x7A)
+    for v in (buf.pos_ids, buf.src_index, buf.row_offsets, buf.kept_count, buf.fuse_map):
+        v.fill_(SENTINEL)
+    buf.workspace.fill_(0xCD)
+    buf.best_sim.copy_(torch.from_numpy(sim))
+    buf.best_idx.copy_(torch.arange(N, dtype=torch.int32, device="cuda"))
+    buf.anchor_index.copy_(torch.from_numpy(anchor))
+    ttf.ttf_regate(x, ttf.TTFOutput(buf, B, F, H, W, C), t=t)
+    torch.cuda.synchronize()
+    rows, counts = _expected_rows(sim, anchor, np.float32(t), N)
+    total = rows.size
+    np.testing.assert_array_equal(buf.kept_count.cpu().numpy(), counts)
+    np.testing.assert_array_equal(buf.row_offsets.cpu().numpy(), np.concatenate([[0], np.cumsum(counts)]))
+    src, pos = buf.src_index.cpu().numpy(), buf.pos_ids.cpu().numpy()
+    flat = rows % (F * N)
+    np.testing.assert_array_equal(src[:total], flat)
+    np.testing.assert_array_equal(pos[:, :total], np.stack([flat // N, flat % N // W, flat % N % W]))
+    assert (src[total:] == SENTINEL).all() and (pos[:, total:] == SENTINEL).all()
+    want = x.view(torch.int16).view(B * F * N, C)[torch.from_numpy(rows).cuda()]
+    assert torch.equal(buf.tokens_out.view(torch.int16)[:total], want)
+    assert (buf.tokens_out.view(torch.int16)[total:] == 0x7A7A).all()
+
+
+@pytest.mark.parametrize("B,F,H,W,C", [
+    (2, 260, 32, 33, 512),       # 4420 shared words behind the scan, rows of 1 KiB
+    (3, 130, 9, 9, 512),         # 260 words: ids with the offsets
+    (3, 127, 9, 9, 64),          # 254: one launch
+])
+def test_tied_row_placement(B, F, H, W, C):
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, sigma=0.5, shared_motion=True)
+    batch, res = _tied_case(cfg, cfg.t[0], F // 2)
+    _compare_tied(batch.x, _run_tied(batch.x, cfg.r, cfg.t[0], F // 2), res)
+    assert 0 < (res.fuse_map >= 0).mean() < 1
+
+
+def test_segment_row_placement_behind_the_scan():
+    from oracle import streaming as S
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=3, F=87, H=32, W=33, C=512, sigma=0.5)
+    batch = _segment_case(cfg, cfg.t[0])
+    anchor, seg = batch.x[:, 0], np.ascontiguousarray(batch.x[:, 1:])
+    want = S.compress_segment(seg, anchor, cfg.r, cfg.t[0], frame_offset=5)
+    _compare_segment(seg, _run_segment(seg, anchor, 5, cfg.r, cfg.t[0]), want)
