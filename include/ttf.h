@@ -115,10 +115,12 @@ ttf_status ttf_workspace_size(const ttf_params* params, size_t* bytes);
  * more than 2^25 tokens (frames rounded up to 64), r < 0, t not finite, anchor_index outside [-F,F) in FIXED mode, unknown
  * anchor_mode), UNSUPPORTED (unknown dtype; features, tokens_out or workspace misaligned),
  * WORKSPACE_TOO_SMALL, HIP.  Any C, grid and radius work.  Fast paths: bf16 and fp32 input with
- * C % 32 == 0 (large bf16 problems of at least 768 channels: C % 8 == 0) and r <= 2 runs the window search on the matrix cores (fp32 as three bf16 pieces
- * per value, 24 significant bits) (any grid; grids exactly 16
- * or 32 tokens wide with H*W % 64 == 0 are the best case); rows whose byte length is a multiple
- * of 16 are read and copied with 16-byte accesses.
+ * C % 32 == 0 and r <= 2 runs the window search on the matrix cores (fp32 as three bf16 pieces per
+ * value, 24 significant bits) on any grid; grids exactly 16 or 32 tokens wide with H*W % 64 == 0 are
+ * the best case.  So do larger bf16 problems with C % 8 == 0 and C >= 768 (see ttf_search_route), for
+ * which ttf_workspace_size() asks for more than the other kernels need: a workspace that is only
+ * large enough for those, about B*H*ceil(W/16)*16*(C rounded up to 32, minus C)*2 bytes less, is taken too and
+ * runs them.  Rows whose byte length is a multiple of 16 are read and copied with 16-byte accesses.
  */
 ttf_status ttf_compress(const ttf_params* params, const void* features,
                         void* workspace, size_t workspace_bytes,
@@ -127,13 +129,14 @@ ttf_status ttf_compress(const ttf_params* params, const void* features,
 /*
  * ttf_compress for callers that cannot allocate device memory or hand over a workspace: code
  * running under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, outputs, kernels and errors as ttf_compress, but the workspace is a fixed array of
+ * arguments, outputs and errors as ttf_compress on a workspace of this size, but it is a fixed array of
  * TTF_STATIC_WORKSPACE_BYTES that lives in the library's device image (every GPU the library is
  * used on holds its own copy from the first use until the process ends).  The call allocates and
  * frees nothing.
  *   - Problems whose ttf_workspace_size() exceeds TTF_STATIC_WORKSPACE_BYTES are refused with
  *     TTF_ERR_WORKSPACE_TOO_SMALL before anything is launched.  (bf16 rows with C % 32 != 0 count as they
- *     are, without the room that lets large problems of such rows take the matrix-core search.)
+ *     are; where the room for the matrix-core search of such rows does not fit as well, they take the
+ *     general kernels, whose similarities differ in the last bits: see ttf_search_route.)
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two
  *     streams, two threads) race and give undefined outputs; order them on one stream or with events.
  *     The array keeps the previous call's contents; nothing in it needs to start at zero.
@@ -298,7 +301,14 @@ ttf_status ttf_set_speculation(int mode);
 
 /*
  * Which window-search kernels a problem takes (Section 3, "Pointwise Matching with Local Window
- * Search"): a host-side query, no GPU work.  Results never depend on the route, only the time does.
+ * Search"): a host-side query, no GPU work.  The routes add the channels in different orders:
+ * similarities agree to about 3e-7 (each within 1e-5 of the exact value), and only a token whose
+ * similarity lies that close to t, or to another candidate's, may be gated or matched differently.
+ * For most problems the route depends on dtype, r, C and the grid.  For bf16 with C % 32 != 0 (C % 8 == 0,
+ * C >= 768) it also depends on B and F -- small problems and few-column grids are searched faster by the
+ * general kernels -- and on the workspace: the answer is for one of ttf_workspace_size() bytes (a
+ * smaller one that ttf_compress still takes runs the general kernels).  A segment takes the route of the
+ * clip it equals: ask with F + 1 frames.
  *   params  host; checked as in ttf_compress.
  *   route   host, out: one of the TTF_ROUTE_* values.
  * Errors: INVALID_ARG (NULL pointer, bad params), UNSUPPORTED (unknown dtype).
@@ -314,7 +324,8 @@ ttf_status ttf_search_route(const ttf_params* params, int* route);
  *   0 frame sums (speculative route: over the guess channels only)   1 anchor scores (two-pass
  *     route only)   2 anchor choice + norms   3 window search + gate
  *   4 anchor verification (speculative route only: exact rule from the search's sums, repeated
- *     search of refuted clips)   5 offsets scan   6 row emission
+ *     search of refuted clips)   5 offsets scan (nothing up to 256 keep words, nor up to 4096 with rows of
+ *     1 KiB and more: there stage 6 counts the rows itself)   6 row emission
  * ttf_profile_enable(slots), 1 <= slots <= TTF_PROFILE_MAX_SLOTS, makes every following
  * ttf_compress on the calling thread record HIP events around each stage on the call's
  * stream; successive calls use `slots` event sets round-robin (created once, reused), so up to

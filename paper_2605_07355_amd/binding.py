@@ -447,7 +447,8 @@ ROUTE_NAMES = {0: "general", 1: "mfma_bf16", 2: "mfma_bf16_padded", 3: "mfma_f32
 
 def ttf_search_route(B: int, F: int, H: int, W: int, C: int, dtype: torch.dtype = torch.bfloat16,
                      r: int = 1, t: float = 0.7, anchor: Union[str, int] = "auto") -> str:
-    """Name of the window-search kernels this problem takes (see ROUTE_NAMES); host-side query."""
+    """Name of the window-search kernels this problem takes (see ROUTE_NAMES) on a workspace of
+    ``ttf_workspace_size`` bytes; host-side query.  For a segment of F frames ask with F + 1."""
     p = _make_params(B, F, H, W, C, _dtype_code(dtype), r, t, anchor)
     route = ctypes.c_int(-1)
     _check(load_library().ttf_search_route(ctypes.byref(p), ctypes.byref(route)))

@@ -238,8 +238,8 @@ __global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, 
 //
 // Step 1: the offsets (row_offsets, kept_count), the ids of every kept token and, in src_row[r], the input
 // token that output row r copies.  Block = kPlaceWords consecutive keep words of one clip, which counts the
-// rows ahead of it itself from L2 instead of waiting for a scan kernel (whole calls: 512 words 164.0 -> 161.8
-// us, 1024 words 84.7 -> 83.3, 4096 words 919 -> 917).  Tied-batch mode: the mask is the shared one, one clip.
+// rows ahead of it itself from L2 instead of waiting for a scan kernel (figures above, at the constants).
+// Tied-batch mode: the mask is the shared one, one clip.
 __global__ __launch_bounds__(256) void k_place_ids(const uint64_t* __restrict__ keep_bits,
                                                    const int32_t* __restrict__ anchor_index,
                                                    int32_t* __restrict__ kept_count, int32_t* __restrict__ row_offsets,
@@ -284,9 +284,8 @@ __global__ __launch_bounds__(256) void k_place_ids(const uint64_t* __restrict__ 
     }
 }
 
-// The same ids behind k_offsets_scan, one wave per keep word: calls of more than kPlaceIdsWords keep words,
-// where every block counting from the start would read more than the scan costs.  tied_rows > 0: the mask is the
-// shared one ([F,NW]); ids and src_row are those of one clip.
+// The same ids behind k_offsets_scan, one wave per keep word: calls of more than kPlaceIdsWords keep words.
+// Tied-batch mode: `words` and the mask are the shared ones ([F,NW]); ids and src_row are those of one clip.
 __global__ __launch_bounds__(256) void k_emit_ids(const uint64_t* __restrict__ keep_bits,
                                                   const int32_t* __restrict__ frame_base,
                                                   int32_t* __restrict__ pos_ids, int32_t* __restrict__ src_index,

@@ -94,7 +94,7 @@ inline bool tail_channels(const ttf_params& p)
 
 // tail: with room for the whole last K-step of tail_channels() rows in the anchor's fragment copy.
 // Without it the workspace is a little smaller and such rows take the general kernels (callers whose
-// workspace is that small: the fixed one, or one sized for the rows as they are).
+// workspace is that small: the fixed one, or one sized for the rows as they are; calls without a search).
 inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
 {
     const size_t B = p.B, F = p.F, N = (size_t)p.H * p.W, C = p.C, NW = (N + 63) / 64;
@@ -174,6 +174,7 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 // Keep words rebuilt from the fuse map (for searches whose work units do not line up with keep words).
 hipError_t launch_pack_keep(const ttf_params& p, const int32_t* fuse_map, const int32_t* anchor_index,
                             const Workspace& w, hipStream_t s);
+// Output row offsets; launches nothing where the emission counts them itself.
 hipError_t launch_offsets_scan(const ttf_params& p, const Workspace& w, const int32_t* anchor_index,
                                int32_t* kept_count, int32_t* row_offsets, bool tied, hipStream_t s);
 // Output rows, ids and -- where launch_offsets_scan leaves that to it -- kept_count and row_offsets.
