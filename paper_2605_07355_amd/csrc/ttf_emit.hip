@@ -177,10 +177,12 @@ __device__ __forceinline__ int first_row(int clips, int words, int k, int a, int
 // of B1 F8 16x16 C4096 29.1 -> 24.4, B1 F32 16x16 C2048 50.5 -> 47.4).  Larger calls and longer rows keep the
 // faster copy of k_copy_rows.  tied_rows as for k_emit_rows: blockIdx.y = clip, the mask is the shared one ([F,NW]).
 //
-// Blocks go round robin to the XCDs, and inside an XCD to its CUs.  The quarter a block takes moves on with its
-// word, so that the filled quarters of short frames (N <= 48) meet every XCD; each 256 blocks are turned by
-// five CUs against those before, so that anchor frames a power of two of words apart do not meet on one CU
-// (re-gating, quarters in block order -> so: B64 F4 4x4, 8 KiB rows 26.2 -> 14.1 us, B4 F64 8x8, 4 KiB rows 18.9 -> 15.5).
+// Blocks go round robin to the XCDs, and inside an XCD to its CUs.  Frames of at most 48 tokens: the quarter a block
+// takes moves on with its word, so that the filled quarters meet every XCD.  Longer frames keep quarters in block
+// order, the order of the wave-per-token search, whose rows then lie in the XCD's own L2 (B1 F4 28x16 C912 fp32, kernel
+// alone: 6.1 us, with moving quarters 10.4).  Each 256 blocks are turned by five CUs against those before, so that anchor
+// frames a power of two of words apart do not meet on one CU.  Re-gating, quarters in block order -> so: B64 F4 4x4,
+// 8 KiB rows 26.2 -> 14.1 us, B4 F64 8x8, 4 KiB rows 18.9 -> 15.5.
 template <int U>
 __global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, const uint64_t* __restrict__ keep_bits,
                                                     const int32_t* __restrict__ anchor_index,
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(256) void k_place_rows(const char* __restrict__ x, 
     const unsigned turn = (blockIdx.x | 255u) < gridDim.x ? 40u * (blockIdx.x >> 8) : 0u;
     const unsigned slot = (blockIdx.x & ~255u) | ((blockIdx.x + turn) & 255u);
     const int wd = (int)(slot >> 2);                         // keep word over all clips
-    const int quarter = (int)((slot + (slot >> 3)) & 3u);
+    const int quarter = (int)((slot + (N <= 48 ? slot >> 3 : 0u)) & 3u);
     const int per_clip = F * NW;
     const int b = wd / per_clip, word = wd % per_clip;
     const int k = word / NW, q = word % NW;
