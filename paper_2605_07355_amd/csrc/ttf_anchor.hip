@@ -19,14 +19,15 @@ constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every 
 // One block = one frame x one slice of 64*V channels x one of `parts` runs of rows (whole rounds of 16 rows
 // but for the last run).  Wave w adds rows w, w+4, ... of the run; the four partial sums are combined through
 // LDS in wave order, so the result is order-stable, and stored as share `part` of the frame:
-// out[frame][part][C].  Bound by HBM on large inputs and by latency where there are few blocks.  Four rows are
+// out[frame][part][C].  Bound by HBM on large inputs and by latency where there are few blocks.  R rows are
 // in flight per wave, and none behind a guard of its own: a load under a guard is waited for before the next
 // one is issued.  Kernel alone, eight guarded rows -> four plain ones: B64 F32 16x16 C256 76 -> 45 us (6.0
-// TB/s), B16 F32 16x16 C4000 196 -> 178, B1 F64 14x14 C2048 26 -> 12.  One block per frame and slice -> parts:
-// B1 F32 16x16 C2048 13.5 -> 7.8, B3 F23 24x18 C1000 22 -> 13, B1 F32 64x64 C256 151 -> 22.
+// TB/s), B16 F32 16x16 C4000 196 -> 178, B1 F64 14x14 C2048 26 -> 12.  Eight plain ones pay for fp32 rows in at
+// most 256 blocks (sums and their addition, four -> eight: B1 F4 28x16 C912 20.0 -> 17.3, B1 F20 22x23 C272
+// 25.6 -> 22.6; 612 blocks, B9 F34 32x32 C320: 75 -> 86).
 // `spec` (may be null): per clip {guessed anchor, guess trusted, ...}; clips with a trusted guess get
 // their exact sums from the search and are skipped here.
-template <typename T, int V>
+template <typename T, int V, int R>
 __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, float* __restrict__ out,
                                                     int N, int C, int F, int parts, const int32_t* __restrict__ spec)
 {
@@ -44,22 +45,21 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
     if (c0 < C) {
         const T* base = x + frame * (size_t)N * C + c0;
         int i = lo + wave;
-        for (; i + 12 < hi; i += 16) {         // four rows in flight per wave
-            RowVec<T, V> r[4];
+        auto add_rows = [&](auto count) {
+            constexpr int n = decltype(count)::value;
+            RowVec<T, V> r[n];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r[u].template load<true>(base + (size_t)(i + 4 * u) * C);
+            for (int u = 0; u < n; ++u) r[u].template load<true>(base + (size_t)(i + 4 * u) * C);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < n; ++u) {
 #pragma unroll
                 for (int e = 0; e < V; ++e) acc[e] += r[u].v[e];
             }
-        }
-        for (; i < hi; i += 4) {
-            RowVec<T, V> r0;
-            r0.template load<true>(base + (size_t)i * C);
-#pragma unroll
-            for (int e = 0; e < V; ++e) acc[e] += r0.v[e];
-        }
+            i += 4 * n;
+        };
+        while (i + 4 * (R - 1) < hi) add_rows(std::integral_constant<int, R>{});
+        while (i + 12 < hi) add_rows(std::integral_constant<int, 4>{});
+        while (i < hi) add_rows(std::integral_constant<int, 1>{});
     }
 #pragma unroll
     for (int e = 0; e < V; ++e) part[wave][lane * V + e] = acc[e];
@@ -798,11 +798,12 @@ static bool frame_sums_by_slab(const ttf_params& p)
     return p.C % (256 * V) == 0 && (size_t)p.B * p.F * (p.C / (256 * V)) >= 512;
 }
 
-// Runs of rows a frame is cut into by k_frame_sums: as many as make no more than 512 blocks, two for every CU,
-// of at least 32 rows.  Beyond that a share more costs more than it hides (sums and their addition together,
-// us, by blocks without parts): 128 blocks (B4 F16 16x16 C1024) 22 / two 16 / four 14 / eight 14.6; 240 (B1 F40
-// 32x32 C3000) 58.5 / two 46 / four 51; 350 (B1 F50 32x16 C3328) 37.4 / two 37.5 / three 41; 512 (B4 F64 16x16
-// C1024) 29.6 / two 31.2; 612 (B9 F34 32x32 C320 fp32) 72 / two 82.
+// Runs of rows a frame is cut into by k_frame_sums, of at least 32 rows each: as many as make no more than 512
+// blocks, two for every CU; two where one run each would leave most CUs a block and some two (257 to 384 blocks);
+// whole frames beyond.  Sums and their addition together, us, by blocks without runs: 128 (B4 F16 16x16 C1024)
+// 22 / two 16 / four 14 / eight 14.6; 240 (B1 F40 32x32 C3000) 58 / two 46 / four 51; 340 (B5 F34 24x24 C1024) 42 /
+// two 39 / three 40; 384 (B4 F32 16x16 C1504) 27 / two 24 / three 26; 400 (B4 F50 24x24 C960) 43 / two 47.5 / three 46;
+// 512 (B4 F64 16x16 C1024) 29.6 / two 31.2; 612 (B9 F34 32x32 C320 fp32) 72 / two 82.
 // The shares stand in the anchor's fragment copy, which is written after the anchor has been chosen, so
 // they have to fit there (short clips and long rows may get fewer).  Row lengths of whole 16-byte pieces
 // only: k_anchor_partials adds the shares with 16-byte loads.
@@ -812,7 +813,7 @@ static int frame_sum_parts(const ttf_params& p, const Workspace& w)
     if (p.C % V != 0 || frame_sums_by_slab(p)) return 1;
     const size_t blocks = (size_t)p.B * p.F * ((p.C + 64 * V - 1) / (64 * V));
     const size_t share = (size_t)p.B * p.F * p.C * sizeof(float);
-    size_t parts = std::min<size_t>(8, 512 / blocks);
+    size_t parts = blocks <= 256 ? std::min<size_t>(8, 512 / blocks) : (blocks <= 384 ? 2 : 1);
     parts = std::min<size_t>(parts, (size_t)p.H * p.W / 32);
     parts = std::min<size_t>(parts, w.frag_bytes / share);
     if (parts < 2) return 1;
@@ -836,8 +837,14 @@ hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace
         const int parts = skip_trusted ? 1 : frame_sum_parts(p, w);
         float* out = parts > 1 ? reinterpret_cast<float*>(w.anchor_frag) : w.frame_sum;
         dim3 grid((unsigned)(p.B * p.F * parts), (unsigned)((p.C + 64 * V - 1) / (64 * V)));
-        k_frame_sums<T, V><<<grid, 256, 0, s>>>(static_cast<const T*>(x), out, N, p.C, p.F, parts, spec);
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            kernel<<<grid, 256, 0, s>>>(static_cast<const T*>(x), out, N, p.C, p.F, parts, spec);
+            return hipGetLastError();
+        };
+        if constexpr (sizeof(T) == 4 && V > 1) {
+            if ((size_t)grid.x * grid.y <= 256) return go(k_frame_sums<T, V, 8>);
+        }
+        return go(k_frame_sums<T, V, 4>);
     });
 }
 
