@@ -68,21 +68,33 @@ __device__ __forceinline__ void copy_row(const char* __restrict__ src, char* __r
         const uint4* s = reinterpret_cast<const uint4*>(src);
         uint4* d = reinterpret_cast<uint4*>(dst);
         const int n = (int)(row_bytes / 16);
-        int q = lane;
-        for (; q + 448 < n; q += 512) {                // eight 16-byte pieces in flight per lane
+        int p = 0;
+        for (; p + 512 <= n; p += 512) {               // eight 16-byte pieces in flight per lane
             uint4 v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = ld(s + q + 64 * u);
+            for (int u = 0; u < 8; ++u) v[u] = ld(s + p + lane + 64 * u);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) store16_stream(d + q + 64 * u, v[u]);
+            for (int u = 0; u < 8; ++u) store16_stream(d + p + lane + 64 * u, v[u]);
         }
-        for (; q + 192 < n; q += 256) {
-            const uint4 v0 = ld(s + q), v1 = ld(s + q + 64),
-                        v2 = ld(s + q + 128), v3 = ld(s + q + 192);
-            store16_stream(d + q, v0); store16_stream(d + q + 64, v1);
-            store16_stream(d + q + 128, v2); store16_stream(d + q + 192, v3);
+        if (p + 256 <= n) {
+            const uint4 v0 = ld(s + p + lane), v1 = ld(s + p + lane + 64),
+                        v2 = ld(s + p + lane + 128), v3 = ld(s + p + lane + 192);
+            store16_stream(d + p + lane, v0); store16_stream(d + p + lane + 64, v1);
+            store16_stream(d + p + lane + 128, v2); store16_stream(d + p + lane + 192, v3);
+            p += 256;
         }
-        for (; q < n; q += 64) store16_stream(d + q, ld(s + q));
+        // fewer than four pieces a lane are left: one round too, lanes past the end read the last piece again
+        if (n - p > 64) {
+            const int q = p + lane;
+            const uint4 v0 = ld(s + q), v1 = ld(s + min(q + 64, n - 1)),
+                        v2 = ld(s + min(q + 128, n - 1)), v3 = ld(s + min(q + 192, n - 1));
+            store16_stream(d + q, v0);
+            if (q + 64 < n) store16_stream(d + q + 64, v1);
+            if (q + 128 < n) store16_stream(d + q + 128, v2);
+            if (q + 192 < n) store16_stream(d + q + 192, v3);
+        } else if (p + lane < n) {
+            store16_stream(d + p + lane, ld(s + p + lane));
+        }
     } else if constexpr (U == 4) {
         const uint32_t* s = reinterpret_cast<const uint32_t*>(src);
         uint32_t* d = reinterpret_cast<uint32_t*>(dst);

@@ -17,17 +17,17 @@ constexpr int kPlaceWords = 16;                // keep words per block of k_plac
 //   256 words: 1 KiB rows 8.8 / 10.2 / 11.6, 4 KiB rows (64 MiB) 15.1 / 16.1 / 17.7, 8 KiB (128 MiB) 23.6 / 23.1 / 24.4;
 //   384 words, 2 KiB rows (48 MiB): 14.7 / 14.5 / 16.0;  512 words, 2 KiB rows (64 MiB): 16.9 / 16.3 / 17.5;
 //   1024 words, 1 KiB rows: 20.9 / 16.8 / 17.7.
-// A wave of k_place_rows copies up to four rows one after the other, so rows have a limit too: 64 words of 8 KiB
-// rows 11.0 / 12.1 / 13.1, of 16 KiB rows 18.1 / 15.8 / 17.0, 4 words of 128 KiB rows 52 / 24 / 26.  Whole rounds of
-// four or eight pieces a lane go further than rows that end in single pieces: 128 words of 5008-byte rows
-// 14.7 / 14.9 / 16.4, of 7184 bytes 22.9 / 17.7 / 19.2, of 8192 bytes 17.3 / 17.5 / 19.0.  (Rows that are not whole
+// A wave of k_place_rows copies up to four rows one after the other, so rows have a limit too.  Re-gating 64 words of
+// 6144-byte rows 11.7 / 12.1 / 13.6, 8704 bytes 14.4 / 13.8 / 14.8, 12 000 bytes 18.2 / 16.0 / 17.4, 4 words of 128 KiB
+// rows 52 / 24 / 26.  Whole calls also lose a launch: segment B5 F5 9x21, 8704-byte fp32 rows 71.4 / 75.3 / 77.0, bf16
+// 74.1 / 75.0 / 76.3; compress B4 F8 14x14, 7200 bytes 88.6 / 90.4 / 92.9, 9616 bytes 111.9 / 112.4 / 113.4, 10 400
+// bytes 119.1 / 118.4 / 120.5; B1 F12 16x16, 12 288-byte bf16 rows 63.5 / 61.7 / 63.5.  (Rows that are not whole
 // 16-byte pieces are copied by a wave each in every form.)
 // Counting in every block of k_place_ids against the scan: 4096 words 39.4 / 41.7, 8192 69.3 / 73.0, 16384 131.6 /
 // 137.0 (1 KiB rows); the line stands below the crossing, which was not met.
 constexpr size_t kPlaceAllWords = 256;         // at most this many keep words: offsets, ids and rows in one launch
 constexpr size_t kPlaceAllBytes = 64ull << 20; // ... and this much input
-constexpr size_t kPlaceAllRow = 5120;          // ... in rows of whole 16-byte pieces of at most this length
-constexpr size_t kPlaceAllRounds = 8192;       // ... or this one, if they are whole 4 KiB
+constexpr size_t kPlaceAllRow = 10240;         // ... in rows of whole 16-byte pieces of at most this length
 constexpr size_t kPlaceIdsWords = 4096;        // at most this many: offsets and ids in one launch
 
 // Exclusive scan over the sequence  [N, c(b,0), ..., c(b,F-1)]  for b = 0..B-1, where c(b,k) is
@@ -348,8 +348,7 @@ inline Placement placement(const ttf_params& p, bool tied)
     const size_t row_bytes = (size_t)p.C * (p.dtype == TTF_BF16 ? 2 : 4);
     const size_t tokens_bytes = (size_t)p.B * p.F * p.H * p.W * row_bytes;
     if (tied && p.B > 65535) return Placement::scan;         // (clips ride on gridDim.y)
-    const bool by_wave = row_bytes <= kPlaceAllRow || row_bytes % 16 != 0 ||
-                         (row_bytes % 4096 == 0 && row_bytes <= kPlaceAllRounds);
+    const bool by_wave = row_bytes <= kPlaceAllRow || row_bytes % 16 != 0;
     if (words <= kPlaceAllWords && tokens_bytes <= kPlaceAllBytes && by_wave) return Placement::all;
     if (row_bytes % 16 == 0 && row_bytes >= kRowBlockMin && words <= kPlaceIdsWords) return Placement::ids;
     return Placement::scan;

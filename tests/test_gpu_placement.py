@@ -33,6 +33,12 @@ def test_row_placement(B, F, H, W, C, anchor):
     _parity(cfg, seed=40 + F, anchor=anchor)
 
 
+@pytest.mark.parametrize("pieces", [1, 63, 64, 65, 255, 256, 257, 320, 511, 512, 513, 576, 577, 640])
+def test_every_end_of_a_row_copied_by_a_wave(pieces):
+    """Rows of so many 16-byte pieces: whole rounds of 512, and what is left of at most 64, 256 or 512."""
+    _parity(CONFIGS["qwen3vl_2b"].scaled(B=2, F=3, H=3, W=5, C=8 * pieces, sigma=0.5), seed=pieces, anchor=1)
+
+
 def _regate_us(B, F, H, W, row_bytes):
     """Time of a re-gating call with a third of the tokens kept, from replays of a graph of ten."""
     import paper_2605_07355_amd as ttf
@@ -73,9 +79,10 @@ def test_time_of_unusual_row_sets(B, F, H, W, row_bytes, times):
 
 @pytest.mark.parametrize("B,F,H,W,C,one_launch", [
     (1, 49, 16, 4, 2504, True),      # 5008-byte rows
-    (1, 49, 16, 4, 3592, False),     # 7184: single pieces at their end (regate of 128 words: 17.7 us, by waves 22.9)
-    (1, 49, 16, 4, 4072, False),
+    (1, 49, 16, 4, 3592, True),      # 7184: single pieces at their end
     (1, 8, 8, 8, 4096, True),        # 8 KiB: one whole round a lane
+    (1, 8, 8, 8, 5120, True),        # the longest
+    (1, 8, 8, 8, 5128, False),
     (1, 8, 8, 8, 8192, False),
     (1, 8, 8, 8, 4097, True),        # no whole 16-byte pieces: a wave a row in every form
 ])
