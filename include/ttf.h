@@ -288,9 +288,10 @@ int ttf_last_hip_error(void);
  *                 route together with the refuted clips.  Outputs are those of the
  *                 exact rule in every case; only the time differs (one pass over the input instead
  *                 of two when the guesses hold, one extra search for a clip whose trusted guess
- *                 was wrong).
+ *                 was wrong; on inputs below 256 MiB the two may take different searches, whose
+ *                 similarities agree as those of different routes do, see ttf_search_route).
  *                 Available for bf16 input on grids whose rows fill at least 70 % of the 32-cell
- *                 strips the search cuts them into (12..16, 23..32, 45..64, ... columns; any
+ *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
  *                 height), C % 128 == 0, C >= 1024, r <= 2, F >= 2, automatic anchor.
  * mode  0 (default): speculative for inputs of 256 MiB and more in clips of at most 128 frames
  *       where available, else two-pass;
@@ -304,6 +305,8 @@ ttf_status ttf_set_speculation(int mode);
  * Search"): a host-side query, no GPU work.  The routes add the channels in different orders:
  * similarities agree to about 3e-7 (each within 1e-5 of the exact value), and only a token whose
  * similarity lies that close to t, or to another candidate's, may be gated or matched differently.
+ * So do the kernels behind one route: bf16 problems with C >= 1024 take a search that walks whole frames where it
+ * is the faster one, which depends on the grid, r, C and the size of the input.
  * For most problems the route depends on dtype, r, C and the grid.  For bf16 with C % 32 != 0 (C % 8 == 0,
  * C >= 768) it also depends on B and F -- small problems and few-column grids are searched faster by the
  * general kernels -- and on the workspace: the answer is for one of ttf_workspace_size() bytes (a

@@ -8,13 +8,11 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "ttf_device.h"
+#include "ttf_anchor_pick.h"
 #include "ttf_internal.h"
 
 namespace ttf {
 namespace {
-
-constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every clip is already in anchor_index
 
 // One block = one frame x one slice of 64*V channels x one of `parts` runs of rows (whole rounds of 16 rows
 // but for the last run).  Wave w adds rows w, w+4, ... of the run; the four partial sums are combined through
@@ -26,13 +24,16 @@ constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every 
 // most 256 blocks (sums and their addition, four -> eight: B1 F4 28x16 C912 20.0 -> 17.3, B1 F20 22x23 C272
 // 25.6 -> 22.6; 612 blocks, B9 F34 32x32 C320: 75 -> 86).
 // `spec` (may be null): per clip {guessed anchor, guess trusted, ...}; clips with a trusted guess get
-// their exact sums from the search and are skipped here.
+// their exact sums from the search and are skipped here.  Blocks from keep_from on, the last to run, leave
+// their rows in the Infinity Cache for the search (kept_share()).
 template <typename T, int V, int R>
 __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, float* __restrict__ out,
-                                                    int N, int C, int F, int parts, const int32_t* __restrict__ spec)
+                                                    int N, int C, int F, int parts, const int32_t* __restrict__ spec,
+                                                    unsigned keep_from)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t frame = blockIdx.x / parts;
+    const bool keep = blockIdx.y * gridDim.x + blockIdx.x >= keep_from;   // (block-uniform)
     const int run = blockIdx.x % parts;
     if (spec && spec[4 * (frame / F) + 1]) return;
     const int c0 = (blockIdx.y * 64 + lane) * V;
@@ -48,8 +49,13 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
         auto add_rows = [&](auto count) {
             constexpr int n = decltype(count)::value;
             RowVec<T, V> r[n];
+            if (keep) {
 #pragma unroll
-            for (int u = 0; u < n; ++u) r[u].template load<true>(base + (size_t)(i + 4 * u) * C);
+                for (int u = 0; u < n; ++u) r[u].template load<false>(base + (size_t)(i + 4 * u) * C);
+            } else {
+#pragma unroll
+                for (int u = 0; u < n; ++u) r[u].template load<true>(base + (size_t)(i + 4 * u) * C);
+            }
 #pragma unroll
             for (int u = 0; u < n; ++u) {
 #pragma unroll
@@ -78,9 +84,10 @@ __global__ __launch_bounds__(256) void k_frame_sums(const T* __restrict__ x, flo
 // read 4 KiB of one row together and no cross-wave sum is needed.
 template <typename T, int V>
 __global__ __launch_bounds__(256) void k_frame_sums_slab(const T* __restrict__ x, float* __restrict__ frame_sum,
-                                                         int N, int C, int F, const int32_t* __restrict__ spec)
+                                                         int N, int C, int F, const int32_t* __restrict__ spec, unsigned keep_from)
 {
     const size_t frame = blockIdx.x;
+    const bool keep = blockIdx.y * gridDim.x + blockIdx.x >= keep_from;   // (block-uniform)
     if (spec && spec[4 * (frame / F) + 1]) return;
     const int c0 = (blockIdx.y * 256 + threadIdx.x) * V;
     const T* base = x + frame * (size_t)N * C + c0;
@@ -90,8 +97,13 @@ __global__ __launch_bounds__(256) void k_frame_sums_slab(const T* __restrict__ x
     int i = 0;
     for (; i + 8 <= N; i += 8) {
         RowVec<T, V> r[8];
+        if (keep) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) r[u].template load<true>(base + (size_t)(i + u) * C);
+            for (int u = 0; u < 8; ++u) r[u].template load<false>(base + (size_t)(i + u) * C);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) r[u].template load<true>(base + (size_t)(i + u) * C);
+        }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
 #pragma unroll
@@ -313,148 +325,6 @@ __global__ __launch_bounds__(256) void k_guess_sums(const uint16_t* __restrict__
     guess_sum[(size_t)blockIdx.x * kGuessChannels + threadIdx.x] = t;
 }
 
-// Anchor guess, step 2: the anchor rule evaluated on the guess channels alone (fp64 from the fp32
-// sums of step 1), by all NWV waves of a block together (every thread must call it; it synchronises
-// the block).  The guess is trusted when its score beats the runner-up's by at least kGuessMinGap and
-// no score is NaN; the search then runs against it before the exact rule has been evaluated, and the
-// exact rule (from sums the search produces on the side) confirms it or triggers a second search.
-// Returns the guessed frame (lowest k on ties) and whether it is trusted, to every thread.
-constexpr double kGuessMinGap = 0.1;
-template <int NWV>
-__device__ __forceinline__ void guess_pick_block(const float* __restrict__ guess_sum, int b, int F, int parts,
-                                                 int& guess, bool& trusted)
-{
-    constexpr int UN = 8;                               // frames in flight per wave
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const size_t fstride = (size_t)parts * kGuessChannels;
-    const float* gs = guess_sum + (size_t)b * F * fstride + lane * 4;
-    // this lane's four guess channels of frame k: its parts added in order
-    auto load4 = [&](int k) {
-        float4 v = *reinterpret_cast<const float4*>(gs + (size_t)k * fstride);
-        for (int pp = 1; pp < parts; ++pp) {
-            const float4 q = *reinterpret_cast<const float4*>(gs + (size_t)k * fstride + (size_t)pp * kGuessChannels);
-            v.x += q.x; v.y += q.y; v.z += q.z; v.w += q.w;
-        }
-        return v;
-    };
-    __shared__ double gsh[NWV][kGuessChannels];
-    __shared__ double s_best[NWV], s_second[NWV];
-    __shared__ int s_arg[NWV], s_nan[NWV];
-    __shared__ int s_out[2];
-    // clips of up to NWV*UN frames: every wave's frames stay in its registers for the second pass
-    const bool resident = F <= NWV * UN;
-    float4 v[UN];
-    double gp[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int k0 = wave; k0 < F; k0 += NWV * UN) {
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = k0 + NWV * u;
-            v[u] = float4{0.f, 0.f, 0.f, 0.f};
-            if (k < F) v[u] = load4(k);
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            gp[0] += (double)v[u].x; gp[1] += (double)v[u].y; gp[2] += (double)v[u].z; gp[3] += (double)v[u].w;
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) gsh[wave][lane * 4 + e] = gp[e];
-    __syncthreads();
-    double g[4], vv = 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        double t = gsh[0][lane * 4 + e];
-#pragma unroll
-        for (int w = 1; w < NWV; ++w) t += gsh[w][lane * 4 + e];
-        g[e] = t;
-        vv += t * t;
-    }
-    vv = wave_sum(vv);
-    double best = -1.0e300, second = -1.0e300;          // wave-uniform running top two of this wave's frames
-    int arg = 0x7fffffff, nan = 0;
-    for (int k0 = wave; k0 < F; k0 += NWV * UN) {       // ascending k per wave: strict > keeps the lowest on ties
-        if (!resident) {
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int k = k0 + NWV * u;
-                v[u] = float4{0.f, 0.f, 0.f, 0.f};
-                if (k < F) v[u] = load4(k);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = k0 + NWV * u;
-            const double xv[4] = {(double)v[u].x, (double)v[u].y, (double)v[u].z, (double)v[u].w};
-            double uv = 0.0, uu = 0.0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { uv += xv[e] * g[e]; uu += xv[e] * xv[e]; }
-            uv = wave_sum(uv);
-            uu = wave_sum(uu);
-            const double den = sqrt(uu) * sqrt(vv);
-            const double score = den > 0.0 ? uv / den : 0.0;
-            if (k < F) {                                // wave-uniform
-                if (!(score == score)) nan = 1;
-                if (score > best) { second = best; best = score; arg = k; }
-                else if (score > second) second = score;
-            }
-        }
-    }
-    if (lane == 0) { s_best[wave] = best; s_second[wave] = second; s_arg[wave] = arg; s_nan[wave] = nan; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double bb = -1.0e300, sec = -1.0e300;
-        int aa = 0x7fffffff, nn = 0;
-        for (int w = 0; w < NWV; ++w) {
-            nn |= s_nan[w];
-            if (s_best[w] > bb || (s_best[w] == bb && s_arg[w] < aa)) {
-                sec = fmax(sec, bb);
-                bb = s_best[w];
-                aa = s_arg[w];
-            } else {
-                sec = fmax(sec, s_best[w]);
-            }
-            sec = fmax(sec, s_second[w]);
-        }
-        s_out[0] = aa == 0x7fffffff ? 0 : aa;
-        s_out[1] = (!nn && aa != 0x7fffffff && (F == 1 || bb - sec >= kGuessMinGap)) ? 1 : 0;
-    }
-    __syncthreads();
-    guess = s_out[0];
-    trusted = s_out[1] != 0;
-}
-
-// Arg max over k of cos(frame_sum_k, clip_sum), assembled in fp64 from the per-slice shares
-// (slices added in order); 0 when a norm is 0.  Computed by one wave, every lane gets the result;
-// lowest k on ties; frame 0 if every score is NaN.
-__device__ __forceinline__ int pick_anchor(const double* __restrict__ score_part,
-                                           const double* __restrict__ clip_part, int b, int F, int S, int lane)
-{
-    double vv = 0.0;
-#pragma unroll 8
-    for (int s = 0; s < S; ++s) vv += clip_part[(size_t)b * S + s];
-    double best = -1.0e300;
-    int arg = 0x7fffffff;
-    for (int k = lane; k < F; k += 64) {                // ascending k per lane: strict > keeps the lowest
-        double uv = 0.0, uu = 0.0;
-#pragma unroll 8
-        for (int s = 0; s < S; ++s) {
-            const double2 o = *reinterpret_cast<const double2*>(score_part + (((size_t)b * S + s) * F + k) * 2);
-            uv += o.x;
-            uu += o.y;
-        }
-        const double den = sqrt(uu) * sqrt(vv);
-        const double score = den > 0.0 ? uv / den : 0.0;
-        if (score > best) { best = score; arg = k; }
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const double ob = __shfl_xor(best, m, 64);
-        const int oa = __shfl_xor(arg, m, 64);
-        if (ob > best || (ob == best && oa < arg)) { best = ob; arg = oa; }
-    }
-    return arg == 0x7fffffff ? 0 : arg;
-}
-
 // Batch-tied anchor (tied-batch mode): the frame whose anchor score, averaged over the B clips
 // (fp64), is largest; lowest k on ties.  A fixed frame is simply broadcast.  One workgroup of 16
 // waves: wave w adds the scores of clips w, w+16, ... (ascending) for 64 frames at a time, wave 0
@@ -568,40 +438,16 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
                                                         int32_t* __restrict__ fuse_map, float* __restrict__ best_sim,
                                                         int32_t* __restrict__ best_idx, uint16_t* __restrict__ keep16,
                                                         int F, int N, int C, int S, int fixed_anchor, int tiles,
-                                                        int Wg, int CT, int32_t* __restrict__ spec, int spec_mode,
-                                                        const float* __restrict__ guess_sum, int guess_parts)
+                                                        int Wg, int CT)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int b = blockIdx.x / tiles, tile = blockIdx.x % tiles;
     // the anchor is a frame of x (fixed, picked here, or already chosen: kAnchorGiven), or frame b
     // of ext_anchor (published as -1)
-    int a;
-    if (spec_mode == 0) {
-        a = ext_anchor ? -1
-          : fixed_anchor >= 0 ? fixed_anchor
-          : fixed_anchor == kAnchorGiven ? anchor_index[b]
-                                         : pick_anchor(score_part, clip_part, b, F, S, lane);
-    } else if (spec_mode == 1) {
-        // speculative pass: the guess (anchor rule on a few channels), evaluated by every block of the
-        // clip for itself.  A trusted guess stands in for the anchor until the search has produced exact
-        // frame sums; a clip without one is only summed by the coming search, so nothing is prepared.
-        bool trusted;
-        guess_pick_block<8>(guess_sum, b, F, guess_parts, a, trusted);
-        if (tile == 0 && threadIdx.x == 0) {
-            spec[4 * b + 0] = a;
-            spec[4 * b + 1] = trusted ? 1 : 0;
-            spec[4 * b + 2] = 0;
-            spec[4 * b + 3] = 0;
-        }
-        if (!trusted) return;
-    } else {
-        // after the search: the exact rule.  A trusted guess it confirms: nothing to do.  Otherwise
-        // publish the exact anchor, mark the clip for the second search and prepare its anchor.
-        a = pick_anchor(score_part, clip_part, b, F, S, lane);
-        const bool redo = !spec[4 * b + 1] || a != spec[4 * b];
-        if (tile == 0 && threadIdx.x == 0) spec[4 * b + 2] = redo ? 1 : 0;
-        if (!redo) return;
-    }
+    const int a = ext_anchor ? -1
+                : fixed_anchor >= 0 ? fixed_anchor
+                : fixed_anchor == kAnchorGiven ? anchor_index[b]
+                                               : pick_anchor(score_part, clip_part, b, F, S, lane);
     if (fixed_anchor != kAnchorGiven && tile == 0 && threadIdx.x == 0) anchor_index[b] = a;
     // flat index of the tile's first token, and how many of its 16 columns exist
     const int first = PAD ? (tile / CT) * Wg + 16 * (tile % CT) : 16 * tile;
@@ -671,6 +517,21 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
             inv = 1.0f / sqrtf(ss);
         }
         anchor_inv[((size_t)b * tiles + tile) * 16 + threadIdx.x] = ss > 0.f ? inv : 0.f;
+    }
+}
+
+// The anchor guessed from the sums over the guess channels, one workgroup per clip.
+__global__ __launch_bounds__(512) void k_guess_pick(const float* __restrict__ guess_sum, int32_t* __restrict__ spec, int F,
+                                                    int parts)
+{
+    int a;
+    bool trusted;
+    guess_pick_block<8>(guess_sum, (int)blockIdx.x, F, parts, a, trusted);
+    if (threadIdx.x == 0) {
+        int32_t* o = spec + 4 * blockIdx.x;
+        o[0] = a;
+        o[1] = trusted ? 1 : 0;
+        o[2] = o[3] = 0;
     }
 }
 
@@ -825,12 +686,16 @@ hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace
 {
     const int N = p.H * p.W;
     const int32_t* spec = skip_trusted ? w.spec : nullptr;
+    // (beside a speculative search nobody reads these frames next: only the search of the clips left does)
+    const double kept = skip_trusted ? 0.0 : kept_share(p);
+    auto keep_from = [&](dim3 g) { return (unsigned)((double)g.x * g.y * (1.0 - kept)); };
     return by_layout(p, [&](auto tag, auto vtag) {
         using T = decltype(tag);
         constexpr int V = decltype(vtag)::value;
         if (V > 1 && frame_sums_by_slab(p)) {
             dim3 slabs((unsigned)(p.B * p.F), (unsigned)(p.C / (256 * V)));
-            k_frame_sums_slab<T, V><<<slabs, 256, 0, s>>>(static_cast<const T*>(x), w.frame_sum, N, p.C, p.F, spec);
+            k_frame_sums_slab<T, V><<<slabs, 256, 0, s>>>(static_cast<const T*>(x), w.frame_sum, N, p.C, p.F, spec,
+                                                          keep_from(slabs));
             return hipGetLastError();
         }
         // (beside a speculative search the fragment copy is in use: no parts)
@@ -838,7 +703,7 @@ hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace
         float* out = parts > 1 ? reinterpret_cast<float*>(w.anchor_frag) : w.frame_sum;
         dim3 grid((unsigned)(p.B * p.F * parts), (unsigned)((p.C + 64 * V - 1) / (64 * V)));
         auto go = [&](auto kernel) {
-            kernel<<<grid, 256, 0, s>>>(static_cast<const T*>(x), out, N, p.C, p.F, parts, spec);
+            kernel<<<grid, 256, 0, s>>>(static_cast<const T*>(x), out, N, p.C, p.F, parts, spec, keep_from(grid));
             return hipGetLastError();
         };
         if constexpr (sizeof(T) == 4 && V > 1) {
@@ -848,19 +713,17 @@ hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace
     });
 }
 
-// mixed: clips with a trusted anchor guess take their frame sums from the strip sums the search wrote
-// (w.strip_sum), the others from w.frame_sum; otherwise every clip from w.frame_sum.
-hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, bool mixed, hipStream_t s)
+hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, const float* strip_sum, int strips, hipStream_t s)
 {
     const int S = (p.C + 255) / 256;
     // runs of at least 32 frames, and no more blocks than fill the chip a few times
     int FG = 1;
     while (FG < 16 && (size_t)S * p.B * FG < 512 && p.F >= 64 * FG) FG *= 2;
     const unsigned grid = (unsigned)((size_t)S * p.B * FG);
-    const int strips = (int)spec_strips(p);
+    const bool mixed = strip_sum != nullptr;
     if (mixed && strips > 8) {
         k_reduce_strips<<<dim3((unsigned)(p.B * p.F), (unsigned)((p.C + 1023) / 1024)), 256, 0, s>>>(
-            w.strip_sum, w.frame_sum, w.spec, p.F, p.C, strips);
+            strip_sum, w.frame_sum, w.spec, p.F, p.C, strips);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -870,7 +733,7 @@ hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, bool mi
                                                       reinterpret_cast<const float*>(w.anchor_frag), nullptr);
     else if (mixed && strips <= 8)
         k_anchor_partials<true><<<grid, 1024, 0, s>>>(w.frame_sum, w.score_part, w.clip_part, p.F, p.C, S, FG, strips,
-                                                      w.strip_sum, w.spec);
+                                                      strip_sum, w.spec);
     else
         k_anchor_partials<false><<<grid, 1024, 0, s>>>(w.frame_sum, w.score_part, w.clip_part, p.F, p.C, S, FG, 1,
                                                        nullptr, nullptr);
@@ -886,7 +749,13 @@ hipError_t launch_guess_sums(const ttf_params& p, const void* x, const Workspace
     return hipGetLastError();
 }
 
-static int fixed_frame(const ttf_params& p)
+hipError_t launch_guess_pick(const ttf_params& p, const Workspace& w, hipStream_t s)
+{
+    k_guess_pick<<<(unsigned)p.B, 512, 0, s>>>(w.guess_sum, w.spec, p.F, guess_parts(p));
+    return hipGetLastError();
+}
+
+int fixed_frame(const ttf_params& p)
 {
     if (p.anchor_mode != TTF_ANCHOR_FIXED) return -1;
     return p.anchor_index < 0 ? p.anchor_index + p.F : p.anchor_index;
@@ -918,7 +787,7 @@ hipError_t launch_anchor_norms(const ttf_params& p, const void* x, const void* e
 
 hipError_t launch_anchor_prepare_mfma(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                                       int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
-                                      int32_t* best_idx, bool anchor_given, int spec_mode, hipStream_t s)
+                                      int32_t* best_idx, bool anchor_given, hipStream_t s)
 {
     const int N = p.H * p.W;
     const int fixed = anchor_given ? kAnchorGiven : fixed_frame(p);
@@ -930,9 +799,7 @@ hipError_t launch_anchor_prepare_mfma(const ttf_params& p, const void* x, const 
                                                        static_cast<const uint16_t*>(ext_anchor), w.score_part,
                                                        w.clip_part, anchor_index, w.anchor_inv, w.anchor_frag, fuse_map,
                                                        best_sim, best_idx, reinterpret_cast<uint16_t*>(w.keep_bits),
-                                                       p.F, N, p.C, (p.C + 255) / 256, fixed, tiles, p.W, CT,
-                                                       spec_mode ? w.spec : nullptr, spec_mode, w.guess_sum,
-                                                       guess_parts(p));
+                                                       p.F, N, p.C, (p.C + 255) / 256, fixed, tiles, p.W, CT);
         return hipGetLastError();
     };
     return pad ? go(k_anchor_prepare<true>) : go(k_anchor_prepare<false>);

@@ -19,8 +19,7 @@ hipError_t launch_window_search_generic(const ttf_params& p, const void* x, cons
 
 hipError_t launch_window_search_mfma(const ttf_params& p, const void* x, bool external_anchor, const Workspace& w,
                                      const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
-                                     int32_t* best_idx, float* win_sim, int spec_mode, hipStream_t s);
-bool mfma_search_speculative(const ttf_params& p);
+                                     int32_t* best_idx, float* win_sim, hipStream_t s);
 hipError_t launch_window_search_mfma_f32(const ttf_params& p, const void* x, bool external_anchor, const Workspace& w,
                                          const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
                                          int32_t* best_idx, float* win_sim, hipStream_t s);
@@ -44,13 +43,13 @@ bool use_mfma_path(const ttf_params& p, bool tail, bool external_anchor)
 // Anchor preparation of the matrix-core path for the element type at hand (fp32: three bf16 planes).
 hipError_t launch_anchor_prepare_any(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                                      int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,
-                                     bool anchor_given, int spec_mode, hipStream_t s)
+                                     bool anchor_given, hipStream_t s)
 {
     if (p.dtype == TTF_F32)
         return launch_anchor_prepare_mfma_f32(p, x, ext_anchor, w, anchor_index, fuse_map, best_sim, best_idx,
                                               anchor_given, s);
     return launch_anchor_prepare_mfma(p, x, ext_anchor, w, anchor_index, fuse_map, best_sim, best_idx, anchor_given,
-                                      spec_mode, s);
+                                      s);
 }
 
 hipError_t launch_window_search(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
@@ -62,9 +61,32 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
             return launch_window_search_mfma_f32(p, x, ext_anchor != nullptr, w, anchor_index, fuse_map, best_sim,
                                                  best_idx, win_sim, s);
         return launch_window_search_mfma(p, x, ext_anchor != nullptr, w, anchor_index, fuse_map, best_sim, best_idx,
-                                         win_sim, 0, s);
+                                         win_sim, s);
     }
     return launch_window_search_generic(p, x, ext_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, s);
+}
+
+// Whether the search walks whole frames (ttf_search_walk.hip) where there is no speculation.  Its workgroups are few
+// and long, so it starts slower and streams faster; against the kernels above it also does without the launch that
+// copies the anchor frame, and adds the one that forms the similarities.  Where the lines lie (whole calls, bf16,
+// r 0..2, 130 random shapes; time of the kernels above over the walk's):
+//   tile rows padded to 16 columns, C >= 1024: 0.99 to 2.2 at every size (B1 F23 9x14 C1792 54.2 / 33.8 us, B1 F5 32x23
+//     C4096 r2 106 / 48.5, B8 F59 10x16 C2048 216 / 189); shorter rows 0.91 to 1.14.
+//   aligned 16- and 32-wide grids: 0.78 to 0.97 on small calls (B1 F10 16x16 C2048 27.2 / 34.8, B1 F32 32x32 C1024 58 /
+//     67), 1.0 to 1.3 from 96 MiB on (B6 F17 16x16 C3584 111 / 103, B4 F20 16x16 C3584 r0 95 / 83), with three strips in a row of
+//     32 from 160 MiB (B2 F6 32x32 C2048 53 / 61, B5 F9 32x32 C3072 172 / 145); the 5x5 window from 24 MiB (B5 F14 16x16
+//     C1792 68.5 / 59.0), and rows whose K-steps do not divide over the waves there from 32 MiB (B2 F15 16x16 C2624 61.1 / 49.8).
+static bool use_walk(const ttf_params& p, const Workspace& w, bool external_anchor, WalkPlan& plan, WalkScratch& scratch)
+{
+    if (p.dtype != TTF_BF16 || p.C < 1024) return false;
+    const int frames = external_anchor ? p.F : p.F - 1;      // (a segment takes the search of the clip it equals)
+    if (mfma_search_supported(p)) {
+        const size_t mib = ((size_t)p.B * frames * p.H * p.W * p.C * 2) >> 20;
+        const size_t least = p.r == 2 ? 24 : (p.C % 256 != 0 ? 32 : (p.W == 32 && p.r == 1 ? 160 : 96));
+        if (mib < least) return false;
+    }
+    plan = walk_plan(p, frames, false);
+    return plan.ok && walk_scratch(p, w, plan, false, scratch);
 }
 
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
@@ -180,45 +202,55 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     } while (0)
 
     // The automatic anchor rule needs the sum of every frame, i.e. a pass over the whole input before
-    // the search can start.  Large inputs on the aligned matrix-core path avoid that pass: the rule is
+    // the search can start.  Large inputs on the matrix-core path avoid that pass: the rule is
     // first evaluated on a few channels only (4 x 128 bytes of every token row); where that guess wins
     // clearly the search runs against it at once and adds up, on the side, the exact sums of every
-    // 32-token strip it reads.  The exact rule is then evaluated from those sums: it confirms the
-    // guess (the usual case: nothing else to do) or refutes it, and then the clip's anchor is prepared
-    // again and its search repeated.  A clip whose guess is not clear-cut sits out the first search; its
+    // frame it reads.  The exact rule is then evaluated from those sums: it confirms the
+    // guess (the usual case: nothing else to do) or refutes it, and then the clip's search is repeated
+    // against the exact anchor.  A clip whose guess is not clear-cut sits out the first search; its
     // frame sums are then formed the two-pass way and it is searched with the refuted clips.  Either way
     // every output is what the exact rule gives.
     const int spec_pref = g_speculation.load(std::memory_order_relaxed);
     const unsigned long long in_bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * 2ull;
-    const bool spec = pick && mfma && mfma_search_speculative(p) &&
-                      (spec_pref > 0 ||
-                       (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F <= kSpeculationMaxFrames));
+    WalkPlan plan{};
+    WalkScratch scratch{};
+    bool spec = pick && mfma && speculation_shape(p) &&
+                (spec_pref > 0 ||
+                 (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F <= kSpeculationMaxFrames));
+    if (spec) {
+        plan = walk_plan(p, p.F, true);
+        spec = plan.ok && walk_scratch(p, w, plan, true, scratch);
+    }
+    const bool walk = spec || (mfma && use_walk(p, w, ext_anchor != nullptr, plan, scratch));
 
     mark();                                                    // start of stage 0
     if (spec) TTF_STEP(launch_guess_sums(p, features, w, s));
     else if (pick) TTF_STEP(launch_frame_sums(p, features, w, false, s));
     mark();
-    if (pick && !spec) TTF_STEP(launch_anchor_scores(p, w, false, s));
+    if (pick && !spec) TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     mark();
-    if (mfma)
+    if (spec) TTF_STEP(launch_guess_pick(p, w, s));
+    else if (!walk && mfma)                                    // (a walking search picks the anchor and forms its norms)
         TTF_STEP(launch_anchor_prepare_any(p, features, ext_anchor, w, out->anchor_index, out->fuse_map,
-                                           out->best_sim, out->best_idx, false, spec ? 1 : 0, s));
-    else TTF_STEP(launch_anchor_norms(p, features, ext_anchor, w, out->anchor_index, false, s));
+                                           out->best_sim, out->best_idx, false, s));
+    else if (!walk) TTF_STEP(launch_anchor_norms(p, features, ext_anchor, w, out->anchor_index, false, s));
     mark();
-    if (spec)
-        TTF_STEP(launch_window_search_mfma(p, features, false, w, out->anchor_index, out->fuse_map, out->best_sim,
-                                           out->best_idx, nullptr, 1, s));
-    else
+    if (walk) {
+        TTF_STEP(launch_search_walk(p, features, ext_anchor, w, plan, scratch, out->anchor_index, false, spec ? 1 : 0, s));
+        if (!spec)
+            TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
+                                        nullptr, s));
+    } else {
         TTF_STEP(launch_window_search(p, features, ext_anchor, w, out->anchor_index, out->fuse_map, out->best_sim,
                                       out->best_idx, nullptr, s));
+    }
     mark();
     if (spec) {
         TTF_STEP(launch_frame_sums(p, features, w, true, s));     // clips without a trusted guess only
-        TTF_STEP(launch_anchor_scores(p, w, true, s));
-        TTF_STEP(launch_anchor_prepare_mfma(p, features, nullptr, w, out->anchor_index, out->fuse_map,
-                                            out->best_sim, out->best_idx, false, 2, s));
-        TTF_STEP(launch_window_search_mfma(p, features, false, w, out->anchor_index, out->fuse_map, out->best_sim,
-                                           out->best_idx, nullptr, 2, s));
+        TTF_STEP(launch_anchor_scores(p, w, scratch.strip_sum, plan.lsegs * plan.ysegs, s));
+        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, false, 2, s));
+        TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
+                                    nullptr, s));
     }
     mark();
     TTF_STEP(launch_offsets_scan(p, w, out->anchor_index, out->kept_count, out->row_offsets, false, s));
@@ -333,15 +365,23 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
     } while (0)
     if (p.anchor_mode == TTF_ANCHOR_AUTO) {
         TTF_STEP(launch_frame_sums(p, features, w, false, s));
-        TTF_STEP(launch_anchor_scores(p, w, false, s));
+        TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));
-    if (use_mfma_path(p, w.tail, false))
-        TTF_STEP(launch_anchor_prepare_any(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
-                                           true, 0, s));
-    else TTF_STEP(launch_anchor_norms(p, features, nullptr, w, out->anchor_index, true, s));
-    TTF_STEP(launch_window_search(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
-                                  tw.win_sim, s));
+    WalkPlan plan{};
+    WalkScratch scratch{};
+    const bool mfma = use_mfma_path(p, w.tail, false);
+    if (mfma && use_walk(p, w, false, plan, scratch)) {
+        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, true, 0, s));
+        TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, nullptr, nullptr, nullptr, tw.win_sim, s));
+    } else {
+        if (mfma)
+            TTF_STEP(launch_anchor_prepare_any(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
+                                               true, s));
+        else TTF_STEP(launch_anchor_norms(p, features, nullptr, w, out->anchor_index, true, s));
+        TTF_STEP(launch_window_search(p, features, nullptr, w, out->anchor_index, nullptr, nullptr, nullptr,
+                                      tw.win_sim, s));
+    }
     TTF_STEP(launch_tie(p, w, tw.win_sim, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
                         out->mean_sim, s));
     TTF_STEP(launch_offsets_scan(p, w, out->anchor_index, out->kept_count, tw.row_offsets, true, s));

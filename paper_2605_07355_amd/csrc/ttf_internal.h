@@ -26,6 +26,17 @@ hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 bool mfma_search_f32_supported(const ttf_params& p);
 bool mfma_f32_aligned(const ttf_params& p);
 
+// Share of an input whose reads leave it in the Infinity Cache (256 MiB) for the kernel that reads it next: plain
+// loads instead of non-temporal ones for the end of a pass, a little more than fits.  B2 F256 16x16 C4096 (1 GiB): frame
+// sums 161 us either way and the search behind them 174 -> 162, with 1 GiB of plain loads 179 and 162; B4 F32 16x16
+// C4096 (256 MiB): sums 42.8 -> 41.5, search 47.8 -> 44.6, row copy 33.8 -> 29.9.
+inline double kept_share(const ttf_params& p)
+{
+    const double bytes = (double)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4);
+    const double keep = 320.0 * (1 << 20);
+    return bytes <= keep ? 1.0 : keep / bytes;
+}
+
 // Device scratch carved out of the caller's workspace.  All sections are 256-byte aligned.
 struct Workspace {
     float*    frame_sum;     // [B,F,C]  sum over the N tokens of every frame (anchor rule, inner sum)
@@ -33,7 +44,8 @@ struct Workspace {
     double*   clip_part;     // [B,S]    per slice: |clip sum|^2          (S = ceil(C/256))
     float*    anchor_inv;    // [B,NP]   1/||x_{a,j}|| of every anchor token (0 for a zero token); NP = token count
                              //          of the grid with rows padded to whole 16-column tiles (N when W % 16 == 0)
-    uint16_t* anchor_frag;   // [B,NP/16,ceil(C/32),64,8] bf16 anchor frame in MFMA fragment order (matrix-core path)
+    uint16_t* anchor_frag;   // [B,NP/16,ceil(C/32),64,8] bf16 anchor frame in MFMA fragment order (matrix-core path);
+                             // scratch of the walking search
     uint64_t* keep_bits;     // [B,F,NW] bit i%64 of word i/64 set iff token i is kept (NW=ceil(N/64))
     int32_t*  frame_base;    // [B,F]    output row of the first kept token of every frame
     int32_t*  src_row;       // [B*F*N]  input token (flat over clips and frames) that output row r copies
@@ -41,8 +53,10 @@ struct Workspace {
     float*    guess_sum;     // [B,F,P,kGuessChannels] frame sums over the guess channels only, in P = guess_parts()
                              // shares (one per run of tokens)
     int32_t*  spec;          // [B,4]    guessed anchor, guess trusted (1/0), second search needed (1/0), unused
-    float*    strip_sum;     // [B,F,spec_strips(),C] sum of every 32-cell strip of every frame, written by the search
+    float*    strip_sum;     // room for [B,F,spec_strips(),C] floats: frame sums per run of the grid and window
+                             // products of the walking search (walk_scratch())
     size_t    frag_bytes;    // size of anchor_frag; until the anchor is chosen it holds the frame-sum shares
+    size_t    strip_bytes;   // size of strip_sum
     bool      tail;          // anchor_frag holds the whole last K-step of tail_channels() rows
     size_t    bytes;
 };
@@ -63,8 +77,8 @@ inline int guess_parts(const ttf_params& p)
     const long long n = (long long)p.H * p.W;
     return n >= 2048 ? 8 : (n >= 1024 ? 4 : (n >= 256 ? 2 : 1));   // (16x16 grids: 23 -> 16 us with two)
 }
-// 32-cell strips per frame as the matrix-core search cuts them: aligned grids N/32; padded tile rows: two
-// grid rows per strip up to 16 columns, one row per strip up to 32, ceil(column tiles / 2) per row beyond.
+// Strips of 32 cells per frame: grids 16 or 32 wide N/32; two grid rows per strip up to 16 columns, one row per strip
+// up to 32, ceil(column tiles / 2) per row beyond.  Measures the room for the search's sums and products.
 inline long long spec_strips(const ttf_params& p)
 {
     const bool aligned = (p.W == 16 && p.H % 4 == 0) || (p.W == 32 && p.H % 2 == 0);
@@ -72,9 +86,8 @@ inline long long spec_strips(const ttf_params& p)
     if (p.W <= 16) return (p.H + 1) / 2;
     return (long long)p.H * (((p.W + 15) / 16 + 1) / 2);
 }
-// Shapes the speculative anchor path exists for: the matrix-core search kernels (bf16, C % 128 == 0) on
-// grids whose tokens fill at least 70 % of the padded 32-cell strips (the strip sums are stored per
-// padded strip: 12..16, 23..32, 45..64 columns, ...), with at least 1024 channels, so that the guess
+// Shapes the speculative anchor path exists for: bf16, C % 128 == 0, grids whose tokens fill at least 70 % of
+// such strips (12..16, 23..32, 45..64 columns, ...), with at least 1024 channels, so that the guess
 // channels are a small part of a row.  The radius is not looked at (the workspace must not depend on it).
 inline bool speculation_shape(const ttf_params& p)
 {
@@ -131,6 +144,7 @@ inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
     w.spec        = reinterpret_cast<int32_t*>(c + o_sp2);
     w.strip_sum   = reinterpret_cast<float*>(c + o_ss);
     w.frag_bytes = o_kb - o_af;
+    w.strip_bytes = off - o_ss;
     w.tail = whole;
     w.bytes = off;
     return w;
@@ -139,9 +153,11 @@ inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
 // Stage launchers.  Each enqueues on `s` and returns the launch status.
 // `skip_trusted`: clips with a trusted anchor guess (w.spec) are left out.
 hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, hipStream_t s);
-// Per-slice shares of the anchor scores from w.frame_sum; `mixed`: from w.strip_sum for the clips with a
-// trusted anchor guess.
-hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, bool mixed, hipStream_t s);
+// Per-slice shares of the anchor scores from w.frame_sum; with strip_sum [B,F,strips,C]: from there for the clips
+// with a trusted anchor guess.
+hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, const float* strip_sum, int strips, hipStream_t s);
+// The anchor guessed from w.guess_sum: w.spec[b] = {guess, trusted, 0, 0}.
+hipError_t launch_guess_pick(const ttf_params& p, const Workspace& w, hipStream_t s);
 // Frame sums over the guess channels only (w.guess_sum).
 hipError_t launch_guess_sums(const ttf_params& p, const void* x, const Workspace& w, hipStream_t s);
 // `ext_anchor` (here and below): nullptr when the anchor is a frame of x; otherwise the anchor
@@ -153,15 +169,10 @@ hipError_t launch_anchor_norms(const ttf_params& p, const void* x, const void* e
                                int32_t* anchor_index, bool anchor_given, hipStream_t s);
 // Matrix-core path: anchor choice, inverse norms, the anchor frame re-laid in fragment order, and
 // the anchor-frame rows of fuse_map / best_sim / best_idx / keep bits.
-// spec_mode 0: the plain rule (fixed, given, or the arg max of the exact scores).  1: speculative pass --
-// the anchor is guessed from w.guess_sum; w.spec[b] = {guess, trusted, 0, 0} is written and only clips
-// with a trusted guess are prepared.  2: after the speculative search -- the exact rule from the
-// scores; clips whose guess it confirms are left alone, the others are marked in w.spec[b][2],
-// get the exact anchor published and prepared.
 hipError_t launch_anchor_prepare_mfma(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                                       int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
-                                      int32_t* best_idx, bool anchor_given, int spec_mode, hipStream_t s);
-// The same for fp32 tokens: the anchor frame as three bf16 planes per tile and K-step (no speculative modes).
+                                      int32_t* best_idx, bool anchor_given, hipStream_t s);
+// The same for fp32 tokens: the anchor frame as three bf16 planes per tile and K-step.
 hipError_t launch_anchor_prepare_mfma_f32(const ttf_params& p, const void* x, const void* ext_anchor,
                                           const Workspace& w, int32_t* anchor_index, int32_t* fuse_map,
                                           float* best_sim, int32_t* best_idx, bool anchor_given, hipStream_t s);
@@ -171,6 +182,33 @@ bool tail_search_pays(const ttf_params& p, int frames);   // tail_channels() row
 hipError_t launch_window_search(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                                 const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
                                 int32_t* best_idx, float* win_sim, hipStream_t s);
+// Search by workgroups that walk whole frames (ttf_search_walk.hip): how it is dealt to workgroups, and its
+// scratch, which lies in the sections strip_sum and anchor_frag.
+struct WalkPlan {
+    bool ok;                 // the kernels can run this problem
+    bool patch;              // tiles are 4x4 patches, not runs of a grid row
+    int nk;                  // shares of the channels
+    int lines;               // column strips of the grid
+    int lsegs, ysegs;        // runs of strips, and runs of rows, dealt to different workgroups
+    int groups, nf;          // frame groups of nf frames
+};
+struct WalkScratch {
+    float* part;             // [nk][B*F*N][(2r+1)^2 + 1]
+    float* norm_part;        // [nk][B*N]
+    float* strip_sum;        // [B*F][lsegs*ysegs][C], where sums are kept
+};
+WalkPlan walk_plan(const ttf_params& p, int frames, bool sums);
+bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan, bool sums, WalkScratch& scratch);
+// mode 0: anchor external, fixed_anchor (>= 0), given (kAnchorGiven) or picked from the scores.  1: clips with a
+// trusted guess, every frame, with sums.  2: clips whose guess the exact rule refutes, and those without one.
+hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
+                              const WalkPlan& plan, const WalkScratch& scratch, int32_t* anchor_index,
+                              bool anchor_given, int mode, hipStream_t s);
+// Similarities, arg max, gate and keep words from the walk's products (win_sim: tied-batch mode, see k_tie).
+hipError_t launch_walk_finish(const ttf_params& p, const Workspace& w, const WalkPlan& plan, const WalkScratch& scratch,
+                              const int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,
+                              float* win_sim, hipStream_t s);
+int fixed_frame(const ttf_params& p);              // the fixed anchor frame, or -1 for the automatic rule
 // Keep words rebuilt from the fuse map (for searches whose work units do not line up with keep words).
 hipError_t launch_pack_keep(const ttf_params& p, const int32_t* fuse_map, const int32_t* anchor_index,
                             const Workspace& w, hipStream_t s);

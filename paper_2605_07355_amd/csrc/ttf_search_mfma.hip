@@ -44,40 +44,17 @@ namespace {
 
 constexpr size_t kSimds = 256 * 4;             // SIMDs of the chip: wave slots per unit of occupancy
 
-// B operand that picks 16 of the 32 channels of a K-step: E_h[k][n] = 1 iff k == 16h + n (operand
-// order: lane n + 16g holds rows k = 8g .. 8g+7 of column n).  A source tile times E_h is that
-// tile's tokens x channels 16h .. 16h+15 in the MFMA result layout, i.e. a lane then holds four
-// TOKENS of one channel: the form in which a sum over tokens is cheap.
-__device__ __forceinline__ bf16x8 channel_picker(int h, int lane)
-{
-    const int n = lane & 15, g = lane >> 4;
-    const bool mine = g == 2 * h + (n >> 3);
-    const int e = n & 7;
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = (mine && (e >> 1) == i) ? ((e & 1) ? 0x3F800000u : 0x00003F80u) : 0u;
-    return __builtin_bit_cast(bf16x8, uint4{w[0], w[1], w[2], w[3]});
-}
-
 // FRO: source frames per workgroup, 0 = the shape's default.  Small inputs use 1 frame and long
 // passes (more workgroups, fewer dependent rounds of loads per workgroup).
-// SPEC 0: the plain search.  SPEC 1: the search of the speculative pass -- the anchor in
-// anchor_index may be a guess, so every frame of the clip, the anchor frame included, is walked
-// (its outputs are not written) and the sum over the 32 tokens of every (frame, strip) is written to
-// strip_sum[b][k][strip][channel], from which the exact anchor rule is evaluated afterwards.  The
-// sums come from two extra MFMAs per source tile and K-step (channel_picker) whose accumulators add
-// the two tiles of a strip; four in-lane adds and two cross-row steps finish them.
-// SPEC 2: the plain search for the clips marked in spec[b][2] only (guess refuted); other clips exit.
 // RAG: the K-steps need not divide over the waves and passes.  The passes are dealt to the waves in
 // contiguous runs of nearly equal length (a wave may get none); the wave that owns the end of the
 // channel axis finishes with a pass of the K-steps left over.
-template <int CT, int RAD, int KSW, int NW, bool ALL, int FRO = 0, int SPEC = 0, bool RAG = false>
+template <int CT, int RAD, int KSW, int NW, bool ALL, int FRO = 0, bool RAG = false>
 __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ anchor_frag,
     const int32_t* __restrict__ anchor_index, const float* __restrict__ anchor_inv,
     int32_t* __restrict__ fuse_map, float* __restrict__ best_sim, int32_t* __restrict__ best_idx,
-    uint16_t* __restrict__ keep16, float* __restrict__ win_sim, int F, int H, int C, float t, int passes, int groups,
-    const int32_t* __restrict__ spec, float* __restrict__ strip_sum)
+    uint16_t* __restrict__ keep16, float* __restrict__ win_sim, int F, int H, int C, float t, int passes, int groups)
 {
     using S = Shape<CT, RAD>;
     constexpr int W = S::W, NA = S::NA, NPS = S::NPS, PF = S::PF;
@@ -106,23 +83,12 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
         grp = (blockIdx.x / tpf) % groups;
         b = blockIdx.x / tpf / groups;
     }
-    if constexpr (SPEC == 1) {
-        if (spec[4 * b + 1] == 0) return;                    // no trusted guess: the clip takes the two-pass route
-    }
-    if constexpr (SPEC == 2) {
-        if (spec[4 * b + 2] == 0) return;                    // guess confirmed: nothing to redo
-    }
     const int a_in = anchor_index[b];                        // < 0: the anchor frame lies outside x (segment mode)
-    // frame slot -> frame: the anchor frame is skipped, except in the speculative pass, which walks
-    // every frame (a_skip beyond every frame index)
-    const int a_skip = (SPEC == 1 || a_in < 0) ? 0x7fffffff : a_in;
+    const int a_skip = a_in < 0 ? 0x7fffffff : a_in;         // frame slot -> frame: the anchor frame is skipped
     const int i0 = tp * 32;                                  // first grid cell of this workgroup
 
     const int y0 = i0 / W;                                   // first (or only) source row
     const int ylo = y0 - RAD;
-    // (speculative pass: C % 128 == 0, so the K-step count is even and a ragged split only hands the waves
-    // different numbers of whole two-step passes; the one-step pass below never runs there)
-    static_assert(!(RAG && SPEC == 1) || KSW == 2, "strip sums are stored per pair of K-steps");
     const int KS = C / 32;                                   // K-steps per token
     // first K-step of this wave and how many it has.  RAG: the ceil(KS / KSW) passes are dealt to the
     // waves as evenly as whole passes allow, so only the last wave can end on a short pass; a wave left
@@ -131,7 +97,7 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
     const int kfirst = RAG ? (wave * units / NW) * KSW : wave * (KS / NW);
     const int ks_mine = RAG ? min(KS, ((wave + 1) * units / NW) * KSW) - kfirst : KS / NW;
     const int kbase = (RAG && ks_mine == 0) ? 0 : kfirst;
-    const int nsrc = (SPEC == 1 || a_in < 0) ? F : F - 1;    // frames walked per clip (>= 1 here)
+    const int nsrc = a_in < 0 ? F : F - 1;                   // frames walked per clip (>= 1 here)
 
     // source frame of slot f: the f-th walked frame of this group, the last one repeated past the end
     // (plain 64-bit addresses: the same loads through buffer descriptors, with one shared per-lane
@@ -163,52 +129,6 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
 #pragma unroll
         for (int q = 0; q < NPS; ++q) acc[s][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // speculative pass: the channel pickers, and where this lane's strip sums go (lanes 0..31 hold the
-    // 32 channels of a K-step after the reduction)
-    bf16x8 pick0, pick1;
-    float* sums = nullptr;
-    float held[FR];                                          // first K-step's totals until the second's are there
-    if constexpr (SPEC == 1) {
-        static_assert(KSW <= 2, "strip sums are stored once per pass from the two halves of a wave");
-        pick0 = channel_picker(0, lane);
-        pick1 = channel_picker(1, lane);
-        sums = strip_sum + ((((size_t)b * F + (size_t)grp * FR) * tpf + tp) * (size_t)C) + kbase * 32 +
-               (KSW == 2 ? lane : (lane & 31));
-    }
-
-    // One source tile's share of the strip sums (speculative pass).  Even tile of a frame: start the two
-    // token x channel accumulators; odd tile: add to them, finish the strip and store it.
-    //   lane n + 16g of d0 / d1: tokens 4g..4g+3 (both tiles) of channel n / 16 + n; four in-lane adds;
-    //   the four row groups are added by an fp32 MFMA against a matrix of ones (K = the row group), after
-    //   which every lane n + 16g holds the strip's total of its channel (rows 0, 2 keep channel n, rows
-    //   1, 3 channel 16 + n);
-    //   one 256-byte store per frame and pass: lanes 0..31 the first K-step's 32 channels, lanes 32..63
-    //   the second's.  A slot past the clip's end repeats the last frame and stores the same values to
-    //   the same place again.
-    f32x4 d0, d1;
-#define TTF_STRIP_SUM_STEP(av_, s_, ks_, ks0_)                                                                \
-    do {                                                                                                      \
-        const f32x4 zero_ = {0.f, 0.f, 0.f, 0.f};                                                             \
-        if ((s_) % 2 == 0) {                                                                                  \
-            d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av_, pick0, zero_, 0, 0, 0);                         \
-            d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av_, pick1, zero_, 0, 0, 0);                         \
-        } else {                                                                                              \
-            d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av_, pick0, d0, 0, 0, 0);                            \
-            d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av_, pick1, d1, 0, 0, 0);                            \
-            const float t0_ = (d0[0] + d0[1]) + (d0[2] + d0[3]);                                              \
-            const float t1_ = (d1[0] + d1[1]) + (d1[2] + d1[3]);                                              \
-            const f32x4 r0_ = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, t0_, zero_, 0, 0, 0);                \
-            const f32x4 r1_ = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, t1_, zero_, 0, 0, 0);                \
-            const float mine_ = (g & 1) ? r1_[0] : r0_[0];                                                    \
-            if (KSW == 1 || (ks_) == KSW - 1) {                                                               \
-                const float v_ = (KSW == 2 && lane < 32) ? held[(s_) / 2] : mine_;                            \
-                sums[(size_t)min((s_) / 2, F - 1 - grp * FR) * tpf * C + (ks0_) * 32] = v_;                   \
-            } else {                                                                                          \
-                held[(s_) / 2] = mine_;                                                                       \
-            }                                                                                                 \
-        }                                                                                                     \
-    } while (0)
-
     // One pass over KN_ (<= KSW) K-steps starting at this wave's K-step ks0_.  (A macro on purpose: with
     // the body in a lambda the same code ran 10 % slower.)
     //  * Anchor fragments run PF K-steps ahead of their use in a ring of PF+1 buffers; the first PF are
@@ -251,7 +171,6 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
                 _Pragma("unroll") for (int q = 0; q < NPS; ++q)                                               \
                     acc[s][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(                                      \
                         av, Bt[ks % NB][S::pair_tile(s % 2, q)], acc[s][q], 0, 0, 0);                         \
-                if constexpr (SPEC == 1) TTF_STRIP_SUM_STEP(av, s, ks, ks0);                                  \
             }                                                                                                 \
             __builtin_amdgcn_sched_barrier(0);                                                                \
         }                                                                                                     \
@@ -267,7 +186,6 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
     }
 
 #undef TTF_SEARCH_PASS
-#undef TTF_STRIP_SUM_STEP
 
     // squared-norm partials: lanes 4i..4i+3 hold the four chunks of token i
 #pragma unroll
@@ -275,12 +193,7 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
         nv[s] += __shfl_xor(nv[s], 1, 64);
         nv[s] += __shfl_xor(nv[s], 2, 64);
     }
-    // a slot is live when it is a real frame of the clip whose outputs this search owns (in the
-    // speculative pass the anchor frame is walked for its sums only)
-    auto slot_live = [&](int s) {
-        const int si = grp * FR + s / 2;
-        return si < nsrc && (SPEC != 1 || si != a_in);
-    };
+    auto slot_live = [&](int s) { return grp * FR + s / 2 < nsrc; };   // a slot of a real frame of the clip
     if constexpr (NW == 1) {
         // one wave owns the whole channel axis: its sums are final, the epilogue needs no LDS
 #pragma unroll
@@ -348,8 +261,6 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
 // of the anchor fragments of the pass after next and then the source fragments two passes ahead,
 // and computes the current pass from LDS and registers.
 // PAD: grids narrower than the tile row (Wg <= 16*CT) and of any height; see finish_tile.
-// SPEC: as for k_search_mfma (1: speculative pass -- every frame walked, strip sums written, clips
-// without a trusted guess skipped; 2: second search of the marked clips only).
 // RAG: the K-step count need not be a multiple of KSW; the slots of the last pass beyond it read the
 // last K-step again (valid memory) with the source fragment replaced by zeros.
 // TAIL (with RAG): the row ends inside the last K-step (tail_channels()); 16-byte pieces past its end are
@@ -357,15 +268,13 @@ __global__ __launch_bounds__(NW * 64, (Shape<CT, RAD>::OCC)) void k_search_mfma(
 // wave-per-token kernels, whose lanes add few terms in a row; to be no less exact the products of every
 // three passes (the unrolled loop body) are added to a second set of accumulators and what that addition
 // rounds off stays in the first (compensated sum; one wave per SIMD where two sets need its registers).
-template <int CT, int RAD, int KSW, int FW, bool ALL, bool PAD = false, int SPEC = 0, bool RAG = false, bool TAIL = false>
+template <int CT, int RAD, int KSW, int FW, bool ALL, bool PAD = false, bool RAG = false, bool TAIL = false>
 __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) void k_search_mfma_shared(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ anchor_frag,
     const int32_t* __restrict__ anchor_index, const float* __restrict__ anchor_inv,
     int32_t* __restrict__ fuse_map, float* __restrict__ best_sim, int32_t* __restrict__ best_idx,
-    uint16_t* __restrict__ keep16, float* __restrict__ win_sim, int F, int H, int C, float t, int groups, int Wg,
-    const int32_t* __restrict__ spec, float* __restrict__ strip_sum)
+    uint16_t* __restrict__ keep16, float* __restrict__ win_sim, int F, int H, int C, float t, int groups, int Wg)
 {
-    static_assert(SPEC == 0 || (!ALL && KSW <= 2 && !RAG), "speculative pass: plain outputs, whole passes");
     using S = Shape<CT, RAD>;
     constexpr int W = S::W, NA = S::NA, NPS = S::NPS;
     constexpr int NS = 2 * FW;                               // source tiles per wave (FW frames)
@@ -394,15 +303,9 @@ __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) voi
         grp = (blockIdx.x / tpf) % groups;
         b = blockIdx.x / tpf / groups;
     }
-    if constexpr (SPEC == 1) {
-        if (spec[4 * b + 1] == 0) return;                    // no trusted guess: the clip takes the two-pass route
-    }
-    if constexpr (SPEC == 2) {
-        if (spec[4 * b + 2] == 0) return;                    // guess confirmed: nothing to redo
-    }
     const int a_in = anchor_index[b];
-    const int a = (SPEC == 1 || a_in < 0) ? 0x7fffffff : a_in;   // the speculative pass walks the anchor frame too
-    const int nsrc = (SPEC == 1 || a_in < 0) ? F : F - 1;
+    const int a = a_in < 0 ? 0x7fffffff : a_in;
+    const int nsrc = a_in < 0 ? F : F - 1;
     // first source row y0 and first column tile c0 of the strip; i0 = y0 * W is what finish_tile decodes
     const int y0 = CT == 3 ? tp / spr : tp * 32 / W;
     const int c0 = CT == 3 ? 2 * (tp % spr) : 0;
@@ -504,28 +407,6 @@ __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) voi
         _Pragma("unroll") for (int i = 0; i < GL; ++i)                                                        \
             frag_lds[(buf_) * (KSW * NA * 64) + gslot[i] + lane] = G[i];                                      \
     } while (0)
-    // speculative pass: channel pickers, where this lane's strip sums go (as in k_search_mfma; here a
-    // wave owns whole frames and the whole channel axis), and the first K-step's totals of a pass
-    bf16x8 pick0, pick1;
-    float* sums = nullptr;
-    float held[FW];
-    bool pad_cell[2] = {false, false};                       // PAD: operand lane m of tile kind u holds a padding cell
-    if constexpr (SPEC == 1) {
-        pick0 = channel_picker(0, lane);
-        pick1 = channel_picker(1, lane);
-        const int k0 = min(grp * FRG + wave * FW, F - 1);
-        sums = strip_sum + ((((size_t)b * F + k0) * tpf + tp) * (size_t)C) + (KSW == 2 ? lane : (lane & 31));
-        if constexpr (PAD) {
-            // padding cells were pointed at a real token (their results are dropped); in the strip sums
-            // they must count as zero
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int ys = y0 + (CT == 1 ? u : 0);
-                const int xs = (CT == 1 ? 0 : 16 * (c0 + u)) + m;
-                pad_cell[u] = ys >= H || xs >= Wg;
-            }
-        }
-    }
     auto compute = [&](int buf, const u32x4 (&Abuf)[NS][KSW], int ks0) {
 #pragma unroll
         for (int ks = 0; ks < KSW; ++ks) {
@@ -545,10 +426,6 @@ __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) voi
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) r[e] = (uint32_t)__builtin_amdgcn_ds_bpermute(bperm, (int)r[e]);
-                if constexpr (PAD && SPEC == 1) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) r[e] = pad_cell[s % 2] ? 0u : r[e];
-                }
                 av[s] = __builtin_bit_cast(bf16x8, uint4{r[0], r[1], r[2], r[3]});
             }
             // one anchor tile at a time from LDS, used by every source tile paired with it
@@ -561,32 +438,6 @@ __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) voi
                     for (int q = 0; q < NPS; ++q) {              // the pair (if any) of this source tile that uses tile qa
                         if (S::pair_tile(s % 2, q) == qa)
                             acc[s][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[s], bt, acc[s][q], 0, 0, 0);
-                    }
-                }
-            }
-            if constexpr (SPEC == 1) {
-                // strip sums of this K-step: tokens x channels of both tiles of a frame through the channel
-                // pickers, four in-lane adds, the four row groups by an fp32 MFMA against ones; one
-                // 256-byte store per frame and pass (lanes 0..31 first K-step, 32..63 second).  A slot past
-                // the clip's end repeats the last frame and stores the same values to the same place.
-#pragma unroll
-                for (int f = 0; f < FW; ++f) {
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                    f32x4 d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2 * f], pick0, zero, 0, 0, 0);
-                    f32x4 d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2 * f], pick1, zero, 0, 0, 0);
-                    d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2 * f + 1], pick0, d0, 0, 0, 0);
-                    d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[2 * f + 1], pick1, d1, 0, 0, 0);
-                    const float t0 = (d0[0] + d0[1]) + (d0[2] + d0[3]);
-                    const float t1 = (d1[0] + d1[1]) + (d1[2] + d1[3]);
-                    const f32x4 r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, t0, zero, 0, 0, 0);
-                    const f32x4 r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, t1, zero, 0, 0, 0);
-                    const float mine = (g & 1) ? r1[0] : r0[0];
-                    if (KSW == 1 || ks == KSW - 1) {
-                        const float v = (KSW == 2 && lane < 32) ? held[f] : mine;
-                        const int k0 = min(grp * FRG + wave * FW, F - 1);
-                        sums[(size_t)(min(k0 + f, F - 1) - k0) * tpf * C + ks0 * 32] = v;
-                    } else {
-                        held[f] = mine;
                     }
                 }
             }
@@ -658,35 +509,18 @@ __global__ __launch_bounds__(256, (TAIL && Shape<CT, RAD>::NPS > 6 ? 1 : 2)) voi
 #pragma unroll
         for (int j = 0; j < 4; ++j) nn[j] = __shfl(nv[s], 4 * (4 * g + j), 64);
         const int si = grp * FRG + wave * FW + s / 2;
-        // (in the speculative pass the anchor frame is walked for its sums only)
-        finish_tile<CT, RAD, ALL, PAD>(acc[s], nn, s, si < nsrc && (SPEC != 1 || si != a_in), min(si, nsrc - 1), a, b, F,
-                                       H, i0, t, ai_tile, fuse_map, best_sim, best_idx, keep16, win_sim, lane, Wg, c0);
+        finish_tile<CT, RAD, ALL, PAD>(acc[s], nn, s, si < nsrc, min(si, nsrc - 1), a, b, F, H, i0, t, ai_tile, fuse_map,
+                                       best_sim, best_idx, keep16, win_sim, lane, Wg, c0);
     }
 }
 
-// True when launch_shape<CT, RAD> runs k_search_mfma (and not the LDS-shared kernel) on this
-// problem: the kernel that can also write strip sums.
-template <int CT, int RAD>
-bool shape_uses_plain_kernel(const ttf_params& p, int nsrc)
-{
-    using S = Shape<CT, RAD>;
-    if constexpr (S::NPS > 6) {
-        const int groups8 = (nsrc + 3) / 4;
-        const size_t wgs = (size_t)p.B * groups8 * (p.H * p.W / 32);
-        if (wgs >= 2 * 256 && (p.C / 32) % 2 == 0) return false;
-    }
-    return true;
-}
-
-// spec_mode 0: plain search.  1: speculative pass (every frame walked, strip sums written).  2: plain
-// search restricted to the clips marked for a second search.
 template <int CT, int RAD>
 hipError_t launch_shape(const ttf_params& p, const void* x, bool external_anchor, const Workspace& w,
                         const int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,
-                        float* win_sim, int spec_mode, hipStream_t s)
+                        float* win_sim, hipStream_t s)
 {
     using S = Shape<CT, RAD>;
-    const int nsrc = (external_anchor || spec_mode == 1) ? p.F : p.F - 1;   // frames walked per clip
+    const int nsrc = external_anchor ? p.F : p.F - 1;        // frames walked per clip
     if (nsrc < 1) return hipSuccess;                         // no source frame: the anchor rows are all there is
     const uint16_t* xs = static_cast<const uint16_t*>(x);
     const int N = p.H * p.W;
@@ -695,64 +529,32 @@ hipError_t launch_shape(const ttf_params& p, const void* x, bool external_anchor
     const unsigned grid = (unsigned)blocks;
     const int ks_total = p.C / 32;                           // K-steps per token
     uint16_t* keep16 = reinterpret_cast<uint16_t*>(w.keep_bits);
-    if (spec_mode != 0 && shape_uses_plain_kernel<CT, RAD>(p, p.F - 1)) {
-        // the speculative path is for large inputs: the two layouts that serve those, nothing else
-        if (win_sim) return hipErrorInvalidValue;
-#define TTF_LAUNCH_SPEC(KSW, NW, SPEC)                                                                            \
-    k_search_mfma<CT, RAD, KSW, NW, false, 0, SPEC><<<grid, NW * 64, 0, s>>>(                                     \
-        xs, w.anchor_frag, anchor_index, w.anchor_inv, fuse_map, best_sim, best_idx, keep16, nullptr, p.F, p.H, p.C, \
-        p.t, ks_total / (NW * KSW), groups, w.spec, w.strip_sum)
-#define TTF_LAUNCH_SPEC_AS(KSW, NW)                        \
-    do {                                                   \
-        if (spec_mode == 1) TTF_LAUNCH_SPEC(KSW, NW, 1);   \
-        else TTF_LAUNCH_SPEC(KSW, NW, 2);                  \
-    } while (0)
-#define TTF_LAUNCH_SPEC_RAG(SPEC)                                                                                 \
-    k_search_mfma<CT, RAD, 2, 4, false, 0, SPEC, true><<<grid, 256, 0, s>>>(                                      \
-        xs, w.anchor_frag, anchor_index, w.anchor_inv, fuse_map, best_sim, best_idx, keep16, nullptr, p.F, p.H, p.C, \
-        p.t, 0 /* passes: the waves count their own */, groups, w.spec, w.strip_sum)
-        if (blocks >= 3 * kSimds * S::OCC && ks_total % 2 == 0) TTF_LAUNCH_SPEC_AS(2, 1);
-        else if (ks_total % 8 == 0) TTF_LAUNCH_SPEC_AS(2, 4);
-        else if (spec_mode == 1) TTF_LAUNCH_SPEC_RAG(1);     // (C % 256 == 128: passes dealt unevenly, none short)
-        else TTF_LAUNCH_SPEC_RAG(2);
-#undef TTF_LAUNCH_SPEC_RAG
-#undef TTF_LAUNCH_SPEC_AS
-#undef TTF_LAUNCH_SPEC
-        return hipGetLastError();
-    }
     if constexpr (S::NPS > 6) {
         // many anchor tiles per source tile (32-wide grid, 5x5 window): workgroups of 4 waves x 1 frame
         // sharing the anchor fragments in LDS, as soon as there are enough of them to cover the chip
         // twice (measured on B4 F64 32x32 C4096 r2: 0.48-0.52 ms against 0.58-0.60 ms for one-wave
         // workgroups; for the smaller windows the split-channel kernel below is as fast or faster)
         constexpr int FWS = 1;                               // frames per wave
-        const int nsrc_plain = external_anchor ? p.F : p.F - 1;   // (the route does not depend on the pass kind)
-        const int groups8 = (nsrc_plain + 4 * FWS - 1) / (4 * FWS);
+        const int groups8 = (nsrc + 4 * FWS - 1) / (4 * FWS);
         const size_t wgs = (size_t)p.B * groups8 * (N / 32);
         constexpr int KSWS = 2;                              // K-steps per pass of the shared-anchor kernel
         if (wgs >= 2 * 256 && ks_total % KSWS == 0) {
             const size_t lds = 2 * KSWS * (size_t)S::NA * 1024;
-            auto go = [&](auto kernel, int frames) {
-                const int groups_ = (frames + 4 * FWS - 1) / (4 * FWS);
-                const size_t wgs_ = (size_t)p.B * groups_ * (N / 32);
+            auto go = [&](auto kernel) {
                 hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
                 if (e != hipSuccess) return e;
-                kernel<<<(unsigned)wgs_, 256, lds, s>>>(xs, w.anchor_frag, anchor_index, w.anchor_inv, fuse_map,
-                                                        best_sim, best_idx, keep16, win_sim, p.F, p.H, p.C, p.t, groups_,
-                                                        p.W, w.spec, w.strip_sum);
+                kernel<<<(unsigned)wgs, 256, lds, s>>>(xs, w.anchor_frag, anchor_index, w.anchor_inv, fuse_map, best_sim,
+                                                       best_idx, keep16, win_sim, p.F, p.H, p.C, p.t, groups8, p.W);
                 return hipGetLastError();
             };
-            if (spec_mode == 1) return go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, false, 1>, p.F);
-            if (spec_mode == 2) return go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, false, 2>, p.F - 1);
-            return win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true>, nsrc)
-                           : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false>, nsrc);
+            return win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true>)
+                           : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false>);
         }
     }
 #define TTF_LAUNCH_AS(KSW, NW, ALL)                                                                           \
     k_search_mfma<CT, RAD, KSW, NW, ALL><<<grid, NW * 64, 0, s>>>(xs, w.anchor_frag, anchor_index, w.anchor_inv,  \
                                                                   fuse_map, best_sim, best_idx, keep16, win_sim,  \
-                                                                  p.F, p.H, p.C, p.t, ks_total / (NW * KSW), groups,  \
-                                                                  nullptr, nullptr)
+                                                                  p.F, p.H, p.C, p.t, ks_total / (NW * KSW), groups)
 #define TTF_LAUNCH(KSW, NW)                   \
     do {                                      \
         if (win_sim) TTF_LAUNCH_AS(KSW, NW, true); \
@@ -760,9 +562,9 @@ hipError_t launch_shape(const ttf_params& p, const void* x, bool external_anchor
     } while (0)
     // (ragged: each wave takes ceil(K-steps / NW) K-steps, in passes of KSW)
 #define TTF_LAUNCH_RAG_AS(KSW, NW, ALL)                                                                       \
-    k_search_mfma<CT, RAD, KSW, NW, ALL, 0, 0, true><<<grid, NW * 64, 0, s>>>(                                    \
+    k_search_mfma<CT, RAD, KSW, NW, ALL, 0, true><<<grid, NW * 64, 0, s>>>(                                    \
         xs, w.anchor_frag, anchor_index, w.anchor_inv, fuse_map, best_sim, best_idx, keep16, win_sim, p.F, p.H,   \
-        p.C, p.t, 0 /* passes: the waves count their own */, groups, nullptr, nullptr)
+        p.C, p.t, 0 /* passes: the waves count their own */, groups)
 #define TTF_LAUNCH_RAG(KSW, NW)                       \
     do {                                              \
         if (win_sim) TTF_LAUNCH_RAG_AS(KSW, NW, true); \
@@ -780,13 +582,11 @@ hipError_t launch_shape(const ttf_params& p, const void* x, bool external_anchor
         if (win_sim)
             k_search_mfma<CT, RAD, 8, 4, true, 1><<<grid1, 256, 0, s>>>(xs, w.anchor_frag, anchor_index, w.anchor_inv,
                                                                         fuse_map, best_sim, best_idx, keep16, win_sim,
-                                                                        p.F, p.H, p.C, p.t, ks_total / 32, nsrc, nullptr,
-                                                                        nullptr);
+                                                                        p.F, p.H, p.C, p.t, ks_total / 32, nsrc);
         else
             k_search_mfma<CT, RAD, 8, 4, false, 1><<<grid1, 256, 0, s>>>(xs, w.anchor_frag, anchor_index, w.anchor_inv,
                                                                          fuse_map, best_sim, best_idx, keep16, win_sim,
-                                                                         p.F, p.H, p.C, p.t, ks_total / 32, nsrc, nullptr,
-                                                                        nullptr);
+                                                                         p.F, p.H, p.C, p.t, ks_total / 32, nsrc);
     } else if (blocks >= 3 * kSimds * S::OCC && S::OCC == 1 && ks_total % 4 == 0) TTF_LAUNCH(4, 1);
     else if (blocks >= 3 * kSimds * S::OCC && ks_total % 2 == 0) TTF_LAUNCH(2, 1);
     else if (blocks >= 3 * kSimds * S::OCC) TTF_LAUNCH_RAG(2, 1);     // odd K-step count
@@ -821,10 +621,10 @@ __global__ __launch_bounds__(256) void k_pack_keep(const int32_t* __restrict__ f
 template <int CT, int RAD>
 hipError_t launch_padded(const ttf_params& p, const void* x, bool external_anchor, const Workspace& w,
                          const int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,
-                         float* win_sim, int spec_mode, hipStream_t s)
+                         float* win_sim, hipStream_t s)
 {
     using S = Shape<CT, RAD>;
-    const int nsrc = (external_anchor || spec_mode == 1) ? p.F : p.F - 1;   // frames walked per clip
+    const int nsrc = external_anchor ? p.F : p.F - 1;        // frames walked per clip
     const int N = p.H * p.W, NW = (N + 63) / 64;
     const size_t words = (size_t)p.B * p.F * NW;
     if (nsrc >= 1) {
@@ -842,35 +642,20 @@ hipError_t launch_padded(const ttf_params& p, const void* x, bool external_ancho
             if (e != hipSuccess) return e;
             kernel<<<(unsigned)wgs, 256, lds, s>>>(static_cast<const uint16_t*>(x), w.anchor_frag, anchor_index,
                                                    w.anchor_inv, fuse_map, best_sim, best_idx, nullptr, win_sim, p.F,
-                                                   p.H, p.C, p.t, groups, p.W, w.spec, w.strip_sum);
+                                                   p.H, p.C, p.t, groups, p.W);
             return hipGetLastError();
         };
         const bool ragged = p.C % (32 * KSWS) != 0;          // odd K-step count: the variant with a guarded last pass
-        {
-            // speculative pass (every frame walked, strip sums written; the keep words are packed after the
-            // last search of the call), and the second search of the clips it leaves
-            if (spec_mode == 1) return (win_sim || ragged) ? hipErrorInvalidValue
-                                                           : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true, 1>);
-            if (spec_mode == 2) {
-                if (win_sim || ragged) return hipErrorInvalidValue;
-                const hipError_t e2 = go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true, 2>);
-                if (e2 != hipSuccess) return e2;
-                k_pack_keep<<<(unsigned)((words + 3) / 4), 256, 0, s>>>(fuse_map, anchor_index, w.keep_bits, p.F, N, NW,
-                                                                        words);
-                return hipGetLastError();
-            }
-        }
-        if (spec_mode != 0) return hipErrorInvalidValue;
         auto go_tail = [&]() {
             if constexpr (CT == 3 && RAD == 2) return hipErrorInvalidValue;   // (mfma_search_padded() sends none here)
             else
-                return win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, 1, true, true, 0, true, true>)
-                               : go(k_search_mfma_shared<CT, RAD, KSWS, 1, false, true, 0, true, true>);
+                return win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, 1, true, true, true, true>)
+                               : go(k_search_mfma_shared<CT, RAD, KSWS, 1, false, true, true, true>);
         };
         const hipError_t e =
             tail     ? go_tail()
-            : ragged ? (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true, 0, true>)
-                              : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true, 0, true>))
+            : ragged ? (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true, true>)
+                              : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true, true>))
                    : (win_sim ? go(k_search_mfma_shared<CT, RAD, KSWS, FWS, true, true>)
                               : go(k_search_mfma_shared<CT, RAD, KSWS, FWS, false, true>));
         if (e != hipSuccess) return e;
@@ -942,22 +727,15 @@ bool tail_search_pays(const ttf_params& p, int frames)
     return walked * ((n + 63) / 64) * resident >= words * rounds && walked * ((n + 15) / 16) * resident >= quarters * rounds;
 }
 
-// True when the speculative anchor path can run this problem's search.
-bool mfma_search_speculative(const ttf_params& p)
-{
-    return (mfma_search_supported(p) || mfma_search_padded(p)) && speculation_shape(p) && p.F >= 2;
-}
-
 hipError_t launch_window_search_mfma(const ttf_params& p, const void* x, bool external_anchor, const Workspace& w,
                                      const int32_t* anchor_index, int32_t* fuse_map, float* best_sim,
-                                     int32_t* best_idx, float* win_sim, int spec_mode, hipStream_t s)
+                                     int32_t* best_idx, float* win_sim, hipStream_t s)
 {
     if (mfma_search_padded(p)) {
         const int ct = p.W <= 16 ? 1 : (p.W <= 32 ? 2 : 3);
 #define TTF_PCASE(CT, RAD)                              \
     if (ct == CT && p.r == RAD)                         \
-    return launch_padded<CT, RAD>(p, x, external_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, \
-                                  spec_mode, s)
+    return launch_padded<CT, RAD>(p, x, external_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, s)
         TTF_PCASE(1, 0);
         TTF_PCASE(1, 1);
         TTF_PCASE(1, 2);
@@ -972,8 +750,7 @@ hipError_t launch_window_search_mfma(const ttf_params& p, const void* x, bool ex
     }
 #define TTF_CASE(CT, RAD)             \
     if (p.W == 16 * CT && p.r == RAD) \
-    return launch_shape<CT, RAD>(p, x, external_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, \
-                                 spec_mode, s)
+    return launch_shape<CT, RAD>(p, x, external_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, s)
     TTF_CASE(1, 0);
     TTF_CASE(1, 1);
     TTF_CASE(1, 2);

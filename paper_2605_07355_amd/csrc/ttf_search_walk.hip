@@ -1,0 +1,678 @@
+// Window search of large bf16 inputs: workgroups that walk whole frames (Section 3, "Pointwise Matching
+// with Local Window Search" and "Threshold Gating").
+//
+// What bounds it is how the token rows stream out of HBM.  A workgroup that keeps the products of many
+// tiles in registers has to read its rows a few hundred bytes at a time (k_search_mfma: 128 rows, 512
+// bytes of each per pass, 5.3 TB/s); the same bytes read as 4 KiB runs of consecutive rows come at 6.7.
+// Here a workgroup therefore owns a share of the channels (eight waves x KW K-steps of 32) of a column strip
+// of up to 16 cells in a group of frames, and walks down the rows of the grid: per row one anchor tile and
+// the source tiles of its frames, every tile 16 consecutive tokens.  A tile is finished before the next
+// begins, so its products need (2r+1) accumulators only, and the registers hold the window instead: the
+// anchor tiles of rows y-r .. y+r in MFMA operand order, read straight from the anchor frame, one new tile
+// per row.  The shares of the channels meet in a small array of window products per token (part), and
+// k_walk_finish turns them into similarities.
+//
+//  * Tokens go from memory to LDS without passing the registers (global_load_lds), each wave through a ring of
+//    its own: groups of two K-steps (128 bytes of each of the 16 rows: whole cache lines; 64-byte pieces
+//    ran at 5.7 TB/s), four groups deep, 64 KiB in flight per workgroup.  The ring runs across tiles,
+//    rows and frames, so the stream never drains; a wave waits for its own loads only.
+//  * Pieces of a row are stored at position (piece ^ row / 2), which spreads the 16 rows that an operand
+//    read touches over all LDS banks.
+//  * The products of the eight waves are added through LDS, double-buffered, one barrier per tile; every wave adds
+//    and stores those of two tokens (only the band of the products that the window needs).
+//  * A strip of a grid wider than 16 is 16 - 2r cells wide at most, so that its window lies in one anchor tile.
+//  * Plain loads leave a line in the Infinity Cache and stream slower than non-temporal ones (whole walk plain 193
+//    us, non-temporal 173, B2 F256 16x16 C4096).  Only the last tiles of a workgroup are read that way, for the row copy
+//    (323 -> 302 us); not beside a guess, where fewer rows are kept than that pays for.
+//  * SPEC (the anchor may be a guess): every frame is walked and its sums over the strip are kept, 16 channels
+//    a register: two MFMAs per K-step against 0/1 matrices that pick 16 of the 32 channels leave four tokens
+//    of one channel in a lane.
+// Kernel alone, against the kernels it replaces there: B16 F32 16x16 C4096 with sums 248 -> 180 us (5.9 TB/s of
+// tokens), 14x14 218 -> 147, B2 F256 16x16 C4096 189 -> 174 (162 behind frame sums that leave the Infinity Cache warm), B4
+// F64 32x32 C4096 r 2 with sums 596 -> 488.  With everything but the loads taken out the first runs no faster
+// (179), so it is the walk through memory that is left; of the last 64 us are the stores of the window products and
+// 60 the reduction (rows of 11 cells instead of patches: 575, twice the products and 1.5 times the tiles).
+// Tried: fragments read one group ahead (187 against 181), twice the groups in flight (no change).
+#include "ttf_anchor_pick.h"
+#include "ttf_internal.h"
+#include "ttf_search_tile.h"
+
+#include <algorithm>
+
+namespace ttf {
+namespace {
+
+constexpr int kWalkWaves = 8;
+constexpr int kWalkSteps = 8;                                // K-steps of 32 channels per wave, at most
+constexpr int kWalkGroup = 2048;                             // bytes of a group: 16 rows x 128
+
+struct WalkArgs {
+    const uint16_t* x;
+    const uint16_t* ext_anchor;                              // external anchor frames, or null
+    const double* score_part;
+    const double* clip_part;
+    int32_t* anchor_index;
+    const int32_t* spec;
+    float* part;                                             // [nk][B*F*N][K+1] window products, squared norm
+    float* norm_part;                                        // [nk][B*N] squared norms of the anchor tokens
+    float* strip_sum;                                        // [B*F][strips*ysegs][C]
+    int B, F, H, W, C, S;
+    int nk, groups, nf, lines, lsegs, ysegs;
+    int fixed_anchor, mode;
+    int keep_from;                                           // of 256 parts of a workgroup's tiles, the first left in the cache
+};
+
+// LDS reads of two fragments are complete and no longer need their ring slot.
+__device__ __forceinline__ void settle(u32x4& a, u32x4& b) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b)::"memory"); }
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// 64 lanes x 16 bytes from base + off (per lane) to LDS at lds + 16 * lane.  No register receives the data; the
+// ring's readers wait on vmcnt.
+template <bool STREAM>
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds)
+{
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+// B operand that picks 16 of the 32 channels of a K-step: E_h[k][n] = 1 iff k == 16h + n (operand order: lane
+// n + 16g holds rows k = 8g .. 8g+7 of column n).  A tile times E_h is its tokens x channels 16h .. 16h+15 in
+// the MFMA result layout, i.e. a lane then holds four TOKENS of one channel.
+__device__ __forceinline__ bf16x8 channel_picker(int h, int lane)
+{
+    const int n = lane & 15, g = lane >> 4;
+    const bool mine = g == 2 * h + (n >> 3);
+    const int e = n & 7;
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = (mine && (e >> 1) == i) ? ((e & 1) ? 0x3F800000u : 0x00003F80u) : 0u;
+    return __builtin_bit_cast(bf16x8, w);
+}
+
+// The tiles of a search and the window that the registers hold for one.
+//  Rows (PATCH false): a tile is up to 16 cells of one grid row, its window 2r+1 anchor tiles, the rows y-r .. y+r
+//   with the cells r to either side; the next tile is the row below, whose window needs one new anchor tile.
+//  Patches (PATCH true): a tile is 4x4 cells (token 4 * column + row).  Its window of (4+2r) x (4+2r) cells is 2+r
+//   anchor tiles of two rows each (anchor n: column n % (4+2r), row n / (4+2r)); the next tile lies four rows
+//   below, and its window needs two new ones.
+template <int RAD, bool PATCH>
+struct Tiles {
+    static constexpr int NP = 2 * RAD + 1, KK = NP * NP;
+    static constexpr int SPAN = 4 + 2 * RAD;                 // anchor columns that four neighbouring tokens look at
+    static constexpr int NT = PATCH ? 2 + RAD : NP;          // anchor tiles of a window
+    static constexpr int NEW = PATCH ? 2 : 1;                // ... that the next tile does not share
+    static constexpr int STEP = PATCH ? 4 : 1;               // grid rows of a tile
+    static constexpr int FRS = RAD == 2 ? 2 : 4;             // most frames whose sums fit the registers beside it
+    static constexpr int RING = RAD == 2 ? 6 : 8;            // groups in flight per wave
+    // Lanes of a product tile that hold values of windows, and the 16-byte words that its share of the reduction
+    // takes (a few more, so that the values of a token come from different banks).
+    static constexpr int BAND = PATCH ? 8 * NP + 2 : 4 * SPAN + 4;
+    static constexpr int RED = NT * BAND + 16;               // words per wave: the products, and the diagonal of the tile
+                                                             // against itself
+    static constexpr size_t LDS = kWalkWaves * (RING * kWalkGroup + 2 * RED * 16);
+    static_assert(LDS <= 160 * 1024, "LDS of a CU");
+};
+
+// mode 0: the anchor is external, fixed, given in anchor_index or picked here; the source frames are walked.
+// mode 1 (SPEC): clips with a trusted guess in spec, every frame walked.  mode 2: the exact rule; clips whose
+// guess it confirms exit, the others are walked as in mode 0.
+template <int RAD, bool PATCH, bool SPEC>
+__global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkArgs A)
+{
+    using T = Tiles<RAD, PATCH>;
+    constexpr int NP = T::NP, KK = T::KK, NT = T::NT, NEW = T::NEW, STEP = T::STEP, FRS = T::FRS, KW = kWalkSteps, G2 = KW / 2;
+    extern __shared__ u32x4 lds_mem[];
+    char* const ring = reinterpret_cast<char*>(lds_mem);
+    f32x4* const red = reinterpret_cast<f32x4*>(ring + kWalkWaves * T::RING * kWalkGroup);   // [2][wave][RED]
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = lane & 15, g = lane >> 4;
+    const int H = A.H, W = A.W, N = H * W, F = A.F;
+    // Workgroups are dealt to the XCDs round robin; every XCD gets one contiguous run of the units, in
+    // which the frame groups of one (clip, strip, channel share) are neighbours: their anchor rows are read
+    // from HBM once and then come from that XCD's L2.
+    int u;
+    {
+        const int U = (int)gridDim.x, xcd = (int)blockIdx.x & 7;
+        u = xcd * (U >> 3) + min(xcd, U & 7) + ((int)blockIdx.x >> 3);
+    }
+    const int grp = u % A.groups; u /= A.groups;
+    const int seg = u % (A.lsegs * A.ysegs); u /= A.lsegs * A.ysegs;
+    const int share = u % A.nk;
+    const int b = u / A.nk;
+
+    int a;
+    if (A.mode == 0) {
+        a = A.ext_anchor ? -1
+          : A.fixed_anchor >= 0 ? A.fixed_anchor
+          : A.fixed_anchor == kAnchorGiven ? A.anchor_index[b]
+                                           : pick_anchor(A.score_part, A.clip_part, b, F, A.S, lane);
+    } else if (A.mode == 1) {
+        if (A.spec[4 * b + 1] == 0) return;                  // no trusted guess: the clip takes the two-pass route
+        a = A.spec[4 * b];
+    } else {
+        a = pick_anchor(A.score_part, A.clip_part, b, F, A.S, lane);
+    }
+    a = __builtin_amdgcn_readfirstlane(a);
+    if (A.mode != 1 && A.fixed_anchor != kAnchorGiven && grp + seg + share == 0 && threadIdx.x == 0)
+        A.anchor_index[b] = a;
+    if (A.mode == 2 && A.spec[4 * b + 1] != 0 && A.spec[4 * b] == a) return;   // confirmed: searched already
+
+    // the unit's part of the grid: column strips line_lo .. line_hi-1, tiles step_lo .. step_hi-1 of each
+    const int line_lo = (int)((long long)A.lines * (seg / A.ysegs) / A.lsegs), line_hi = (int)((long long)A.lines * (seg / A.ysegs + 1) / A.lsegs);
+    const int all_steps = (H + STEP - 1) / STEP;
+    const int step_lo = (int)((long long)all_steps * (seg % A.ysegs) / A.ysegs), step_hi = (int)((long long)all_steps * (seg % A.ysegs + 1) / A.ysegs);
+    // first cell and width of a strip; rows of grids wider than 16 keep a margin of r for the window
+    const int margin = PATCH || A.lines == 1 ? 0 : RAD;
+    const int strip_w = W / A.lines, wide_strips = W % A.lines;      // (the first strips are a cell wider where need be)
+    auto strip_x = [&](int line) { return PATCH ? 4 * line : line * strip_w + min(line, wide_strips); };
+    // frames of the group: cnt slots from k0, the anchor left out where it is not walked
+    const int walked = (SPEC || a < 0) ? F : F - 1;
+    const int skip = (SPEC || a < 0) ? 0x7fffffff : a;
+    const int k0 = grp * A.nf;
+    const int cnt = min(A.nf, walked - k0);
+    if (cnt <= 0) return;                                    // (one frame, the anchor: nothing to walk)
+    // channels of this wave: groups q_lo .. q_lo+gq-1 of 64
+    const int total_groups = A.C / 64;
+    const int q_lo = (int)((long long)total_groups * (share * kWalkWaves + wave) / (kWalkWaves * A.nk));
+    const int gq = (int)((long long)total_groups * (share * kWalkWaves + wave + 1) / (kWalkWaves * A.nk)) - q_lo;
+    const size_t row_bytes = (size_t)A.C * 2;
+    const size_t frame_bytes = (size_t)N * row_bytes;
+    const char* const src_frames = reinterpret_cast<const char*>(A.x) + (size_t)b * F * frame_bytes + (size_t)q_lo * 128;
+    const char* const anchor_frame = (a < 0 ? reinterpret_cast<const char*>(A.ext_anchor) + (size_t)b * frame_bytes + (size_t)q_lo * 128
+                                            : src_frames + (size_t)a * frame_bytes);
+
+    // lane l of load i of a group fills piece l of its KiB: row 8i + l/8 of the tile, stored piece l%8
+    const int lrow = lane >> 3;
+    const uint32_t piece0 = (uint32_t)((lane & 7) ^ (lane >> 4)) * 16, piece1 = piece0 ^ 64;
+    // operand lane (token m, channels 8g..8g+7) of K-step j of a group
+    const uint32_t rd0 = (uint32_t)((m >> 3) * 1024 + ((m & 7) * 8 + (g ^ (m >> 1))) * 16), rd1 = rd0 ^ 64;
+    const uint32_t ring_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + (uint32_t)wave * (T::RING * kWalkGroup);
+    const char* const my_ring = ring + wave * (T::RING * kWalkGroup);
+
+    // The stream of tiles, in the order they are used: for every strip the anchor tiles of the first window but the
+    // new ones, then for every step the NEW anchor tiles and the source tiles of the frames.  The state below
+    // belongs to the loads, which run ahead of the use by up to RING groups.  l_e < 0: tiles ahead of the strip's
+    // first step; 0 .. NEW-1: the new anchor tiles; NEW + f: frame f.
+    int left = (line_hi - line_lo) * (NT - NEW + (step_hi - step_lo) * (NEW + cnt)) * gq;   // groups not yet used
+    int to_load = left;                                      // groups not yet requested
+    int l_line = line_lo, l_step = step_lo, l_e = NEW - NT, l_q = 0, l_slot = 0;
+    const char* l_base;
+    uint32_t l_off0, l_off1;
+    bool l_keep = false;
+    auto locate = [&]() {                                    // addresses of the tile at the load state
+        // cells outside the grid read the nearest cell inside (their products are masked, their sums weighted 0)
+        auto cell = [&](int y, int x) {
+            return (uint32_t)(min(max(y, 0), H - 1) * W + min(max(x, 0), W - 1)) * (uint32_t)row_bytes;
+        };
+        const int x0 = strip_x(l_line);
+        if (l_e < NEW) {
+            const int c = NT - NEW + NEW * (l_step - step_lo) + l_e;
+            l_base = anchor_frame;
+            if constexpr (PATCH) {
+                const int y = STEP * step_lo + 2 * c - RAD;
+                l_off0 = cell(y + lrow / T::SPAN, x0 - RAD + lrow % T::SPAN) + piece0;
+                l_off1 = cell(y + min((lrow + 8) / T::SPAN, 1), x0 - RAD + (lrow + 8) % T::SPAN) + piece1;
+            } else {
+                const int y = step_lo + c - RAD;
+                l_off0 = cell(y, x0 - margin + lrow) + piece0;
+                l_off1 = cell(y, x0 - margin + lrow + 8) + piece1;
+            }
+        } else {
+            const int k = k0 + l_e - NEW + (k0 + l_e - NEW >= skip ? 1 : 0);
+            l_base = src_frames + (size_t)k * frame_bytes;
+            if constexpr (!SPEC)
+                l_keep = ((l_line - line_lo) * (step_hi - step_lo) + l_step - step_lo) * 256 >=
+                         (line_hi - line_lo) * (step_hi - step_lo) * A.keep_from;
+            if constexpr (PATCH) {
+                l_off0 = cell(STEP * l_step + (lrow & 3), x0 + (lrow >> 2)) + piece0;
+                l_off1 = cell(STEP * l_step + (lrow & 3), x0 + 2 + (lrow >> 2)) + piece1;
+            } else {
+                const int last = strip_x(l_line + 1) - 1;
+                l_off0 = cell(l_step, min(x0 + lrow, last)) + piece0;
+                l_off1 = cell(l_step, min(x0 + lrow + 8, last)) + piece1;
+            }
+        }
+    };
+    locate();
+    auto request = [&]() {
+        if (to_load == 0) return;
+        --to_load;
+        const uint32_t d = ring_lds + (uint32_t)l_slot * kWalkGroup;
+        if (l_e < NEW) {
+            load_to_lds<false>(l_base, l_off0, d);
+            load_to_lds<false>(l_base, l_off1, d + 1024);
+        } else {
+            if (l_keep) {
+                load_to_lds<false>(l_base, l_off0, d);
+                load_to_lds<false>(l_base, l_off1, d + 1024);
+            } else {
+                load_to_lds<true>(l_base, l_off0, d);
+                load_to_lds<true>(l_base, l_off1, d + 1024);
+            }
+        }
+        l_slot = l_slot + 1 == T::RING ? 0 : l_slot + 1;
+        l_base += 128;
+        if (++l_q == gq) {
+            l_q = 0;
+            if (++l_e == NEW + cnt) {
+                l_e = 0;
+                if (++l_step == step_hi) {
+                    l_step = step_lo;
+                    l_e = NEW - NT;
+                    ++l_line;
+                }
+            }
+            locate();
+        }
+    };
+    for (int i = 0; i < T::RING; ++i) request();
+
+    int slot = 0;
+    // the two K-steps of the next group, in operand order; its ring slot is filled again at once
+    auto take = [&](u32x4& f0, u32x4& f1) {
+        if (left >= T::RING) wait_loads<2 * (T::RING - 1)>();
+        else wait_loads<0>();                                // (the last groups: nothing is requested behind them)
+        const char* s = my_ring + slot * kWalkGroup;
+        f0 = *reinterpret_cast<const u32x4*>(s + rd0);
+        f1 = *reinterpret_cast<const u32x4*>(s + rd1);
+        settle(f0, f1);
+        slot = slot + 1 == T::RING ? 0 : slot + 1;
+        --left;
+        request();
+    };
+    bf16x8 win[NT][KW];                                      // the window of the patch
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+#pragma unroll
+        for (int ks = 0; ks < KW; ++ks) win[q][ks] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    }
+    float sum[SPEC ? FRS : 1][KW][2];
+    bf16x8 pick0, pick1;
+    if constexpr (SPEC) {
+        pick0 = channel_picker(0, lane);
+        pick1 = channel_picker(1, lane);
+#pragma unroll
+        for (int f = 0; f < FRS; ++f) {
+#pragma unroll
+            for (int ks = 0; ks < KW; ++ks) sum[f][ks][0] = sum[f][ks][1] = 0.f;
+        }
+    }
+    // A finished tile has 16 x (KK + 1) numbers worth adding up over the waves: the (2r+1)^2 products of every
+    // token with its window, and its squared norm (the diagonal of the tile against itself).  Wave w adds
+    // those of tokens 2w and 2w + 1, a lane each.
+    constexpr int PER = 2 * (KK + 1);
+    static_assert(PER <= 64, "a lane per value");
+    const bool adds = lane < PER;
+    const int vt = 2 * wave + (lane >= KK + 1 ? 1 : 0), ve = lane >= KK + 1 ? lane - (KK + 1) : lane;
+    const int vy = ve / NP, vx = ve % NP;                    // cell of the window
+    int v_slot, my_slot;                                     // where the value lies, and where this lane's products go
+    bool in_band;
+    if constexpr (PATCH) {
+        const int row = (vt & 3) + vy, span = m % T::SPAN - g;
+        v_slot = (row >> 1) * T::BAND + ((vt >> 2) * 2 + (row & 1)) * NP + vx;
+        in_band = m < 2 * T::SPAN && span >= 0 && span < NP;
+        my_slot = (g * 2 + m / T::SPAN) * NP + span;
+    } else {
+        v_slot = vy * T::BAND + (vt >> 2) * T::SPAN + (vt & 3) + vx;
+        my_slot = m - (4 * g - RAD + margin);
+        in_band = my_slot >= 0 && my_slot < T::SPAN;
+        my_slot += g * T::SPAN;
+    }
+    const bool on_diagonal = (m >> 2) == g;
+    const float* const red_in = reinterpret_cast<const float*>(red) + (!adds ? 0 : (ve < KK ? v_slot : NT * T::BAND + vt) * 4 + (vt & 3));
+    f32x4* const red_out = red + (in_band ? my_slot : 0);
+    int buf = 0;
+    // The shares are read behind the barrier and added and stored in the middle of the next tile, when they have
+    // long arrived.
+    float pend[kWalkWaves];
+    float* pend_out = nullptr;
+    auto fetch_shares = [&](float* out) {
+        lds_barrier();
+        pend_out = adds ? out : nullptr;
+        const float* r = red_in + buf * (kWalkWaves * T::RED * 4);
+#pragma unroll
+        for (int w = 0; w < kWalkWaves; ++w) pend[w] = r[w * (T::RED * 4)];
+        buf ^= 1;
+    };
+    auto store_shares = [&]() {
+        if (pend_out) *pend_out = ((pend[0] + pend[1]) + (pend[2] + pend[3])) + ((pend[4] + pend[5]) + (pend[6] + pend[7]));
+        pend_out = nullptr;
+    };
+    float* const part_out = A.part + ((size_t)share * A.B * F * N + (size_t)b * F * N) * (KK + 1) + ve;
+    auto source_tile = [&](int f, int line, int step, float (&tile_sum)[KW][2]) {
+        const int x0 = strip_x(line), x1 = min(strip_x(line + 1), W);
+        float weight[4];                                     // SPEC: rows of the tile that hold no cell of their own count zero
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            weight[j] = (PATCH ? STEP * step + j < H && x0 + g < W : x0 + 4 * g + j < x1) ? 1.0f : 0.0f;
+        f32x4 acc[NT + 1];
+#pragma unroll
+        for (int q = 0; q <= NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int gi = 0; gi < G2; ++gi) {
+            if (gi < gq) {                                   // wave-uniform
+                u32x4 fr[2];
+                take(fr[0], fr[1]);
+                if (gi == 0) store_shares();
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
+#pragma unroll
+                    for (int q = 0; q < NT; ++q)
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, win[q][2 * gi + j], acc[q], 0, 0, 0);
+                    acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, acc[NT], 0, 0, 0);
+                    if constexpr (SPEC) {
+                        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                        const f32x4 d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick0, zero, 0, 0, 0);
+                        const f32x4 d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick1, zero, 0, 0, 0);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            tile_sum[2 * gi + j][0] = fmaf(d0[e], weight[e], tile_sum[2 * gi + j][0]);
+                            tile_sum[2 * gi + j][1] = fmaf(d1[e], weight[e], tile_sum[2 * gi + j][1]);
+                        }
+                    }
+                }
+            }
+        }
+        const size_t mine = (size_t)(buf * kWalkWaves + wave) * T::RED;
+        if (in_band) {
+#pragma unroll
+            for (int q = 0; q < NT; ++q) red_out[mine + q * T::BAND] = acc[q];
+        }
+        if (on_diagonal) red[mine + NT * T::BAND + m] = acc[NT];
+        const int k = k0 + f + (k0 + f >= skip ? 1 : 0);
+        const int y = PATCH ? STEP * step + (vt & 3) : step, xc = x0 + (PATCH ? vt >> 2 : vt);
+        fetch_shares(y < H && xc < x1 ? part_out + ((size_t)k * N + y * W + xc) * (KK + 1) : nullptr);
+    };
+    auto anchor_tile = [&](int line, int c, bf16x8 (&tile)[KW]) {
+        f32x4 norm = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int gi = 0; gi < G2; ++gi) {
+            if (gi < gq) {
+                u32x4 fr[2];
+                take(fr[0], fr[1]);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
+                    tile[2 * gi + j] = av;
+                    norm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, norm, 0, 0, 0);
+                }
+            }
+        }
+        if (grp == 0) {                                      // one frame group publishes the anchor's norms
+            store_shares();
+            if (on_diagonal) red[(size_t)(buf * kWalkWaves + wave) * T::RED + NT * T::BAND + m] = norm;
+            const int y = STEP * step_lo - RAD + (PATCH ? 2 * c + vt / T::SPAN : c);
+            const int xc = strip_x(line) + (PATCH ? vt % T::SPAN - RAD : vt - margin);
+            fetch_shares(ve == KK && (!PATCH || vt < 2 * T::SPAN) && y >= 0 && y < H && xc >= 0 && xc < W
+                             ? A.norm_part + ((size_t)share * A.B + b) * N + y * W + xc : nullptr);
+        }
+    };
+
+    for (int line = line_lo; line < line_hi; ++line) {
+#pragma unroll
+        for (int q = 0; q + NEW < NT; ++q) anchor_tile(line, q, win[q + NEW]);
+        for (int step = step_lo; step < step_hi; ++step) {
+#pragma unroll
+            for (int q = 0; q + NEW < NT; ++q) {
+#pragma unroll
+                for (int ks = 0; ks < KW; ++ks) win[q][ks] = win[q + NEW][ks];
+            }
+#pragma unroll
+            for (int e = 0; e < NEW; ++e) anchor_tile(line, NT - NEW + NEW * (step - step_lo) + e, win[NT - NEW + e]);
+            if constexpr (SPEC) {
+                source_tile(0, line, step, sum[0]);
+                if (cnt > 1) source_tile(1, line, step, sum[1]);
+                if constexpr (FRS > 2) {
+                    if (cnt > 2) source_tile(2, line, step, sum[2]);
+                    if (cnt > 3) source_tile(3, line, step, sum[3]);
+                }
+            } else {
+                for (int f = 0; f < cnt; ++f) source_tile(f, line, step, sum[0]);
+            }
+        }
+    }
+    store_shares();
+    if constexpr (SPEC) {
+        // a lane holds four tokens' worth of channel m (and 16 + m) of a K-step: the four groups of lanes are
+        // added by an fp32 MFMA against ones, and 256 bytes per frame and group of 64 channels are stored
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int f = 0; f < FRS; ++f) {
+            if (f < cnt) {
+                float* out = A.strip_sum + (((size_t)b * F + k0 + f) * (A.lsegs * A.ysegs) + seg) * A.C + (size_t)q_lo * 64 + lane;
+#pragma unroll
+                for (int gi = 0; gi < G2; ++gi) {
+                    if (gi < gq) {
+                        float total[2];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) {
+                            const f32x4 r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][2 * gi + j][0], zero, 0, 0, 0);
+                            const f32x4 r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][2 * gi + j][1], zero, 0, 0, 0);
+                            total[j] = (g & 1) ? r1[0] : r0[0];
+                        }
+                        out[gi * 64] = lane < 32 ? total[0] : total[1];
+                    }
+                }
+            }
+        }
+    }
+}
+
+// The similarities, arg max, gate and keep words from the window products (one wave per keep word, a lane per
+// token): the shares of the channels are added in order, candidates are met in ascending order of their
+// index, and a NaN wins no comparison.  ALL (tied-batch mode): every similarity of the window is stored to
+// win_sim[b][k][cell of the window][i] instead.
+template <int RAD, bool ALL>
+__global__ __launch_bounds__(256) void k_walk_finish(const float* __restrict__ part, const float* __restrict__ norm_part,
+                                                     const int32_t* __restrict__ anchor_index,
+                                                     int32_t* __restrict__ fuse_map, float* __restrict__ best_sim,
+                                                     int32_t* __restrict__ best_idx, uint64_t* __restrict__ keep_bits,
+                                                     float* __restrict__ win_sim, int B, int F, int H, int W, int NW,
+                                                     int nk, float t, size_t words)
+{
+    constexpr int NP = 2 * RAD + 1, KK = NP * NP;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const size_t wd = (size_t)blockIdx.x * 4 + wave;
+    if (wd >= words) return;
+    const int N = H * W;
+    const size_t frame = wd / NW;
+    const int b = (int)(frame / F), k = (int)(frame % F);
+    const int i = (int)(wd % NW) * 64 + lane;
+    const bool real = i < N;
+    const size_t tok = frame * (size_t)N + i;
+    const int a = anchor_index[b];
+    if (k == a) {                                            // (wave-uniform)
+        if constexpr (!ALL) {
+            if (real) {
+                fuse_map[tok] = -1;
+                if (best_sim) best_sim[tok] = 1.0f;
+                if (best_idx) best_idx[tok] = i;
+            }
+            const uint64_t bits = __ballot(real);
+            if (lane == 0) keep_bits[wd] = bits;
+        }
+        return;
+    }
+    float best = kNegInf;
+    int arg = -1;
+    if (real) {
+        const size_t tokens = (size_t)B * F * N;
+        const int y = i / W, xc = i % W;
+        float v[KK + 1];
+        const float* p = part + tok * (KK + 1);
+#pragma unroll
+        for (int e = 0; e <= KK; ++e) v[e] = p[e];
+        for (int s = 1; s < nk; ++s) {
+            p += tokens * (KK + 1);
+#pragma unroll
+            for (int e = 0; e <= KK; ++e) v[e] += p[e];
+        }
+        const float sinv = v[KK] > 0.f ? __builtin_amdgcn_rsqf(v[KK]) : 0.f;
+#pragma unroll
+        for (int dy = -RAD; dy <= RAD; ++dy) {
+#pragma unroll
+            for (int dx = -RAD; dx <= RAD; ++dx) {
+                const int yy = y + dy, xx = xc + dx, cell = (dy + RAD) * NP + dx + RAD;
+                if (yy >= 0 && yy < H && xx >= 0 && xx < W) {
+                    const int ja = yy * W + xx;
+                    float ss = norm_part[(size_t)b * N + ja];
+                    for (int s = 1; s < nk; ++s) ss += norm_part[((size_t)s * B + b) * N + ja];
+                    const float ai = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+                    const float sim = v[cell] * sinv * ai;
+                    if constexpr (ALL) {
+                        win_sim[(frame * KK + cell) * (size_t)N + i] = sim;
+                    } else if (sim > best) {
+                        best = sim;
+                        arg = ja;
+                    }
+                }
+            }
+        }
+    }
+    if constexpr (!ALL) {
+        const bool fused = best > t;                         // keep = 1[s^ <= t]
+        if (real) {
+            fuse_map[tok] = fused ? arg : -1;
+            if (best_sim) best_sim[tok] = best;
+            if (best_idx) best_idx[tok] = arg;
+        }
+        const uint64_t bits = __ballot(real && !fused);
+        if (lane == 0) keep_bits[wd] = bits;
+    }
+}
+
+}  // namespace
+
+// How the walk is dealt to workgroups (one per CU at a time).  `frames` are walked per clip.
+WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
+{
+    WalkPlan w{};
+    if (p.dtype != TTF_BF16 || p.r > 2 || p.C % 64 != 0 || p.C < 512 || frames < 1) return w;
+    if ((unsigned long long)p.H * p.W * p.C * 2 >= (1ull << 32)) return w;   // (32-bit offsets inside a frame)
+    w.patch = p.r == 2;
+    w.nk = (p.C / 32 + kWalkWaves * kWalkSteps - 1) / (kWalkWaves * kWalkSteps);
+    w.lines = w.patch ? (p.W + 3) / 4 : (p.W <= 16 ? 1 : (p.W + 15 - 2 * p.r) / (16 - 2 * p.r));
+    const int steps = w.patch ? (p.H + 3) / 4 : p.H, fresh = w.patch ? 2 : 1, held = w.patch ? p.r : 2 * p.r;
+    // Time of a deal in tiles: a workgroup starts up (two tiles' time), reads the anchor tiles of its run (which
+    // come from L2: a third each) and its source tiles.  The last round of workgroups may not fill the chip;
+    // half of its time is that of its CUs, half that of the memory (B4 F32 16x16 C4096: 64 / 128 / 256 workgroups
+    // 102 / 64 / 46 us).
+    // Frame sums are stored per run of the grid: as many runs as leave the products room in the strip-sum section.
+    const long long products = (long long)w.nk * ((2 * p.r + 1) * (2 * p.r + 1) + 1) * p.H * p.W;
+    const long long most_runs = sums ? std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C) : 1 << 20;
+    double best = 1e300;
+    const int most = sums ? (p.r == 2 ? Tiles<2, true>::FRS : Tiles<1, false>::FRS) : 32;
+    for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
+        for (int ysegs = 1; ysegs <= 4 && ysegs <= steps && lsegs * ysegs <= most_runs; ysegs *= 2) {
+            int last = 0;
+            for (int want = 1; want <= most; ++want) {
+                const int groups = (frames + want - 1) / want, nf = (frames + groups - 1) / groups;
+                if (nf == last) continue;
+                last = nf;
+                const double units = (double)p.B * w.nk * groups * lsegs * ysegs;
+                if (units > 1e8) continue;
+                const double lines = (w.lines + lsegs - 1) / lsegs, run = (steps + ysegs - 1) / ysegs;   // (of the longest)
+                const double tiles = 2.0 + lines * (run * (nf + 0.35 * fresh) + 0.35 * held);
+                const double whole = (double)((long long)units / 256), rest = units - 256 * whole;
+                const double time = tiles * (whole + (rest > 0 ? 0.5 + 0.5 * rest / 256 : 0.0));
+                if (time < best) {
+                    best = time;
+                    w.nf = nf; w.groups = groups; w.lsegs = lsegs; w.ysegs = ysegs;
+                }
+            }
+        }
+    }
+    w.ok = best < 1e300;
+    return w;
+}
+
+// The scratch of the walk in the strip-sum and fragment sections of the workspace, where they have room.
+bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan, bool sums, WalkScratch& scratch)
+{
+    const size_t tokens = (size_t)p.B * p.F * p.H * p.W, KK = (size_t)(2 * p.r + 1) * (2 * p.r + 1);
+    char* base[2] = {reinterpret_cast<char*>(w.strip_sum), reinterpret_cast<char*>(w.anchor_frag)};
+    size_t room[2] = {w.strip_bytes, w.frag_bytes};
+    bool fits = true;
+    auto take = [&](size_t floats) -> float* {
+        const size_t n = align_up(floats * sizeof(float), 256);
+        for (int i = 0; i < 2; ++i) {
+            if (n > room[i]) continue;
+            char* at = base[i];
+            base[i] += n;
+            room[i] -= n;
+            return reinterpret_cast<float*>(at);
+        }
+        fits = false;
+        return nullptr;
+    };
+    scratch.part = take(plan.nk * tokens * (KK + 1));
+    scratch.strip_sum = sums ? take((size_t)p.B * p.F * plan.lsegs * plan.ysegs * p.C) : nullptr;
+    scratch.norm_part = take((size_t)plan.nk * p.B * p.H * p.W);
+    return fits;
+}
+
+hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
+                              const WalkPlan& plan, const WalkScratch& scratch, int32_t* anchor_index, bool anchor_given,
+                              int mode, hipStream_t s)
+{
+    WalkArgs a{};
+    a.x = static_cast<const uint16_t*>(x);
+    a.ext_anchor = static_cast<const uint16_t*>(ext_anchor);
+    a.score_part = w.score_part;
+    a.clip_part = w.clip_part;
+    a.anchor_index = anchor_index;
+    a.spec = w.spec;
+    a.part = scratch.part;
+    a.norm_part = scratch.norm_part;
+    a.strip_sum = scratch.strip_sum;
+    a.B = p.B; a.F = p.F; a.H = p.H; a.W = p.W; a.C = p.C; a.S = (p.C + 255) / 256;
+    a.nk = plan.nk; a.groups = plan.groups; a.nf = plan.nf;
+    a.lines = plan.lines; a.lsegs = plan.lsegs; a.ysegs = plan.ysegs;
+    a.fixed_anchor = anchor_given ? kAnchorGiven : fixed_frame(p);
+    a.mode = mode;
+    a.keep_from = 256 - (int)(256 * kept_share(p));
+    const unsigned grid = (unsigned)((size_t)p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs);
+    auto go = [&](auto kernel, size_t lds) {
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
+        if (e != hipSuccess) return e;
+        kernel<<<grid, kWalkWaves * 64, lds, s>>>(a);
+        return hipGetLastError();
+    };
+    const bool sums = mode == 1;
+    switch (p.r) {
+        case 0: return sums ? go(k_search_walk<0, false, true>, Tiles<0, false>::LDS) : go(k_search_walk<0, false, false>, Tiles<0, false>::LDS);
+        case 1: return sums ? go(k_search_walk<1, false, true>, Tiles<1, false>::LDS) : go(k_search_walk<1, false, false>, Tiles<1, false>::LDS);
+        case 2: return sums ? go(k_search_walk<2, true, true>, Tiles<2, true>::LDS) : go(k_search_walk<2, true, false>, Tiles<2, true>::LDS);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_walk_finish(const ttf_params& p, const Workspace& w, const WalkPlan& plan, const WalkScratch& scratch,
+                              const int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,
+                              float* win_sim, hipStream_t s)
+{
+    const int NW = (p.H * p.W + 63) / 64;
+    const size_t words = (size_t)p.B * p.F * NW;
+    auto go = [&](auto kernel) {
+        kernel<<<(unsigned)((words + 3) / 4), 256, 0, s>>>(scratch.part, scratch.norm_part, anchor_index, fuse_map, best_sim,
+                                                           best_idx, w.keep_bits, win_sim, p.B, p.F, p.H, p.W, NW, plan.nk,
+                                                           p.t, words);
+        return hipGetLastError();
+    };
+    switch (p.r) {
+        case 0: return win_sim ? go(k_walk_finish<0, true>) : go(k_walk_finish<0, false>);
+        case 1: return win_sim ? go(k_walk_finish<1, true>) : go(k_walk_finish<1, false>);
+        case 2: return win_sim ? go(k_walk_finish<2, true>) : go(k_walk_finish<2, false>);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace ttf
