@@ -290,10 +290,12 @@ int ttf_last_hip_error(void);
  *                 of two when the guesses hold, one extra search for a clip whose trusted guess
  *                 was wrong; on inputs below 256 MiB the two may take different searches, whose
  *                 similarities agree as those of different routes do, see ttf_search_route).
- *                 Available for bf16 input on grids whose rows fill at least 70 % of the 32-cell
+ *                 Available with C >= 1024, F >= 2 and the automatic anchor for fp32 input with C % 32 == 0
+ *                 and r <= 1, and for bf16 input with C % 128 == 0 and r <= 2 on grids whose rows fill at least 70 % of the 32-cell
  *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
- *                 height), C % 128 == 0, C >= 1024, r <= 2, F >= 2, automatic anchor.
- * mode  0 (default): speculative for inputs of 256 MiB and more in clips of at most 128 frames
+ *                 height); not where B, F and the grid are such that the sums have no room in the
+ *                 workspace (many frames of few tokens, and fp32 clips of about 100 frames and more).
+ * mode  0 (default): speculative for inputs of 256 MiB and more in clips of at most 64 frames
  *       where available, else two-pass;
  *       1: speculative wherever available;  -1: always two-pass.
  * Process-wide; takes effect for calls made after it returns.  INVALID_ARG for other values.
@@ -305,8 +307,9 @@ ttf_status ttf_set_speculation(int mode);
  * Search"): a host-side query, no GPU work.  The routes add the channels in different orders:
  * similarities agree to about 3e-7 (each within 1e-5 of the exact value), and only a token whose
  * similarity lies that close to t, or to another candidate's, may be gated or matched differently.
- * So do the kernels behind one route: bf16 problems with C >= 1024 take a search that walks whole frames where it
- * is the faster one, which depends on the grid, r, C and the size of the input.
+ * So do the kernels behind one route: problems with C >= 1024 (fp32: 768, r <= 1) take a search that walks whole
+ * frames where it is the faster one, which depends on the grid, r, C and the size of the input; it makes fp32 problems
+ * of 32 MiB and more matrix-core ones that would otherwise be too small.
  * For most problems the route depends on dtype, r, C and the grid.  For bf16 with C % 32 != 0 (C % 8 == 0,
  * C >= 768) it also depends on B and F -- small problems and few-column grids are searched faster by the
  * general kernels -- and on the workspace: the answer is for one of ttf_workspace_size() bytes (a

@@ -281,47 +281,48 @@ __global__ __launch_bounds__(256) void k_reduce_strips(const float* __restrict__
     *reinterpret_cast<float4*>(frame_sum + frame * (size_t)C + c) = acc;
 }
 
-// Anchor guess, step 1 (bf16 rows): sums over the tokens of a frame of the kGuessChannels guess
-// channels only (kGuessSegments runs of 128 bytes per token row).  Block (frame, part) covers tokens
-// part*per .. (part+1)*per - 1: thread t reads 16-byte piece t%32 of the guess channels of its tokens
-// t/32, t/32 + 8, ...; the eight token groups are added through LDS in order.  The parts of a frame
-// are added by guess_pick_block.
-__global__ __launch_bounds__(256) void k_guess_sums(const uint16_t* __restrict__ x, float* __restrict__ guess_sum,
+// Anchor guess, step 1: sums over the tokens of a frame of the kGuessChannels guess channels only
+// (kGuessSegments runs of 64 channels per token row).  Block (frame, part) covers tokens part*per ..
+// (part+1)*per - 1: thread t reads 16-byte piece t%P of the guess channels of its tokens t/P, t/P + 256/P, ...
+// (P = 32 pieces of bf16, 64 of fp32 rows); the token groups are added through LDS in order.  The parts
+// of a frame are added by guess_pick_block.
+template <typename T>
+__global__ __launch_bounds__(256) void k_guess_sums(const T* __restrict__ x, float* __restrict__ guess_sum,
                                                     int N, int C, int parts)
 {
-    static_assert(kGuessSegChannels == 64 && kGuessSegments * 8 == 32, "32 sixteen-byte pieces per token");
+    constexpr int V = 16 / (int)sizeof(T), SEG = kGuessSegChannels / V, P = kGuessSegments * SEG, G = 256 / P;
     const size_t frame = blockIdx.x / parts;
     const int part = blockIdx.x % parts;
     const int per = (N + parts - 1) / parts;
     const int n_lo = part * per, n_hi = min(N, n_lo + per);
-    const int ts = threadIdx.x >> 5, q = threadIdx.x & 31;
-    const int ch = guess_segment_start(C, q >> 3) + (q & 7) * 8;
-    const uint16_t* base = x + frame * (size_t)N * C + ch;
-    float acc[8];
+    const int ts = threadIdx.x / P, q = threadIdx.x % P;
+    const int ch = guess_segment_start(C, q / SEG) + (q % SEG) * V;
+    const T* base = x + frame * (size_t)N * C + ch;
+    float acc[V];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-    for (int i0 = n_lo + ts; i0 < n_hi; i0 += 64) {
-        RowVec<bf16_t, 8> r[8];
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    for (int i0 = n_lo + ts; i0 < n_hi; i0 += 8 * G) {
+        RowVec<T, V> r[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int i = i0 + 8 * u;
-            if (i < n_hi) r[u].template load<true>(reinterpret_cast<const bf16_t*>(base + (size_t)i * C));
+            const int i = i0 + G * u;
+            if (i < n_hi) r[u].template load<true>(base + (size_t)i * C);
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            if (i0 + 8 * u < n_hi) {
+            if (i0 + G * u < n_hi) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] += r[u].v[e];
+                for (int e = 0; e < V; ++e) acc[e] += r[u].v[e];
             }
         }
     }
-    __shared__ float part_s[8][kGuessChannels];
+    __shared__ float part_s[G][kGuessChannels];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part_s[ts][q * 8 + e] = acc[e];
+    for (int e = 0; e < V; ++e) part_s[ts][q * V + e] = acc[e];
     __syncthreads();
     float t = part_s[0][threadIdx.x];
 #pragma unroll
-    for (int w = 1; w < 8; ++w) t += part_s[w][threadIdx.x];
+    for (int w = 1; w < G; ++w) t += part_s[w][threadIdx.x];
     guess_sum[(size_t)blockIdx.x * kGuessChannels + threadIdx.x] = t;
 }
 
@@ -682,12 +683,11 @@ static int frame_sum_parts(const ttf_params& p, const Workspace& w)
     return (int)((N + per - 1) / per);                       // (no run is empty)
 }
 
-hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, hipStream_t s)
+hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, double kept,
+                             hipStream_t s)
 {
     const int N = p.H * p.W;
     const int32_t* spec = skip_trusted ? w.spec : nullptr;
-    // (beside a speculative search nobody reads these frames next: only the search of the clips left does)
-    const double kept = skip_trusted ? 0.0 : kept_share(p);
     auto keep_from = [&](dim3 g) { return (unsigned)((double)g.x * g.y * (1.0 - kept)); };
     return by_layout(p, [&](auto tag, auto vtag) {
         using T = decltype(tag);
@@ -744,9 +744,13 @@ hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, const f
 hipError_t launch_guess_sums(const ttf_params& p, const void* x, const Workspace& w, hipStream_t s)
 {
     const int parts = guess_parts(p);
-    k_guess_sums<<<(unsigned)(p.B * p.F * parts), 256, 0, s>>>(static_cast<const uint16_t*>(x), w.guess_sum, p.H * p.W,
-                                                               p.C, parts);
-    return hipGetLastError();
+    auto go = [&](auto tag) {
+        using T = decltype(tag);
+        k_guess_sums<T><<<(unsigned)(p.B * p.F * parts), 256, 0, s>>>(static_cast<const T*>(x), w.guess_sum, p.H * p.W, p.C,
+                                                                      parts);
+        return hipGetLastError();
+    };
+    return p.dtype == TTF_BF16 ? go(bf16_t{}) : go(float{});
 }
 
 hipError_t launch_guess_pick(const ttf_params& p, const Workspace& w, hipStream_t s)

@@ -30,13 +30,18 @@ hipError_t launch_window_search_mfma_f32(const ttf_params& p, const void* x, boo
 // frames that are walked (all of them against an external anchor, all but the anchor otherwise); larger
 // radii and other channel counts take the general wave-per-token kernel.  The environment variable
 // TTF_SEARCH=general, read once per process, forces the general kernels (for comparisons).
-bool use_mfma_path(const ttf_params& p, bool tail, bool external_anchor)
+static bool forced_general()
 {
     static const bool general = [] {
         const char* force = std::getenv("TTF_SEARCH");
         return force && std::strcmp(force, "general") == 0;
     }();
-    if (general || (tail_channels(p) && !(tail && tail_search_pays(p, external_anchor ? p.F : p.F - 1)))) return false;
+    return general;
+}
+
+bool use_mfma_path(const ttf_params& p, bool tail, bool external_anchor)
+{
+    if (forced_general() || (tail_channels(p) && !(tail && tail_search_pays(p, external_anchor ? p.F : p.F - 1)))) return false;
     return mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p);
 }
 
@@ -76,14 +81,21 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 //     67), 1.0 to 1.3 from 96 MiB on (B6 F17 16x16 C3584 111 / 103, B4 F20 16x16 C3584 r0 95 / 83), with three strips in a row of
 //     32 from 160 MiB (B2 F6 32x32 C2048 53 / 61, B5 F9 32x32 C3072 172 / 145); the 5x5 window from 24 MiB (B5 F14 16x16
 //     C1792 68.5 / 59.0), and rows whose K-steps do not divide over the waves there from 32 MiB (B2 F15 16x16 C2624 61.1 / 49.8).
-static bool use_walk(const ttf_params& p, const Workspace& w, bool external_anchor, WalkPlan& plan, WalkScratch& scratch)
+// fp32 tokens, windows up to 3x3 (90 shapes): against the matrix-core search 1.02 to 2.8 from C 1024 on (B3 F7 16x21 C1024
+//   73 / 50 us, B2 F21 16x13 C4096 264 / 94, B16 F14 16x16 C3072 387 / 314), 0.84 to 1.57 below; against the wave-per-token
+//   search of small problems from 32 MiB and C 768 on 0.97 to 1.9 (B1 F12 16x16 C3072 64 / 48), below 32 MiB 0.6 to 1.4.
+static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool external_anchor, WalkPlan& plan,
+                     WalkScratch& scratch)
 {
-    if (p.dtype != TTF_BF16 || p.C < 1024) return false;
     const int frames = external_anchor ? p.F : p.F - 1;      // (a segment takes the search of the clip it equals)
-    if (mfma_search_supported(p)) {
-        const size_t mib = ((size_t)p.B * frames * p.H * p.W * p.C * 2) >> 20;
-        const size_t least = p.r == 2 ? 24 : (p.C % 256 != 0 ? 32 : (p.W == 32 && p.r == 1 ? 160 : 96));
-        if (mib < least) return false;
+    const size_t mib = ((size_t)p.B * frames * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4)) >> 20;
+    if (p.dtype == TTF_F32) {
+        if (forced_general() || !((mfma && p.C >= 1024) || (p.C >= 768 && mib >= 32))) return false;
+    } else {
+        if (!mfma || p.C < 1024) return false;
+        if (mfma_search_supported(p) &&
+            mib < (size_t)(p.r == 2 ? 24 : (p.C % 256 != 0 ? 32 : (p.W == 32 && p.r == 1 ? 160 : 96))))
+            return false;
     }
     plan = walk_plan(p, frames, false);
     return plan.ok && walk_scratch(p, w, plan, false, scratch);
@@ -110,11 +122,12 @@ thread_local int g_last_hip_error = 0;
 
 // Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of at most
 // kSpeculationMaxFrames frames, 1 whenever the shape allows.  (Long clips: the more frames, the closer the
-// best two anchor scores; at 256 frames no guess of the synthetic workloads clears the trust gap, every
-// clip falls back to the two-pass kernels and the guess costs 0.05 ms for nothing.)
+// best two anchor scores.  With scenes of 32 frames the guess is clear in clips of one or two scenes and clears the
+// trust gap in some or none of three and more, which then pay for it: B3 F84 32x26 C1536 r2 500 to 570 us, two-pass 435,
+// 420 were every guess right; B2 F256 16x16 C4096 no clip.)
 std::atomic<int> g_speculation{0};
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
-constexpr int kSpeculationMaxFrames = 128;
+constexpr int kSpeculationMaxFrames = 64;
 
 // Event sets for stage timing: `slots` sets of TTF_NUM_STAGES+1 events, used round-robin by
 // successive profiled calls so that a benchmark can time many calls and read them afterwards.
@@ -211,21 +224,25 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     // frame sums are then formed the two-pass way and it is searched with the refuted clips.  Either way
     // every output is what the exact rule gives.
     const int spec_pref = g_speculation.load(std::memory_order_relaxed);
-    const unsigned long long in_bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * 2ull;
+    const unsigned long long in_bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2ull : 4ull);
     WalkPlan plan{};
     WalkScratch scratch{};
-    bool spec = pick && mfma && speculation_shape(p) &&
+    bool spec = pick && mfma && speculation_possible(p) &&
                 (spec_pref > 0 ||
                  (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F <= kSpeculationMaxFrames));
     if (spec) {
         plan = walk_plan(p, p.F, true);
         spec = plan.ok && walk_scratch(p, w, plan, true, scratch);
+        if (spec) {
+            w.guess_sum = scratch.guess_sum;
+            w.spec = scratch.spec;
+        }
     }
-    const bool walk = spec || (mfma && use_walk(p, w, ext_anchor != nullptr, plan, scratch));
+    const bool walk = spec || use_walk(p, w, mfma, ext_anchor != nullptr, plan, scratch);
 
     mark();                                                    // start of stage 0
     if (spec) TTF_STEP(launch_guess_sums(p, features, w, s));
-    else if (pick) TTF_STEP(launch_frame_sums(p, features, w, false, s));
+    else if (pick) TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk), s));
     mark();
     if (pick && !spec) TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     mark();
@@ -246,7 +263,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     }
     mark();
     if (spec) {
-        TTF_STEP(launch_frame_sums(p, features, w, true, s));     // clips without a trusted guess only
+        TTF_STEP(launch_frame_sums(p, features, w, true, 0.0, s));     // clips without a trusted guess only
         TTF_STEP(launch_anchor_scores(p, w, scratch.strip_sum, plan.lsegs * plan.ysegs, s));
         TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, false, 2, s));
         TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
@@ -363,15 +380,15 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
     do {                               \
         if (e == hipSuccess) e = (call); \
     } while (0)
+    WalkPlan plan{};
+    WalkScratch scratch{};
+    const bool mfma = use_mfma_path(p, w.tail, false), walk = use_walk(p, w, mfma, false, plan, scratch);
     if (p.anchor_mode == TTF_ANCHOR_AUTO) {
-        TTF_STEP(launch_frame_sums(p, features, w, false, s));
+        TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk), s));
         TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));
-    WalkPlan plan{};
-    WalkScratch scratch{};
-    const bool mfma = use_mfma_path(p, w.tail, false);
-    if (mfma && use_walk(p, w, false, plan, scratch)) {
+    if (walk) {
         TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, true, 0, s));
         TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, nullptr, nullptr, nullptr, tw.win_sim, s));
     } else {
@@ -498,7 +515,11 @@ ttf_status ttf_search_route(const ttf_params* params, int* route)
     const ttf_status st = check_params(params);
     if (st != TTF_OK) return st;
     const ttf_params& p = *params;
-    *route = !use_mfma_path(p, true, false) ? TTF_ROUTE_GENERAL
+    const bool mfma = use_mfma_path(p, true, false);
+    WalkPlan plan;
+    WalkScratch scratch;
+    const bool walk = p.r <= 2 && use_walk(p, carve(p, nullptr), mfma, false, plan, scratch);
+    *route = !mfma && !walk                 ? TTF_ROUTE_GENERAL
            : p.dtype == TTF_F32             ? TTF_ROUTE_MFMA_F32
            : mfma_search_supported(p)       ? TTF_ROUTE_MFMA_BF16
                                             : TTF_ROUTE_MFMA_BF16_PADDED;

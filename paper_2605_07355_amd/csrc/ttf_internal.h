@@ -27,14 +27,17 @@ bool mfma_search_f32_supported(const ttf_params& p);
 bool mfma_f32_aligned(const ttf_params& p);
 
 // Share of an input whose reads leave it in the Infinity Cache (256 MiB) for the kernel that reads it next: plain
-// loads instead of non-temporal ones for the end of a pass, a little more than fits.  B2 F256 16x16 C4096 (1 GiB): frame
-// sums 161 us either way and the search behind them 174 -> 162, with 1 GiB of plain loads 179 and 162; B4 F32 16x16
-// C4096 (256 MiB): sums 42.8 -> 41.5, search 47.8 -> 44.6, row copy 33.8 -> 29.9.
-inline double kept_share(const ttf_params& p)
+// loads instead of non-temporal ones for the end of a pass, a little more than fits where the input does not.
+// B2 F256 16x16 C4096 (1 GiB): frame sums 161 us either way and the search behind them 174 -> 162, with 1 GiB of plain
+// loads 179 and 162; B4 F32 16x16 C4096 (256 MiB): sums 42.8 -> 41.5, search 47.8 -> 44.6, row copy 33.8 -> 29.9.  Searches
+// that read with plain loads themselves (`walks` false) push out the end of a larger input before they reach it: there
+// it costs (B2 F256 32x23 C384, 276 MiB: sums 44 -> 50, whole call 278 -> 295).
+inline double kept_share(const ttf_params& p, bool walks)
 {
     const double bytes = (double)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4);
-    const double keep = 320.0 * (1 << 20);
-    return bytes <= keep ? 1.0 : keep / bytes;
+    const double mib = 1 << 20;
+    if (!walks) return bytes <= 256 * mib ? 1.0 : 0.0;
+    return bytes <= 320 * mib ? 1.0 : 320 * mib / bytes;
 }
 
 // Device scratch carved out of the caller's workspace.  All sections are 256-byte aligned.
@@ -52,7 +55,7 @@ struct Workspace {
     // Speculative anchor (single pass over the input, see ttf_api.hip); sized 0 where it cannot apply
     float*    guess_sum;     // [B,F,P,kGuessChannels] frame sums over the guess channels only, in P = guess_parts()
                              // shares (one per run of tokens)
-    int32_t*  spec;          // [B,4]    guessed anchor, guess trusted (1/0), second search needed (1/0), unused
+    int32_t*  spec;          // [B,4]    guessed anchor, guess trusted (1/0), unused
     float*    strip_sum;     // room for [B,F,spec_strips(),C] floats: frame sums per run of the grid and window
                              // products of the walking search (walk_scratch())
     size_t    frag_bytes;    // size of anchor_frag; until the anchor is chosen it holds the frame-sum shares
@@ -93,6 +96,13 @@ inline bool speculation_shape(const ttf_params& p)
 {
     if (p.dtype != TTF_BF16 || p.C % 128 != 0 || p.C < 1024 || p.F < 2) return false;
     return 10ll * p.H * p.W >= 7ll * 32 * spec_strips(p);
+}
+// ... and fp32 tokens in whole 32-channel K-steps with windows up to 3x3, whose sums, products and guess all stand in
+// the fragment section.
+inline bool speculation_possible(const ttf_params& p)
+{
+    if (p.dtype == TTF_F32) return p.C % 32 == 0 && p.C >= 1024 && p.F >= 2 && p.r <= 1;
+    return speculation_shape(p);
 }
 
 // bf16 rows that are whole 16-byte pieces but not whole 32-channel K-steps: the matrix-core kernels end
@@ -151,8 +161,10 @@ inline Workspace carve(const ttf_params& p, void* base, bool tail = true)
 }
 
 // Stage launchers.  Each enqueues on `s` and returns the launch status.
-// `skip_trusted`: clips with a trusted anchor guess (w.spec) are left out.
-hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, hipStream_t s);
+// `skip_trusted`: clips with a trusted anchor guess (w.spec) are left out.  `kept`: share of the input left in the
+// Infinity Cache.
+hipError_t launch_frame_sums(const ttf_params& p, const void* x, const Workspace& w, bool skip_trusted, double kept,
+                             hipStream_t s);
 // Per-slice shares of the anchor scores from w.frame_sum; with strip_sum [B,F,strips,C]: from there for the clips
 // with a trusted anchor guess.
 hipError_t launch_anchor_scores(const ttf_params& p, const Workspace& w, const float* strip_sum, int strips, hipStream_t s);
@@ -196,11 +208,13 @@ struct WalkScratch {
     float* part;             // [nk][B*F*N][(2r+1)^2 + 1]
     float* norm_part;        // [nk][B*N]
     float* strip_sum;        // [B*F][lsegs*ysegs][C], where sums are kept
+    float* guess_sum;        // the sections of the same names (in the fragment section for fp32 tokens)
+    int32_t* spec;
 };
 WalkPlan walk_plan(const ttf_params& p, int frames, bool sums);
 bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan, bool sums, WalkScratch& scratch);
-// mode 0: anchor external, fixed_anchor (>= 0), given (kAnchorGiven) or picked from the scores.  1: clips with a
-// trusted guess, every frame, with sums.  2: clips whose guess the exact rule refutes, and those without one.
+// mode 0: anchor external, fixed, given or picked from the scores.  1: clips with a trusted guess, every frame,
+// with sums.  2: clips whose guess the exact rule refutes, and those without one.
 hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
                               const WalkPlan& plan, const WalkScratch& scratch, int32_t* anchor_index,
                               bool anchor_given, int mode, hipStream_t s);

@@ -1,4 +1,4 @@
-// Window search of large bf16 inputs: workgroups that walk whole frames (Section 3, "Pointwise Matching
+// Window search of large inputs: workgroups that walk whole frames (Section 3, "Pointwise Matching
 // with Local Window Search" and "Threshold Gating").
 //
 // What bounds it is how the token rows stream out of HBM.  A workgroup that keeps the products of many
@@ -27,7 +27,12 @@
 //  * SPEC (the anchor may be a guess): every frame is walked and its sums over the strip are kept, 16 channels
 //    a register: two MFMAs per K-step against 0/1 matrices that pick 16 of the 32 channels leave four tokens
 //    of one channel in a lane.
-// Kernel alone, against the kernels it replaces there: B16 F32 16x16 C4096 with sums 248 -> 180 us (5.9 TB/s of
+//  * fp32 tokens: a group is one K-step, every value cut into three bf16 planes as it is used (the window holds the
+//    planes), six plane products per MFMA of the bf16 form.  Norms and sums are plain fp32: eight channels of a token in a
+//    lane, sums by exchanging halves inside a row of 16 lanes until two lanes hold one channel.  Bound by the
+//    arithmetic and its latency: B16 F32 16x16 C4096 (2 GiB) 380 us plain (452 for k_search_mfma_f32), 500 with sums, which
+//    save the 322 us of k_frame_sums_slab; eight frames a workgroup instead of four 522 -> 502.
+// Kernel alone, bf16, against the kernels it replaces there: B16 F32 16x16 C4096 with sums 248 -> 180 us (5.9 TB/s of
 // tokens), 14x14 218 -> 147, B2 F256 16x16 C4096 189 -> 174 (162 behind frame sums that leave the Infinity Cache warm), B4
 // F64 32x32 C4096 r 2 with sums 596 -> 488.  With everything but the loads taken out the first runs no faster
 // (179), so it is the walk through memory that is left; of the last 64 us are the stores of the window products and
@@ -43,12 +48,18 @@ namespace ttf {
 namespace {
 
 constexpr int kWalkWaves = 8;
-constexpr int kWalkSteps = 8;                                // K-steps of 32 channels per wave, at most
-constexpr int kWalkGroup = 2048;                             // bytes of a group: 16 rows x 128
+constexpr int kWalkGroups = 4;                               // groups of a tile per wave, at most
+constexpr int kWalkGroup = 2048;                             // bytes of a group: 16 rows x 128 (two K-steps of 32 bf16
+                                                             // channels, or one of 32 fp32 channels)
+
+// Most frames of a workgroup that keeps sums: what fits the registers beside the window (fp32: one register for a group's
+// 32 channels, four for 64 of bf16).
+template <typename E, int RAD>
+constexpr int spec_frames() { return sizeof(E) == 4 ? 8 : (RAD == 2 ? 2 : 4); }
 
 struct WalkArgs {
-    const uint16_t* x;
-    const uint16_t* ext_anchor;                              // external anchor frames, or null
+    const char* x;
+    const char* ext_anchor;                                  // external anchor frames, or null
     const double* score_part;
     const double* clip_part;
     int32_t* anchor_index;
@@ -80,6 +91,24 @@ __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
 
+// The three bf16 pieces of two fp32 values, each pair packed into one word: hi = bf16(v), mid = bf16(v - hi), lo =
+// bf16(v - hi - mid), round to nearest even; both subtractions are exact.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    const float ra = a - __builtin_bit_cast(float, hi << 16), rb = b - __builtin_bit_cast(float, hi & 0xffff0000u);
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
+    const float sa = ra - __builtin_bit_cast(float, mid << 16), sb = rb - __builtin_bit_cast(float, mid & 0xffff0000u);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
+}
+// A value from another lane of the row of 16 (the DPP control names which).
+template <int DPP_CTRL>
+__device__ __forceinline__ float row_move(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), DPP_CTRL, 0xf, 0xf, true));
+}
+
 // B operand that picks 16 of the 32 channels of a K-step: E_h[k][n] = 1 iff k == 16h + n (operand order: lane
 // n + 16g holds rows k = 8g .. 8g+7 of column n).  A tile times E_h is its tokens x channels 16h .. 16h+15 in
 // the MFMA result layout, i.e. a lane then holds four TOKENS of one channel.
@@ -107,7 +136,6 @@ struct Tiles {
     static constexpr int NT = PATCH ? 2 + RAD : NP;          // anchor tiles of a window
     static constexpr int NEW = PATCH ? 2 : 1;                // ... that the next tile does not share
     static constexpr int STEP = PATCH ? 4 : 1;               // grid rows of a tile
-    static constexpr int FRS = RAD == 2 ? 2 : 4;             // most frames whose sums fit the registers beside it
     static constexpr int RING = RAD == 2 ? 6 : 8;            // groups in flight per wave
     // Lanes of a product tile that hold values of windows, and the 16-byte words that its share of the reduction
     // takes (a few more, so that the values of a token come from different banks).
@@ -119,13 +147,17 @@ struct Tiles {
 };
 
 // mode 0: the anchor is external, fixed, given in anchor_index or picked here; the source frames are walked.
-// mode 1 (SPEC): clips with a trusted guess in spec, every frame walked.  mode 2: the exact rule; clips whose
-// guess it confirms exit, the others are walked as in mode 0.
-template <int RAD, bool PATCH, bool SPEC>
+// mode 1 (SPEC): clips with a trusted guess, every frame walked.  mode 2: the exact rule; clips whose
+// guess it confirms are left out, the others walked as in mode 0.  (Units are made of the clips to search alone, so
+// that a few of them still meet all XCDs.)
+template <typename E, int RAD, bool PATCH, bool SPEC>
 __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkArgs A)
 {
     using T = Tiles<RAD, PATCH>;
-    constexpr int NP = T::NP, KK = T::KK, NT = T::NT, NEW = T::NEW, STEP = T::STEP, FRS = T::FRS, KW = kWalkSteps, G2 = KW / 2;
+    constexpr int NP = T::NP, KK = T::KK, NT = T::NT, NEW = T::NEW, STEP = T::STEP, FRS = spec_frames<E, RAD>(), GM = kWalkGroups;
+    constexpr bool F32 = sizeof(E) == 4;
+    constexpr int PL = F32 ? 3 : 2;                          // fragments of a group: three bf16 planes, or two K-steps
+    constexpr int SL = F32 ? 1 : 4;                          // registers of a group's sums
     extern __shared__ u32x4 lds_mem[];
     char* const ring = reinterpret_cast<char*>(lds_mem);
     f32x4* const red = reinterpret_cast<f32x4*>(ring + kWalkWaves * T::RING * kWalkGroup);   // [2][wave][RED]
@@ -134,18 +166,58 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, g = lane >> 4;
     const int H = A.H, W = A.W, N = H * W, F = A.F;
+    // The clips to search (mode 2: up to kPickClips, whose anchors the waves pick between them; more clips pick their
+    // own below and leave where there is nothing to do), and how many units they make.
+    const int per_clip = A.groups * A.lsegs * A.ysegs * A.nk;
+    constexpr int kPickClips = 32;
+    int32_t* const picked = reinterpret_cast<int32_t*>(red); // [2][kPickClips] exact anchor, search again
+    const bool choose = A.mode == 1 || (A.mode == 2 && A.B <= kPickClips);
+    if (A.mode == 2 && choose) {
+        for (int c = wave; c < A.B; c += kWalkWaves) {
+            const int exact = pick_anchor(A.score_part, A.clip_part, c, F, A.S, lane);
+            if (lane == 0) {
+                picked[c] = exact;
+                picked[kPickClips + c] = A.spec[4 * c + 1] == 0 || A.spec[4 * c] != exact;
+                if (blockIdx.x == 0) A.anchor_index[c] = exact;
+            }
+        }
+        __syncthreads();
+    }
+    auto flags = [&](int b0) {                               // of the 64 clips from b0 on
+        const int bb = b0 + lane;
+        bool mine = false;
+        if (bb < A.B) mine = A.mode == 1 ? A.spec[4 * bb + 1] != 0 : picked[kPickClips + bb] != 0;
+        return (uint64_t)__ballot(mine);
+    };
+    int clips = A.B;
+    if (choose) {
+        clips = 0;
+        for (int b0 = 0; b0 < A.B; b0 += 64) clips += __popcll(flags(b0));
+    }
     // Workgroups are dealt to the XCDs round robin; every XCD gets one contiguous run of the units, in
     // which the frame groups of one (clip, strip, channel share) are neighbours: their anchor rows are read
     // from HBM once and then come from that XCD's L2.
     int u;
     {
-        const int U = (int)gridDim.x, xcd = (int)blockIdx.x & 7;
-        u = xcd * (U >> 3) + min(xcd, U & 7) + ((int)blockIdx.x >> 3);
+        const int U = clips * per_clip, xcd = (int)blockIdx.x & 7, nth = (int)blockIdx.x >> 3;
+        if (nth >= (U >> 3) + (xcd < (U & 7) ? 1 : 0)) return;   // (workgroup-uniform)
+        u = xcd * (U >> 3) + min(xcd, U & 7) + nth;
     }
     const int grp = u % A.groups; u /= A.groups;
     const int seg = u % (A.lsegs * A.ysegs); u /= A.lsegs * A.ysegs;
     const int share = u % A.nk;
-    const int b = u / A.nk;
+    int b = u / A.nk;
+    if (choose) {                                            // the b-th clip of those to search
+        int left_out = b, b0 = 0;
+        uint64_t set = flags(0);
+        while (left_out >= (int)__popcll(set)) {
+            left_out -= (int)__popcll(set);
+            b0 += 64;
+            set = flags(b0);
+        }
+        for (; left_out > 0; --left_out) set &= set - 1;
+        b = b0 + __ffsll((unsigned long long)set) - 1;
+    }
 
     int a;
     if (A.mode == 0) {
@@ -154,15 +226,17 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
           : A.fixed_anchor == kAnchorGiven ? A.anchor_index[b]
                                            : pick_anchor(A.score_part, A.clip_part, b, F, A.S, lane);
     } else if (A.mode == 1) {
-        if (A.spec[4 * b + 1] == 0) return;                  // no trusted guess: the clip takes the two-pass route
         a = A.spec[4 * b];
     } else {
-        a = pick_anchor(A.score_part, A.clip_part, b, F, A.S, lane);
+        a = choose ? picked[b] : pick_anchor(A.score_part, A.clip_part, b, F, A.S, lane);
     }
     a = __builtin_amdgcn_readfirstlane(a);
-    if (A.mode != 1 && A.fixed_anchor != kAnchorGiven && grp + seg + share == 0 && threadIdx.x == 0)
+    if ((A.mode == 0 ? A.fixed_anchor != kAnchorGiven : A.mode == 2 && !choose) && grp + seg + share == 0 && threadIdx.x == 0)
         A.anchor_index[b] = a;
-    if (A.mode == 2 && A.spec[4 * b + 1] != 0 && A.spec[4 * b] == a) return;   // confirmed: searched already
+    if (A.mode == 2) {
+        if (!choose && A.spec[4 * b + 1] != 0 && A.spec[4 * b] == a) return;   // confirmed: searched already
+        __syncthreads();                                     // `picked` is read: its place is free
+    }
 
     // the unit's part of the grid: column strips line_lo .. line_hi-1, tiles step_lo .. step_hi-1 of each
     const int line_lo = (int)((long long)A.lines * (seg / A.ysegs) / A.lsegs), line_hi = (int)((long long)A.lines * (seg / A.ysegs + 1) / A.lsegs);
@@ -178,14 +252,14 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     const int k0 = grp * A.nf;
     const int cnt = min(A.nf, walked - k0);
     if (cnt <= 0) return;                                    // (one frame, the anchor: nothing to walk)
-    // channels of this wave: groups q_lo .. q_lo+gq-1 of 64
-    const int total_groups = A.C / 64;
+    // channels of this wave: groups q_lo .. q_lo+gq-1 of 128 bytes
+    const int total_groups = A.C / (128 / (int)sizeof(E));
     const int q_lo = (int)((long long)total_groups * (share * kWalkWaves + wave) / (kWalkWaves * A.nk));
     const int gq = (int)((long long)total_groups * (share * kWalkWaves + wave + 1) / (kWalkWaves * A.nk)) - q_lo;
-    const size_t row_bytes = (size_t)A.C * 2;
+    const size_t row_bytes = (size_t)A.C * sizeof(E);
     const size_t frame_bytes = (size_t)N * row_bytes;
-    const char* const src_frames = reinterpret_cast<const char*>(A.x) + (size_t)b * F * frame_bytes + (size_t)q_lo * 128;
-    const char* const anchor_frame = (a < 0 ? reinterpret_cast<const char*>(A.ext_anchor) + (size_t)b * frame_bytes + (size_t)q_lo * 128
+    const char* const src_frames = A.x + (size_t)b * F * frame_bytes + (size_t)q_lo * 128;
+    const char* const anchor_frame = (a < 0 ? A.ext_anchor + (size_t)b * frame_bytes + (size_t)q_lo * 128
                                             : src_frames + (size_t)a * frame_bytes);
 
     // lane l of load i of a group fills piece l of its KiB: row 8i + l/8 of the tile, stored piece l%8
@@ -287,13 +361,16 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
         --left;
         request();
     };
-    bf16x8 win[NT][KW];                                      // the window of the patch
+    bf16x8 win[NT][GM][PL];                                  // the window of the tile
 #pragma unroll
     for (int q = 0; q < NT; ++q) {
 #pragma unroll
-        for (int ks = 0; ks < KW; ++ks) win[q][ks] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        for (int gi = 0; gi < GM; ++gi) {
+#pragma unroll
+            for (int e = 0; e < PL; ++e) win[q][gi][e] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        }
     }
-    float sum[SPEC ? FRS : 1][KW][2];
+    float sum[SPEC ? FRS : 1][GM][SL];
     bf16x8 pick0, pick1;
     if constexpr (SPEC) {
         pick0 = channel_picker(0, lane);
@@ -301,7 +378,10 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
 #pragma unroll
         for (int f = 0; f < FRS; ++f) {
 #pragma unroll
-            for (int ks = 0; ks < KW; ++ks) sum[f][ks][0] = sum[f][ks][1] = 0.f;
+            for (int gi = 0; gi < GM; ++gi) {
+#pragma unroll
+                for (int e = 0; e < SL; ++e) sum[f][gi][e] = 0.f;
+            }
         }
     }
     // A finished tile has 16 x (KK + 1) numbers worth adding up over the waves: the (2r+1)^2 products of every
@@ -346,36 +426,92 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
         pend_out = nullptr;
     };
     float* const part_out = A.part + ((size_t)share * A.B * F * N + (size_t)b * F * N) * (KK + 1) + ve;
-    auto source_tile = [&](int f, int line, int step, float (&tile_sum)[KW][2]) {
+    // fp32: the fragments of a group as bf16 planes, and this lane's share of the tokens' squared norms
+    auto planes = [&](const u32x4 (&fr)[2], bf16x8 (&pl)[PL], float& nn) {
+        const uint32_t r[8] = {fr[0][0], fr[0][1], fr[0][2], fr[0][3], fr[1][0], fr[1][1], fr[1][2], fr[1][3]};
+        uint32_t w[3][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float v0 = __builtin_bit_cast(float, r[2 * e]), v1 = __builtin_bit_cast(float, r[2 * e + 1]);
+            nn = fmaf(v1, v1, fmaf(v0, v0, nn));
+            uint32_t h, mi, l;
+            split_bf16x3(v0, v1, h, mi, l);
+            w[0][e] = h; w[1][e] = mi; w[2][e] = l;
+        }
+#pragma unroll
+        for (int e = 0; e < PL; ++e) pl[e] = __builtin_bit_cast(bf16x8, uint4{w[e][0], w[e][1], w[e][2], w[e][3]});
+    };
+    // ... summed over the lanes that share a token and put where the diagonal of a tile's products stands
+    auto put_norm = [&](size_t mine, float nn) {
+        nn += __shfl_xor(nn, 16, 64);
+        nn += __shfl_xor(nn, 32, 64);
+        if (on_diagonal) reinterpret_cast<float*>(red + mine + NT * T::BAND + m)[m & 3] = nn;
+    };
+    auto source_tile = [&](int f, int line, int step, float (&tile_sum)[GM][SL]) {
         const int x0 = strip_x(line), x1 = min(strip_x(line + 1), W);
+        f32x4 acc[NT + 1];
+        float nn = 0.f;
+#pragma unroll
+        for (int q = 0; q <= NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
         float weight[4];                                     // SPEC: rows of the tile that hold no cell of their own count zero
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             weight[j] = (PATCH ? STEP * step + j < H && x0 + g < W : x0 + 4 * g + j < x1) ? 1.0f : 0.0f;
-        f32x4 acc[NT + 1];
+        const bool full = !PATCH && x1 - x0 == 16;
+        const bool own = PATCH ? STEP * step + (m & 3) < H && x0 + (m >> 2) < W : x0 + m < x1;
 #pragma unroll
-        for (int q = 0; q <= NT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int gi = 0; gi < G2; ++gi) {
+        for (int gi = 0; gi < GM; ++gi) {
             if (gi < gq) {                                   // wave-uniform
                 u32x4 fr[2];
                 take(fr[0], fr[1]);
                 if (gi == 0) store_shares();
+                if constexpr (F32) {
+                    bf16x8 pl[PL];
+                    planes(fr, pl, nn);
+                    // six of the nine products of the planes, the smallest first
+                    constexpr int SP[6] = {2, 0, 1, 1, 0, 0}, WP[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
+                    for (int term = 0; term < 6; ++term) {
 #pragma unroll
-                    for (int q = 0; q < NT; ++q)
-                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, win[q][2 * gi + j], acc[q], 0, 0, 0);
-                    acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, acc[NT], 0, 0, 0);
+                        for (int q = 0; q < NT; ++q)
+                            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[SP[term]], win[q][gi][WP[term] % PL], acc[q], 0, 0, 0);
+                    }
                     if constexpr (SPEC) {
-                        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                        const f32x4 d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick0, zero, 0, 0, 0);
-                        const f32x4 d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick1, zero, 0, 0, 0);
+                        // a lane's eight channels over the 16 tokens (the lanes of its row): halves are exchanged until
+                        // two lanes hold one channel
+                        const uint32_t r[8] = {fr[0][0], fr[0][1], fr[0][2], fr[0][3], fr[1][0], fr[1][1], fr[1][2], fr[1][3]};
+                        float v[8];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            tile_sum[2 * gi + j][0] = fmaf(d0[e], weight[e], tile_sum[2 * gi + j][0]);
-                            tile_sum[2 * gi + j][1] = fmaf(d1[e], weight[e], tile_sum[2 * gi + j][1]);
+                        for (int e = 0; e < 8; ++e) v[e] = __builtin_bit_cast(float, r[e]);
+                        if (!full) {                         // (wave-uniform)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) v[e] = own ? v[e] : 0.f;
+                        }
+                        float h[4], q2[2];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) h[e] = ((m & 8) ? v[e + 4] : v[e]) + row_move<0x128>((m & 8) ? v[e] : v[e + 4]);
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) q2[e] = ((m & 4) ? h[e + 2] : h[e]) + row_move<0x141>((m & 4) ? h[e] : h[e + 2]);
+                        const float o = ((m & 2) ? q2[1] : q2[0]) + row_move<0x4E>((m & 2) ? q2[0] : q2[1]);
+                        tile_sum[gi][0] += o + row_move<0xB1>(o);
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
+#pragma unroll
+                        for (int q = 0; q < NT; ++q)
+                            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, win[q][gi][j], acc[q], 0, 0, 0);
+                        acc[NT] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, acc[NT], 0, 0, 0);
+                        if constexpr (SPEC) {
+                            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                            const f32x4 d0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick0, zero, 0, 0, 0);
+                            const f32x4 d1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pick1, zero, 0, 0, 0);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                tile_sum[gi][2 * j % SL] = fmaf(d0[e], weight[e], tile_sum[gi][2 * j % SL]);
+                                tile_sum[gi][(2 * j + 1) % SL] = fmaf(d1[e], weight[e], tile_sum[gi][(2 * j + 1) % SL]);
+                            }
                         }
                     }
                 }
@@ -386,29 +522,37 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
 #pragma unroll
             for (int q = 0; q < NT; ++q) red_out[mine + q * T::BAND] = acc[q];
         }
-        if (on_diagonal) red[mine + NT * T::BAND + m] = acc[NT];
+        if constexpr (F32) put_norm(mine, nn);
+        else if (on_diagonal) red[mine + NT * T::BAND + m] = acc[NT];
         const int k = k0 + f + (k0 + f >= skip ? 1 : 0);
         const int y = PATCH ? STEP * step + (vt & 3) : step, xc = x0 + (PATCH ? vt >> 2 : vt);
         fetch_shares(y < H && xc < x1 ? part_out + ((size_t)k * N + y * W + xc) * (KK + 1) : nullptr);
     };
-    auto anchor_tile = [&](int line, int c, bf16x8 (&tile)[KW]) {
+    auto anchor_tile = [&](int line, int c, bf16x8 (&tile)[GM][PL]) {
         f32x4 norm = {0.f, 0.f, 0.f, 0.f};
+        float nn = 0.f;
 #pragma unroll
-        for (int gi = 0; gi < G2; ++gi) {
+        for (int gi = 0; gi < GM; ++gi) {
             if (gi < gq) {
                 u32x4 fr[2];
                 take(fr[0], fr[1]);
+                if constexpr (F32) {
+                    planes(fr, tile[gi], nn);
+                } else {
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
-                    tile[2 * gi + j] = av;
-                    norm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, norm, 0, 0, 0);
+                    for (int j = 0; j < 2; ++j) {
+                        const bf16x8 av = __builtin_bit_cast(bf16x8, fr[j]);
+                        tile[gi][j] = av;
+                        norm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, av, norm, 0, 0, 0);
+                    }
                 }
             }
         }
         if (grp == 0) {                                      // one frame group publishes the anchor's norms
             store_shares();
-            if (on_diagonal) red[(size_t)(buf * kWalkWaves + wave) * T::RED + NT * T::BAND + m] = norm;
+            const size_t mine = (size_t)(buf * kWalkWaves + wave) * T::RED;
+            if constexpr (F32) put_norm(mine, nn);
+            else if (on_diagonal) red[mine + NT * T::BAND + m] = norm;
             const int y = STEP * step_lo - RAD + (PATCH ? 2 * c + vt / T::SPAN : c);
             const int xc = strip_x(line) + (PATCH ? vt % T::SPAN - RAD : vt - margin);
             fetch_shares(ve == KK && (!PATCH || vt < 2 * T::SPAN) && y >= 0 && y < H && xc >= 0 && xc < W
@@ -423,11 +567,26 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
 #pragma unroll
             for (int q = 0; q + NEW < NT; ++q) {
 #pragma unroll
-                for (int ks = 0; ks < KW; ++ks) win[q][ks] = win[q + NEW][ks];
+                for (int gi = 0; gi < GM; ++gi) {
+#pragma unroll
+                    for (int e = 0; e < PL; ++e) win[q][gi][e] = win[q + NEW][gi][e];
+                }
             }
 #pragma unroll
             for (int e = 0; e < NEW; ++e) anchor_tile(line, NT - NEW + NEW * (step - step_lo) + e, win[NT - NEW + e]);
-            if constexpr (SPEC) {
+            if constexpr (SPEC && F32) {
+                for (int f = 0; f < cnt; ++f) {
+                    float add[GM][SL] = {};
+                    source_tile(f, line, step, add);
+#pragma unroll
+                    for (int e = 0; e < FRS; ++e) {
+                        if (e == f) {                        // (wave-uniform)
+#pragma unroll
+                            for (int gi = 0; gi < GM; ++gi) sum[e][gi][0] += add[gi][0];
+                        }
+                    }
+                }
+            } else if constexpr (SPEC) {
                 source_tile(0, line, step, sum[0]);
                 if (cnt > 1) source_tile(1, line, step, sum[1]);
                 if constexpr (FRS > 2) {
@@ -441,24 +600,29 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     }
     store_shares();
     if constexpr (SPEC) {
-        // a lane holds four tokens' worth of channel m (and 16 + m) of a K-step: the four groups of lanes are
-        // added by an fp32 MFMA against ones, and 256 bytes per frame and group of 64 channels are stored
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int f = 0; f < FRS; ++f) {
             if (f < cnt) {
-                float* out = A.strip_sum + (((size_t)b * F + k0 + f) * (A.lsegs * A.ysegs) + seg) * A.C + (size_t)q_lo * 64 + lane;
+                float* out = A.strip_sum + (((size_t)b * F + k0 + f) * (A.lsegs * A.ysegs) + seg) * A.C + (size_t)q_lo * (128 / sizeof(E));
 #pragma unroll
-                for (int gi = 0; gi < G2; ++gi) {
+                for (int gi = 0; gi < GM; ++gi) {
                     if (gi < gq) {
-                        float total[2];
+                        if constexpr (F32) {
+                            // (pieces g and 4 + g of the group: channels 4g .. and 16 + 4g ..)
+                            if (!(m & 1)) out[gi * 32 + ((m & 8) ? 16 : 0) + 4 * g + ((m >> 1) & 3)] = sum[f][gi][0];
+                        } else {
+                            // a lane holds four tokens' worth of channel m (and 16 + m) of a K-step: the four groups of
+                            // lanes are added by an fp32 MFMA against ones; 256 bytes per frame and group
+                            float total[2];
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const f32x4 r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][2 * gi + j][0], zero, 0, 0, 0);
-                            const f32x4 r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][2 * gi + j][1], zero, 0, 0, 0);
-                            total[j] = (g & 1) ? r1[0] : r0[0];
+                            for (int j = 0; j < 2; ++j) {
+                                const f32x4 r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][gi][2 * j % SL], zero, 0, 0, 0);
+                                const f32x4 r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, sum[f][gi][(2 * j + 1) % SL], zero, 0, 0, 0);
+                                total[j] = (g & 1) ? r1[0] : r0[0];
+                            }
+                            out[gi * 64 + lane] = lane < 32 ? total[0] : total[1];
                         }
-                        out[gi * 64] = lane < 32 ? total[0] : total[1];
                     }
                 }
             }
@@ -555,10 +719,12 @@ __global__ __launch_bounds__(256) void k_walk_finish(const float* __restrict__ p
 WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 {
     WalkPlan w{};
-    if (p.dtype != TTF_BF16 || p.r > 2 || p.C % 64 != 0 || p.C < 512 || frames < 1) return w;
-    if ((unsigned long long)p.H * p.W * p.C * 2 >= (1ull << 32)) return w;   // (32-bit offsets inside a frame)
+    const int piece = p.dtype == TTF_BF16 ? 64 : 32;         // channels of a group
+    const int groups_all = p.C / piece;
+    if (p.r > (p.dtype == TTF_BF16 ? 2 : 1) || p.C % piece != 0 || groups_all < kWalkWaves || frames < 1) return w;
+    if ((unsigned long long)p.H * p.W * p.C * (128 / piece) >= (1ull << 32)) return w;   // (32-bit offsets inside a frame)
     w.patch = p.r == 2;
-    w.nk = (p.C / 32 + kWalkWaves * kWalkSteps - 1) / (kWalkWaves * kWalkSteps);
+    w.nk = (groups_all + kWalkWaves * kWalkGroups - 1) / (kWalkWaves * kWalkGroups);
     w.lines = w.patch ? (p.W + 3) / 4 : (p.W <= 16 ? 1 : (p.W + 15 - 2 * p.r) / (16 - 2 * p.r));
     const int steps = w.patch ? (p.H + 3) / 4 : p.H, fresh = w.patch ? 2 : 1, held = w.patch ? p.r : 2 * p.r;
     // Time of a deal in tiles: a workgroup starts up (two tiles' time), reads the anchor tiles of its run (which
@@ -567,9 +733,9 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     // 102 / 64 / 46 us).
     // Frame sums are stored per run of the grid: as many runs as leave the products room in the strip-sum section.
     const long long products = (long long)w.nk * ((2 * p.r + 1) * (2 * p.r + 1) + 1) * p.H * p.W;
-    const long long most_runs = sums ? std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C) : 1 << 20;
+    const long long most_runs = !sums ? 1 << 20 : p.dtype == TTF_F32 ? 2 : std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C);
     double best = 1e300;
-    const int most = sums ? (p.r == 2 ? Tiles<2, true>::FRS : Tiles<1, false>::FRS) : 32;
+    const int most = !sums ? 32 : p.dtype == TTF_F32 ? spec_frames<float, 1>() : (p.r == 2 ? spec_frames<bf16_t, 2>() : spec_frames<bf16_t, 1>());
     for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
         for (int ysegs = 1; ysegs <= 4 && ysegs <= steps && lsegs * ysegs <= most_runs; ysegs *= 2) {
             int last = 0;
@@ -616,6 +782,13 @@ bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan,
     scratch.part = take(plan.nk * tokens * (KK + 1));
     scratch.strip_sum = sums ? take((size_t)p.B * p.F * plan.lsegs * plan.ysegs * p.C) : nullptr;
     scratch.norm_part = take((size_t)plan.nk * p.B * p.H * p.W);
+    // the guess has sections of its own beside bf16 tokens
+    scratch.guess_sum = w.guess_sum;
+    scratch.spec = w.spec;
+    if (sums && p.dtype == TTF_F32) {
+        scratch.guess_sum = take((size_t)p.B * p.F * guess_parts(p) * kGuessChannels);
+        scratch.spec = reinterpret_cast<int32_t*>(take((size_t)p.B * 4));
+    }
     return fits;
 }
 
@@ -624,8 +797,8 @@ hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ex
                               int mode, hipStream_t s)
 {
     WalkArgs a{};
-    a.x = static_cast<const uint16_t*>(x);
-    a.ext_anchor = static_cast<const uint16_t*>(ext_anchor);
+    a.x = static_cast<const char*>(x);
+    a.ext_anchor = static_cast<const char*>(ext_anchor);
     a.score_part = w.score_part;
     a.clip_part = w.clip_part;
     a.anchor_index = anchor_index;
@@ -638,7 +811,7 @@ hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ex
     a.lines = plan.lines; a.lsegs = plan.lsegs; a.ysegs = plan.ysegs;
     a.fixed_anchor = anchor_given ? kAnchorGiven : fixed_frame(p);
     a.mode = mode;
-    a.keep_from = 256 - (int)(256 * kept_share(p));
+    a.keep_from = 256 - (int)(256 * kept_share(p, true));
     const unsigned grid = (unsigned)((size_t)p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs);
     auto go = [&](auto kernel, size_t lds) {
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
@@ -647,12 +820,11 @@ hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ex
         return hipGetLastError();
     };
     const bool sums = mode == 1;
-    switch (p.r) {
-        case 0: return sums ? go(k_search_walk<0, false, true>, Tiles<0, false>::LDS) : go(k_search_walk<0, false, false>, Tiles<0, false>::LDS);
-        case 1: return sums ? go(k_search_walk<1, false, true>, Tiles<1, false>::LDS) : go(k_search_walk<1, false, false>, Tiles<1, false>::LDS);
-        case 2: return sums ? go(k_search_walk<2, true, true>, Tiles<2, true>::LDS) : go(k_search_walk<2, true, false>, Tiles<2, true>::LDS);
-    }
-    return hipErrorInvalidValue;
+#define TTF_WALK(E, RAD, PATCH) \
+    (sums ? go(k_search_walk<E, RAD, PATCH, true>, Tiles<RAD, PATCH>::LDS) : go(k_search_walk<E, RAD, PATCH, false>, Tiles<RAD, PATCH>::LDS))
+    if (p.dtype == TTF_F32) return p.r == 0 ? TTF_WALK(float, 0, false) : TTF_WALK(float, 1, false);
+    return p.r == 0 ? TTF_WALK(bf16_t, 0, false) : (p.r == 1 ? TTF_WALK(bf16_t, 1, false) : TTF_WALK(bf16_t, 2, true));
+#undef TTF_WALK
 }
 
 hipError_t launch_walk_finish(const ttf_params& p, const Workspace& w, const WalkPlan& plan, const WalkScratch& scratch,
