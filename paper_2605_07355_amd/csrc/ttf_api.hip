@@ -120,14 +120,17 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 
-// Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of at most
-// kSpeculationMaxFrames frames, 1 whenever the shape allows.  (Long clips: the more frames, the closer the
-// best two anchor scores.  With scenes of 32 frames the guess is clear in clips of one or two scenes and clears the
-// trust gap in some or none of three and more, which then pay for it: B3 F84 32x26 C1536 r2 500 to 570 us, two-pass 435,
-// 420 were every guess right; B2 F256 16x16 C4096 no clip.)
+// Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of kSpeculationMinFrames to
+// kSpeculationMaxFrames frames (fp32: on grids of one strip, up to 16 columns), 1 whenever the shape allows.  Where the
+// lines lie (two-pass / with the guess, us, two inputs in turn): 256 to 320 MiB about even (B4 F21 27x32 C2048 r0 135 / 137),
+// beyond 1.02 to 1.3 (B12 F34 32x16 C2048 342 / 288, B13 F40 16x16 C4096 404 / 312).  Short clips clear the trust gap in some
+// clips of a batch only, whose two searches then each fill part of the chip (B12 F7 16x29 C4096 170 / 249, B13 F13 32x24
+// C2048 235 / 246).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
+// guess right.  fp32 with sums is bound by its arithmetic, which strips of 11 cells do not fill (B1 F44 32x32 C3584 336 /
+// 437, B6 F22 16x16 C2816 186 / 177, B16 F32 16x16 C4096 970 / 812).
 std::atomic<int> g_speculation{0};
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
-constexpr int kSpeculationMaxFrames = 64;
+constexpr int kSpeculationMinFrames = 16, kSpeculationMaxFrames = 64;
 
 // Event sets for stage timing: `slots` sets of TTF_NUM_STAGES+1 events, used round-robin by
 // successive profiled calls so that a benchmark can time many calls and read them afterwards.
@@ -229,7 +232,8 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     WalkScratch scratch{};
     bool spec = pick && mfma && speculation_possible(p) &&
                 (spec_pref > 0 ||
-                 (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F <= kSpeculationMaxFrames));
+                 (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F >= kSpeculationMinFrames &&
+                  p.F <= kSpeculationMaxFrames && (p.dtype == TTF_BF16 || p.W <= 16)));
     if (spec) {
         plan = walk_plan(p, p.F, true);
         spec = plan.ok && walk_scratch(p, w, plan, true, scratch);
