@@ -521,13 +521,16 @@ __global__ __launch_bounds__(512) void k_anchor_prepare(const uint16_t* __restri
     }
 }
 
-// The anchor guessed from the sums over the guess channels, one workgroup per clip.
-__global__ __launch_bounds__(1024) void k_guess_pick(const float* __restrict__ guess_sum, int32_t* __restrict__ spec, int F,
+// The anchor guessed from the sums over the guess channels, one workgroup per clip.  Bound by the fp64 sums over the
+// lanes, two for each of a wave's UN frames, real or not: 32 frames of 16 clips with four a wave 7.9 us,
+// with eight 9.8, on 16 waves with eight 12.9.
+template <int UN>
+__global__ __launch_bounds__(512) void k_guess_pick(const float* __restrict__ guess_sum, int32_t* __restrict__ spec, int F,
                                                     int parts)
 {
     int a;
     bool trusted;
-    guess_pick_block<16>(guess_sum, (int)blockIdx.x, F, parts, a, trusted);
+    guess_pick_block<8, UN>(guess_sum, (int)blockIdx.x, F, parts, a, trusted);
     if (threadIdx.x == 0) {
         int32_t* o = spec + 4 * blockIdx.x;
         o[0] = a;
@@ -755,7 +758,8 @@ hipError_t launch_guess_sums(const ttf_params& p, const void* x, const Workspace
 
 hipError_t launch_guess_pick(const ttf_params& p, const Workspace& w, hipStream_t s)
 {
-    k_guess_pick<<<(unsigned)p.B, 1024, 0, s>>>(w.guess_sum, w.spec, p.F, guess_parts(p));
+    if (p.F <= 32) k_guess_pick<4><<<(unsigned)p.B, 512, 0, s>>>(w.guess_sum, w.spec, p.F, guess_parts(p));
+    else k_guess_pick<8><<<(unsigned)p.B, 512, 0, s>>>(w.guess_sum, w.spec, p.F, guess_parts(p));
     return hipGetLastError();
 }
 

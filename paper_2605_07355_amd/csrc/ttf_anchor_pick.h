@@ -18,11 +18,10 @@ constexpr int kAnchorGiven = -2;   // "fixed_anchor" value: the anchor of every 
 // exact rule (from sums the search produces on the side) confirms it or triggers a second search.
 // Returns the guessed frame (lowest k on ties) and whether it is trusted, to every thread.
 constexpr double kGuessMinGap = 0.1;
-template <int NWV>
+template <int NWV, int UN>                              // UN: frames in flight per wave
 __device__ __forceinline__ void guess_pick_block(const float* __restrict__ guess_sum, int b, int F, int parts,
                                                  int& guess, bool& trusted)
 {
-    constexpr int UN = 8;                               // frames in flight per wave
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t fstride = (size_t)parts * kGuessChannels;
     const float* gs = guess_sum + (size_t)b * F * fstride + lane * 4;
