@@ -744,7 +744,7 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
                 if (nf == last) continue;
                 last = nf;
                 const double units = (double)p.B * w.nk * groups * lsegs * ysegs;
-                if (units > 1e8) continue;
+                if (units * (kWalkWaves * 64) >= 4294967296.0) continue;   // (threads of a launch)
                 const double lines = (w.lines + lsegs - 1) / lsegs, run = (steps + ysegs - 1) / ysegs;   // (of the longest)
                 const double tiles = 2.0 + lines * (run * (nf + 0.35 * fresh) + 0.35 * held);
                 const double whole = (double)((long long)units / 256), rest = units - 256 * whole;

@@ -1,0 +1,36 @@
+"""The library's host-side choice of a search, through its C++ symbols (no GPU needed)."""
+import ctypes
+import functools
+
+import torch
+
+CUS = 256                                                   # compute units: one workgroup of the walk on each
+
+
+class WalkPlan(ctypes.Structure):
+    """struct WalkPlan of csrc/ttf_internal.h."""
+    _fields_ = [("ok", ctypes.c_bool), ("patch", ctypes.c_bool)] + [
+        (n, ctypes.c_int) for n in ("nk", "lines", "lsegs", "ysegs", "groups", "nf")]
+
+
+def params(B, F, H, W, C, dtype, r=1):
+    from paper_2605_07355_amd import binding
+    return binding._Params(B, F, H, W, C, binding.TTF_F32 if dtype == torch.float32 else binding.TTF_BF16, r, 0.7, 0, 0)
+
+
+@functools.lru_cache(None)
+def _symbol(name, restype, *argtypes):
+    import paper_2605_07355_amd as ttf
+    f = getattr(ttf.load_library(), name)
+    f.restype, f.argtypes = restype, list(argtypes)
+    return f
+
+
+def walk_plan(p, frames, sums):
+    """How the walk deals `frames` frames a clip to workgroups."""
+    f = _symbol("_ZN3ttf9walk_planERK10ttf_paramsib", WalkPlan, ctypes.c_void_p, ctypes.c_int, ctypes.c_bool)
+    return f(ctypes.addressof(p), frames, sums)
+
+
+def units(p, plan):
+    return p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs
