@@ -737,7 +737,9 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     double best = 1e300;
     const int most = !sums ? 32 : p.dtype == TTF_F32 ? spec_frames<float, 1>() : (p.r == 2 ? spec_frames<bf16_t, 2>() : spec_frames<bf16_t, 1>());
     for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
-        for (int ysegs = 1; ysegs <= 4 && ysegs <= steps && lsegs * ysegs <= most_runs; ysegs *= 2) {
+        for (int ysegs = 1; ysegs <= steps && (long long)lsegs * ysegs <= most_runs; ysegs *= 2) {
+            // (more runs are looked at while the half of them, with the largest frame groups, does not fill the chip twice)
+            if (ysegs > 4 && (double)p.B * w.nk * ((frames + most - 1) / most) * lsegs * (ysegs / 2) >= 512) break;
             int last = 0;
             for (int want = 1; want <= most; ++want) {
                 const int groups = (frames + want - 1) / want, nf = (frames + groups - 1) / groups;
