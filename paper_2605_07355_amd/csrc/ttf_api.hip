@@ -41,8 +41,9 @@ static bool forced_general()
 
 bool use_mfma_path(const ttf_params& p, bool tail, bool external_anchor)
 {
-    if (forced_general() || (tail_channels(p) && !(tail && tail_search_pays(p, external_anchor ? p.F : p.F - 1)))) return false;
-    return mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p);
+    const int frames = external_anchor ? p.F : p.F - 1;      // (a segment takes the search of the clip it equals)
+    if (forced_general() || (tail_channels(p) && !(tail && tail_search_pays(p, frames)))) return false;
+    return mfma_search_supported(p) || mfma_search_padded(p) || mfma_search_f32_supported(p, frames);
 }
 
 // Anchor preparation of the matrix-core path for the element type at hand (fp32: three bf16 planes).

@@ -23,7 +23,7 @@ constexpr size_t kMaxBlocks256 = (1u << 24) - 1;
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 // fp32 tokens on the matrix cores (ttf_search_mfma_f32.hip): can this problem take them; is its grid one
 // whose keep words the search writes itself (exactly 16 or 32 wide, whole 64-token words)
-bool mfma_search_f32_supported(const ttf_params& p);
+bool mfma_search_f32_supported(const ttf_params& p, int frames);   // `frames` searched per clip
 bool mfma_f32_aligned(const ttf_params& p);
 
 // Share of an input whose reads leave it in the Infinity Cache (256 MiB) for the kernel that reads it next: plain

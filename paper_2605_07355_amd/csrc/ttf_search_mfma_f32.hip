@@ -313,13 +313,13 @@ bool mfma_f32_aligned(const ttf_params& p)
 // each on an idle chip), so a handful of them is slower than the wave-per-token kernels, which spread
 // the same tokens over hundreds of waves (measured: B1 F16 16x16 C2048, 16 workgroups, 0.104 against
 // 0.033 ms; B4 F16 16x16 C1024, 64 workgroups, 0.059 against 0.069 ms).
-bool mfma_search_f32_supported(const ttf_params& p)
+bool mfma_search_f32_supported(const ttf_params& p, int frames)
 {
     if (p.dtype != TTF_F32 || p.r > 2 || p.C % 32 != 0) return false;
     const int ct = p.W <= 16 ? 1 : (p.W <= 32 ? 2 : 3);
     const int nps = (ct == 1 ? 1 : ct) * (2 * p.r + 1);              // anchor tiles paired with a source tile
     const int frames_per_wg = nps <= 3 ? 8 : 4;
-    const long long groups = (std::max(p.F - 1, 1) + frames_per_wg - 1) / frames_per_wg;
+    const long long groups = (std::max(frames, 1) + frames_per_wg - 1) / frames_per_wg;
     const long long strips = mfma_f32_aligned(p) ? (long long)p.H * p.W / 32
                            : ct == 1 ? (p.H + 1) / 2 : (ct == 2 ? p.H : (long long)p.H * (((p.W + 15) / 16 + 1) / 2));
     return (long long)p.B * groups * strips >= 48;

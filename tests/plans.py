@@ -34,3 +34,9 @@ def walk_plan(p, frames, sums):
 
 def units(p, plan):
     return p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs
+
+
+def matrix_cores(p, segment=False):
+    """Whether a search that does not walk runs on the matrix cores."""
+    f = _symbol("_ZN3ttf13use_mfma_pathERK10ttf_paramsbb", ctypes.c_bool, ctypes.c_void_p, ctypes.c_bool, ctypes.c_bool)
+    return f(ctypes.addressof(p), True, segment)

@@ -1,8 +1,10 @@
-"""Host-side: how the search that walks whole frames is dealt to workgroups."""
+"""Host-side: which problems are searched by walking whole frames, and how they are dealt to workgroups."""
+import random
+
 import pytest
 import torch
 
-from plans import CUS, params, units, walk_plan
+from plans import CUS, matrix_cores, params, units, walk_plan
 
 BF, F32 = torch.bfloat16, torch.float32
 
@@ -31,3 +33,14 @@ def test_tall_grids_fill_the_chip(B, frames, H, W, C, r, dtype):
     p = params(B, frames + 1, H, W, C, dtype, r)
     plan = walk_plan(p, frames, False)
     assert plan.ok and units(p, plan) >= 0.75 * CUS
+
+
+def test_a_segment_takes_the_search_of_its_clip():
+    rng = random.Random(7)
+    for _ in range(4000):
+        B, F = rng.choice([1, 1, 2, 3, 4, 8, 16]), rng.choice([2, 3, 4, 5, 9, 10, 17, 18, 31, 55, 64, 65, 100, 154, 200])
+        H, W = rng.choice([1, 2, 3, 8, 14, 16, 18, 32]), rng.choice([1, 4, 8, 13, 14, 16, 17, 18, 20, 24, 32, 33, 40, 48])
+        C = rng.choice([64, 256, 768, 1000, 1024, 1056, 1088, 1152, 2048, 2112, 4096, 4160])
+        dtype, r = rng.choice([BF, BF, F32]), rng.choice([0, 1, 1, 2])
+        clip, seg = params(B, F, H, W, C, dtype, r), params(B, F - 1, H, W, C, dtype, r)
+        assert matrix_cores(seg, True) == matrix_cores(clip), (B, F, H, W, C, dtype, r)
