@@ -99,7 +99,21 @@ static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool ex
             return false;
     }
     plan = walk_plan(p, frames, false);
-    return plan.ok && walk_scratch(p, w, plan, false, scratch);
+    if (!plan.ok) return false;
+    // The products of all frames have to fit the workspace at once.  A segment's workspace is that of F frames, its
+    // clip's that of F + 1: asked is whether they fit the clip's, where there is less room for a frame.
+    ttf_params clip = p;
+    clip.F = frames + 1;
+    WalkScratch fits{};
+    return walk_scratch(clip, carve(clip, nullptr), plan, false, fits) && walk_scratch(p, w, plan, false, scratch);
+}
+
+bool search_walks(const ttf_params& p, bool external_anchor)
+{
+    const Workspace w = carve(p, nullptr);
+    WalkPlan plan{};
+    WalkScratch scratch{};
+    return use_walk(p, w, use_mfma_path(p, w.tail, external_anchor), external_anchor, plan, scratch);
 }
 
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
@@ -520,10 +534,7 @@ ttf_status ttf_search_route(const ttf_params* params, int* route)
     const ttf_status st = check_params(params);
     if (st != TTF_OK) return st;
     const ttf_params& p = *params;
-    const bool mfma = use_mfma_path(p, true, false);
-    WalkPlan plan;
-    WalkScratch scratch;
-    const bool walk = p.r <= 2 && use_walk(p, carve(p, nullptr), mfma, false, plan, scratch);
+    const bool mfma = use_mfma_path(p, true, false), walk = search_walks(p, false);
     *route = !mfma && !walk                 ? TTF_ROUTE_GENERAL
            : p.dtype == TTF_F32             ? TTF_ROUTE_MFMA_F32
            : mfma_search_supported(p)       ? TTF_ROUTE_MFMA_BF16

@@ -36,6 +36,11 @@ def units(p, plan):
     return p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs
 
 
+def search_walks(p, segment=False):
+    f = _symbol("_ZN3ttf12search_walksERK10ttf_paramsb", ctypes.c_bool, ctypes.c_void_p, ctypes.c_bool)
+    return f(ctypes.addressof(p), segment)
+
+
 def matrix_cores(p, segment=False):
     """Whether a search that does not walk runs on the matrix cores."""
     f = _symbol("_ZN3ttf13use_mfma_pathERK10ttf_paramsbb", ctypes.c_bool, ctypes.c_void_p, ctypes.c_bool, ctypes.c_bool)

@@ -4,7 +4,7 @@ import random
 import pytest
 import torch
 
-from plans import CUS, matrix_cores, params, units, walk_plan
+from plans import CUS, matrix_cores, params, search_walks, units, walk_plan
 
 BF, F32 = torch.bfloat16, torch.float32
 
@@ -35,6 +35,24 @@ def test_tall_grids_fill_the_chip(B, frames, H, W, C, r, dtype):
     assert plan.ok and units(p, plan) >= 0.75 * CUS
 
 
+def _limit(B, H, W, C, dtype, r):
+    """The most frames of a clip that still walks."""
+    return max(F for F in range(2, 400) if search_walks(params(B, F, H, W, C, dtype, r)))
+
+
+@pytest.mark.parametrize("B,H,W,C,dtype,r,most", [
+    (1, 16, 20, 1024, BF, 2, 31),             # products of all frames in the room of the anchor's copy
+    (1, 14, 14, 1088, BF, 1, 62),
+    (1, 18, 18, 2048, BF, 2, 69),
+    (1, 16, 16, 4096, F32, 1, None),
+])
+def test_a_segment_walks_where_its_clip_does(B, H, W, C, dtype, r, most):
+    limit = _limit(B, H, W, C, dtype, r)
+    assert limit < 399 and most in (None, limit), limit
+    for F in range(2, limit + 3):
+        assert search_walks(params(B, F - 1, H, W, C, dtype, r), segment=True) == search_walks(params(B, F, H, W, C, dtype, r)), F
+
+
 def test_a_segment_takes_the_search_of_its_clip():
     rng = random.Random(7)
     for _ in range(4000):
@@ -43,4 +61,5 @@ def test_a_segment_takes_the_search_of_its_clip():
         C = rng.choice([64, 256, 768, 1000, 1024, 1056, 1088, 1152, 2048, 2112, 4096, 4160])
         dtype, r = rng.choice([BF, BF, F32]), rng.choice([0, 1, 1, 2])
         clip, seg = params(B, F, H, W, C, dtype, r), params(B, F - 1, H, W, C, dtype, r)
+        assert search_walks(seg, True) == search_walks(clip), (B, F, H, W, C, dtype, r)
         assert matrix_cores(seg, True) == matrix_cores(clip), (B, F, H, W, C, dtype, r)
