@@ -738,8 +738,12 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     const int most = !sums ? 32 : p.dtype == TTF_F32 ? spec_frames<float, 1>() : (p.r == 2 ? spec_frames<bf16_t, 2>() : spec_frames<bf16_t, 1>());
     for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
         for (int ysegs = 1; ysegs <= steps && (long long)lsegs * ysegs <= most_runs; ysegs *= 2) {
-            // (more runs are looked at while the half of them, with the largest frame groups, does not fill the chip twice)
-            if (ysegs > 4 && (double)p.B * w.nk * ((frames + most - 1) / most) * lsegs * (ysegs / 2) >= 512) break;
+            // More than four runs only where fewer leave the chip empty, as on tall grids of few columns and frames: with
+            // four, segment B1 F6 848x16 C1024 430 us / with as many as it takes 63 (tile-wise kernels 75), tied B1 F2 3428x16
+            // C1152 2254 / 401 (457), fp32 tied B1 F2 2868x13 C896 2887 / 247 (486), B2 F10 116x16 C2048 r 0 125 / 81 (105).
+            // Elsewhere short runs leave too little of a pass in the Infinity Cache (B2 F256 16x16 C4096, runs of two
+            // rows: 669 -> 691).
+            if (ysegs > 4 && (double)p.B * w.nk * frames * lsegs * (ysegs / 2) >= 1024) break;
             int last = 0;
             for (int want = 1; want <= most; ++want) {
                 const int groups = (frames + want - 1) / want, nf = (frames + groups - 1) / groups;

@@ -35,6 +35,12 @@ def test_tall_grids_fill_the_chip(B, frames, H, W, C, r, dtype):
     assert plan.ok and units(p, plan) >= 0.75 * CUS
 
 
+@pytest.mark.parametrize("B,frames,C", [(2, 255, 4096), (16, 31, 4096), (8, 40, 1024)])
+def test_long_runs_where_frames_fill_the_chip(B, frames, C):
+    plan = walk_plan(params(B, frames + 1, 16, 16, C, BF), frames, False)
+    assert plan.ok and plan.ysegs <= 4          # the kept part of a pass is measured in whole rows of a run
+
+
 def _limit(B, H, W, C, dtype, r):
     """The most frames of a clip that still walks."""
     return max(F for F in range(2, 400) if search_walks(params(B, F, H, W, C, dtype, r)))
