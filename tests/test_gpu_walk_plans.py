@@ -62,3 +62,28 @@ def test_segment_gives_the_bits_of_its_clip(B, F, H, W, C, r, dtype):
     assert torch.equal(seg.best_sim, whole.best_sim[:, 1:])
     assert torch.equal(seg.best_idx, whole.best_idx[:, 1:])
     assert torch.equal(seg.fuse_map, whole.fuse_map[:, 1:])
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r", [(1, 12, 16, 16, 3072, 1), (1, 33, 16, 16, 1024, 1), (1, 9, 32, 32, 1024, 0),
+                                          (1, 13, 12, 19, 3296, 1), (1, 22, 9, 17, 2976, 0)])
+def test_fp32_error_is_no_larger_than_the_wave_per_token_search(B, F, H, W, C, r):
+    """fp32 problems that are too small for the tile-wise matrix-core search walk all the same.  Relative error of
+    the similarities against 64 bits, over the tokens that match their own cell: 7.5e-8 to 8.6e-8 on the wave-per-token
+    kernels over 30 such shapes."""
+    import paper_2605_07355_amd as ttf
+    p = params(B, F, H, W, C, torch.float32, r)
+    assert search_walks(p) and not matrix_cores(p)
+    g = torch.Generator(device="cuda").manual_seed(C + F)
+    a = torch.randn((B, 1, H, W, C), device="cuda", generator=g)
+    amp = 0.3 + 1.4 * torch.rand((B, F - 1, H, W, 1), device="cuda", generator=g)
+    x = torch.cat([a, a + amp * torch.randn((B, F - 1, H, W, C), device="cuda", generator=g)], 1).contiguous()
+    buf = ttf.TTFBuffers.allocate(B, F, H, W, C, x.dtype, x.device)
+    ttf.ttf_compress(x, r=r, t=0.7, anchor=0, buffers=buf)
+    torch.cuda.synchronize()
+    xd = x.double()
+    n = xd.norm(dim=-1)
+    want = ((xd[:, 1:] * xd[:, :1]).sum(-1) / (n[:, 1:] * n[:, :1])).flatten(2)
+    own = buf.best_idx[:, 1:] == torch.arange(H * W, device="cuda", dtype=torch.int32)
+    assert own.float().mean() > 0.9
+    err = (buf.best_sim[:, 1:].double() - want)[own]
+    assert (err.norm() / want[own].norm()).item() < 7.4e-8
