@@ -286,12 +286,12 @@ int ttf_last_hip_error(void);
  *                 confirms the guess, or the clip is searched again against the exact anchor.
  *                 A clip without a clear guess sits out the first search and takes the two-pass
  *                 route together with the refuted clips.  Outputs are those of the
- *                 exact rule in every case; only the time differs (one pass over the input instead
- *                 of two when the guesses hold, one extra search for a clip whose trusted guess
- *                 was wrong; on inputs below 256 MiB the two may take different searches, whose
- *                 similarities agree as those of different routes do, see ttf_search_route).
- *                 Available with C >= 1024, F >= 2 and the automatic anchor for fp32 input with C % 32 == 0
- *                 and r <= 1, and for bf16 input with C % 128 == 0 and r <= 2 on grids whose rows fill at least 70 % of the 32-cell
+ *                 exact rule in every case, bit for bit the same as on the two-pass route; only the time
+ *                 differs (one pass over the input instead of two when the guesses hold, one extra search
+ *                 for a clip whose trusted guess was wrong).
+ *                 Available where the search walks whole frames (see ttf_search_route) with C >= 1024, F >= 2
+ *                 and the automatic anchor: for fp32 input with C % 32 == 0 and r <= 1, and for bf16 input with
+ *                 C % 128 == 0 and r <= 2 on grids whose rows fill at least 70 % of the 32-cell
  *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
  *                 height); not where B, F and the grid are such that the sums have no room in the
  *                 workspace (many frames of few tokens, and fp32 clips of about 100 frames and more).
@@ -307,9 +307,11 @@ ttf_status ttf_set_speculation(int mode);
  * Search"): a host-side query, no GPU work.  The routes add the channels in different orders:
  * similarities agree to about 3e-7 (each within 1e-5 of the exact value), and only a token whose
  * similarity lies that close to t, or to another candidate's, may be gated or matched differently.
- * So do the kernels behind one route: problems with C >= 1024 (fp32: 768, r <= 1) take a search that walks whole
- * frames where it is the faster one, which depends on the grid, r, C and the size of the input; it makes fp32 problems
- * of 32 MiB and more matrix-core ones that would otherwise be too small.
+ * So do the kernels behind one route: problems with C >= 1024 (fp32: 768, r <= 1) and whole 128-byte groups of
+ * channels take a search that walks whole frames where it is the faster one, which depends on the grid, r, C and the
+ * size of the input (bf16 grids exactly 16 or 32 wide with whole keep words: from 24 to 160 MiB on), and where the
+ * window products of all its frames have room in the workspace; it makes fp32 problems of 32 MiB and more matrix-core
+ * ones that would otherwise be too small.
  * For most problems the route depends on dtype, r, C and the grid.  For bf16 with C % 32 != 0 (C % 8 == 0,
  * C >= 768) it also depends on B and F -- small problems and few-column grids are searched faster by the
  * general kernels -- and on the workspace: the answer is for one of ttf_workspace_size() bytes (a

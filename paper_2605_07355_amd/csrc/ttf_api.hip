@@ -116,6 +116,46 @@ bool search_walks(const ttf_params& p, bool external_anchor)
     return use_walk(p, w, use_mfma_path(p, w.tail, external_anchor), external_anchor, plan, scratch);
 }
 
+// Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of kSpeculationMinFrames to
+// kSpeculationMaxFrames frames (fp32: on grids of one strip, up to 16 columns), 1 whenever the shape allows.  Where the
+// lines lie (two-pass / with the guess, us, two inputs in turn): 256 to 320 MiB about even (B4 F21 27x32 C2048 r0 135 / 137),
+// beyond 1.02 to 1.3 (B12 F34 32x16 C2048 342 / 288, B13 F40 16x16 C4096 404 / 312).  Short clips clear the trust gap in some
+// clips of a batch only, whose two searches then each fill part of the chip (B12 F7 16x29 C4096 170 / 249, B13 F13 32x24
+// C2048 235 / 246).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
+// guess right.  fp32 with sums is bound by its arithmetic, which strips of 11 cells do not fill (B1 F44 32x32 C3584 336 /
+// 437, B6 F22 16x16 C2816 186 / 177, B16 F32 16x16 C4096 970 / 812).
+constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
+constexpr int kSpeculationMinFrames = 16, kSpeculationMaxFrames = 64;
+
+// Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
+// then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have
+// the bits of its similarities depend on the setting.
+static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mode, WalkPlan& plan, WalkScratch& scratch)
+{
+    if (p.anchor_mode != TTF_ANCHOR_AUTO || !mfma || !speculation_possible(p) || mode < 0) return false;
+    if (mode == 0) {
+        const unsigned long long bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2ull : 4ull);
+        if (bytes < kSpeculationMinBytes || p.F < kSpeculationMinFrames || p.F > kSpeculationMaxFrames ||
+            (p.dtype == TTF_F32 && p.W > 16))
+            return false;
+    }
+    const WalkPlan with_sums = walk_plan(p, p.F, true);
+    WalkScratch its{};
+    if (!with_sums.ok || !walk_scratch(p, w, with_sums, true, its)) return false;
+    plan = with_sums;
+    scratch = its;
+    return true;
+}
+
+bool search_guesses(const ttf_params& p, int mode)
+{
+    const Workspace w = carve(p, nullptr);
+    const bool mfma = use_mfma_path(p, w.tail, false);
+    WalkPlan plan{};
+    WalkScratch scratch{};
+    return use_walk(p, w, mfma, false, plan, scratch) && use_guess(p, w, mfma, mode, plan, scratch);
+}
+
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
 {
     static std::mutex mutex;
@@ -135,17 +175,7 @@ namespace {
 
 thread_local int g_last_hip_error = 0;
 
-// Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of kSpeculationMinFrames to
-// kSpeculationMaxFrames frames (fp32: on grids of one strip, up to 16 columns), 1 whenever the shape allows.  Where the
-// lines lie (two-pass / with the guess, us, two inputs in turn): 256 to 320 MiB about even (B4 F21 27x32 C2048 r0 135 / 137),
-// beyond 1.02 to 1.3 (B12 F34 32x16 C2048 342 / 288, B13 F40 16x16 C4096 404 / 312).  Short clips clear the trust gap in some
-// clips of a batch only, whose two searches then each fill part of the chip (B12 F7 16x29 C4096 170 / 249, B13 F13 32x24
-// C2048 235 / 246).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
-// guess right.  fp32 with sums is bound by its arithmetic, which strips of 11 cells do not fill (B1 F44 32x32 C3584 336 /
-// 437, B6 F22 16x16 C2816 186 / 177, B16 F32 16x16 C4096 970 / 812).
 std::atomic<int> g_speculation{0};
-constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
-constexpr int kSpeculationMinFrames = 16, kSpeculationMaxFrames = 64;
 
 // Event sets for stage timing: `slots` sets of TTF_NUM_STAGES+1 events, used round-robin by
 // successive profiled calls so that a benchmark can time many calls and read them afterwards.
@@ -241,23 +271,14 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     // against the exact anchor.  A clip whose guess is not clear-cut sits out the first search; its
     // frame sums are then formed the two-pass way and it is searched with the refuted clips.  Either way
     // every output is what the exact rule gives.
-    const int spec_pref = g_speculation.load(std::memory_order_relaxed);
-    const unsigned long long in_bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2ull : 4ull);
     WalkPlan plan{};
     WalkScratch scratch{};
-    bool spec = pick && mfma && speculation_possible(p) &&
-                (spec_pref > 0 ||
-                 (spec_pref == 0 && in_bytes >= kSpeculationMinBytes && p.F >= kSpeculationMinFrames &&
-                  p.F <= kSpeculationMaxFrames && (p.dtype == TTF_BF16 || p.W <= 16)));
+    const bool walk = use_walk(p, w, mfma, ext_anchor != nullptr, plan, scratch);
+    const bool spec = walk && pick && use_guess(p, w, mfma, g_speculation.load(std::memory_order_relaxed), plan, scratch);
     if (spec) {
-        plan = walk_plan(p, p.F, true);
-        spec = plan.ok && walk_scratch(p, w, plan, true, scratch);
-        if (spec) {
-            w.guess_sum = scratch.guess_sum;
-            w.spec = scratch.spec;
-        }
+        w.guess_sum = scratch.guess_sum;
+        w.spec = scratch.spec;
     }
-    const bool walk = spec || use_walk(p, w, mfma, ext_anchor != nullptr, plan, scratch);
 
     mark();                                                    // start of stage 0
     if (spec) TTF_STEP(launch_guess_sums(p, features, w, s));

@@ -215,6 +215,8 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums);
 bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan, bool sums, WalkScratch& scratch);
 // Whether a problem with a workspace of ttf_workspace_size() bytes is searched so (ttf_api.hip).
 bool search_walks(const ttf_params& p, bool external_anchor);
+// Whether its automatic anchor is guessed first, with the setting `mode` of ttf_set_speculation().
+bool search_guesses(const ttf_params& p, int mode);
 // mode 0: anchor external, fixed, given or picked from the scores.  1: clips with a trusted guess, every frame,
 // with sums.  2: clips whose guess the exact rule refutes, and those without one.
 hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,

@@ -3,10 +3,10 @@ and frame groups a problem is cut into is read from the library's own plan."""
 import pytest
 import torch
 
-from workloads import CONFIGS
+from workloads import CONFIGS, make_clip_batch
 
 from helpers import compare_with_oracle, run_gpu
-from plans import matrix_cores, params, search_walks, walk_plan
+from plans import matrix_cores, params, search_guesses, search_walks, walk_plan
 from test_gpu_parity import _prepared
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +87,26 @@ def test_fp32_error_is_no_larger_than_the_wave_per_token_search(B, F, H, W, C, r
     assert own.float().mean() > 0.9
     err = (buf.best_sim[:, 1:].double() - want)[own]
     assert (err.norm() / want[own].norm()).item() < 7.4e-8
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,guesses", [
+    (3, 6, 16, 16, 1024, 1, "bf16", False),     # below the line from which such grids walk
+    (2, 6, 16, 16, 1024, 2, "bf16", False),
+    (2, 9, 8, 32, 1024, 1, "bf16", False),
+    (1, 7, 16, 16, 2048, 0, "bf16", False),
+    (2, 33, 16, 16, 1024, 1, "bf16", False),
+    (16, 8, 16, 16, 2048, 1, "bf16", True),
+    (2, 6, 13, 16, 1024, 1, "bf16", True),
+    (2, 11, 14, 14, 1024, 2, "bf16", True),
+    (4, 18, 16, 16, 1024, 1, "f32", True),
+])
+def test_bits_do_not_depend_on_the_setting(B, F, H, W, C, r, dtype, guesses):
+    assert search_guesses(params(B, F, H, W, C, _torch(dtype), r), 1) == guesses
+    batch = make_clip_batch(_cfg(B, F, H, W, C, r, dtype), seed=1300 + F)
+    first = None
+    for mode in (-1, 1, None):
+        _, out = run_gpu(batch.x, r, 0.7, speculation=mode)
+        b, n = out.buffers, int(out.buffers.row_offsets[-1])
+        got = (b.best_sim, b.best_idx, b.fuse_map, b.anchor_index, b.row_offsets, b.src_index[:n])
+        first = first or got
+        assert all(torch.equal(u, v) for u, v in zip(first, got)), mode

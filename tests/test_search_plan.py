@@ -4,7 +4,7 @@ import random
 import pytest
 import torch
 
-from plans import CUS, matrix_cores, params, search_walks, units, walk_plan
+from plans import CUS, matrix_cores, params, search_guesses, search_walks, units, walk_plan
 
 BF, F32 = torch.bfloat16, torch.float32
 
@@ -69,3 +69,17 @@ def test_a_segment_takes_the_search_of_its_clip():
         clip, seg = params(B, F, H, W, C, dtype, r), params(B, F - 1, H, W, C, dtype, r)
         assert search_walks(seg, True) == search_walks(clip), (B, F, H, W, C, dtype, r)
         assert matrix_cores(seg, True) == matrix_cores(clip), (B, F, H, W, C, dtype, r)
+
+
+def test_only_problems_that_walk_guess_their_anchor():
+    """The search of a problem, and so the bits of its similarities, do not depend on the setting."""
+    rng, guessing = random.Random(8), 0
+    for _ in range(6000):
+        B, F = rng.choice([1, 2, 3, 4, 8, 16, 40]), rng.choice([1, 2, 3, 6, 9, 16, 32, 64, 100, 200])
+        H, W = rng.choice([1, 4, 8, 13, 14, 16, 32, 64]), rng.choice([3, 13, 14, 16, 16, 17, 24, 32, 32, 48])
+        C, r = rng.choice([512, 1000, 1024, 1056, 1152, 2048, 4096]), rng.choice([0, 1, 1, 2, 3])
+        p = params(B, F, H, W, C, rng.choice([BF, BF, F32]), r)
+        guesses = [search_guesses(p, mode) for mode in (-1, 0, 1)]
+        assert not guesses[0] and guesses[1] <= guesses[2] <= search_walks(p), (B, F, H, W, C, r, guesses)
+        guessing += guesses[2]
+    assert guessing > 300
