@@ -296,7 +296,8 @@ int ttf_last_hip_error(void);
  *                 height); not where B, F and the grid are such that the sums have no room in the
  *                 workspace (many frames of few tokens, and fp32 clips of about 100 frames and more).
  * mode  0 (default): speculative for inputs of 256 MiB and more in clips of 16 to 64 frames
- *       where available (fp32: on grids of up to 16 columns), else two-pass;
+ *       where available (fp32: on grids of up to 16 columns) and where enough of the clips have a clear guess,
+ *       else two-pass;
  *       1: speculative wherever available;  -1: always two-pass.
  * Process-wide; takes effect for calls made after it returns.  INVALID_ARG for other values.
  */

@@ -124,13 +124,17 @@ bool search_walks(const ttf_params& p, bool external_anchor)
 // C2048 235 / 246).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
 // guess right.  fp32 with sums is bound by its arithmetic, which strips of 11 cells do not fill (B1 F44 32x32 C3584 336 /
 // 437, B6 F22 16x16 C2816 186 / 177, B16 F32 16x16 C4096 970 / 812).
+// Where too few clips of a batch have a clear guess, all are dropped on the device (min_trusted): B8 F20 24x24 C2048, 6 of 8
+// clear, 195 two-pass, 290 with the guesses, 226 with them dropped; B16 F32 16x16 C4096, 4 of 16, 561 / 683 / 591.
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
 constexpr int kSpeculationMinFrames = 16, kSpeculationMaxFrames = 64;
 
 // Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
 // then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have
 // the bits of its similarities depend on the setting.
-static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mode, WalkPlan& plan, WalkScratch& scratch)
+// `plan` comes as that of use_walk(), the search without a guess, and goes as that of the walk beside one.
+static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mode, WalkPlan& plan, WalkScratch& scratch,
+                      int& min_trusted)
 {
     if (p.anchor_mode != TTF_ANCHOR_AUTO || !mfma || !speculation_possible(p) || mode < 0) return false;
     if (mode == 0) {
@@ -142,18 +146,21 @@ static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mo
     const WalkPlan with_sums = walk_plan(p, p.F, true);
     WalkScratch its{};
     if (!with_sums.ok || !walk_scratch(p, w, with_sums, true, its)) return false;
+    min_trusted = 0;                                         // (forced: however few)
+    if (mode == 0) min_trusted = guess_cost(p, with_sums, plan).min_trusted;
     plan = with_sums;
     scratch = its;
     return true;
 }
 
-bool search_guesses(const ttf_params& p, int mode)
+int search_guesses(const ttf_params& p, int mode)
 {
     const Workspace w = carve(p, nullptr);
     const bool mfma = use_mfma_path(p, w.tail, false);
     WalkPlan plan{};
     WalkScratch scratch{};
-    return use_walk(p, w, mfma, false, plan, scratch) && use_guess(p, w, mfma, mode, plan, scratch);
+    int min_trusted = 0;
+    return use_walk(p, w, mfma, false, plan, scratch) && use_guess(p, w, mfma, mode, plan, scratch, min_trusted) ? min_trusted : -1;
 }
 
 hipError_t allow_dynamic_lds(const void* kernel, size_t bytes)
@@ -274,7 +281,10 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     WalkPlan plan{};
     WalkScratch scratch{};
     const bool walk = use_walk(p, w, mfma, ext_anchor != nullptr, plan, scratch);
-    const bool spec = walk && pick && use_guess(p, w, mfma, g_speculation.load(std::memory_order_relaxed), plan, scratch);
+    const WalkPlan again = plan;
+    int min_trusted = 0;
+    const bool spec = walk && pick &&
+                      use_guess(p, w, mfma, g_speculation.load(std::memory_order_relaxed), plan, scratch, min_trusted);
     if (spec) {
         w.guess_sum = scratch.guess_sum;
         w.spec = scratch.spec;
@@ -293,7 +303,8 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     else if (!walk) TTF_STEP(launch_anchor_norms(p, features, ext_anchor, w, out->anchor_index, false, s));
     mark();
     if (walk) {
-        TTF_STEP(launch_search_walk(p, features, ext_anchor, w, plan, scratch, out->anchor_index, false, spec ? 1 : 0, s));
+        TTF_STEP(launch_search_walk(p, features, ext_anchor, w, plan, plan, scratch, out->anchor_index, false, spec ? 1 : 0,
+                                    min_trusted, s));
         if (!spec)
             TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
                                         nullptr, s));
@@ -303,9 +314,9 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     }
     mark();
     if (spec) {
-        TTF_STEP(launch_frame_sums(p, features, w, true, 0.0, s));     // clips without a trusted guess only
+        TTF_STEP(launch_frame_sums(p, features, w, true, kept_share(p, true), s));     // clips without a trusted guess only
         TTF_STEP(launch_anchor_scores(p, w, scratch.strip_sum, plan.lsegs * plan.ysegs, s));
-        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, false, 2, s));
+        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, again, scratch, out->anchor_index, false, 2, 0, s));
         TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
                                     nullptr, s));
     }
@@ -429,7 +440,7 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));
     if (walk) {
-        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, scratch, out->anchor_index, true, 0, s));
+        TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, plan, scratch, out->anchor_index, true, 0, 0, s));
         TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, nullptr, nullptr, nullptr, tw.win_sim, s));
     } else {
         if (mfma)

@@ -203,6 +203,14 @@ struct WalkPlan {
     int lines;               // column strips of the grid
     int lsegs, ysegs;        // runs of strips, and runs of rows, dealt to different workgroups
     int groups, nf;          // frame groups of nf frames
+    double tiles;            // time of a workgroup, in tiles
+};
+struct WalkDeal {
+    int lsegs, ysegs, groups, nf;   // as in WalkPlan
+};
+// The guessed anchor: how many clips have to have a clear guess for any to be taken.
+struct GuessCost {
+    int min_trusted;
 };
 struct WalkScratch {
     float* part;             // [nk][B*F*N][(2r+1)^2 + 1]
@@ -212,16 +220,19 @@ struct WalkScratch {
     int32_t* spec;
 };
 WalkPlan walk_plan(const ttf_params& p, int frames, bool sums);
+GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again);
 bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan, bool sums, WalkScratch& scratch);
 // Whether a problem with a workspace of ttf_workspace_size() bytes is searched so (ttf_api.hip).
 bool search_walks(const ttf_params& p, bool external_anchor);
-// Whether its automatic anchor is guessed first, with the setting `mode` of ttf_set_speculation().
-bool search_guesses(const ttf_params& p, int mode);
+// How many of its clips have to have a clear guess for their anchors to be guessed, with the setting `mode` of
+// ttf_set_speculation(); -1: the anchors are not guessed.
+int search_guesses(const ttf_params& p, int mode);
 // mode 0: anchor external, fixed, given or picked from the scores.  1: clips with a trusted guess, every frame,
-// with sums.  2: clips whose guess the exact rule refutes, and those without one.
+// with sums; fewer such clips than min_trusted lose their mark.  2: clips whose guess the
+// exact rule refutes, and those without one; dealt as in `all` where no clip has a trusted guess.
 hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
-                              const WalkPlan& plan, const WalkScratch& scratch, int32_t* anchor_index,
-                              bool anchor_given, int mode, hipStream_t s);
+                              const WalkPlan& plan, const WalkPlan& all, const WalkScratch& scratch, int32_t* anchor_index,
+                              bool anchor_given, int mode, int min_trusted, hipStream_t s);
 // Similarities, arg max, gate and keep words from the walk's products (win_sim: tied-batch mode, see k_tie).
 hipError_t launch_walk_finish(const ttf_params& p, const Workspace& w, const WalkPlan& plan, const WalkScratch& scratch,
                               const int32_t* anchor_index, int32_t* fuse_map, float* best_sim, int32_t* best_idx,

@@ -63,13 +63,15 @@ struct WalkArgs {
     const double* score_part;
     const double* clip_part;
     int32_t* anchor_index;
-    const int32_t* spec;
+    int32_t* spec;
     float* part;                                             // [nk][B*F*N][K+1] window products, squared norm
     float* norm_part;                                        // [nk][B*N] squared norms of the anchor tokens
     float* strip_sum;                                        // [B*F][strips*ysegs][C]
     int B, F, H, W, C, S;
-    int nk, groups, nf, lines, lsegs, ysegs;
+    int nk, lines;
+    WalkDeal deal, all;                                      // `all`: mode 2, where no clip has a trusted guess
     int fixed_anchor, mode;
+    int min_trusted;                                         // mode 1: with fewer trusted guesses than this none is taken
     int keep_from;                                           // of 256 parts of a workgroup's tiles, the first left in the cache
 };
 
@@ -168,7 +170,10 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     const int H = A.H, W = A.W, N = H * W, F = A.F;
     // The clips to search (mode 2: up to kPickClips, whose anchors the waves pick between them; more clips pick their
     // own below and leave where there is nothing to do), and how many units they make.
-    const int per_clip = A.groups * A.lsegs * A.ysegs * A.nk;
+    bool guessed = A.mode != 2;
+    for (int b0 = 0; !guessed && b0 < A.B; b0 += 64) guessed = __ballot(b0 + lane < A.B && A.spec[4 * min(b0 + lane, A.B - 1) + 1] != 0) != 0;
+    const WalkDeal deal = guessed ? A.deal : A.all;
+    const int per_clip = deal.groups * deal.lsegs * deal.ysegs * A.nk;
     constexpr int kPickClips = 32;
     int32_t* const picked = reinterpret_cast<int32_t*>(red); // [2][kPickClips] exact anchor, search again
     const bool choose = A.mode == 1 || (A.mode == 2 && A.B <= kPickClips);
@@ -193,6 +198,14 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     if (choose) {
         clips = 0;
         for (int b0 = 0; b0 < A.B; b0 += 64) clips += __popcll(flags(b0));
+        if (A.mode == 1 && clips < A.min_trusted) {
+            // No guess is taken (guess_cost()): the marks go, for this launch and those behind it.  A workgroup
+            // that counts some of them gone comes to the same answer.
+            if (blockIdx.x == 0) {
+                for (int c = threadIdx.x; c < A.B; c += kWalkWaves * 64) A.spec[4 * c + 1] = 0;
+            }
+            return;
+        }
     }
     // Workgroups are dealt to the XCDs round robin; every XCD gets one contiguous run of the units, in
     // which the frame groups of one (clip, strip, channel share) are neighbours: their anchor rows are read
@@ -203,8 +216,8 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
         if (nth >= (U >> 3) + (xcd < (U & 7) ? 1 : 0)) return;   // (workgroup-uniform)
         u = xcd * (U >> 3) + min(xcd, U & 7) + nth;
     }
-    const int grp = u % A.groups; u /= A.groups;
-    const int seg = u % (A.lsegs * A.ysegs); u /= A.lsegs * A.ysegs;
+    const int grp = u % deal.groups; u /= deal.groups;
+    const int seg = u % (deal.lsegs * deal.ysegs); u /= deal.lsegs * deal.ysegs;
     const int share = u % A.nk;
     int b = u / A.nk;
     if (choose) {                                            // the b-th clip of those to search
@@ -239,9 +252,9 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     }
 
     // the unit's part of the grid: column strips line_lo .. line_hi-1, tiles step_lo .. step_hi-1 of each
-    const int line_lo = (int)((long long)A.lines * (seg / A.ysegs) / A.lsegs), line_hi = (int)((long long)A.lines * (seg / A.ysegs + 1) / A.lsegs);
+    const int line_lo = (int)((long long)A.lines * (seg / deal.ysegs) / deal.lsegs), line_hi = (int)((long long)A.lines * (seg / deal.ysegs + 1) / deal.lsegs);
     const int all_steps = (H + STEP - 1) / STEP;
-    const int step_lo = (int)((long long)all_steps * (seg % A.ysegs) / A.ysegs), step_hi = (int)((long long)all_steps * (seg % A.ysegs + 1) / A.ysegs);
+    const int step_lo = (int)((long long)all_steps * (seg % deal.ysegs) / deal.ysegs), step_hi = (int)((long long)all_steps * (seg % deal.ysegs + 1) / deal.ysegs);
     // first cell and width of a strip; rows of grids wider than 16 keep a margin of r for the window
     const int margin = PATCH || A.lines == 1 ? 0 : RAD;
     const int strip_w = W / A.lines, wide_strips = W % A.lines;      // (the first strips are a cell wider where need be)
@@ -249,8 +262,8 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     // frames of the group: cnt slots from k0, the anchor left out where it is not walked
     const int walked = (SPEC || a < 0) ? F : F - 1;
     const int skip = (SPEC || a < 0) ? 0x7fffffff : a;
-    const int k0 = grp * A.nf;
-    const int cnt = min(A.nf, walked - k0);
+    const int k0 = grp * deal.nf;
+    const int cnt = min(deal.nf, walked - k0);
     if (cnt <= 0) return;                                    // (one frame, the anchor: nothing to walk)
     // channels of this wave: groups q_lo .. q_lo+gq-1 of 128 bytes
     const int total_groups = A.C / (128 / (int)sizeof(E));
@@ -604,7 +617,7 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
 #pragma unroll
         for (int f = 0; f < FRS; ++f) {
             if (f < cnt) {
-                float* out = A.strip_sum + (((size_t)b * F + k0 + f) * (A.lsegs * A.ysegs) + seg) * A.C + (size_t)q_lo * (128 / sizeof(E));
+                float* out = A.strip_sum + (((size_t)b * F + k0 + f) * (deal.lsegs * deal.ysegs) + seg) * A.C + (size_t)q_lo * (128 / sizeof(E));
 #pragma unroll
                 for (int gi = 0; gi < GM; ++gi) {
                     if (gi < gq) {
@@ -717,6 +730,14 @@ __global__ __launch_bounds__(256) void k_walk_finish(const float* __restrict__ p
 
 }  // namespace
 
+// Rounds that this many workgroups take, one per CU at a time.  The last one may not fill the chip; half of its time is
+// that of its CUs, half that of the memory (B4 F32 16x16 C4096: 64 / 128 / 256 workgroups 102 / 64 / 46 us).
+static double deal_rounds(double units)
+{
+    const double whole = (double)((long long)units / 256), rest = units - 256 * whole;
+    return whole + (rest > 0 ? 0.5 + 0.5 * rest / 256 : 0.0);
+}
+
 // How the walk is dealt to workgroups (one per CU at a time).  `frames` are walked per clip.
 WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 {
@@ -730,9 +751,7 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     w.lines = w.patch ? (p.W + 3) / 4 : (p.W <= 16 ? 1 : (p.W + 15 - 2 * p.r) / (16 - 2 * p.r));
     const int steps = w.patch ? (p.H + 3) / 4 : p.H, fresh = w.patch ? 2 : 1, held = w.patch ? p.r : 2 * p.r;
     // Time of a deal in tiles: a workgroup starts up (two tiles' time), reads the anchor tiles of its run (which
-    // come from L2: a third each) and its source tiles.  The last round of workgroups may not fill the chip;
-    // half of its time is that of its CUs, half that of the memory (B4 F32 16x16 C4096: 64 / 128 / 256 workgroups
-    // 102 / 64 / 46 us).
+    // come from L2: a third each) and its source tiles.
     // Frame sums are stored per run of the grid: as many runs as leave the products room in the strip-sum section.
     const long long products = (long long)w.nk * ((2 * p.r + 1) * (2 * p.r + 1) + 1) * p.H * p.W;
     const long long most_runs = !sums ? 1 << 20 : p.dtype == TTF_F32 ? 2 : std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C);
@@ -755,10 +774,10 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
                 if (units * (kWalkWaves * 64) >= 4294967296.0) continue;   // (threads of a launch)
                 const double lines = (w.lines + lsegs - 1) / lsegs, run = (steps + ysegs - 1) / ysegs;   // (of the longest)
                 const double tiles = 2.0 + lines * (run * (nf + 0.35 * fresh) + 0.35 * held);
-                const double whole = (double)((long long)units / 256), rest = units - 256 * whole;
-                const double time = tiles * (whole + (rest > 0 ? 0.5 + 0.5 * rest / 256 : 0.0));
+                const double time = tiles * deal_rounds(units);
                 if (time < best) {
                     best = time;
+                    w.tiles = tiles;
                     w.nf = nf; w.groups = groups; w.lsegs = lsegs; w.ysegs = ysegs;
                 }
             }
@@ -766,6 +785,39 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     }
     w.ok = best < 1e300;
     return w;
+}
+
+// How many clips need a clear guess for any to be taken: beside unclear clips it saves
+// their share of a read and costs two searches and a pass for frame sums that may each fill part of the chip.  B16 F32
+// 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16 walks
+// 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
+// The times are those of the model of walk_plan(), a tile of 2048 (fp32 1024) channels 2.6 us (fp32 and 5x5 window 3.6; with sums
+// 4 to 30 % more), a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
+// of a frame.  Measured ratio of taking the guesses to dropping them / the model's: B16 F32 16x16 C4096, 12 of 16 clear, 1.07 / 1.09;
+// B8 F20 24x24 C2048, 6 of 8, 1.27 / 1.5; B128 F16 16x16 C2048, 124 of 128, 0.88 / 0.81; B32 F20 24x24 C2048, 31 of 32, 0.89 / 0.92.
+GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again)
+{
+    const bool f32 = p.dtype == TTF_F32;
+    const double tile = (f32 || p.r == 2 ? 3.6 : 2.6) * p.C / (first.nk * (f32 ? 1024.0 : 2048.0));
+    const double with_sums = f32 ? 1.3 : (p.r == 2 ? 1.1 : 1.04);
+    const double clip = (double)p.F * p.H * p.W * p.C * (f32 ? 4 : 2) / 6.6e6;
+    const double units = (double)first.nk * first.groups * first.lsegs * first.ysegs;
+    auto sums = [&](int n) {
+        const double blocks = (double)n * p.F * p.C * (f32 ? 4 : 2) / 4096;
+        return std::max(n * clip, std::min(p.B * clip, (double)p.H * p.W / 8 * (0.8 + 1.8 * std::min(1.0, blocks / 256))));
+    };
+    auto walk = [&](int n) { return tile * first.tiles * deal_rounds(units * n); };
+    const double without = p.B * clip + tile * again.tiles * deal_rounds((double)p.B * again.nk * again.groups * again.lsegs * again.ysegs);
+    GuessCost cost{};
+    cost.min_trusted = p.B + 1;
+    const int step = (p.B + 63) / 64;                        // (no more than 64 of the counts are looked at)
+    for (int n = p.B; n > 0; n -= step) {
+        const int rest = p.B - n;
+        const double time = with_sums * walk(n) + (rest > 0 ? sums(rest) + walk(rest) : 0.0);
+        if (time > without) break;
+        cost.min_trusted = n;
+    }
+    return cost;
 }
 
 // The scratch of the walk in the strip-sum and fragment sections of the workspace, where they have room.
@@ -801,8 +853,8 @@ bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan,
 }
 
 hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ext_anchor, const Workspace& w,
-                              const WalkPlan& plan, const WalkScratch& scratch, int32_t* anchor_index, bool anchor_given,
-                              int mode, hipStream_t s)
+                              const WalkPlan& plan, const WalkPlan& all, const WalkScratch& scratch, int32_t* anchor_index,
+                              bool anchor_given, int mode, int min_trusted, hipStream_t s)
 {
     WalkArgs a{};
     a.x = static_cast<const char*>(x);
@@ -815,12 +867,15 @@ hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ex
     a.norm_part = scratch.norm_part;
     a.strip_sum = scratch.strip_sum;
     a.B = p.B; a.F = p.F; a.H = p.H; a.W = p.W; a.C = p.C; a.S = (p.C + 255) / 256;
-    a.nk = plan.nk; a.groups = plan.groups; a.nf = plan.nf;
-    a.lines = plan.lines; a.lsegs = plan.lsegs; a.ysegs = plan.ysegs;
+    a.nk = plan.nk; a.lines = plan.lines;
+    a.deal = {plan.lsegs, plan.ysegs, plan.groups, plan.nf};
+    a.all = {all.lsegs, all.ysegs, all.groups, all.nf};
     a.fixed_anchor = anchor_given ? kAnchorGiven : fixed_frame(p);
     a.mode = mode;
+    a.min_trusted = min_trusted;
     a.keep_from = 256 - (int)(256 * kept_share(p, true));
-    const unsigned grid = (unsigned)((size_t)p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs);
+    auto units = [&](const WalkPlan& w) { return (size_t)p.B * w.nk * w.groups * w.lsegs * w.ysegs; };
+    const unsigned grid = (unsigned)(mode == 2 ? std::max(units(plan), units(all)) : units(plan));
     auto go = [&](auto kernel, size_t lds) {
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
         if (e != hipSuccess) return e;

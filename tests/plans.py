@@ -10,7 +10,7 @@ CUS = 256                                                   # compute units: one
 class WalkPlan(ctypes.Structure):
     """struct WalkPlan of csrc/ttf_internal.h."""
     _fields_ = [("ok", ctypes.c_bool), ("patch", ctypes.c_bool)] + [
-        (n, ctypes.c_int) for n in ("nk", "lines", "lsegs", "ysegs", "groups", "nf")]
+        (n, ctypes.c_int) for n in ("nk", "lines", "lsegs", "ysegs", "groups", "nf")] + [("tiles", ctypes.c_double)]
 
 
 def params(B, F, H, W, C, dtype, r=1):
@@ -48,5 +48,6 @@ def matrix_cores(p, segment=False):
 
 
 def search_guesses(p, mode):
-    f = _symbol("_ZN3ttf14search_guessesERK10ttf_paramsi", ctypes.c_bool, ctypes.c_void_p, ctypes.c_int)
+    """How many clips have to have a clear guess for any to be taken; -1: anchors are not guessed."""
+    f = _symbol("_ZN3ttf14search_guessesERK10ttf_paramsi", ctypes.c_int, ctypes.c_void_p, ctypes.c_int)
     return f(ctypes.addressof(p), mode)

@@ -1,5 +1,6 @@
 """GPU parity of the search that walks whole frames, at deals that are asserted and not assumed: how many runs of rows
 and frame groups a problem is cut into is read from the library's own plan."""
+import numpy as np
 import pytest
 import torch
 
@@ -8,6 +9,8 @@ from workloads import CONFIGS, make_clip_batch
 from helpers import compare_with_oracle, run_gpu
 from plans import matrix_cores, params, search_guesses, search_walks, walk_plan
 from test_gpu_parity import _prepared
+from test_gpu_speculative import TRUST_GAP, anchor_scores, guess_channels
+from workloads.ttf_gen import bf16_bits_to_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -101,7 +104,7 @@ def test_fp32_error_is_no_larger_than_the_wave_per_token_search(B, F, H, W, C, r
     (4, 18, 16, 16, 1024, 1, "f32", True),
 ])
 def test_bits_do_not_depend_on_the_setting(B, F, H, W, C, r, dtype, guesses):
-    assert search_guesses(params(B, F, H, W, C, _torch(dtype), r), 1) == guesses
+    assert (search_guesses(params(B, F, H, W, C, _torch(dtype), r), 1) >= 0) == guesses
     batch = make_clip_batch(_cfg(B, F, H, W, C, r, dtype), seed=1300 + F)
     first = None
     for mode in (-1, 1, None):
@@ -110,3 +113,82 @@ def test_bits_do_not_depend_on_the_setting(B, F, H, W, C, r, dtype, guesses):
         got = (b.best_sim, b.best_idx, b.fuse_map, b.anchor_index, b.row_offsets, b.src_index[:n])
         first = first or got
         assert all(torch.equal(u, v) for u, v in zip(first, got)), mode
+
+
+def _guess(clip):
+    """Guessed frame of a clip and its lead, from the rule that the header documents."""
+    v = clip.reshape(clip.shape[0], -1, clip.shape[-1])[:, :, guess_channels(clip.shape[-1])]
+    score = anchor_scores((bf16_bits_to_f32(v) if v.dtype == np.uint16 else v).sum(1, dtype=np.float64))
+    best, second = np.argsort(-score, kind="stable")[:2]
+    return best, score[best] - score[second]
+
+
+def _kinds(x, anchors):
+    """What becomes of every clip's guess."""
+    kinds = []
+    for clip, anchor in zip(x, anchors):
+        best, gap = _guess(clip)
+        assert abs(gap - TRUST_GAP) > 0.005, "guess too close to the trust threshold for a robust test"
+        kinds.append("unclear" if gap < TRUST_GAP else ("confirmed" if best == anchor else "refuted"))
+    return kinds
+
+
+def _mixed(cfg, seed, refuted, unclear):
+    """A batch of clear clips but for `refuted` (the guess channels are those of a clip with another low-noise frame)
+    and `unclear` (no frame stands out); the batch and the oracle's result."""
+    from oracle import margins
+    batch = make_clip_batch(cfg, seed=seed)
+    idx = guess_channels(cfg.C)
+    for b in refuted:
+        for other_seed in range(seed + 1, seed + 40):
+            other = make_clip_batch(cfg.scaled(B=1), seed=other_seed + 100 * b)
+            if other.clean_frame[0, 0] != batch.clean_frame[b, 0]:
+                batch.x[b][..., idx] = other.x[0][..., idx]
+                break
+    for b in unclear:
+        flat = next(f for f in (make_clip_batch(cfg.scaled(B=1, clean_sigma=1.2), seed=seed + 7000 + b + 1000 * i) for i in range(9))
+                    if _guess(f.x[0])[1] < 0.9 * TRUST_GAP)
+        batch.x[b] = flat.x[0]
+        batch.amplitude[b], batch.changed[b], batch.offsets[b] = flat.amplitude[0], flat.changed[0], flat.offsets[0]
+    res = margins.enforce_margins(batch, cfg.r, cfg.t, want_tokens=False)
+    want = ["refuted" if b in refuted else ("unclear" if b in unclear else "confirmed") for b in range(cfg.B)]
+    return batch, res, want
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,nf,refuted,unclear", [
+    (33, 11, 6, 14, 1024, 1, "bf16", 4, (0, 32), (5, 31)),           # more clips than the second walk picks in its prologue
+    (70, 10, 2, 14, 1024, 1, "bf16", 4, (0, 34, 69), (1, 35, 65)),   # more than one word of clips; groups of 4, 4 and 2 frames
+    (70, 9, 2, 14, 1024, 2, "bf16", 2, (3, 66), (64,)),              # patches; the last group holds one frame
+    (70, 10, 3, 25, 1024, 0, "bf16", 4, (69,), (0, 68)),             # two strips
+    (40, 25, 6, 14, 1024, 1, "bf16", 3, (), tuple(range(40))),       # no clear guess: the second walk is dealt as without one
+    (70, 13, 2, 14, 1024, 1, "f32", 5, (0, 40), (2, 69)),            # groups of 5, 5 and 3
+    (70, 23, 2, 14, 1024, 0, "f32", 8, (12, 64), (63,)),             # groups of 8, 8 and 7
+])
+def test_batches_of_all_kinds(B, F, H, W, C, r, dtype, nf, refuted, unclear):
+    p = params(B, F, H, W, C, _torch(dtype), r)
+    plan = walk_plan(p, F, True)
+    assert search_guesses(p, 1) >= 0 and plan.nf == nf and plan.groups * nf > F
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, r=r, max_offset=min(max(r, 1), 2), sigma=1.2,
+                                       clean_sigma=0.1, dtype=dtype)
+    batch, res, want = _mixed(cfg, 5000 + B + F, refuted, unclear)
+    assert _kinds(batch.x, res.anchor_index) == want
+    for mode in (1, -1):
+        _, out = run_gpu(batch.x, r, cfg.t[0], speculation=mode)
+        compare_with_oracle(batch.x, out, res)
+
+
+def test_guesses_are_dropped_where_too_few_are_clear():
+    """256 MiB at the default setting: with three clips of eight refuted or unclear, the guess is taken for none, or,
+    forced, for all that are clear; either way the outputs are those of the two-pass route."""
+    B, F, H, W, C, r = 8, 16, 16, 16, 4096, 1
+    p = params(B, F, H, W, C, torch.bfloat16, r)
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, r=r, max_offset=1, sigma=1.2, clean_sigma=0.1)
+    batch, res, want = _mixed(cfg, 5300, (0,), (2, 5))
+    assert _kinds(batch.x, res.anchor_index) == want
+    assert search_guesses(p, 0) > B - 2 and search_guesses(p, 1) == 0
+    bits = []
+    for mode in (None, 1, -1):
+        _, out = run_gpu(batch.x, r, cfg.t[0], speculation=mode)
+        compare_with_oracle(batch.x, out, res)
+        bits.append(out.buffers.best_sim)
+    assert torch.equal(bits[0], bits[2]) and torch.equal(bits[1], bits[2])
