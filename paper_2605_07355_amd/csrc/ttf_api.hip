@@ -119,15 +119,14 @@ bool search_walks(const ttf_params& p, bool external_anchor)
 // Speculative anchor: -1 never, 0 for inputs of at least kSpeculationMinBytes in clips of kSpeculationMinFrames to
 // kSpeculationMaxFrames frames (fp32: on grids of one strip, up to 16 columns), 1 whenever the shape allows.  Where the
 // lines lie (two-pass / with the guess, us, two inputs in turn): 256 to 320 MiB about even (B4 F21 27x32 C2048 r0 135 / 137),
-// beyond 1.02 to 1.3 (B12 F34 32x16 C2048 342 / 288, B13 F40 16x16 C4096 404 / 312).  Short clips clear the trust gap in some
-// clips of a batch only, whose two searches then each fill part of the chip (B12 F7 16x29 C4096 170 / 249, B13 F13 32x24
-// C2048 235 / 246).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
+// beyond 1.02 to 1.3 (B12 F34 32x16 C2048 342 / 288, B13 F40 16x16 C4096 404 / 312).  Shorter clips clear the trust gap too
+// seldom (B32 F4 16x16 C4096 150 / 177, none of 32; B16 F12 203 / 163 and B16 F15 242 / 195, all of 16).  Long ones of three scenes and more the same: B3 F84 32x26 C1536 r2 435 / 500 to 570, 420 were every
 // guess right.  fp32 with sums is bound by its arithmetic, which strips of 11 cells do not fill (B1 F44 32x32 C3584 336 /
 // 437, B6 F22 16x16 C2816 186 / 177, B16 F32 16x16 C4096 970 / 812).
 // Where too few clips of a batch have a clear guess, all are dropped on the device (min_trusted): B8 F20 24x24 C2048, 6 of 8
 // clear, 195 two-pass, 290 with the guesses, 226 with them dropped; B16 F32 16x16 C4096, 4 of 16, 561 / 683 / 591.
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
-constexpr int kSpeculationMinFrames = 16, kSpeculationMaxFrames = 64;
+constexpr int kSpeculationMinFrames = 12, kSpeculationMaxFrames = 64;
 
 // Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
 // then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have

@@ -95,3 +95,8 @@ def test_only_problems_that_walk_guess_their_anchor():
 ])
 def test_clips_that_need_a_clear_guess(B, F, H, W, C, r, least):
     assert search_guesses(params(B, F, H, W, C, BF, r), 0) == least
+
+
+def test_default_frame_counts_of_the_guess():
+    took = [F for F in range(2, 130) if search_guesses(params(16, F, 16, 16, 4096, BF), 0) >= 0]
+    assert took == list(range(12, 65))        # F 12: 203 us two-pass, 163 with the guesses; F 15: 242 / 195
