@@ -295,9 +295,9 @@ int ttf_last_hip_error(void);
  *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
  *                 height); not where B, F and the grid are such that the sums have no room in the
  *                 workspace (many frames of few tokens, and fp32 clips of about 100 frames and more).
- * mode  0 (default): speculative for inputs of 256 MiB and more in clips of 12 to 64 frames
- *       where available (fp32: on grids of up to 16 columns) and where enough of the clips have a clear guess,
- *       else two-pass;
+ * mode  0 (default): speculative where it is expected to be faster (from 256 MiB on, clips of 12 to 64
+ *       frames, fp32 on grids of up to 16 columns; depends on B, F, the grid, r and C), and there only if
+ *       enough of the clips have a clear guess: else all take the two-pass route;
  *       1: speculative wherever available;  -1: always two-pass.
  * Process-wide; takes effect for calls made after it returns.  INVALID_ARG for other values.
  */

@@ -787,7 +787,7 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     return w;
 }
 
-// How many clips need a clear guess for any to be taken: beside unclear clips it saves
+// What the guess saves where every clip has a clear one, and how many clips need one: beside unclear clips it saves
 // their share of a read and costs two searches and a pass for frame sums that may each fill part of the chip.  B16 F32
 // 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16 walks
 // 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
@@ -809,6 +809,7 @@ GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan&
     auto walk = [&](int n) { return tile * first.tiles * deal_rounds(units * n); };
     const double without = p.B * clip + tile * again.tiles * deal_rounds((double)p.B * again.nk * again.groups * again.lsegs * again.ysegs);
     GuessCost cost{};
+    cost.saves = without - with_sums * walk(p.B) - p.B * clip * 1.2 * kGuessChannels / p.C;
     cost.min_trusted = p.B + 1;
     const int step = (p.B + 63) / 64;                        // (no more than 64 of the counts are looked at)
     for (int n = p.B; n > 0; n -= step) {

@@ -100,3 +100,15 @@ def test_clips_that_need_a_clear_guess(B, F, H, W, C, r, least):
 def test_default_frame_counts_of_the_guess():
     took = [F for F in range(2, 130) if search_guesses(params(16, F, 16, 16, 4096, BF), 0) >= 0]
     assert took == list(range(12, 65))        # F 12: 203 us two-pass, 163 with the guesses; F 15: 242 / 195
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,taken", [
+    (2, 64, 32, 32, 1024, 1, False),          # all clear: 157 us two-pass, 176 with the guesses
+    (4, 40, 32, 26, 1536, 2, False),          # 205 / 265
+    (8, 12, 32, 32, 2048, 2, False),          # 197 / 224
+    (4, 64, 32, 32, 4096, 2, True),           # 986 / 816
+    (16, 12, 16, 16, 4096, 1, True),          # 203 / 163
+    (16, 64, 16, 16, 1024, 1, True),          # 248 / 233
+])
+def test_guess_where_it_pays(B, F, H, W, C, r, taken):
+    assert (search_guesses(params(B, F, H, W, C, BF, r), 0) >= 0) == taken
