@@ -293,8 +293,8 @@ int ttf_last_hip_error(void);
  *                 and the automatic anchor: for fp32 input with C % 32 == 0 and r <= 1, and for bf16 input with
  *                 C % 128 == 0 and r <= 2 on grids whose rows fill at least 70 % of the 32-cell
  *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
- *                 height); not where B, F and the grid are such that the sums have no room in the
- *                 workspace (many frames of few tokens, and fp32 clips of about 100 frames and more).
+ *                 height); fp32 clips only while the guess, 1 to 8 KiB a frame, fits beside the window products
+ *                 (a few frames fewer than walk; many fewer on grids of some dozen tokens).
  * mode  0 (default): speculative where it is expected to be faster (from 256 MiB on, clips of 12 to 64
  *       frames, fp32 on grids of up to 16 columns; depends on B, F, the grid, r and C), and there only if
  *       enough of the clips have a clear guess: else all take the two-pass route;
@@ -311,8 +311,12 @@ ttf_status ttf_set_speculation(int mode);
  * So do the kernels behind one route: problems with C >= 1024 (fp32: 768, r <= 1) and whole 128-byte groups of
  * channels take a search that walks whole frames where it is the faster one, which depends on the grid, r, C and the
  * size of the input (bf16 grids exactly 16 or 32 wide with whole keep words: from 24 to 160 MiB on), and where the
- * window products of all its frames have room in the workspace; it makes fp32 problems of 32 MiB and more matrix-core
- * ones that would otherwise be too small.
+ * window products of all its frames have room in the workspace.  They are n * ((2r+1)^2 + 1) floats a token, n = C / 2048
+ * (fp32: C / 1024) rounded up; where the speculative route exists for bf16 (see ttf_set_speculation) there is room for any
+ * F, elsewhere it is that of the anchor's copy, 2C (fp32: 6C) bytes for every cell of a frame with rows padded to
+ * whole 16 columns: 31 frames of 16x20 C 1024 r 2, 54 of 16x16 C 1088 r 1, 153 of fp32 16x16 C 4096 r 1.  A clip one
+ * frame too long takes the search it would take below the size lines.  The walk makes fp32 problems of 32 MiB and
+ * more matrix-core ones that would otherwise be too small.
  * For most problems the route depends on dtype, r, C and the grid.  For bf16 with C % 32 != 0 (C % 8 == 0,
  * C >= 768) it also depends on B and F -- small problems and few-column grids are searched faster by the
  * general kernels -- and on the workspace: the answer is for one of ttf_workspace_size() bytes (a

@@ -217,7 +217,7 @@ struct GuessCost {
 struct WalkScratch {
     float* part;             // [nk][B*F*N][(2r+1)^2 + 1]
     float* norm_part;        // [nk][B*N]
-    float* strip_sum;        // [B*F][lsegs*ysegs][C], where sums are kept
+    float* strip_sum;        // [B*F][lsegs*ysegs][C], where sums are kept (frame_sum for a single run)
     float* guess_sum;        // the sections of the same names (in the fragment section for fp32 tokens)
     int32_t* spec;
 };

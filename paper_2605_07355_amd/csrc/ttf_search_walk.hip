@@ -752,9 +752,16 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
     const int steps = w.patch ? (p.H + 3) / 4 : p.H, fresh = w.patch ? 2 : 1, held = w.patch ? p.r : 2 * p.r;
     // Time of a deal in tiles: a workgroup starts up (two tiles' time), reads the anchor tiles of its run (which
     // come from L2: a third each) and its source tiles.
-    // Frame sums are stored per run of the grid: as many runs as leave the products room in the strip-sum section.
+    // Frame sums are stored per run of the grid: as many runs as leave the products room.
     const long long products = (long long)w.nk * ((2 * p.r + 1) * (2 * p.r + 1) + 1) * p.H * p.W;
-    const long long most_runs = !sums ? 1 << 20 : p.dtype == TTF_F32 ? 2 : std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C);
+    long long most_runs = !sums ? 1 << 20 : p.dtype == TTF_F32 ? 2 : std::max(1ll, spec_strips(p) - (products + p.C - 1) / p.C);
+    if (sums && most_runs > 1) {
+        WalkPlan all_runs = w;
+        all_runs.lsegs = (int)most_runs;
+        all_runs.ysegs = 1;
+        WalkScratch room{};
+        if (!walk_scratch(p, carve(p, nullptr), all_runs, true, room)) most_runs = 1;
+    }
     double best = 1e300;
     const int most = !sums ? 32 : p.dtype == TTF_F32 ? spec_frames<float, 1>() : (p.r == 2 ? spec_frames<bf16_t, 2>() : spec_frames<bf16_t, 1>());
     for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
@@ -841,7 +848,9 @@ bool walk_scratch(const ttf_params& p, const Workspace& w, const WalkPlan& plan,
         return nullptr;
     };
     scratch.part = take(plan.nk * tokens * (KK + 1));
-    scratch.strip_sum = sums ? take((size_t)p.B * p.F * plan.lsegs * plan.ysegs * p.C) : nullptr;
+    // (sums of one run are whole frame sums and stand in their own section)
+    const size_t runs = (size_t)plan.lsegs * plan.ysegs;
+    scratch.strip_sum = !sums ? nullptr : (runs == 1 ? w.frame_sum : take((size_t)p.B * p.F * runs * p.C));
     scratch.norm_part = take((size_t)plan.nk * p.B * p.H * p.W);
     // the guess has sections of its own beside bf16 tokens
     scratch.guess_sum = w.guess_sum;

@@ -192,3 +192,22 @@ def test_guesses_are_dropped_where_too_few_are_clear():
         compare_with_oracle(batch.x, out, res)
         bits.append(out.buffers.best_sim)
     assert torch.equal(bits[0], bits[2]) and torch.equal(bits[1], bits[2])
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype", [
+    (3, 40, 2, 14, 1024, 1, "bf16"),
+    (2, 60, 2, 16, 1024, 2, "bf16"),
+    (5, 40, 4, 13, 1056, 1, "f32"),
+])
+def test_sums_of_one_run_stand_with_the_frame_sums(B, F, H, W, C, r, dtype):
+    """Many frames of few tokens, whose sums find no room beside the products; an unclear clip among them."""
+    p = params(B, F, H, W, C, _torch(dtype), r)
+    plan = walk_plan(p, F, True)
+    assert search_guesses(p, 1) == 0 and plan.lsegs * plan.ysegs == 1
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, r=r, max_offset=min(max(r, 1), 2), sigma=1.2,
+                                       clean_sigma=0.1, dtype=dtype)
+    batch, res, want = _mixed(cfg, 5600 + F, (), (1,))
+    assert _kinds(batch.x, res.anchor_index) == want
+    for mode in (1, -1):
+        _, out = run_gpu(batch.x, r, cfg.t[0], speculation=mode)
+        compare_with_oracle(batch.x, out, res)

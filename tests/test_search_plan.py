@@ -112,3 +112,28 @@ def test_default_frame_counts_of_the_guess():
 ])
 def test_guess_where_it_pays(B, F, H, W, C, r, taken):
     assert (search_guesses(params(B, F, H, W, C, BF, r), 0) >= 0) == taken
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype", [
+    (33, 40, 2, 14, 1024, 1, BF),             # many frames of few tokens: no room for sums beside the products
+    (2, 300, 2, 16, 1024, 2, BF),
+    (70, 60, 1, 28, 1152, 1, BF),
+    (3, 64, 16, 16, 1056, 1, F32),            # no room for the sums of two runs
+    (5, 40, 4, 13, 1056, 1, F32),
+])
+def test_the_guess_finds_room_for_its_sums(B, F, H, W, C, r, dtype):
+    p = params(B, F, H, W, C, dtype, r)
+    assert search_walks(p) and search_guesses(p, 1) == 0
+
+
+def test_guess_is_available_wherever_such_shapes_walk():
+    rng = random.Random(9)
+    for _ in range(3000):
+        B, F = rng.choice([1, 3, 16, 70]), rng.choice([2, 5, 12, 40, 64, 100, 300])
+        H, W = rng.randint(1, 40), rng.choice([12, 13, 14, 16, 16, 24, 30, 32, 48, 64])
+        C, r = rng.choice([1024, 1152, 2048, 2176, 4096, 4224]), rng.choice([0, 1, 2])
+        p = params(B, F, H, W, C, BF, r)
+        strips = H * W // 32 if (W == 16 and H % 4 == 0) or (W == 32 and H % 2 == 0) else (
+            (H + 1) // 2 if W <= 16 else H * (((W + 15) // 16 + 1) // 2))
+        if search_walks(p) and 10 * H * W >= 7 * 32 * strips:
+            assert search_guesses(p, 1) == 0, (B, F, H, W, C, r)
