@@ -83,7 +83,8 @@ __device__ __forceinline__ void wait_loads()
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 // 64 lanes x 16 bytes from base + off (per lane) to LDS at lds + 16 * lane.  No register receives the data; the
-// ring's readers wait on vmcnt.
+// ring's readers wait on vmcnt.  m0 holds the LDS address; it is a reserved register that the compiler sets right before
+// each use of its own and keeps nothing in, so it need not (and, being reserved, cannot) be named as clobbered.
 template <bool STREAM>
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint32_t lds)
 {

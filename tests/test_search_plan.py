@@ -116,7 +116,7 @@ def test_guess_where_it_pays(B, F, H, W, C, r, taken):
 
 @pytest.mark.parametrize("B,F,H,W,C,r,dtype", [
     (33, 40, 2, 14, 1024, 1, BF),             # many frames of few tokens: no room for sums beside the products
-    (2, 300, 2, 16, 1024, 2, BF),
+    (2, 300, 2, 16, 1024, 1, BF),
     (70, 60, 1, 28, 1152, 1, BF),
     (3, 64, 16, 16, 1056, 1, F32),            # no room for the sums of two runs
     (5, 40, 4, 13, 1056, 1, F32),
@@ -137,3 +137,20 @@ def test_guess_is_available_wherever_such_shapes_walk():
             (H + 1) // 2 if W <= 16 else H * (((W + 15) // 16 + 1) // 2))
         if search_walks(p) and 10 * H * W >= 7 * 32 * strips:
             assert search_guesses(p, 1) == 0, (B, F, H, W, C, r)
+
+
+@pytest.mark.parametrize("B,F,H,W,C,segment,walks", [
+    # 5x5 window: time of the other search, time of the walk, us
+    (64, 40, 2, 16, 1024, True, False),       # 66 / 88
+    (64, 40, 2, 12, 1024, False, False),      # 123 / 140 (tied)
+    (32, 24, 2, 12, 1152, True, False),       # 37 / 42
+    (32, 24, 2, 8, 1152, True, True),         # 37 / 34
+    (64, 24, 2, 14, 1536, True, False),       # 61 / 69
+    (64, 8, 2, 16, 1536, False, True),        # 103 / 100 (tied)
+    (32, 8, 2, 16, 2048, True, True),         # 40 / 30
+    (1, 10, 48, 16, 2048, False, False),      # 41 / 48.5
+    (1, 10, 64, 16, 1536, True, False),       # 30 / 33
+    (4, 5, 88, 16, 1280, False, True),        # 75 / 65
+])
+def test_lines_of_the_5x5_window(B, F, H, W, C, segment, walks):
+    assert search_walks(params(B, F, H, W, C, BF, 2), segment) == walks
