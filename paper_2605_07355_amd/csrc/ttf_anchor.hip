@@ -418,8 +418,6 @@ __global__ __launch_bounds__(256) void k_anchor_norms(const T* __restrict__ x, c
     if (lane == 0) anchor_inv[(size_t)b * N + j] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
 }
 
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
 // Matrix-core path.  One workgroup (8 waves) per anchor tile of 16 tokens: picks the anchor,
 // writes the anchor-frame rows of the per-token outputs (never fused, all keep bits set), reads
 // the tile once with coalesced loads (lane l: chunk l%4 of token l/4), accumulates squared
@@ -537,19 +535,6 @@ __global__ __launch_bounds__(512) void k_guess_pick(const float* __restrict__ gu
         o[1] = trusted ? 1 : 0;
         o[2] = o[3] = 0;
     }
-}
-
-// The three bf16 pieces of two fp32 values, each pair packed into one 32-bit word: hi = bf16(v),
-// mid = bf16(v - hi), lo = bf16(v - hi - mid), round to nearest even.  Both subtractions are exact in
-// fp32, so hi + mid + lo carries 24 significant bits of v.
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
-{
-    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-    const float ra = a - __builtin_bit_cast(float, hi << 16), rb = b - __builtin_bit_cast(float, hi & 0xffff0000u);
-    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
-    const float sa = ra - __builtin_bit_cast(float, mid << 16), sb = rb - __builtin_bit_cast(float, mid & 0xffff0000u);
-    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
 }
 
 // Matrix-core path for fp32 tokens.  As k_anchor_prepare, but the anchor frame is stored as three

@@ -56,6 +56,21 @@ struct RowVec {
     }
 };
 
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+
+// The three bf16 pieces of two fp32 values, each pair packed into one 32-bit word: hi = bf16(v),
+// mid = bf16(v - hi), lo = bf16(v - hi - mid), round to nearest even.  Both subtractions are exact in
+// fp32, so hi + mid + lo carries 24 significant bits of v.
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    const float ra = a - __builtin_bit_cast(float, hi << 16), rb = b - __builtin_bit_cast(float, hi & 0xffff0000u);
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
+    const float sa = ra - __builtin_bit_cast(float, mid << 16), sb = rb - __builtin_bit_cast(float, mid & 0xffff0000u);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
+}
+
 // Bit-exact copy of one token row by one wavefront.  U = bytes moved per lane per step: 16 (row
 // bytes % 16 == 0, both addresses 16-byte aligned), 4 or 2.
 template <int U, bool STREAM = true>

@@ -134,7 +134,6 @@ __global__ __launch_bounds__(1024) void k_search_generic(
 
 // acc + sum over the 16 bytes of a[i]*b[i]: four packed dot products for bf16 (exact products,
 // fp32 accumulation), four FMAs for fp32.
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 template <typename T>
 __device__ __forceinline__ float dot16(u32x4 a, u32x4 b, float acc)
 {

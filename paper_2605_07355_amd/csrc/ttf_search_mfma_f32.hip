@@ -29,19 +29,6 @@
 namespace ttf {
 namespace {
 
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-// hi / mid / lo bf16 pieces of two fp32 values, each pair packed into one word (round to nearest even;
-// both subtractions are exact in fp32)
-__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
-{
-    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-    const float ra = a - __builtin_bit_cast(float, hi << 16), rb = b - __builtin_bit_cast(float, hi & 0xffff0000u);
-    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
-    const float sa = ra - __builtin_bit_cast(float, mid << 16), sb = rb - __builtin_bit_cast(float, mid & 0xffff0000u);
-    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
-}
-
 // PAD: grids that are not exactly 16*CT wide or whose height leaves partial strips (see finish_tile).
 // ALL: tied-batch mode, every in-window cosine is stored instead of the arg max.
 // (Two workgroups per CU wherever two double buffers of anchor planes fit the 160 KiB of LDS; the 5x5

@@ -94,17 +94,6 @@ __device__ __forceinline__ void load_to_lds(const char* base, uint32_t off, uint
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
 
-// The three bf16 pieces of two fp32 values, each pair packed into one word: hi = bf16(v), mid = bf16(v - hi), lo =
-// bf16(v - hi - mid), round to nearest even; both subtractions are exact.
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo)
-{
-    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
-    const float ra = a - __builtin_bit_cast(float, hi << 16), rb = b - __builtin_bit_cast(float, hi & 0xffff0000u);
-    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
-    const float sa = ra - __builtin_bit_cast(float, mid << 16), sb = rb - __builtin_bit_cast(float, mid & 0xffff0000u);
-    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
-}
 // A value from another lane of the row of 16 (the DPP control names which).
 template <int DPP_CTRL>
 __device__ __forceinline__ float row_move(float v)
