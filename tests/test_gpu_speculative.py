@@ -2,9 +2,10 @@
 256 channels, the search runs against a trusted guess while adding up exact frame sums on the side,
 and the exact rule then confirms the guess or has the clip searched again.  Whatever happens on the
 way, every output must equal the oracle's.  The cases force the route on small inputs
-(ttf_set_speculation(1)) and cover: confirmed guesses on every kernel layout the route has,
-guesses that are trusted but wrong (second search), clips without a clear guess (two-pass
-fallback), and all three kinds in one batch.  Which kind a clip is, is recomputed here in NumPy
+(ttf_set_speculation(1)) and cover: confirmed guesses, guesses that are trusted but wrong (second
+search), clips without a clear guess (two-pass fallback), and all three kinds in one batch.  Where a
+problem is too small to walk (grids exactly 16 or 32 wide below the size lines) both settings take
+the two-pass route; test_gpu_walk_plans.py has the same kinds on shapes that are asserted to guess.  Which kind a clip is, is recomputed here in NumPy
 from the rule the header documents, so that each case is known to exercise its branch."""
 import numpy as np
 import pytest
@@ -56,32 +57,32 @@ def _check(batch, cfg, expect):
 
 SHAPES = [
     # B, F,  H,  W,  C,    r
-    (3, 6, 16, 16, 1024, 1),     # 4 waves x 2 K-steps per pass
-    (2, 9, 8, 32, 1024, 1),      # 32-wide grid
-    (2, 6, 16, 16, 1152, 1),     # 36 K-steps: one K-step per pass
+    (3, 6, 16, 16, 1024, 1),     # 16- and 32-wide grids: two-pass up to (2, 33, ...)
+    (2, 9, 8, 32, 1024, 1),
+    (2, 6, 16, 16, 1152, 1),     # 36 K-steps
     (1, 7, 16, 16, 2048, 0),     # 1x1 window
     (2, 6, 16, 16, 1024, 2),     # 5x5 window on a 16-wide grid
     (1, 9, 4, 32, 1024, 0),      # two keep words per frame on a 32-wide grid
-    (2, 8, 16, 32, 1024, 2),     # 5x5 window on a 32-wide grid (few workgroups: the plain kernel)
+    (2, 8, 16, 32, 1024, 2),     # 5x5 window on a 32-wide grid
     (1, 2, 16, 16, 1024, 1),     # one source frame
-    (2, 33, 16, 16, 1024, 1),    # 33 frames: nine groups of four, the last with one frame
-    (40, 13, 16, 16, 1024, 1),   # enough workgroups for the one-wave layout (6144 and more)
-    (2, 18, 64, 32, 1024, 2),    # 5x5 window on a large 32-wide input: the kernel with anchors shared through LDS
-    (1, 21, 128, 32, 1024, 2),   # the same kernel, 21 frames: five full groups of four and one frame
-    # grids that are not exactly 16 or 32 wide, or whose height leaves partial strips: padded tile rows
-    # (padding cells must not count in the strip sums)
-    (2, 6, 14, 14, 1024, 1),     # 14x14: two columns of padding per row, two frames per wave
-    (2, 11, 14, 14, 1024, 2),    # 5x5 window, ten source frames: three groups of four frames
-    (1, 7, 13, 16, 1024, 1),     # 16 wide, odd height: the last strip has one real row
-    (2, 6, 9, 24, 1024, 1),      # 24 wide: the second column tile half empty
+    (2, 33, 16, 16, 1024, 1),    # 33 frames
+    (40, 13, 16, 16, 1024, 1),   # 130 MiB: guessed
+    (2, 18, 64, 32, 1024, 2),    # 5x5 window on a large 32-wide input
+    (1, 21, 128, 32, 1024, 2),   # the same, 21 frames
+    # grids that are not exactly 16 or 32 wide, or of odd height
+    # (cells outside the grid must not count in the frame sums)
+    (2, 6, 14, 14, 1024, 1),     # 14x14: two columns of every tile are outside
+    (2, 11, 14, 14, 1024, 2),    # 5x5 window, patches that reach beyond the grid
+    (1, 7, 13, 16, 1024, 1),     # 16 wide, odd height
+    (2, 6, 9, 24, 1024, 1),      # 24 wide: two strips
     (1, 7, 11, 31, 2048, 2),     # 31 wide, 5x5 window
     (2, 6, 12, 12, 1152, 0),     # 1x1 window, 36 K-steps
-    (1, 10, 40, 30, 1024, 1),    # 40 strips per frame: the streaming strip reduction ahead of the scores
-    # wider than 32: strips of 32 columns with the neighbouring column tiles on both sides
-    (1, 6, 9, 48, 1024, 1),      # three column tiles: the second strip of a row is half padding
-    (2, 5, 6, 64, 1024, 2),      # whole tiles, 5x5 window
-    (1, 7, 5, 100, 2048, 0),     # seven column tiles, 1x1 window
-    (1, 6, 7, 45, 1024, 1),      # the emptiest rows the route takes (45 of 64 strip cells)
+    (1, 10, 40, 30, 1024, 1),    # sums in many runs of the grid
+    # wider than 32
+    (1, 6, 9, 48, 1024, 1),      # four strips
+    (2, 5, 6, 64, 1024, 2),      # 5x5 window
+    (1, 7, 5, 100, 2048, 0),     # 1x1 window
+    (1, 6, 7, 45, 1024, 1),      # the emptiest rows the route takes (45 of 64 cells)
 ]
 
 

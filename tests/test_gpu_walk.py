@@ -1,6 +1,7 @@
 """GPU parity of the search whose workgroups walk whole frames (bf16, C >= 1024: grids that are not whole 16-
-or 32-wide tiles take it at every size; fp32): the ends of its column strips, patches, channel shares and frame
-groups, as a pass on both anchor routes, as a segment and as a tied batch."""
+or 32-wide tiles take it at every size; fp32): the ends of its column strips, patches and channel shares, as a
+pass (on both anchor routes where the guess is available), as a segment and as a tied batch.  Most problems this small
+are dealt one frame to a workgroup; several frames a workgroup, asserted, are in test_gpu_walk_plans.py."""
 import numpy as np
 import pytest
 import torch
@@ -19,11 +20,11 @@ SHAPES = [
     (1, 4, 5, 17, 1024, 1),      # two strips, eight and nine cells wide
     (2, 5, 3, 30, 1088, 1),      # three strips; 17 groups of 64 channels over eight waves
     (1, 3, 1, 16, 2112, 0),      # one grid row; two shares of the channels, 66 K-steps
-    (1, 36, 2, 14, 1024, 1),     # more frames than a workgroup takes
+    (1, 36, 2, 14, 1024, 1),     # many frames of two rows; also beside a guess
     (1, 6, 10, 18, 4160, 1),     # three shares
     (1, 9, 7, 40, 1024, 0),      # three strips without a margin
     (2, 3, 6, 13, 1024, 2),      # patches that end inside the grid's last rows and columns
-    (1, 5, 9, 33, 2176, 2),      # patches, two shares, frame groups of two
+    (1, 5, 9, 33, 2176, 2),      # patches, two shares
     (1, 2, 1, 3, 1024, 2),       # a grid smaller than the window
     (1, 7, 30, 12, 1152, 2),     # 18 groups over eight waves
 ]
@@ -61,7 +62,7 @@ def test_walking_search_tied(B, F, H, W, C, r):
 
 F32_SHAPES = [
     # B, F,  H,  W,  C,    r   (enough work for the matrix cores, see ttf_search_route)
-    (4, 18, 16, 16, 1024, 1),    # a whole tile per row; three frame groups beside a guess
+    (4, 18, 16, 16, 1024, 1),    # a whole tile per row
     (5, 13, 14, 14, 1056, 1),    # 33 groups of 32 channels over two shares
     (6, 9, 9, 31, 1024, 0),      # two strips, 1x1 window
     (3, 8, 16, 32, 2048, 1),     # three strips

@@ -8,7 +8,8 @@ from workloads import CONFIGS, make_clip_batch
 
 from helpers import compare_with_oracle, run_gpu
 from plans import matrix_cores, params, search_guesses, search_walks, walk_plan
-from test_gpu_parity import _prepared
+from test_gpu_nonfinite import test_nonfinite_entries as nonfinite_entries
+from test_gpu_parity import _prepared, test_graph_capture_and_replay as graph_capture_and_replay
 from test_gpu_speculative import TRUST_GAP, anchor_scores, guess_channels
 from workloads.ttf_gen import bf16_bits_to_f32
 
@@ -161,6 +162,8 @@ def _mixed(cfg, seed, refuted, unclear):
     (70, 9, 2, 14, 1024, 2, "bf16", 2, (3, 66), (64,)),              # patches; the last group holds one frame
     (70, 10, 3, 25, 1024, 0, "bf16", 4, (69,), (0, 68)),             # two strips
     (40, 25, 6, 14, 1024, 1, "bf16", 3, (), tuple(range(40))),       # no clear guess: the second walk is dealt as without one
+    (33, 11, 16, 16, 1024, 1, "bf16", 4, (0, 20), (32,)),            # grids exactly 16 and 32 wide
+    (20, 11, 8, 32, 2048, 1, "bf16", 3, (19,), (0, 7)),
     (70, 13, 2, 14, 1024, 1, "f32", 5, (0, 40), (2, 69)),            # groups of 5, 5 and 3
     (70, 23, 2, 14, 1024, 0, "f32", 8, (12, 64), (63,)),             # groups of 8, 8 and 7
 ])
@@ -211,3 +214,26 @@ def test_sums_of_one_run_stand_with_the_frame_sums(B, F, H, W, C, r, dtype):
     for mode in (1, -1):
         _, out = run_gpu(batch.x, r, cfg.t[0], speculation=mode)
         compare_with_oracle(batch.x, out, res)
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,spec", [
+    (8, 6, 14, 14, 1056, 1, "f32", None),
+    (8, 6, 14, 14, 1056, 0, "f32", 1),
+    (6, 5, 9, 31, 1024, 1, "f32", 1),          # two strips
+    (2, 5, 9, 33, 2176, 2, "bf16", None),      # patches, two shares
+])
+@pytest.mark.parametrize("anchor", [1, "auto"])
+def test_nonfinite_values_in_the_walk(oracle, B, F, H, W, C, r, dtype, spec, anchor):
+    p = params(B, F, H, W, C, _torch(dtype), r)
+    assert search_walks(p) and (spec is None or search_guesses(p, spec) == 0)
+    nonfinite_entries(oracle, "walk", B, F, H, W, C, dtype, r, spec, anchor)
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,spec", [
+    (8, 6, 14, 14, 1056, 1, "f32", 1),
+    (70, 10, 2, 14, 1024, 1, "bf16", 1),       # four frames a workgroup, more clips than the second walk picks in its prologue
+    (8, 16, 16, 16, 4096, 1, "bf16", None),    # 256 MiB: guesses that may be dropped
+])
+def test_walk_in_a_graph(B, F, H, W, C, r, dtype, spec):
+    assert search_guesses(params(B, F, H, W, C, _torch(dtype), r), spec or 0) >= 0
+    graph_capture_and_replay("walk", B, F, H, W, C, dtype, r, spec)
