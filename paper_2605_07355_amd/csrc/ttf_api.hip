@@ -140,7 +140,9 @@ bool search_walks(const ttf_params& p, bool external_anchor)
 // clear, 195 two-pass, 290 with the guesses, 226 with them dropped; B16 F32 16x16 C4096, 4 of 16, 561 / 683 / 591.
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20, kSpeculationMinSaved = 224ull << 20;
 constexpr int kSpeculationMinFrames = 12, kSpeculationMaxFrames = 64;
-constexpr double kGuessOverhead = 20.0;                      // us
+// us that the model has to save (saved by the model / measured, fp32: B7 F33 32x16 C1088 16 / 11, B16 F32 16x16 C2048 83 / 74;
+// bf16: B2 F64 32x32 C1024 23 / -20, B16 F13 16x16 C4096 33 / 30)
+constexpr double kGuessOverhead = 20.0, kGuessOverheadF32 = 10.0;
 
 // Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
 // then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have
@@ -162,7 +164,7 @@ static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mo
     min_trusted = 0;                                         // (forced: however few)
     if (mode == 0) {
         const GuessCost cost = guess_cost(p, with_sums, plan);
-        if (cost.saves < kGuessOverhead) return false;
+        if (cost.saves < (p.dtype == TTF_F32 ? kGuessOverheadF32 : kGuessOverhead)) return false;
         min_trusted = cost.min_trusted;
     }
     plan = with_sums;

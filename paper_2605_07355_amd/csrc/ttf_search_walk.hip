@@ -789,14 +789,14 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 // 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16 walks
 // 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
 // The times are those of the model of walk_plan(), a tile of 2048 (fp32 1024) channels 2.6 us (fp32 and 5x5 window 3.6; with sums
-// 4 to 30 % more), a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
+// 4 to 20 % more), a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
 // of a frame.  Measured ratio of taking the guesses to dropping them / the model's: B16 F32 16x16 C4096, 12 of 16 clear, 1.07 / 1.09;
 // B8 F20 24x24 C2048, 6 of 8, 1.27 / 1.5; B128 F16 16x16 C2048, 124 of 128, 0.88 / 0.81; B32 F20 24x24 C2048, 31 of 32, 0.89 / 0.92.
 GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again)
 {
     const bool f32 = p.dtype == TTF_F32;
     const double tile = (f32 || p.r == 2 ? 3.6 : 2.6) * p.C / (first.nk * (f32 ? 1024.0 : 2048.0));
-    const double with_sums = f32 ? 1.3 : (p.r == 2 ? 1.1 : 1.04);
+    const double with_sums = f32 ? 1.2 : (p.r == 2 ? 1.1 : 1.04);
     const double clip = (double)p.F * p.H * p.W * p.C * (f32 ? 4 : 2) / 6.6e6;
     const double units = (double)first.nk * first.groups * first.lsegs * first.ysegs;
     auto sums = [&](int n) {

@@ -102,16 +102,18 @@ def test_default_frame_counts_of_the_guess():
     assert took == list(range(12, 65))        # F 12: 203 us two-pass, 163 with the guesses; F 15: 242 / 195
 
 
-@pytest.mark.parametrize("B,F,H,W,C,r,taken", [
-    (2, 64, 32, 32, 1024, 1, False),          # all clear: 157 us two-pass, 176 with the guesses
-    (4, 40, 32, 26, 1536, 2, False),          # 205 / 265
-    (8, 12, 32, 32, 2048, 2, False),          # 197 / 224
-    (4, 64, 32, 32, 4096, 2, True),           # 986 / 816
-    (16, 12, 16, 16, 4096, 1, True),          # 203 / 163
-    (16, 64, 16, 16, 1024, 1, True),          # 248 / 233
+@pytest.mark.parametrize("B,F,H,W,C,r,taken,dtype", [
+    (2, 64, 32, 32, 1024, 1, False, BF),      # all clear: 157 us two-pass, 176 with the guesses
+    (4, 40, 32, 26, 1536, 2, False, BF),      # 205 / 265
+    (8, 12, 32, 32, 2048, 2, False, BF),      # 197 / 224
+    (4, 64, 32, 32, 4096, 2, True, BF),       # 986 / 816
+    (16, 12, 16, 16, 4096, 1, True, BF),      # 203 / 163
+    (16, 64, 16, 16, 1024, 1, True, BF),      # 248 / 233
+    (7, 33, 32, 16, 1088, 1, True, F32),      # 323 / 312
+    (16, 32, 16, 16, 2048, 1, True, F32),     # 470 / 396
 ])
-def test_guess_where_it_pays(B, F, H, W, C, r, taken):
-    assert (search_guesses(params(B, F, H, W, C, BF, r), 0) >= 0) == taken
+def test_guess_where_it_pays(B, F, H, W, C, r, taken, dtype):
+    assert (search_guesses(params(B, F, H, W, C, dtype, r), 0) >= 0) == taken
 
 
 @pytest.mark.parametrize("B,F,H,W,C,r,dtype", [
