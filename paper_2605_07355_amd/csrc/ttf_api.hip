@@ -90,6 +90,10 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 // fp32 tokens, windows up to 3x3 (90 shapes): against the matrix-core search 1.02 to 2.8 from C 1024 on (B3 F7 16x21 C1024
 //   73 / 50 us, B2 F21 16x13 C4096 264 / 94, B16 F14 16x16 C3072 387 / 314), 0.84 to 1.57 below; against the wave-per-token
 //   search of small problems from 32 MiB and C 768 on 0.97 to 1.9 (B1 F12 16x16 C3072 64 / 48), below 32 MiB 0.6 to 1.4.
+//   Rows of 32 cells are three strips of 11: arithmetic for 33 of every 48 cells only.  From 480 MiB on that bounds them where the
+//   32-channel groups do not divide over the waves either (B1 F33 64x32 C3424, 107 groups over 32 waves, 503 / 539; B8 F33 32x32 C832
+//   526 / 551; B8 F17 16x32 C3200 tied 519 / 540); where they do 0.99 to 1.13 (B1 F73 32x32 C3584 583 / 518), below 480 MiB 0.93 to 2.3
+//   (B2 F17 32x32 C2560 230 / 246, segment B2 F33 16x32 C3104 237 / 199).
 static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool external_anchor, WalkPlan& plan,
                      WalkScratch& scratch)
 {
@@ -97,6 +101,9 @@ static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool ex
     const size_t mib = ((size_t)p.B * frames * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4)) >> 20;
     if (p.dtype == TTF_F32) {
         if (forced_general() || !((mfma && p.C >= 1024) || (p.C >= 768 && mib >= 32))) return false;
+        const int groups = p.C / 32, waves = 8 * ((groups + 31) / 32);
+        if (p.W == 32 && p.r == 1 && mfma_f32_aligned(p) && mib >= 480 && 100 * groups < 85 * waves * ((groups + waves - 1) / waves))
+            return false;
     } else {
         if (!mfma || p.C < 1024) return false;
         if (mfma_search_supported(p) &&

@@ -156,3 +156,16 @@ def test_guess_is_available_wherever_such_shapes_walk():
 ])
 def test_lines_of_the_5x5_window(B, F, H, W, C, segment, walks):
     assert search_walks(params(B, F, H, W, C, BF, 2), segment) == walks
+
+
+@pytest.mark.parametrize("B,F,H,C,walks", [
+    # fp32 on rows of 32 cells: time of the other search, time of the walk, us
+    (1, 33, 64, 3424, False),                 # 503 / 539
+    (8, 33, 32, 832, False),                  # 526 / 551
+    (1, 73, 32, 3584, True),                  # 583 / 518
+    (2, 34, 16, 3104, True),                  # 237 / 199 (segment)
+    (4, 48, 32, 1024, True),                  # 473 / 444 (tied)
+    (1, 9, 32, 3008, True),                   # 176 / 95
+])
+def test_fp32_rows_of_32_cells(B, F, H, C, walks):
+    assert search_walks(params(B, F, H, 32, C, F32, 1)) == walks
