@@ -133,23 +133,18 @@ bool search_walks(const ttf_params& p, bool external_anchor)
 }
 
 // Speculative anchor: -1 never, 1 whenever the shape allows, 0 where it is expected to pay (two-pass / with the guess below, us):
-//  * inputs of 256 MiB and more, 224 MiB and more without the guess channels: below that the launches eat the gain (B2 F64
-//    32x32 C1024, 256 MiB, 157 / 176; B2 F128 16x16 C2048 136 / 145; B16 F64 16x16 C1024 248 / 233);
+//  * inputs of 256 MiB and more;
 //  * clips of 12 to 64 frames.  Shorter ones clear the trust gap too seldom (B32 F4 16x16 C4096 150 / 177, none of 32;
 //    B16 F12 203 / 163 and B16 F15 242 / 195, all of 16).  Longer ones of one scene gain or lose (B2 F100 16x16 C4096 r 0 202 / 175, B7
 //    F79 16x16 C2816 351 / 323; B1 F92 32x25 C2048 158 / 174, B2 F70 32x32 C2048 r 2 274 / 325), of several scenes they
 //    lose (B7 F79 450 / 523, B3 F84 32x26 C1536 r 2 375 / 604), and neither is known before the call;
-//  * where the deals of the two walks let it gain, see guess_cost(): B4 F40 32x26 C1536 r 2, 390 MiB, 205 / 265; B8 F12 32x32
-//    C2048 r 2 197 / 224; B4 F64 32x32 C4096 r 2 986 / 816;
+//  * where the model of the two ways, guess_cost(), has it save anything;
 //  * fp32 on grids of one strip: with sums it is bound by its arithmetic, which strips of 11 cells do not fill (B6 F32
 //    16x32 C2048 449 / 478, B16 F32 16x16 C4096 944 / 749).
 // Where too few clips of a batch have a clear guess, all are dropped on the device (min_trusted): B8 F20 24x24 C2048, 6 of 8
 // clear, 195 two-pass, 290 with the guesses, 226 with them dropped; B16 F32 16x16 C4096, 4 of 16, 561 / 683 / 591.
-constexpr unsigned long long kSpeculationMinBytes = 256ull << 20, kSpeculationMinSaved = 224ull << 20;
+constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
 constexpr int kSpeculationMinFrames = 12, kSpeculationMaxFrames = 64;
-// us that the model has to save (saved by the model / measured, fp32: B7 F33 32x16 C1088 16 / 11, B16 F32 16x16 C2048 83 / 74;
-// bf16: B2 F64 32x32 C1024 23 / -20, B16 F13 16x16 C4096 33 / 30)
-constexpr double kGuessOverhead = 20.0, kGuessOverheadF32 = 10.0;
 
 // Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
 // then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have
@@ -161,7 +156,7 @@ static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mo
     if (p.anchor_mode != TTF_ANCHOR_AUTO || !mfma || !speculation_possible(p) || mode < 0) return false;
     if (mode == 0) {
         const unsigned long long bytes = (unsigned long long)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2ull : 4ull);
-        if (bytes < kSpeculationMinBytes || bytes - bytes / p.C * kGuessChannels < kSpeculationMinSaved || p.F < kSpeculationMinFrames || p.F > kSpeculationMaxFrames ||
+        if (bytes < kSpeculationMinBytes || p.F < kSpeculationMinFrames || p.F > kSpeculationMaxFrames ||
             (p.dtype == TTF_F32 && p.W > 16))
             return false;
     }
@@ -171,7 +166,7 @@ static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mo
     min_trusted = 0;                                         // (forced: however few)
     if (mode == 0) {
         const GuessCost cost = guess_cost(p, with_sums, plan);
-        if (cost.saves < (p.dtype == TTF_F32 ? kGuessOverheadF32 : kGuessOverhead)) return false;
+        if (cost.saves < 0.0) return false;
         min_trusted = cost.min_trusted;
     }
     plan = with_sums;

@@ -208,8 +208,7 @@ struct WalkPlan {
 struct WalkDeal {
     int lsegs, ysegs, groups, nf;   // as in WalkPlan
 };
-// The guessed anchor: microseconds that it saves where every clip has a clear guess (of about 20 that it costs in
-// launches), and how many clips have to have one for any to be taken.
+// The guessed anchor: microseconds that it saves where every clip has a clear guess, and how many clips have to have one for any to be taken.
 struct GuessCost {
     double saves;
     int min_trusted;

@@ -788,15 +788,20 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 // their share of a read and costs two searches and a pass for frame sums that may each fill part of the chip.  B16 F32
 // 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16 walks
 // 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
-// The times are those of the model of walk_plan(), a tile of 2048 (fp32 1024) channels 2.6 us (fp32 and 5x5 window 3.6; with sums
-// 4 to 20 % more), a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
+// The times are those of the model of walk_plan(), a tile of 2048 (fp32 1024) channels 2.5 us (fp32 3.0, 5x5 window 2.8; with sums
+// 1.04, 1.2 and 1.0 of that), the guess channels 5.5 TB/s or 4 us for what a block has in flight, a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
 // of a frame.  Measured ratio of taking the guesses to dropping them / the model's: B16 F32 16x16 C4096, 12 of 16 clear, 1.07 / 1.09;
 // B8 F20 24x24 C2048, 6 of 8, 1.27 / 1.5; B128 F16 16x16 C2048, 124 of 128, 0.88 / 0.81; B32 F20 24x24 C2048, 31 of 32, 0.89 / 0.92.
+// The launches beside them, and what the model leaves out of the 5x5 window, of few channels and of sums in many runs of the
+// grid, are 10 to 70 us, fitted to 100 shapes of 256 MiB to 2 GiB: saved by the model / measured B16 F32 16x16 C4096 113 / 115, B16
+// F64 16x16 C1024 12 / 15, B2 F64 32x32 C1024 -17 / -20, B23 F14 32x16 C2048 60 / 50, B9 F24 24x14 C2048 8 / 8, B5 F40 12x48 C2304 5 / -4;
+// 5x5 window B4 F64 32x32 C4096 117 / 163, B4 F40 32x26 C1536 -65 / -60, B3 F64 27x16 C2304 -31 / -11; fp32 B16 F32 16x16 C4096 185 /
+// 198, B7 F33 32x16 C1088 3 / 11; many runs B1 F32 200x16 C4096 53 / 48, B1 F64 64x64 C1024 -16 / -12.
 GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again)
 {
     const bool f32 = p.dtype == TTF_F32;
-    const double tile = (f32 || p.r == 2 ? 3.6 : 2.6) * p.C / (first.nk * (f32 ? 1024.0 : 2048.0));
-    const double with_sums = f32 ? 1.2 : (p.r == 2 ? 1.1 : 1.04);
+    const double tile = (f32 ? 3.0 : (p.r == 2 ? 2.8 : 2.5)) * p.C / (first.nk * (f32 ? 1024.0 : 2048.0));
+    const double with_sums = f32 ? 1.2 : (p.r == 2 ? 1.0 : 1.04);
     const double clip = (double)p.F * p.H * p.W * p.C * (f32 ? 4 : 2) / 6.6e6;
     const double units = (double)first.nk * first.groups * first.lsegs * first.ysegs;
     auto sums = [&](int n) {
@@ -806,7 +811,11 @@ GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan&
     auto walk = [&](int n) { return tile * first.tiles * deal_rounds(units * n); };
     const double without = p.B * clip + tile * again.tiles * deal_rounds((double)p.B * again.nk * again.groups * again.lsegs * again.ysegs);
     GuessCost cost{};
-    cost.saves = without - with_sums * walk(p.B) - p.B * clip * 1.2 * kGuessChannels / p.C;
+    const int in_flight = f32 ? 32 : 64, rows = (p.H * p.W + guess_parts(p) - 1) / guess_parts(p);   // of a block of k_guess_sums
+    const double guess = std::max(p.B * clip * 1.2 * kGuessChannels / p.C, 4.0 * ((rows + in_flight - 1) / in_flight));
+    const double launches = f32 ? 10.0 : 20.0 + (p.F > 32 ? 8.0 : 0.0) + (p.C < 1536 ? 8.0 : 0.0) + (p.r == 2 ? 25.0 : 0.0) +
+                                             (first.lsegs * first.ysegs > 8 ? 20.0 : 0.0);
+    cost.saves = without - with_sums * walk(p.B) - guess - launches;
     cost.min_trusted = p.B + 1;
     const int step = (p.B + 63) / 64;                        // (no more than 64 of the counts are looked at)
     for (int n = p.B; n > 0; n -= step) {
