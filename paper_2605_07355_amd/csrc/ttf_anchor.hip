@@ -124,9 +124,9 @@ __global__ __launch_bounds__(256) void k_frame_sums_slab(const T* __restrict__ x
 // each of sixteen interleaved groups, groups added in order), then for every frame the slice's share
 // of <frame_sum_k, g> and |frame_sum_k|^2, and the slice's share of |g|^2.  The cosine of the
 // anchor rule is assembled from these shares by pick_anchor().
-// STRIPS: a frame sum is not stored as such but as `strips` partial sums (one per 32-token strip, as
-// the window search writes them: fs[k][strip][C]); they are added in ascending strip order (fp32)
-// as they are loaded.  UN: frames in flight per wave.
+// STRIPS: a frame sum is not stored as such but as `strips` partial sums (one per run of the grid, as the
+// walking search writes them, or of rows, as k_frame_sums: fs[k][strip][C]); they are added in ascending
+// order (fp32) as they are loaded.  UN: frames in flight per wave.
 template <int UN, bool STRIPS>
 __device__ __forceinline__ void anchor_partials_body(const float* __restrict__ fs, double* __restrict__ score_part,
                                                      double* __restrict__ clip_part, size_t b, int slice, int fg,
@@ -233,8 +233,8 @@ __device__ __forceinline__ void anchor_partials_body(const float* __restrict__ f
     }
 }
 
-// MIXED: clips with a trusted anchor guess (spec[b][1]) have their frame sums as strip sums
-// (strip_sum [B,F,strips,C]), the other clips in frame_sum [B,F,C]; otherwise every clip in frame_sum, or
+// MIXED: clips with a trusted anchor guess (spec[b][1]) have their frame sums in parts
+// (strip_sum [B,F,strips,C], frame_sum itself for a single part), the other clips in frame_sum [B,F,C]; otherwise every clip in frame_sum, or
 // (spec null, strip_sum given) every clip as the shares that k_frame_sums leaves in strip_sum.
 template <bool MIXED>
 __global__ __launch_bounds__(1024) void k_anchor_partials(const float* __restrict__ frame_sum,
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(1024) void k_anchor_partials(const float* __restric
                                        1, gsh);
 }
 
-// Strip sums -> frame sums for the clips with a trusted anchor guess (grids with many strips per
+// Partial sums -> frame sums for the clips with a trusted anchor guess (grids in many runs per
 // frame: a plain streaming reduction ahead of k_anchor_partials<false> keeps the chip full, where the
 // fused form has too few blocks).  Block (frame, 1024-channel slab): thread t adds its four channels
 // over the strips in ascending order, eight loads in flight.

@@ -72,7 +72,7 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
     return launch_window_search_generic(p, x, ext_anchor, w, anchor_index, fuse_map, best_sim, best_idx, win_sim, s);
 }
 
-// Whether the search walks whole frames (ttf_search_walk.hip) where there is no speculation.  Its workgroups are few
+// Whether the search walks whole frames (ttf_search_walk.hip).  Its workgroups are few
 // and long, so it starts slower and streams faster; against the kernels above it also does without the launch that
 // copies the anchor frame, and adds the one that forms the similarities.  Where the lines lie (whole calls, bf16,
 // r 0..2, 130 random shapes; time of the kernels above over the walk's):

@@ -30,11 +30,11 @@
 //  * fp32 tokens: a group is one K-step, every value cut into three bf16 planes as it is used (the window holds the
 //    planes), six plane products per MFMA of the bf16 form.  Norms and sums are plain fp32: eight channels of a token in a
 //    lane, sums by exchanging halves inside a row of 16 lanes until two lanes hold one channel.  Bound by the
-//    arithmetic and its latency: B16 F32 16x16 C4096 (2 GiB) 380 us plain (452 for k_search_mfma_f32), 500 with sums, which
-//    save the 322 us of k_frame_sums_slab; eight frames a workgroup instead of four 522 -> 502.
+//    arithmetic and its latency: B16 F32 16x16 C4096 (2 GiB) 380 us plain (452 for k_search_mfma_f32), 487 with sums, which
+//    save the 322 us of k_frame_sums_slab; eight frames a workgroup instead of four 522 -> 502 when that was tried.
 // Kernel alone, bf16, against the kernels it replaces there: B16 F32 16x16 C4096 with sums 248 -> 180 us (5.9 TB/s of
-// tokens), 14x14 218 -> 147, B2 F256 16x16 C4096 189 -> 174 (162 behind frame sums that leave the Infinity Cache warm), B4
-// F64 32x32 C4096 r 2 with sums 596 -> 488.  With everything but the loads taken out the first runs no faster
+// tokens), 14x14 218 -> 152, B2 F256 16x16 C4096 189 -> 174 (162 behind frame sums that leave the Infinity Cache warm), B4
+// F64 32x32 C4096 r 2 with sums 596 -> 496.  With everything but the loads taken out the first runs no faster
 // (179), so it is the walk through memory that is left; of the last 64 us are the stores of the window products and
 // 60 the reduction (rows of 11 cells instead of patches: 575, twice the products and 1.5 times the tiles).
 // Tried: fragments read one group ahead (187 against 181), twice the groups in flight (no change).
