@@ -1,10 +1,11 @@
 // C ABI of the TTF library: argument checks, workspace carving, the launch sequence of
 // Section 3 (anchor selection -> window search + gate -> offsets -> row emission) and the
 // optional per-stage event timing.  Nothing here allocates device memory.
+#include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <atomic>
 #include <map>
 #include <mutex>
 #include <utility>
@@ -268,7 +269,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     if (ext_anchor && !aligned(ext_anchor, 16)) return TTF_ERR_UNSUPPORTED;
 
     ttf_params p = *params;
-    p.r = p.r > (p.H > p.W ? p.H : p.W) ? (p.H > p.W ? p.H : p.W) : p.r;   // beyond the grid = whole grid
+    p.r = std::min(p.r, std::max(p.H, p.W));                 // beyond the grid = whole grid
     Workspace w = carve(p, workspace);
     if (workspace_bytes < w.bytes) w = carve(p, workspace, false);
     if (workspace_bytes < w.bytes) return TTF_ERR_WORKSPACE_TOO_SMALL;
@@ -586,7 +587,8 @@ ttf_status ttf_search_route(const ttf_params* params, int* route)
     if (!route) return TTF_ERR_INVALID_ARG;
     const ttf_status st = check_params(params);
     if (st != TTF_OK) return st;
-    const ttf_params& p = *params;
+    ttf_params p = *params;
+    p.r = std::min(p.r, std::max(p.H, p.W));                 // (as ttf_compress)
     const bool mfma = use_mfma_path(p, true, false), walk = search_walks(p, false);
     *route = !mfma && !walk                 ? TTF_ROUTE_GENERAL
            : p.dtype == TTF_F32             ? TTF_ROUTE_MFMA_F32

@@ -183,3 +183,13 @@ def test_lines_of_the_5x5_window(B, F, H, W, C, segment, walks):
 ])
 def test_fp32_rows_of_32_cells(B, F, H, C, walks):
     assert search_walks(params(B, F, H, 32, C, F32, 1)) == walks
+
+
+@pytest.mark.parametrize("H,W,C,dtype,r,want", [
+    (2, 2, 1024, BF, 5, "mfma_bf16_padded"),  # a radius beyond the grid is the grid's own: 2
+    (1, 1, 256, BF, 9, "mfma_bf16_padded"),
+    (3, 2, 1024, BF, 5, "general"),           # 3
+])
+def test_route_of_a_radius_beyond_the_grid(H, W, C, dtype, r, want):
+    import paper_2605_07355_amd as ttf
+    assert ttf.ttf_search_route(2, 4, H, W, C, dtype, r=r) == ttf.ttf_search_route(2, 4, H, W, C, dtype, r=max(H, W)) == want
