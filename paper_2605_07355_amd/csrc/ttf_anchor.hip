@@ -234,8 +234,9 @@ __device__ __forceinline__ void anchor_partials_body(const float* __restrict__ f
 }
 
 // MIXED: clips with a trusted anchor guess (spec[b][1]) have their frame sums in parts
-// (strip_sum [B,F,strips,C], frame_sum itself for a single part), the other clips in frame_sum [B,F,C]; otherwise every clip in frame_sum, or
-// (spec null, strip_sum given) every clip as the shares that k_frame_sums leaves in strip_sum.
+// (strip_sum [B,F,strips,C], frame_sum itself for a single part), the other clips in frame_sum [B,F,C];
+// otherwise every clip in frame_sum, or (spec null, strip_sum given) every clip as the shares that
+// k_frame_sums leaves in strip_sum.
 template <bool MIXED>
 __global__ __launch_bounds__(1024) void k_anchor_partials(const float* __restrict__ frame_sum,
                                                          double* __restrict__ score_part,

@@ -161,7 +161,8 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     // The clips to search (mode 2: up to kPickClips, whose anchors the waves pick between them; more clips pick their
     // own below and leave where there is nothing to do), and how many units they make.
     bool guessed = A.mode != 2;
-    for (int b0 = 0; !guessed && b0 < A.B; b0 += 64) guessed = __ballot(b0 + lane < A.B && A.spec[4 * min(b0 + lane, A.B - 1) + 1] != 0) != 0;
+    for (int b0 = 0; !guessed && b0 < A.B; b0 += 64)
+        guessed = __ballot(b0 + lane < A.B && A.spec[4 * min(b0 + lane, A.B - 1) + 1] != 0) != 0;
     const WalkDeal deal = guessed ? A.deal : A.all;
     const int per_clip = deal.groups * deal.lsegs * deal.ysegs * A.nk;
     constexpr int kPickClips = 32;
@@ -242,9 +243,11 @@ __global__ __launch_bounds__(kWalkWaves * 64, 2) void k_search_walk(const WalkAr
     }
 
     // the unit's part of the grid: column strips line_lo .. line_hi-1, tiles step_lo .. step_hi-1 of each
-    const int line_lo = (int)((long long)A.lines * (seg / deal.ysegs) / deal.lsegs), line_hi = (int)((long long)A.lines * (seg / deal.ysegs + 1) / deal.lsegs);
+    const int line_lo = (int)((long long)A.lines * (seg / deal.ysegs) / deal.lsegs);
+    const int line_hi = (int)((long long)A.lines * (seg / deal.ysegs + 1) / deal.lsegs);
     const int all_steps = (H + STEP - 1) / STEP;
-    const int step_lo = (int)((long long)all_steps * (seg % deal.ysegs) / deal.ysegs), step_hi = (int)((long long)all_steps * (seg % deal.ysegs + 1) / deal.ysegs);
+    const int step_lo = (int)((long long)all_steps * (seg % deal.ysegs) / deal.ysegs);
+    const int step_hi = (int)((long long)all_steps * (seg % deal.ysegs + 1) / deal.ysegs);
     // first cell and width of a strip; rows of grids wider than 16 keep a margin of r for the window
     const int margin = PATCH || A.lines == 1 ? 0 : RAD;
     const int strip_w = W / A.lines, wide_strips = W % A.lines;      // (the first strips are a cell wider where need be)
@@ -786,17 +789,19 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 
 // What the guess saves where every clip has a clear one, and how many clips need one: beside unclear clips it saves
 // their share of a read and costs two searches and a pass for frame sums that may each fill part of the chip.  B16 F32
-// 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16 walks
-// 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
-// The times are those of the model of walk_plan(), a tile of 2048 (fp32 1024) channels 2.5 us (fp32 3.0, 5x5 window 2.8; with sums
-// 1.04, 1.2 and 1.0 of that), the guess channels 5.5 TB/s or 4 us for what a block has in flight, a pass for frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows
-// of a frame.  Measured ratio of taking the guesses to dropping them / the model's: B16 F32 16x16 C4096, 12 of 16 clear, 1.07 / 1.09;
-// B8 F20 24x24 C2048, 6 of 8, 1.27 / 1.5; B128 F16 16x16 C2048, 124 of 128, 0.88 / 0.81; B32 F20 24x24 C2048, 31 of 32, 0.89 / 0.92.
-// The launches beside them, and what the model leaves out of the 5x5 window, of few channels and of sums in many runs of the
-// grid, are 10 to 70 us, fitted to 100 shapes of 256 MiB to 2 GiB: saved by the model / measured B16 F32 16x16 C4096 113 / 115, B16
-// F64 16x16 C1024 12 / 15, B2 F64 32x32 C1024 -17 / -20, B23 F14 32x16 C2048 60 / 50, B9 F24 24x14 C2048 8 / 8, B5 F40 12x48 C2304 5 / -4;
-// 5x5 window B4 F64 32x32 C4096 117 / 163, B4 F40 32x26 C1536 -65 / -60, B3 F64 27x16 C2304 -31 / -11; fp32 B16 F32 16x16 C4096 185 /
-// 198, B7 F33 32x16 C1088 3 / 11; many runs B1 F32 200x16 C4096 53 / 48, B1 F64 64x64 C1024 -16 / -12.
+// 16x16 C4096: walk with sums 180 us where all guesses are clear, 164 + 155 for sums without; with 12 clear ones of 16
+// walks 151 + 114 and sums 84.  With fewer than min_trusted the guesses of all clips are dropped in the first walk.
+// The times are those of the model of walk_plan(): a tile of 2048 (fp32 1024) channels takes 2.5 us (fp32 3.0, 5x5 window
+// 2.8), with sums 1.04, 1.2 and 1.0 of that; the guess channels 5.5 TB/s, or 4 us for what a block has in flight; a pass for
+// frame sums 6.6 TB/s, or 0.8 (few blocks) to 2.6 us (one on every CU) for every eight rows of a frame.  Measured ratio of
+// taking the guesses to dropping them / the model's: B16 F32 16x16 C4096, 12 of 16 clear, 1.07 / 1.09; B8 F20 24x24 C2048,
+// 6 of 8, 1.27 / 1.5; B128 F16 16x16 C2048, 124 of 128, 0.88 / 0.81; B32 F20 24x24 C2048, 31 of 32, 0.89 / 0.92.
+// The launches beside them, and what the model leaves out of the 5x5 window, of few channels and of sums in many runs of
+// the grid, are 10 to 70 us, fitted to 100 shapes of 256 MiB to 2 GiB.  Saved by the model / measured: B16 F32 16x16 C4096
+// 113 / 115, B16 F64 16x16 C1024 12 / 15, B2 F64 32x32 C1024 -17 / -20, B23 F14 32x16 C2048 60 / 50, B9 F24 24x14 C2048 8 / 8,
+// B5 F40 12x48 C2304 5 / -4; 5x5 window B4 F64 32x32 C4096 117 / 163, B4 F40 32x26 C1536 -65 / -60, B3 F64 27x16 C2304 -31 / -11;
+// fp32 B16 F32 16x16 C4096 185 / 198, B7 F33 32x16 C1088 3 / 11; many runs B1 F32 200x16 C4096 53 / 48, B1 F64 64x64 C1024
+// -16 / -12.
 GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again)
 {
     const bool f32 = p.dtype == TTF_F32;
