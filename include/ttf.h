@@ -295,8 +295,9 @@ int ttf_last_hip_error(void);
  *                 strips (two rows each up to 16 columns, one up to 32: 12..16, 23..32, 45..64, ... columns; any
  *                 height); fp32 clips only while the guess, 1 to 8 KiB a frame, fits beside the window products
  *                 (a few frames fewer than walk; many fewer on grids of some dozen tokens).
- * mode  0 (default): speculative where it is expected to be faster (from 256 MiB on, clips of 12 to 64
- *       frames, fp32 on grids of up to 16 columns; depends on B, F, the grid, r and C), and there only if
+ * mode  0 (default): speculative where it is expected to be faster (from 256 MiB on, clips of 12 to 128
+ *       frames, those of more than 64 only where it is expected to save much; fp32 on grids of up to 16 columns;
+ *       depends on B, F, the grid, r and C), and there only if
  *       enough of the clips have a clear guess: else all take the two-pass route;
  *       1: speculative wherever available;  -1: always two-pass.
  * Process-wide; takes effect for calls made after it returns.  INVALID_ARG for other values.

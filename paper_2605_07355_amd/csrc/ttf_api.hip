@@ -135,17 +135,20 @@ bool search_walks(const ttf_params& p, bool external_anchor)
 
 // Speculative anchor: -1 never, 1 whenever the shape allows, 0 where it is expected to pay (two-pass / with the guess below, us):
 //  * inputs of 256 MiB and more;
-//  * clips of 12 to 64 frames.  Shorter ones clear the trust gap too seldom (B32 F4 16x16 C4096 150 / 177, none of 32;
-//    B16 F12 203 / 163 and B16 F15 242 / 195, all of 16).  Longer ones of one scene gain or lose (B2 F100 16x16 C4096 r 0 202 / 175, B7
-//    F79 16x16 C2816 351 / 323; B1 F92 32x25 C2048 158 / 174, B2 F70 32x32 C2048 r 2 274 / 325), of several scenes they
-//    lose (B7 F79 450 / 523, B3 F84 32x26 C1536 r 2 375 / 604), and neither is known before the call;
+//  * clips of 12 to 128 frames.  Shorter ones clear the trust gap too seldom (B32 F4 16x16 C4096 150 / 177, none of 32;
+//    B16 F12 203 / 163 and B16 F15 242 / 195, all of 16), longer ones hardly ever.
+//  * clips of more than 64 frames are as often of several scenes, which have no clear guess, as of one, and neither is known
+//    before the call: there the guess has to save half as much again as one that is dropped costs, by guess_cost().  One
+//    scene, then scenes of 32 frames: B8 F128 16x16 C4096 968 / 672 and 1351 / 1398, B16 F66 16x16 C2048 489 / 422 and 602 / 647,
+//    B8 F72 16x16 C4096 r 0 494 / 403 and 639 / 674; not where that is not expected: B4 F100 24x24 C2048 408 / 378 and 552 / 593,
+//    B3 F117 9x16 C3584 184 / 172 and 236 / 268, B14 F84 20x28 C1024 r 0 595 / 560 and 766 / 845.
 //  * where the model of the two ways, guess_cost(), has it save anything;
 //  * fp32 on grids of one strip: with sums it is bound by its arithmetic, which strips of 11 cells do not fill (B6 F32
 //    16x32 C2048 449 / 478, B16 F32 16x16 C4096 944 / 749).
 // Where too few clips of a batch have a clear guess, all are dropped on the device (min_trusted): B8 F20 24x24 C2048, 6 of 8
 // clear, 195 two-pass, 290 with the guesses, 226 with them dropped; B16 F32 16x16 C4096, 4 of 16, 561 / 683 / 591.
 constexpr unsigned long long kSpeculationMinBytes = 256ull << 20;
-constexpr int kSpeculationMinFrames = 12, kSpeculationMaxFrames = 64;
+constexpr int kSpeculationMinFrames = 12, kSpeculationSceneFrames = 64, kSpeculationMaxFrames = 128;
 
 // Whether the anchor of a clip that walks (use_walk()) is guessed first, and the deal and scratch of the walk that
 // then keeps sums.  Only such clips: one that took the walk beside a guess and another search without one would have
@@ -167,7 +170,7 @@ static bool use_guess(const ttf_params& p, const Workspace& w, bool mfma, int mo
     min_trusted = 0;                                         // (forced: however few)
     if (mode == 0) {
         const GuessCost cost = guess_cost(p, with_sums, plan);
-        if (cost.saves < 0.0) return false;
+        if (cost.saves < (p.F > kSpeculationSceneFrames ? 1.5 * cost.dropped : 0.0)) return false;
         min_trusted = cost.min_trusted;
     }
     plan = with_sums;

@@ -208,9 +208,10 @@ struct WalkPlan {
 struct WalkDeal {
     int lsegs, ysegs, groups, nf;   // as in WalkPlan
 };
-// The guessed anchor: microseconds that it saves where every clip has a clear guess, and how many clips have to have one for any to be taken.
+// The guessed anchor: microseconds that it saves where every clip has a clear guess, and that it costs where it is dropped, and how
+// many clips have to have a clear one for any to be taken.
 struct GuessCost {
-    double saves;
+    double saves, dropped;
     int min_trusted;
 };
 struct WalkScratch {

@@ -803,6 +803,9 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
 // B5 F40 12x48 C2304 5 / -4; 5x5 window B4 F64 32x32 C4096 117 / 163, B4 F40 32x26 C1536 -65 / -60, B3 F64 27x16 C2304 -31 / -11;
 // fp32 B16 F32 16x16 C4096 185 / 198, B7 F33 32x16 C1088 3 / 11; many runs B1 F32 200x16 C4096 53 / 48, B1 F64 64x64 C1024
 // -16 / -12.
+// A guess that is dropped costs the pass over its channels, the pick and a walk that does nothing: model / measured B16 F66
+// 16x16 C2048 49 / 45, B8 F128 16x16 C4096 44 / 47, B30 F65 16x16 C1536 70 / 70, B3 F126 32x14 C4096 r 0 40 / 42, fp32 B4 F100 16x16
+// C4096 43 / 43.
 GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan& again)
 {
     const bool f32 = p.dtype == TTF_F32;
@@ -822,6 +825,7 @@ GuessCost guess_cost(const ttf_params& p, const WalkPlan& first, const WalkPlan&
     const double launches = f32 ? 10.0 : 20.0 + (p.F > 32 ? 8.0 : 0.0) + (p.C < 1536 ? 8.0 : 0.0) + (p.r == 2 ? 25.0 : 0.0) +
                                              (first.lsegs * first.ysegs > 8 ? 20.0 : 0.0);
     cost.saves = without - with_sums * walk(p.B) - guess - launches;
+    cost.dropped = guess + 24.0;
     cost.min_trusted = p.B + 1;
     const int step = (p.B + 63) / 64;                        // (no more than 64 of the counts are looked at)
     for (int n = p.B; n > 0; n -= step) {

@@ -237,3 +237,21 @@ def test_nonfinite_values_in_the_walk(oracle, B, F, H, W, C, r, dtype, spec, anc
 def test_walk_in_a_graph(B, F, H, W, C, r, dtype, spec):
     assert search_guesses(params(B, F, H, W, C, _torch(dtype), r), spec or 0) >= 0
     graph_capture_and_replay("walk", B, F, H, W, C, dtype, r, spec)
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,unclear", [
+    (5, 70, 2, 14, 1024, 1, "bf16", (1,)),
+    (5, 70, 2, 14, 1024, 2, "bf16", (0, 1, 2, 3, 4)),   # no guess is left: the second walk picks clip by clip
+    (3, 129, 2, 13, 1024, 0, "bf16", ()),
+    (4, 67, 3, 13, 1056, 1, "f32", (2,)),
+])
+def test_guess_of_clips_of_more_frames_than_its_registers_hold(B, F, H, W, C, r, dtype, unclear):
+    p = params(B, F, H, W, C, _torch(dtype), r)
+    assert F > 64 and search_guesses(p, 1) == 0
+    cfg = CONFIGS["qwen3vl_2b"].scaled(B=B, F=F, H=H, W=W, C=C, r=r, max_offset=min(max(r, 1), 2), sigma=1.2,
+                                       clean_sigma=0.1, dtype=dtype)
+    batch, res, want = _mixed(cfg, 5700 + F, (), unclear)
+    assert _kinds(batch.x, res.anchor_index) == want
+    for mode in (1, -1):
+        _, out = run_gpu(batch.x, r, cfg.t[0], speculation=mode)
+        compare_with_oracle(batch.x, out, res)

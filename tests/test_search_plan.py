@@ -105,7 +105,24 @@ def test_guesses_taken_with_so_many_clear_clips(B, F, H, W, C, r, clear, taken):
 
 def test_default_frame_counts_of_the_guess():
     took = [F for F in range(2, 130) if search_guesses(params(16, F, 16, 16, 4096, BF), 0) >= 0]
-    assert took == list(range(12, 65))        # F 12: 203 us two-pass, 163 with the guesses; F 15: 242 / 195
+    assert took == list(range(12, 129))       # F 12: 203 us two-pass, 163 with the guesses; F 15: 242 / 195
+
+
+@pytest.mark.parametrize("B,F,H,W,C,r,taken,dtype", [
+    # us two-pass / with the guess of clips of one scene, and of scenes of 32 frames
+    (8, 128, 16, 16, 4096, 1, True, BF),      # 968 / 672, 1351 / 1398
+    (16, 66, 16, 16, 2048, 1, True, BF),      # 489 / 422, 602 / 647
+    (8, 72, 16, 16, 4096, 0, True, BF),       # 494 / 403, 639 / 674
+    (6, 66, 32, 32, 3072, 2, True, BF),       # 1163 / 1096, 1458 / 1529
+    (4, 100, 16, 16, 4096, 1, True, F32),     # 748 / 609, 1008 / 1050
+    (2, 100, 16, 16, 4096, 0, False, BF),     # 202 / 175, 258 / 290
+    (4, 100, 24, 24, 2048, 1, False, BF),     # 408 / 378, 552 / 593
+    (14, 84, 20, 28, 1024, 0, False, BF),     # 595 / 560, 766 / 845
+    (16, 100, 14, 14, 1024, 1, False, BF),    # 308 / 323, 396 / 460
+    (8, 129, 16, 16, 4096, 1, False, BF),
+])
+def test_guess_of_long_clips(B, F, H, W, C, r, taken, dtype):
+    assert (search_guesses(params(B, F, H, W, C, dtype, r), 0) >= 0) == taken
 
 
 @pytest.mark.parametrize("B,F,H,W,C,r,taken,dtype", [
