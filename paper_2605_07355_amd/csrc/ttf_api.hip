@@ -125,6 +125,26 @@ static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool ex
     return walk_scratch(clip, carve(clip, nullptr), plan, false, fits) && walk_scratch(p, w, plan, false, scratch);
 }
 
+// Inputs, or the end of a pass over larger ones, are left in the Infinity Cache (256 MiB): plain
+// loads instead of non-temporal ones, for a little more than fits where the input does not.
+// B2 F256 16x16 C4096 (1 GiB): frame sums 161 us either way and the search behind them 174 -> 162, with 1 GiB of plain
+// loads 179 and 162; B4 F32 16x16 C4096 (256 MiB): sums 42.8 -> 41.5, search 47.8 -> 44.6, row copy 33.8 -> 29.9.  Searches
+// that read with plain loads themselves (`walks` false) push out the end of a larger input before they reach it: there
+// it costs (B2 F256 32x23 C384, 276 MiB: sums 44 -> 50, whole call 278 -> 295).
+// The wave-per-token search gains by it too from 16 MiB on (90 shapes, 2 to 20 %).  Below, where most of the input still stands
+// in some XCD's L2 when the search starts, it can be slower: kernel 34.5 -> 46 us, B1 F4 14x16 C4096 fp32.  (That it comes with
+// the plain loads is measured; that it is the lines in other XCDs' L2s is a guess.)  From 6 to 16 MiB a call takes 0.89 to 1.34
+// times what it takes with non-temporal loads (118 shapes, mean 1.006; fp32 B1 F3 16x14 C4096 52 / 68, B1 F7 32x16 C896 r 3
+// 70 / 78, but B2 F2 14x32 C2048 59.5 / 53), on less there is no difference.
+double kept_share(const ttf_params& p, bool walks, bool mfma)
+{
+    const double bytes = (double)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4);
+    const double mib = 1 << 20;
+    if (!walks && !mfma && bytes < 16 * mib) return 0.0;
+    if (!walks) return bytes <= 256 * mib ? 1.0 : 0.0;
+    return bytes <= 320 * mib ? 1.0 : 320 * mib / bytes;
+}
+
 bool search_walks(const ttf_params& p, bool external_anchor)
 {
     const Workspace w = carve(p, nullptr);
@@ -317,7 +337,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
 
     mark();                                                    // start of stage 0
     if (spec) TTF_STEP(launch_guess_sums(p, features, w, s));
-    else if (pick) TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk), s));
+    else if (pick) TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk, mfma), s));
     mark();
     if (pick && !spec) TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     mark();
@@ -339,7 +359,7 @@ static ttf_status run_pass(const ttf_params* params, const void* features, const
     }
     mark();
     if (spec) {
-        TTF_STEP(launch_frame_sums(p, features, w, true, kept_share(p, true), s));     // clips without a trusted guess only
+        TTF_STEP(launch_frame_sums(p, features, w, true, kept_share(p, true, mfma), s));     // clips without a trusted guess only
         TTF_STEP(launch_anchor_scores(p, w, scratch.strip_sum, plan.lsegs * plan.ysegs, s));
         TTF_STEP(launch_search_walk(p, features, nullptr, w, plan, again, scratch, out->anchor_index, false, 2, 0, s));
         TTF_STEP(launch_walk_finish(p, w, plan, scratch, out->anchor_index, out->fuse_map, out->best_sim, out->best_idx,
@@ -460,7 +480,7 @@ ttf_status ttf_compress_tied(const ttf_params* params, const void* features, voi
     WalkScratch scratch{};
     const bool mfma = use_mfma_path(p, w.tail, false), walk = use_walk(p, w, mfma, false, plan, scratch);
     if (p.anchor_mode == TTF_ANCHOR_AUTO) {
-        TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk), s));
+        TTF_STEP(launch_frame_sums(p, features, w, false, kept_share(p, walk, mfma), s));
         TTF_STEP(launch_anchor_scores(p, w, nullptr, 0, s));
     }
     TTF_STEP(launch_tied_anchor(p, w, out->anchor_index, s));

@@ -26,19 +26,9 @@ hipError_t allow_dynamic_lds(const void* kernel, size_t bytes);
 bool mfma_search_f32_supported(const ttf_params& p, int frames);   // `frames` searched per clip
 bool mfma_f32_aligned(const ttf_params& p);
 
-// Share of an input whose reads leave it in the Infinity Cache (256 MiB) for the kernel that reads it next: plain
-// loads instead of non-temporal ones for the end of a pass, a little more than fits where the input does not.
-// B2 F256 16x16 C4096 (1 GiB): frame sums 161 us either way and the search behind them 174 -> 162, with 1 GiB of plain
-// loads 179 and 162; B4 F32 16x16 C4096 (256 MiB): sums 42.8 -> 41.5, search 47.8 -> 44.6, row copy 33.8 -> 29.9.  Searches
-// that read with plain loads themselves (`walks` false) push out the end of a larger input before they reach it: there
-// it costs (B2 F256 32x23 C384, 276 MiB: sums 44 -> 50, whole call 278 -> 295).
-inline double kept_share(const ttf_params& p, bool walks)
-{
-    const double bytes = (double)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4);
-    const double mib = 1 << 20;
-    if (!walks) return bytes <= 256 * mib ? 1.0 : 0.0;
-    return bytes <= 320 * mib ? 1.0 : 320 * mib / bytes;
-}
+// Share of an input whose reads by the frame sums or the walk leave it in the caches for the kernel that reads it next; the
+// search that follows walks (`walks`), or runs on the matrix cores (`mfma`), or neither.
+double kept_share(const ttf_params& p, bool walks, bool mfma);
 
 // Device scratch carved out of the caller's workspace.  All sections are 256-byte aligned.
 struct Workspace {

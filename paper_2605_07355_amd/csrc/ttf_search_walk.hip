@@ -892,7 +892,7 @@ hipError_t launch_search_walk(const ttf_params& p, const void* x, const void* ex
     a.fixed_anchor = anchor_given ? kAnchorGiven : fixed_frame(p);
     a.mode = mode;
     a.min_trusted = min_trusted;
-    a.keep_from = 256 - (int)(256 * kept_share(p, true));
+    a.keep_from = 256 - (int)(256 * kept_share(p, true, true));
     auto units = [&](const WalkPlan& w) { return (size_t)p.B * w.nk * w.groups * w.lsegs * w.ysegs; };
     const unsigned grid = (unsigned)(mode == 2 ? std::max(units(plan), units(all)) : units(plan));
     auto go = [&](auto kernel, size_t lds) {

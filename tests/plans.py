@@ -51,3 +51,9 @@ def search_guesses(p, mode):
     """How many clips have to have a clear guess for any to be taken; -1: anchors are not guessed."""
     f = _symbol("_ZN3ttf14search_guessesERK10ttf_paramsi", ctypes.c_int, ctypes.c_void_p, ctypes.c_int)
     return f(ctypes.addressof(p), mode)
+
+
+def kept_share(p, walks, mfma):
+    """Share of the input that the frame sums leave in the caches for the search."""
+    f = _symbol("_ZN3ttf10kept_shareERK10ttf_paramsbb", ctypes.c_double, ctypes.c_void_p, ctypes.c_bool, ctypes.c_bool)
+    return f(ctypes.addressof(p), walks, mfma)

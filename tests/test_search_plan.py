@@ -4,7 +4,7 @@ import random
 import pytest
 import torch
 
-from plans import CUS, matrix_cores, params, search_guesses, search_walks, units, walk_plan
+from plans import CUS, kept_share, matrix_cores, params, search_guesses, search_walks, units, walk_plan
 
 BF, F32 = torch.bfloat16, torch.float32
 
@@ -210,3 +210,16 @@ def test_fp32_rows_of_32_cells(B, F, H, C, walks):
 def test_route_of_a_radius_beyond_the_grid(H, W, C, dtype, r, want):
     import paper_2605_07355_amd as ttf
     assert ttf.ttf_search_route(2, 4, H, W, C, dtype, r=r) == ttf.ttf_search_route(2, 4, H, W, C, dtype, r=max(H, W)) == want
+
+
+@pytest.mark.parametrize("B,F,H,W,C,dtype,r,kept", [
+    (1, 4, 14, 16, 4096, F32, 1, 0.0),        # wave-per-token search below 16 MiB: us left in the caches / not, 75.5 / 56.5
+    (2, 6, 16, 15, 1280, F32, 2, 0.0),        # 62.5 / 57.5
+    (3, 2, 32, 24, 1000, F32, 0, 1.0),        # above: 45.8 / 54.8
+    (1, 10, 24, 16, 2048, F32, 1, 1.0),       # 50.5 / 56
+    (1, 4, 16, 16, 2048, BF, 1, 1.0),         # on the matrix cores
+    (2, 256, 16, 16, 4096, BF, 1, 0.3125),
+])
+def test_what_the_frame_sums_leave_in_the_caches(B, F, H, W, C, dtype, r, kept):
+    p = params(B, F, H, W, C, dtype, r)
+    assert kept_share(p, search_walks(p), matrix_cores(p)) == kept
