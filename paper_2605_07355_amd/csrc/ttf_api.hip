@@ -79,8 +79,8 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 // r 0..2, 130 random shapes; time of the kernels above over the walk's):
 //   tile rows padded to 16 columns, C >= 1024: 0.99 to 2.2 at every size (B1 F23 9x14 C1792 54.2 / 33.8 us, B1 F5 32x23
 //     C4096 r2 106 / 48.5, B8 F59 10x16 C2048 216 / 189); shorter rows 0.91 to 1.14.  Without the anchor rule, whose sums leave
-//     the end of the input in the cache, C < 1536 also 0.90 to 1.26 with the 5x5 window and up to 16 columns (60 segments and tied
-//     batches, 1.03 on average; segment B4 F135 14x14 C1152 85.5 / 95, tied B1 F30 18x16 C1024 52 / 57): one rule for all calls.
+//     the end of the input in the cache, C < 1536 also 0.90 to 1.27 with the 5x5 window and up to 16 columns (40 segments and tied
+//     batches, 1.04 on average; segment B4 F135 14x14 C1152 85.5 / 95, tied B1 F30 18x16 C1024 52 / 57): one rule for all calls.
 //   aligned 16- and 32-wide grids: 0.78 to 0.97 on small calls (B1 F10 16x16 C2048 27.2 / 34.8, B1 F32 32x32 C1024 58 /
 //     67), 1.0 to 1.3 from 96 MiB on (B6 F17 16x16 C3584 111 / 103, B4 F20 16x16 C3584 r0 95 / 83), with three strips in a row of
 //     32 from 160 MiB (B2 F6 32x32 C2048 53 / 61, B5 F9 32x32 C3072 172 / 145); the 5x5 window from 24 MiB (B5 F14 16x16
