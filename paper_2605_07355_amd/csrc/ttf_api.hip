@@ -86,8 +86,9 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 //     32 from 160 MiB (B2 F6 32x32 C2048 53 / 61, B5 F9 32x32 C3072 172 / 145); the 5x5 window from 24 MiB (B5 F14 16x16
 //     C1792 68.5 / 59.0), and rows whose K-steps do not divide over the waves there from 32 MiB (B2 F15 16x16 C2624 61.1 / 49.8).
 //   the 5x5 window, 16 wide: 0.95 to 1.2 from 24 to 64 MiB (85 shapes; B4 F5 88x16 C1280 75 / 65, segment B8 F5 12x16 C2112 34 /
-//     37), but not where the walk makes fewer than 160 workgroups of such a problem (B1 F10 48x16 C2048 41 / 48.5; C 3072 and
-//     4096 0.98 to 1.2).  Grids of two rows fill half of every patch, and whole strips of the kernels above: C < 1536 from 32 MiB
+//     37), but up to 48 MiB not where the walk makes fewer than 256 workgroups of such a problem: 102 shapes 0.96 on average, 0.80 to
+//     1.26 (segment B2 F17 24x16 C1024 25 / 29, B1 F10 48x16 C2048 38 / 45); with 256 28 shapes 1.01 (C 3072 and 4096 0.98 to 1.2).
+//     Grids of two rows fill half of every patch, and whole strips of the kernels above: C < 1536 from 32 MiB
 //     0.75 to 0.98 (segment B64 F40 2x16 C1024 66 / 88, B32 F24 2x12 C1152 37 / 42), longer rows from 96 MiB 0.88 to 1.03
 //     (B64 F24 2x14 C1536 61 / 69), below 1.0 to 1.4.
 // fp32 tokens, windows up to 3x3 (90 shapes): against the matrix-core search 1.02 to 2.8 from C 1024 on (B3 F7 16x21 C1024
@@ -117,7 +118,7 @@ static bool use_walk(const ttf_params& p, const Workspace& w, bool mfma, bool ex
     plan = walk_plan(p, frames, false);
     if (!plan.ok) return false;
     if (p.r == 2 && p.W == 16 && p.C < 2560 && mfma_search_supported(p) && mib < 48 &&
-        (size_t)p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs < 160)
+        (size_t)p.B * plan.nk * plan.groups * plan.lsegs * plan.ysegs < 256)
         return false;
     // The products of all frames have to fit the workspace at once.  A segment's workspace is that of F frames, its
     // clip's that of F + 1: asked is whether they fit the clip's, where there is less room for a frame.
