@@ -756,9 +756,29 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
         WalkScratch room{};
         if (!walk_scratch(p, carve(p, nullptr), all_runs, true, room)) most_runs = 1;
     }
+    const bool in_cache = (double)p.B * p.F * p.H * p.W * p.C * (p.dtype == TTF_BF16 ? 2 : 4) <= 256.0 * (1 << 20);
     double best = 1e300;
     const int most = !sums ? 32 : p.dtype == TTF_F32 ? spec_frames<float, 1>() : (p.r == 2 ? spec_frames<bf16_t, 2>() : spec_frames<bf16_t, 1>());
-    for (int lsegs = 1; lsegs <= w.lines; lsegs = std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs)) {
+    auto deal = [&](int lsegs, int ysegs, double least_units) {   // the frame groups for these runs of the grid
+        int last = 0;
+        for (int want = 1; want <= most; ++want) {
+            const int groups = (frames + want - 1) / want, nf = (frames + groups - 1) / groups;
+            if (nf == last) continue;
+            last = nf;
+            const double units = (double)p.B * w.nk * groups * lsegs * ysegs;
+            if (units < least_units || units * (kWalkWaves * 64) >= 4294967296.0) continue;   // (threads of a launch)
+            const double lines = (w.lines + lsegs - 1) / lsegs, run = (steps + ysegs - 1) / ysegs;   // (of the longest)
+            const double tiles = 2.0 + lines * (run * (nf + 0.35 * fresh) + 0.35 * held);
+            const double time = tiles * deal_rounds(units);
+            if (time < best) {
+                best = time;
+                w.tiles = tiles;
+                w.nf = nf; w.groups = groups; w.lsegs = lsegs; w.ysegs = ysegs;
+            }
+        }
+    };
+    auto next_lsegs = [&](int lsegs) { return std::min(2 * lsegs, lsegs < w.lines ? w.lines : 2 * lsegs); };
+    for (int lsegs = 1; lsegs <= w.lines; lsegs = next_lsegs(lsegs)) {
         for (int ysegs = 1; ysegs <= steps && (long long)lsegs * ysegs <= most_runs; ysegs *= 2) {
             // More than four runs only where fewer leave the chip empty, as on tall grids of few columns and frames: with
             // four, segment B1 F6 848x16 C1024 430 us / with as many as it takes 63 (tile-wise kernels 75), tied B1 F2 3428x16
@@ -766,21 +786,20 @@ WalkPlan walk_plan(const ttf_params& p, int frames, bool sums)
             // Elsewhere short runs leave too little of a pass in the Infinity Cache (B2 F256 16x16 C4096, runs of two
             // rows: 669 -> 691).
             if (ysegs > 4 && (double)p.B * w.nk * frames * lsegs * (ysegs / 2) >= 1024) break;
-            int last = 0;
-            for (int want = 1; want <= most; ++want) {
-                const int groups = (frames + want - 1) / want, nf = (frames + groups - 1) / groups;
-                if (nf == last) continue;
-                last = nf;
-                const double units = (double)p.B * w.nk * groups * lsegs * ysegs;
-                if (units * (kWalkWaves * 64) >= 4294967296.0) continue;   // (threads of a launch)
-                const double lines = (w.lines + lsegs - 1) / lsegs, run = (steps + ysegs - 1) / ysegs;   // (of the longest)
-                const double tiles = 2.0 + lines * (run * (nf + 0.35 * fresh) + 0.35 * held);
-                const double time = tiles * deal_rounds(units);
-                if (time < best) {
-                    best = time;
-                    w.tiles = tiles;
-                    w.nf = nf; w.groups = groups; w.lsegs = lsegs; w.ysegs = ysegs;
-                }
+            deal(lsegs, ysegs, 0.0);
+        }
+    }
+    // Three, five and six runs where they fill the chip better by more than 5 %: grids of few tiles a column, which powers of two
+    // cut unevenly (97 of 600 drawn shapes up to 700 MiB, 0.94 of the time on average, 0.81 to 1.03: segment B1 F68 20x16 C3200 r 2, five rows
+    // of patches, 71 us on 184 workgroups of one run, 58 on 240 of five, tile-wise kernels 69; segment B1 F33 18x32 C2368 57 / 48.5 / 57;
+    // less than 5 % 0.99 on average; fewer than 128 workgroups 1.00 to 1.03).  More than four beyond the Infinity Cache only where
+    // two leave the chip empty.  Not with sums, whose number of runs is limited by their room.
+    if (!sums) {
+        best *= 0.95;
+        for (int lsegs = 1; lsegs <= w.lines; lsegs = next_lsegs(lsegs)) {
+            for (int ysegs : {3, 5, 6}) {
+                if (ysegs > steps || (ysegs > 4 && !in_cache && (double)p.B * w.nk * frames * lsegs * 2 >= 1024)) break;
+                deal(lsegs, ysegs, 128.0);
             }
         }
     }

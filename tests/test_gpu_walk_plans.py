@@ -40,6 +40,32 @@ def test_tall_grids_in_many_runs(B, F, H, W, C, r, dtype):
         compare_with_oracle(batch.x, out, res)
 
 
+@pytest.mark.parametrize("B,F,H,W,C,r,dtype,ysegs", [
+    (1, 16, 9, 9, 1024, 2, "bf16", 3),         # three rows of patches, the last a quarter full
+    (1, 10, 17, 9, 1024, 2, "bf16", 5),
+    (1, 9, 22, 9, 1088, 2, "bf16", 6),
+    (1, 23, 9, 9, 1024, 0, "bf16", 6),         # runs of one and two rows
+    (1, 27, 9, 9, 1024, 1, "bf16", 5),
+    (1, 53, 9, 9, 1024, 1, "bf16", 3),
+    (1, 14, 12, 20, 1024, 1, "f32", 6),
+    (2, 34, 9, 9, 1088, 0, "f32", 5),          # three frames a workgroup
+])
+def test_uneven_runs(B, F, H, W, C, r, dtype, ysegs):
+    import paper_2605_07355_amd as ttf
+    p = params(B, F, H, W, C, _torch(dtype), r)
+    assert search_walks(p) and walk_plan(p, F - 1, False).ysegs == ysegs
+    cfg = _cfg(B, F, H, W, C, r, dtype)
+    batch, res = _prepared(cfg, seed=1250 + F + H)
+    x, out = run_gpu(batch.x, r, cfg.t[0], speculation=-1)
+    compare_with_oracle(batch.x, out, res)
+    _, whole = run_gpu(batch.x, r, cfg.t[0], anchor=0)
+    seg = ttf.TTFBuffers.allocate(B, F - 1, H, W, C, x.dtype, x.device)
+    ttf.ttf_compress_segment(x[:, 1:].contiguous(), x[:, 0].contiguous(), 0, r=r, t=cfg.t[0], buffers=seg)
+    torch.cuda.synchronize()
+    assert torch.equal(seg.best_sim, whole.buffers.best_sim[:, 1:])
+    assert torch.equal(seg.fuse_map, whole.buffers.fuse_map[:, 1:])
+
+
 @pytest.mark.parametrize("B,F,H,W,C,r,dtype", [
     (1, 31, 16, 20, 1024, 2, "bf16"),          # the last clip that walks ...
     (1, 32, 16, 20, 1024, 2, "bf16"),          # ... and the first that does not

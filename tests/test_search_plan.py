@@ -41,6 +41,20 @@ def test_long_runs_where_frames_fill_the_chip(B, frames, C):
     assert plan.ok and plan.ysegs <= 4          # the kept part of a pass is measured in whole rows of a run
 
 
+@pytest.mark.parametrize("B,frames,H,W,C,r,ysegs", [
+    # segments: us at a power of two of runs, at this many, on the tile-wise kernels
+    (1, 68, 20, 16, 3200, 2, 5),              # 71 / 58 / 69
+    (2, 24, 12, 16, 3200, 2, 3),              # 44 / 37 / 43
+    (8, 5, 24, 14, 2048, 2, 6),               # 40 / 34 / 46
+    (1, 33, 18, 32, 2368, 1, 6),              # 57 / 48.5 / 57
+    (1, 2, 33, 16, 1152, 2, 8),               # (tied) 48.5 / 49 with five
+    (2, 256, 16, 16, 4096, 1, 4),
+])
+def test_runs_that_fill_the_chip(B, frames, H, W, C, r, ysegs):
+    plan = walk_plan(params(B, frames, H, W, C, BF, r), frames, False)
+    assert plan.ok and plan.ysegs == ysegs
+
+
 def _limit(B, H, W, C, dtype, r):
     """The most frames of a clip that still walks."""
     return max(F for F in range(2, 400) if search_walks(params(B, F, H, W, C, dtype, r)))
