@@ -80,13 +80,13 @@ hipError_t launch_window_search(const ttf_params& p, const void* x, const void* 
 //   tile rows padded to 16 columns, C >= 1024: 0.99 to 2.2 at every size (B1 F23 9x14 C1792 54.2 / 33.8 us, B1 F5 32x23
 //     C4096 r2 106 / 48.5, B8 F59 10x16 C2048 216 / 189); shorter rows 0.91 to 1.14.  Without the anchor rule, whose sums leave
 //     the end of the input in the cache, C < 1536 also 0.90 to 1.27 with the 5x5 window and up to 16 columns (40 segments and tied
-//     batches, 1.04 on average; segment B4 F135 14x14 C1152 85.5 / 95, tied B1 F30 18x16 C1024 52 / 57): one rule for all calls.
+//     batches, 1.04 on average; segment B4 F135 14x14 C1152 85 / 94, tied B8 F23 18x14 C1088 94 / 103): one rule for all calls.
 //   aligned 16- and 32-wide grids: 0.78 to 0.97 on small calls (B1 F10 16x16 C2048 27.2 / 34.8, B1 F32 32x32 C1024 58 /
 //     67), 1.0 to 1.3 from 96 MiB on (B6 F17 16x16 C3584 111 / 103, B4 F20 16x16 C3584 r0 95 / 83), with three strips in a row of
 //     32 from 160 MiB (B2 F6 32x32 C2048 53 / 61, B5 F9 32x32 C3072 172 / 145); the 5x5 window from 24 MiB (B5 F14 16x16
 //     C1792 68.5 / 59.0), and rows whose K-steps do not divide over the waves there from 32 MiB (B2 F15 16x16 C2624 61.1 / 49.8).
-//   the 5x5 window, 16 wide: 0.95 to 1.2 from 24 to 64 MiB (85 shapes; B4 F5 88x16 C1280 75 / 65, segment B8 F5 12x16 C2112 34 /
-//     37), but up to 48 MiB not where the walk makes fewer than 256 workgroups of such a problem: 102 shapes 0.96 on average, 0.80 to
+//   the 5x5 window, 16 wide: 0.95 to 1.2 from 24 to 64 MiB (85 shapes; B4 F5 88x16 C1280 75 / 65, segment B2 F9 48x16 C2304 37 /
+//     44), but up to 48 MiB not where the walk makes fewer than 256 workgroups of such a problem: 102 shapes 0.96 on average, 0.80 to
 //     1.26 (segment B2 F17 24x16 C1024 25 / 29, B1 F10 48x16 C2048 38 / 45); with 256 28 shapes 1.01 (C 3072 and 4096 0.98 to 1.2).
 //     Grids of two rows fill half of every patch, and whole strips of the kernels above: C < 1536 from 32 MiB
 //     0.75 to 0.98 (segment B64 F40 2x16 C1024 66 / 88, B32 F24 2x12 C1152 37 / 42), longer rows from 96 MiB 0.88 to 1.03
